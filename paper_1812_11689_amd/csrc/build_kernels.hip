@@ -208,7 +208,7 @@ __global__ __launch_bounds__(256) void k_level_small(
         const int64_t hs = (int64_t)t * H + (sg.heap - 1);
         split[hs] = val_of(phi);
         split_idx[hs] = (int32_t)plo;
-        chosen[hs] = ch;
+        if (chosen) chosen[hs] = ch;
         if (lefts != (uint32_t)half) atomicOr(err, 1);
     }
 }
@@ -341,7 +341,7 @@ __global__ __launch_bounds__(256) void k_level_fed_wave(const SegDesc *__restric
         const int64_t hs = (int64_t)t * H + (sg.heap - 1);
         split[hs] = val_of(phi);
         split_idx[hs] = (int32_t)plo;
-        chosen[hs] = 0;
+        if (chosen) chosen[hs] = 0;
         if (lefts != (uint32_t)half) atomicOr(err, 1);
     }
 }
@@ -549,11 +549,9 @@ void launch_subtree(hipStream_t s, bool vec, const float *X, int d, const float 
 // Q8: rows read from the int8 grid copy Xq (stride dq) instead of X; the same values
 template <bool VEC, bool LEAD, bool Q8 = false>
 __global__ __launch_bounds__(256) void k_proj_chunks(
-    const float *__restrict__ X, int d, const float *__restrict__ R, int64_t H, int n_try,
+    const float *__restrict__ X, int d, const float *__restrict__ R, int64_t H,
     const SegDesc *__restrict__ segs, const ChunkDesc *__restrict__ chunks,
-    const int32_t *__restrict__ perm, int64_t n, SelState *__restrict__ state, int nseg,
-    int mode,  // 0: final projection -> keys + digit-0 histogram; 1: raw projection of try `tr`
-    int tr, uint64_t *__restrict__ keys, double *__restrict__ praw, uint32_t *__restrict__ hist,
+    const int32_t *__restrict__ perm, int64_t n, int nseg, uint64_t *__restrict__ keys, uint32_t *__restrict__ hist,
     const LookDesc *__restrict__ look, double2 *__restrict__ ahead, const int8_t *__restrict__ Xq, int dq) {
     // the node's direction (binary32); on a lead level it and its children's, as binary64
     extern __shared__ __align__(16) uint8_t s_dir[];
@@ -563,12 +561,9 @@ __global__ __launch_bounds__(256) void k_proj_chunks(
     const ChunkDesc c = chunks[blockIdx.x];
     const SegDesc sg = segs[c.seg];
     const int tid = threadIdx.x;
-    const SelState *st = state + (int64_t)t * nseg + c.seg;
-    const int ch = mode == 0 ? st->chosen : tr;
-    const float *Rn = R + (((int64_t)t * H + (sg.heap - 1)) * n_try + ch) * (int64_t)d;
+    const float *Rn = R + ((int64_t)t * H + (sg.heap - 1)) * (int64_t)d;
     const int32_t *pp = perm + (int64_t)t * n;
-    if (mode == 0)
-        for (int b = tid; b < kDigitBins; b += 256) s_hist[b] = 0;
+    for (int b = tid; b < kDigitBins; b += 256) s_hist[b] = 0;
     const int g = tid & 7, pt = tid >> 3;
     if (LEAD && d <= 1024) {  // lead level: the children's projections from the same read of X
         const LookDesc lk = look[c.seg];
@@ -610,13 +605,9 @@ __global__ __launch_bounds__(256) void k_proj_chunks(
             if constexpr (Q8) p = group8_dot64_q8<VEC>(Xq + (int64_t)pp[s] * dq, s_r, d, g);
             else p = group8_dot64<VEC>(X + (int64_t)pp[s] * d, s_r, d, g);
             if (g == 0 && i < c.len) {
-                if (mode == 0) {
-                    uint64_t u = key_of(p);
-                    keys[(int64_t)t * n + s] = u;
-                    atomicAdd(&s_hist[(uint32_t)(u >> 53)], 1u);
-                } else {
-                    praw[(int64_t)t * n + s] = p;
-                }
+                uint64_t u = key_of(p);
+                keys[(int64_t)t * n + s] = u;
+                atomicAdd(&s_hist[(uint32_t)(u >> 53)], 1u);
             }
         }
     } else {
@@ -627,22 +618,16 @@ __global__ __launch_bounds__(256) void k_proj_chunks(
             if constexpr (Q8) p = group8_dot64_q8<false>(Xq + (int64_t)pp[s] * dq, Rn, d, g);
             else p = group8_dot64<false>(X + (int64_t)pp[s] * d, Rn, d, g);
             if (g == 0 && i < c.len) {
-                if (mode == 0) {
-                    uint64_t u = key_of(p);
-                    keys[(int64_t)t * n + s] = u;
-                    atomicAdd(&s_hist[(uint32_t)(u >> 53)], 1u);
-                } else {
-                    praw[(int64_t)t * n + s] = p;
-                }
+                uint64_t u = key_of(p);
+                keys[(int64_t)t * n + s] = u;
+                atomicAdd(&s_hist[(uint32_t)(u >> 53)], 1u);
             }
         }
     }
-    if (mode == 0) {
-        __syncthreads();
-        uint32_t *gh = hist + ((int64_t)t * nseg + c.seg) * kDigitBins;
-        for (int b = tid; b < kDigitBins; b += 256)
-            if (s_hist[b]) atomicAdd(&gh[b], s_hist[b]);
-    }
+    __syncthreads();
+    uint32_t *gh = hist + ((int64_t)t * nseg + c.seg) * kDigitBins;
+    for (int b = tid; b < kDigitBins; b += 256)
+        if (s_hist[b]) atomicAdd(&gh[b], s_hist[b]);
 }
 
 __global__ void k_sel_init(const SegDesc *__restrict__ segs, int nseg, int T, SelState *state) {
@@ -656,11 +641,7 @@ __global__ void k_sel_init(const SegDesc *__restrict__ segs, int nseg, int T, Se
     s.rank = sg.size / 2;
     s.cnt = sg.size;
     s.mode = SEL_HIST;
-    s.chosen = 0;
-    s.best_s2 = 0.0;
-    s.s1 = 0.0;
     s.counted = 0;
-    s.pad = 0;
     state[i] = s;
 }
 
@@ -902,7 +883,7 @@ __global__ __launch_bounds__(256) void k_sel_finish(const SegDesc *__restrict__ 
         const int64_t hs = (int64_t)t * H + (segs[k].heap - 1);
         split[hs] = val_of(fin.pfx_hi);
         split_idx[hs] = (int32_t)fin.pfx_lo;
-        chosen[hs] = fin.chosen;
+        if (chosen) chosen[hs] = 0;  // one direction per node (else Alg. 2's pick stands already)
         if (fin.mode != SEL_DONE) atomicOr(err, 8);
     }
 }
@@ -1118,60 +1099,363 @@ __global__ __launch_bounds__(256) void k_proj_root(const float *__restrict__ X, 
     }
 }
 
-// ---- Alg. 2 on large segments: canonical sums over aligned power-of-two chunks
+// ================================================================ several tries per node (Alg. 2)
+//
+// Every try's projections are made from one read of each row (NT tries at a time), in
+// canonical order, and its two canonical sums (of p, then of (p - mean)^2) are pairwise
+// trees over the members in position order.  Bound: binary64 arithmetic (d fma per member and
+// try); before, each try re-read the rows and each level summed through LDS with a workgroup
+// barrier per tree level.
+//   - k_level_try: nodes of at most try_cap members, one workgroup per (node, tree): the
+//     projections of all tries stay in LDS, one wave sums one try, and the whole step
+//     (pick, median, partition) ends in the same workgroup.
+//   - larger nodes: k_try_proj / k_try_mean / k_try_dev / k_try_pick / k_try_keys over pieces
+//     of 256 members, which are aligned subtrees of the sums; then the level's selection runs
+//     from the chosen try's keys as on a fed level.
 
-// partial canon_sum of one chunk: of p (what = 0) or of (p - mu)^2 (what = 1)
-__global__ __launch_bounds__(256) void k_chunk_sum(const ChunkDesc *__restrict__ chunks, int nchunk,
-                                                   const SegDesc *__restrict__ segs,
-                                                   const double *__restrict__ praw, int64_t n,
-                                                   const SelState *__restrict__ state, int nseg,
-                                                   int what, double *__restrict__ part) {
-    __shared__ double s[kChunk];
-    const int t = blockIdx.y, tid = threadIdx.x;
-    const ChunkDesc c = chunks[blockIdx.x];
-    const SegDesc sg = segs[c.seg];
-    const double mu = what ? state[(int64_t)t * nseg + c.seg].s1 / (double)sg.size : 0.0;
-    for (int i = tid; i < kChunk; i += 256) {
-        double v = 0.0;
-        if (i < c.len) {
-            double p = praw[(int64_t)t * n + c.start + i];
-            if (what) {
-                double dev = p - mu;
-                v = __dmul_rn(dev, dev);
-            } else {
-                v = p;
-            }
-        }
-        s[i] = v;
-    }
-    __syncthreads();
-    for (int h = 1; h < kChunk; h <<= 1) {
-        for (int i = 2 * h * tid; i < kChunk; i += 2 * h * 256) s[i] = s[i] + s[i + h];
-        __syncthreads();
-    }
-    if (tid == 0) part[(int64_t)t * nchunk + blockIdx.x] = s[0];
+// directions tr .. tr + NT - 1 of a node (binary64, zero past n_try and past d)
+template <int NT>
+__device__ inline void stage_tries(const float *__restrict__ Rn, int tr, int n_try, int d, int ds, double *s_rd) {
+#pragma unroll
+    for (int k = 0; k < NT; k++)
+        for (int j = threadIdx.x; j < ds; j += blockDim.x)
+            s_rd[k * ds + j] = tr + k < n_try && j < d ? (double)Rn[(int64_t)(tr + k) * d + j] : 0.0;
 }
 
-// combine chunk partials of each segment by the same tree; what = 0 stores S1, what = 1
-// compares S2 with the best so far (Alg. 2: strictly larger wins)
-__global__ void k_seg_sum(const SegDesc *__restrict__ segs, int nseg, int nchunk,
-                          double *__restrict__ part, SelState *__restrict__ state, int what, int tr) {
-    const int t = blockIdx.y;
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nseg) return;
-    const SegDesc sg = segs[k];
-    // pairwise tree over the chunk partials in place; a missing right operand is the +0.0
-    // padding, and x + 0.0 == x for the non-negative-zero-free values summed here
-    double *v = part + (int64_t)t * nchunk + sg.chunk0;
-    for (int h = 1; h < sg.nchunk; h <<= 1)
-        for (int i = 0; i + h < sg.nchunk; i += 2 * h) v[i] = v[i] + v[i + h];
-    SelState *st = state + (int64_t)t * nseg + k;
-    if (what == 0) {
-        st->s1 = v[0];
-    } else if (v[0] > st->best_s2) {
-        st->best_s2 = v[0];
-        st->chosen = tr;
+template <bool VEC, int NT>
+__global__ __launch_bounds__(256) void k_level_try(const float *__restrict__ X, int d, const float *__restrict__ R,
+                                                   int64_t H, int n_try, int mp, const SegDesc *__restrict__ segs,
+                                                   const int32_t *__restrict__ perm_in, int32_t *__restrict__ perm_out,
+                                                   int64_t n, double *__restrict__ split, int32_t *__restrict__ split_idx,
+                                                   int32_t *__restrict__ chosen, int32_t *__restrict__ err) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    const int t = blockIdx.y, tid = threadIdx.x, nthr = blockDim.x;
+    const SegDesc sg = segs[blockIdx.x];
+    const int m = sg.size, ds = (d + 3) & ~3;
+    double *s_rd = reinterpret_cast<double *>(smem);  // [NT][ds]
+    double *s_p = s_rd + NT * ds;                     // [n_try][mp], mp even
+    double *s_s2 = s_p + (int64_t)n_try * mp;         // [n_try]
+    int32_t *s_perm = reinterpret_cast<int32_t *>(s_s2 + n_try);  // [mp]
+    uint32_t *s_w = reinterpret_cast<uint32_t *>(s_perm + mp);    // [4]
+    const int32_t *pin = perm_in + (int64_t)t * n + sg.off;
+    for (int i = tid; i < m; i += nthr) s_perm[i] = pin[i];
+    const float *Rn = R + ((int64_t)t * H + (sg.heap - 1)) * n_try * (int64_t)d;
+    const int g = tid & 7, pt = tid >> 3, per = nthr >> 3;
+    for (int tr = 0; tr < n_try; tr += NT) {
+        __syncthreads();
+        stage_tries<NT>(Rn, tr, n_try, d, ds, s_rd);
+        __syncthreads();
+        for (int base = 0; base < m; base += 2 * per) {
+            const int ia = base + pt, ib = ia + per;
+            const float *const x[2] = {X + (int64_t)s_perm[ia < m ? ia : 0] * d, X + (int64_t)s_perm[ib < m ? ib : 0] * d};
+            double p[2 * NT];
+            group8_dots<VEC, NT, 2>(x, s_rd, ds, d, g, p);
+#pragma unroll
+            for (int k = 0; k < NT; k++)
+                if (g == k && tr + k < n_try) {
+                    if (ia < m) s_p[(tr + k) * mp + ia] = p[2 * k];
+                    if (ib < m) s_p[(tr + k) * mp + ib] = p[2 * k + 1];
+                }
+        }
     }
+    __syncthreads();
+    // the spread of every try: one wave per try, 256 members of the pairwise tree at a time
+    // (at most two such pieces: try_cap <= 512)
+    for (int k = tid >> 6; k < n_try; k += nthr >> 6) {
+        const double *pk = s_p + k * mp;
+        double s1 = wave_canon256([&](int i) { return i < m ? pk[i] : 0.0; });
+        if (m > 256) s1 = s1 + wave_canon256([&](int i) { return i + 256 < m ? pk[i + 256] : 0.0; });
+        const double mu = s1 / (double)m;
+        auto sq = [&](int i) {
+            if (i >= m) return 0.0;
+            const double dev = pk[i] - mu;
+            return __dmul_rn(dev, dev);
+        };
+        double s2 = wave_canon256(sq);
+        if (m > 256) s2 = s2 + wave_canon256([&](int i) { return sq(i + 256); });
+        if ((tid & 63) == 0) s_s2[k] = s2;
+    }
+    __syncthreads();
+    int ch = 0;
+    double best = 0.0;
+    for (int k = 0; k < n_try; k++)  // the largest spread; the first wins ties
+        if (s_s2[k] > best) { best = s_s2[k]; ch = k; }
+    uint64_t *s_key = reinterpret_cast<uint64_t *>(s_p + ch * mp);
+    for (int i = tid; i < mp; i += nthr) s_key[i] = i < m ? key_of(s_p[ch * mp + i]) : ~0ull;
+    __syncthreads();
+    // rank of every member in (key, position) order: positions ascend with the index, so this
+    // is the (p, index) order.  The member of rank floor(m/2) splits the node.
+    const int half = m / 2;
+    int32_t *pout = perm_out + (int64_t)t * n + sg.off;
+    const int64_t hs = (int64_t)t * H + (sg.heap - 1);
+    uint32_t lefts = 0;
+    for (int base = 0; base < m; base += nthr) {
+        const int i = base + tid;
+        const bool valid = i < m;
+        int rank = m;
+        if (valid) {
+            const uint64_t u = s_key[i];
+            rank = 0;
+            for (int q = 0; q < m; q += 2) {
+                const ulonglong2 v = *reinterpret_cast<const ulonglong2 *>(s_key + q);
+                rank += (v.x < u || (v.x == u && q < i)) ? 1 : 0;
+                rank += (v.y < u || (v.y == u && q + 1 < i)) ? 1 : 0;
+            }
+            if (rank == half) {
+                split[hs] = val_of(u);
+                split_idx[hs] = s_perm[i];
+                chosen[hs] = ch;
+            }
+        }
+        const bool left = valid && rank < half;
+        const uint64_t mask = __ballot(left);
+        if ((tid & 63) == 0) s_w[tid >> 6] = (uint32_t)__popcll(mask);
+        __syncthreads();
+        uint32_t lb = lefts + mask_rank(mask);
+        for (int w = 0; w < nthr >> 6; w++) {
+            if (w < tid >> 6) lb += s_w[w];
+            lefts += s_w[w];
+        }
+        if (valid) {
+            const int pos = left ? (int)lb : half + (i - (int)lb);
+            if (pos >= 0 && pos < m) pout[pos] = s_perm[i];  // always true when the ranks are consistent
+        }
+        __syncthreads();
+    }
+    if (tid == 0 && lefts != (uint32_t)half) atomicOr(err, 1);
+}
+
+// Projections of tries tr0 .. tr0 + ntr - 1 over one piece of a node, and the partial of each
+// try's sum.
+template <bool VEC, int NT>
+__global__ __launch_bounds__(256) void k_try_proj(const float *__restrict__ X, int d, const float *__restrict__ R,
+                                                  int64_t H, int n_try, int tr0, int ntr,
+                                                  const SegDesc *__restrict__ segs, const ChunkDesc *__restrict__ subs,
+                                                  const int32_t *__restrict__ perm, int64_t n,
+                                                  double *__restrict__ praw, double *__restrict__ part) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    const int ds = (d + 3) & ~3;
+    double *s_rd = reinterpret_cast<double *>(smem);  // [NT][ds]
+    double *s_p = s_rd + NT * ds;                     // [NT][kTrySub]
+    const int t = blockIdx.y, T = gridDim.y, tid = threadIdx.x;
+    const ChunkDesc c = subs[blockIdx.x];
+    const int32_t *pp = perm + (int64_t)t * n + c.start;
+    const float *Rn = R + ((int64_t)t * H + (segs[c.seg].heap - 1)) * n_try * (int64_t)d;
+    const int g = tid & 7, pt = tid >> 3;
+    for (int tr = 0; tr < ntr; tr += NT) {
+        __syncthreads();
+        stage_tries<NT>(Rn, tr0 + tr, n_try, d, ds, s_rd);
+        __syncthreads();
+        for (int base = 0; base < c.len; base += 64) {
+            const int ia = base + pt, ib = ia + 32;
+            const float *const x[2] = {X + (int64_t)pp[ia < c.len ? ia : 0] * d, X + (int64_t)pp[ib < c.len ? ib : 0] * d};
+            double p[2 * NT];
+            group8_dots<VEC, NT, 2>(x, s_rd, ds, d, g, p);
+#pragma unroll
+            for (int k = 0; k < NT; k++)
+                if (g == k) {
+                    s_p[k * kTrySub + ia] = ia < c.len ? p[2 * k] : 0.0;
+                    s_p[k * kTrySub + ib] = ib < c.len ? p[2 * k + 1] : 0.0;
+                }
+        }
+        __syncthreads();
+        for (int k = tid >> 6; k < NT && tr + k < ntr; k += 4) {
+            const double *pk = s_p + k * kTrySub;
+            const double s1 = wave_canon256([&](int i) { return i < c.len ? pk[i] : 0.0; });
+            const int64_t row = (int64_t)(tr + k) * T + t;
+            if ((tid & 63) == 0) part[row * gridDim.x + blockIdx.x] = s1;
+            for (int i = tid & 63; i < c.len; i += 64) praw[row * n + c.start + i] = pk[i];
+        }
+    }
+}
+
+// canon_sum of a node's N partials (each an aligned piece of kTrySub members) by one wave; st:
+// 32 doubles of LDS of its own.  Pieces of 256 partials combine as a binary counter does.
+__device__ inline double wave_canon_list(const double *__restrict__ v, int N, double *st) {
+    const int nb = (N + 255) / 256;
+    double w = 0.0;
+    for (int b = 0; b < nb; b++) {
+        w = wave_canon256([&](int i) { return 256 * b + i < N ? v[256 * b + i] : 0.0; });
+        int l = 0;
+        for (int k = b; k & 1; k >>= 1) w = st[l++] + w;
+        st[l] = w;
+        wave_sync();
+    }
+    if (nb & (nb - 1)) {  // the pieces that have no partner meet zeros
+        bool have = false;
+        for (int l = 0; nb >> l; l++)
+            if ((nb >> l) & 1) {
+                w = have ? st[l] + w : st[l];
+                have = true;
+            }
+    }
+    return w;
+}
+
+__global__ __launch_bounds__(256) void k_try_mean(const SegDesc *__restrict__ segs, int nseg, int nsub,
+                                                  const double *__restrict__ part, double *__restrict__ mean) {
+    __shared__ double s_st[4][32];
+    const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (k >= nseg) return;
+    const int64_t row = (int64_t)blockIdx.z * gridDim.y + blockIdx.y;  // (try, tree)
+    const SegDesc sg = segs[k];
+    const double s1 = wave_canon_list(part + row * nsub + sg.sub0, (sg.size + kTrySub - 1) / kTrySub, s_st[threadIdx.x >> 6]);
+    if ((threadIdx.x & 63) == 0) mean[row * nseg + k] = s1 / (double)sg.size;
+}
+
+__global__ __launch_bounds__(256) void k_try_dev(const ChunkDesc *__restrict__ subs, int ntr,
+                                                 const double *__restrict__ praw, int64_t n,
+                                                 const double *__restrict__ mean, int nseg,
+                                                 double *__restrict__ part) {
+    const int t = blockIdx.y, T = gridDim.y;
+    const ChunkDesc c = subs[blockIdx.x];
+    for (int k = threadIdx.x >> 6; k < ntr; k += 4) {
+        const int64_t row = (int64_t)k * T + t;
+        const double mu = mean[row * nseg + c.seg];
+        const double *pk = praw + row * n + c.start;
+        const double s2 = wave_canon256([&](int i) {
+            if (i >= c.len) return 0.0;
+            const double dev = pk[i] - mu;
+            return __dmul_rn(dev, dev);
+        });
+        if ((threadIdx.x & 63) == 0) part[row * gridDim.x + blockIdx.x] = s2;
+    }
+}
+
+// The try of largest spread so far (Alg. 2: strictly larger wins), into `chosen`.
+__global__ __launch_bounds__(256) void k_try_pick(const SegDesc *__restrict__ segs, int nsub, int tr0, int ntr,
+                                                  const double *__restrict__ part, double *__restrict__ best,
+                                                  int64_t H, int32_t *__restrict__ chosen) {
+    __shared__ double s_st[4][32];
+    __shared__ double s_s2[32];  // ntr <= 32
+    const int t = blockIdx.y, T = gridDim.y, nseg = gridDim.x, w = threadIdx.x >> 6;
+    const SegDesc sg = segs[blockIdx.x];
+    for (int k = w; k < ntr; k += 4) {
+        const double s2 = wave_canon_list(part + ((int64_t)k * T + t) * nsub + sg.sub0,
+                                          (sg.size + kTrySub - 1) / kTrySub, s_st[w]);
+        if ((threadIdx.x & 63) == 0) s_s2[k] = s2;
+    }
+    __syncthreads();
+    if (threadIdx.x) return;
+    const int64_t hs = (int64_t)t * H + (sg.heap - 1);
+    double b = tr0 ? best[(int64_t)t * nseg + blockIdx.x] : 0.0;
+    int ch = tr0 ? chosen[hs] : 0;
+    for (int k = 0; k < ntr; k++)
+        if (s_s2[k] > b) { b = s_s2[k]; ch = tr0 + k; }
+    best[(int64_t)t * nseg + blockIdx.x] = b;
+    chosen[hs] = ch;
+}
+
+// Keys of the chosen try: from the projections when all tries were held at once, else by
+// projecting onto the chosen direction again.
+template <bool VEC>
+__global__ __launch_bounds__(256) void k_try_keys(const float *__restrict__ X, int d, const float *__restrict__ R,
+                                                  int64_t H, int n_try, const SegDesc *__restrict__ segs,
+                                                  const ChunkDesc *__restrict__ subs, const int32_t *__restrict__ perm,
+                                                  int64_t n, const double *__restrict__ praw,
+                                                  const int32_t *__restrict__ chosen, uint64_t *__restrict__ keys) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    const int t = blockIdx.y, tid = threadIdx.x;
+    const ChunkDesc c = subs[blockIdx.x];
+    const int64_t hs = (int64_t)t * H + (segs[c.seg].heap - 1);
+    const int ch = chosen[hs];
+    uint64_t *kk = keys + (int64_t)t * n + c.start;
+    if (praw) {
+        if (tid < c.len) kk[tid] = key_of(praw[((int64_t)ch * gridDim.y + t) * n + c.start + tid]);
+        return;
+    }
+    const int ds = (d + 3) & ~3, g = tid & 7, pt = tid >> 3;
+    double *s_rd = reinterpret_cast<double *>(smem);
+    stage_tries<1>(R + hs * n_try * (int64_t)d, ch, n_try, d, ds, s_rd);
+    __syncthreads();
+    const int32_t *pp = perm + (int64_t)t * n + c.start;
+    for (int base = 0; base < c.len; base += 64) {
+        const int ia = base + pt, ib = ia + 32;
+        const float *const x[2] = {X + (int64_t)pp[ia < c.len ? ia : 0] * d, X + (int64_t)pp[ib < c.len ? ib : 0] * d};
+        double p[2];
+        group8_dots<VEC, 1, 2>(x, s_rd, ds, d, g, p);
+        if (g == 0 && ia < c.len) kk[ia] = key_of(p[0]);
+        if (g == 0 && ib < c.len) kk[ib] = key_of(p[1]);
+    }
+}
+
+// Tries projected per read of the rows: at most five (their sums take 80 registers), their
+// directions within 80 KB of LDS, evenly spread over the passes.
+static int try_width(int n_try, int d) {
+    const int ds = (d + 3) & ~3;
+    int most = (int)(80 * 1024 / (8 * (size_t)ds));
+    most = most > 5 ? 5 : most < 2 ? 2 : most;
+    const int passes = (n_try + most - 1) / most;
+    const int w = (n_try + passes - 1) / passes;
+    return w < 2 ? 2 : w;
+}
+
+size_t level_try_lds(int max_m, int d, int n_try) {
+    const size_t mp = (size_t)((max_m + 1) & ~1), ds = (size_t)((d + 3) & ~3);
+    return 8 * (try_width(n_try, d) * ds + n_try * mp + n_try) + 4 * (mp + 4);
+}
+
+template <typename F>
+static void with_tries(bool vec, int w, const F &go) {
+    auto nt = [&](auto v) {
+        constexpr bool V = decltype(v)::value;
+        if (w == 2) go(std::integral_constant<bool, V>{}, std::integral_constant<int, 2>{});
+        else if (w == 3) go(std::integral_constant<bool, V>{}, std::integral_constant<int, 3>{});
+        else if (w == 4) go(std::integral_constant<bool, V>{}, std::integral_constant<int, 4>{});
+        else go(std::integral_constant<bool, V>{}, std::integral_constant<int, 5>{});
+    };
+    if (vec) nt(std::true_type{});
+    else nt(std::false_type{});
+}
+
+void launch_level_try(hipStream_t s, bool vec, const float *X, int d, const float *R, int64_t H, int n_try,
+                      const SegDesc *segs, int nseg, int max_m, int T, const int32_t *pin, int32_t *pout, int64_t n,
+                      double *split, int32_t *split_idx, int32_t *chosen, int32_t *err) {
+    const size_t lds = level_try_lds(max_m, d, n_try);
+    // a workgroup's rows per step are a quarter of its threads: small nodes take small workgroups
+    const int threads = max_m <= 64 ? 64 : max_m <= 128 ? 128 : 256;
+    with_tries(vec, try_width(n_try, d), [&](auto v, auto w) {
+        auto kern = k_level_try<decltype(v)::value, decltype(w)::value>;
+        hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipLaunchKernelGGL(kern, dim3(nseg, T), dim3(threads), lds, s, X, d, R, H, n_try, (max_m + 1) & ~1, segs, pin,
+                           pout, n, split, split_idx, chosen, err);
+    });
+    launch_check(s, "k_level_try");
+}
+
+// Scores the tries of every node of a level over many blocks: `chosen` and the chosen try's
+// keys ([T][n], by position).
+void launch_level_score(hipStream_t s, bool vec, const float *X, int d, const float *R, int64_t H, int n_try,
+                        const SegDesc *segs, int nseg, const ChunkDesc *subs, int nsub, int T, const int32_t *pin,
+                        int64_t n, const TryBufs &tb, int32_t *chosen, uint64_t *keys) {
+    const dim3 gp(nsub, T);
+    const size_t ds = (size_t)((d + 3) & ~3);
+    for (int tr0 = 0; tr0 < n_try; tr0 += tb.group) {
+        const int ntr = std::min(tb.group, n_try - tr0);
+        with_tries(vec, try_width(ntr, d), [&](auto v, auto w) {
+            constexpr int NT = decltype(w)::value;
+            auto kern = k_try_proj<decltype(v)::value, NT>;
+            const size_t lds = 8 * NT * (ds + kTrySub);
+            hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            hipLaunchKernelGGL(kern, gp, dim3(256), lds, s, X, d, R, H, n_try, tr0, ntr, segs, subs, pin, n, tb.praw,
+                               tb.part);
+        });
+        launch_check(s, "k_try_proj");
+        hipLaunchKernelGGL(k_try_mean, dim3((nseg + 3) / 4, T, ntr), dim3(256), 0, s, segs, nseg, nsub, tb.part, tb.mean);
+        launch_check(s, "k_try_mean");
+        hipLaunchKernelGGL(k_try_dev, gp, dim3(256), 0, s, subs, ntr, tb.praw, n, tb.mean, nseg, tb.part);
+        launch_check(s, "k_try_dev");
+        hipLaunchKernelGGL(k_try_pick, dim3(nseg, T), dim3(256), 0, s, segs, nsub, tr0, ntr, tb.part, tb.best, H, chosen);
+        launch_check(s, "k_try_pick");
+    }
+    const bool held = tb.group >= n_try;
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, gp, dim3(256), held ? 0 : 8 * ds, s, X, d, R, H, n_try, segs, subs, pin, n,
+                           held ? tb.praw : nullptr, chosen, keys);
+    };
+    if (vec) go(k_try_keys<true>);
+    else go(k_try_keys<false>);
+    launch_check(s, "k_try_keys");
 }
 
 __global__ void k_copy_segments(const LeafDesc *__restrict__ segs, int nseg,
@@ -1578,29 +1862,25 @@ void launch_level_small(hipStream_t s, bool vec, const float *X, int d, const fl
 size_t cand_bytes() { return sizeof(Cand); }
 
 template <bool VEC>
-static void proj_chunks(hipStream_t s, dim3 gc, const float *X, int d, const float *R, int64_t H, int n_try,
+static void proj_chunks(hipStream_t s, dim3 gc, const float *X, int d, const float *R, int64_t H,
                         const SegDesc *segs, const ChunkDesc *chunks, const int32_t *pin, int64_t n,
-                        const LargeBufs &b, int nseg, int mode, int tr, const LevelLink &lk) {
+                        const LargeBufs &b, int nseg, const LevelLink &lk) {
     const size_t ds = (size_t)((d + 3) & ~3);
     const size_t lds = d > 1024 ? 0 : lk.look ? 3 * ds * sizeof(double) : ds * sizeof(float);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, gc, dim3(256), lds, s, X, d, R, H, segs, chunks, pin, n, nseg, b.keys, b.hist, lk.look,
+                           lk.ahead, lk.xq, lk.dq);
+    };
     const bool q8 = lk.xq != nullptr;
-    if (lk.look && q8)
-        hipLaunchKernelGGL((k_proj_chunks<VEC, true, true>), gc, dim3(256), lds, s, X, d, R, H, n_try, segs, chunks,
-                           pin, n, b.state, nseg, mode, tr, b.keys, b.praw, b.hist, lk.look, lk.ahead, lk.xq, lk.dq);
-    else if (lk.look)
-        hipLaunchKernelGGL((k_proj_chunks<VEC, true>), gc, dim3(256), lds, s, X, d, R, H, n_try, segs, chunks, pin, n,
-                           b.state, nseg, mode, tr, b.keys, b.praw, b.hist, lk.look, lk.ahead, lk.xq, lk.dq);
-    else if (q8)
-        hipLaunchKernelGGL((k_proj_chunks<VEC, false, true>), gc, dim3(256), lds, s, X, d, R, H, n_try, segs, chunks,
-                           pin, n, b.state, nseg, mode, tr, b.keys, b.praw, b.hist, lk.look, lk.ahead, lk.xq, lk.dq);
-    else
-        hipLaunchKernelGGL((k_proj_chunks<VEC, false>), gc, dim3(256), lds, s, X, d, R, H, n_try, segs, chunks, pin, n,
-                           b.state, nseg, mode, tr, b.keys, b.praw, b.hist, lk.look, lk.ahead, lk.xq, lk.dq);
+    if (lk.look && q8) go(k_proj_chunks<VEC, true, true>);
+    else if (lk.look) go(k_proj_chunks<VEC, true>);
+    else if (q8) go(k_proj_chunks<VEC, false, true>);
+    else go(k_proj_chunks<VEC, false>);
     launch_check(s, "k_proj_chunks");
 }
 
 void launch_level_large(hipStream_t s, bool vec, const float *X, int d, const float *R, int64_t H,
-                        int n_try, const SegDesc *segs, int nseg, const ChunkDesc *chunks, int nchunk,
+                        const SegDesc *segs, int nseg, const ChunkDesc *chunks, int nchunk,
                         int T, const int32_t *pin, int32_t *pout, int64_t n, double *split,
                         int32_t *split_idx, int32_t *chosen, int32_t *err, const LargeBufs &b0,
                         double proj_bytes, const LevelLink &lk) {
@@ -1617,23 +1897,6 @@ void launch_level_large(hipStream_t s, bool vec, const float *X, int d, const fl
     if (lk.hist_next) fill_u32(lk.hist_next, (int64_t)kDigitBins * lk.nseg_next * T, 0, s);
     fill_u32(b.cand_cnt, (int64_t)nseg * T, 0, s);
     launch_check(s, "select memsets");
-    if (n_try > 1) {
-        for (int tr = 0; tr < n_try; tr++) {
-            {
-                ProfScope ps(s, "proj_try", proj_bytes, 0);
-                if (vec) proj_chunks<true>(s, gc, X, d, R, H, n_try, segs, chunks, pin, n, b, nseg, 1, tr, LevelLink{});
-                else proj_chunks<false>(s, gc, X, d, R, H, n_try, segs, chunks, pin, n, b, nseg, 1, tr, LevelLink{});
-            }
-            for (int what = 0; what < 2; what++) {
-                hipLaunchKernelGGL(k_chunk_sum, gc, dim3(256), 0, s, chunks, nchunk, segs, b.praw, n, b.state,
-                                   nseg, what, b.part);
-                launch_check(s, "k_chunk_sum");
-                hipLaunchKernelGGL(k_seg_sum, dim3((nseg + 63) / 64, T), dim3(64), 0, s, segs, nseg, nchunk, b.part,
-                                   b.state, what, tr);
-                launch_check(s, "k_seg_sum");
-            }
-        }
-    }
     if (lk.roots) {  // every tree's root projections from one read of X, then the first digit
         ProfScope ps(s, "proj_roots", proj_bytes, 0);
         hipLaunchKernelGGL(k_proj_root, dim3(nchunk, kChunk / 64), dim3(256), 0, s, X, d, R, H, T, segs, chunks,
@@ -1642,10 +1905,14 @@ void launch_level_large(hipStream_t s, bool vec, const float *X, int d, const fl
         hipLaunchKernelGGL(k_sel_pass, gc, dim3(256), 0, s, chunks, b.keys, pin, n, b.state, nseg, b.hist, b.cand,
                            b.cand_cnt, b.lcount, nchunk);
         launch_check(s, "k_sel_pass");
+    } else if (lk.keys_ready) {
+        hipLaunchKernelGGL(k_sel_pass, gc, dim3(256), 0, s, chunks, b.keys, pin, n, b.state, nseg, b.hist, b.cand,
+                           b.cand_cnt, b.lcount, nchunk);
+        launch_check(s, "k_sel_pass");
     } else if (!lk.keys_in) {
         ProfScope ps(s, lk.look ? "proj_chunks_x3" : "proj_chunks", proj_bytes, 0);
-        if (vec) proj_chunks<true>(s, gc, X, d, R, H, n_try, segs, chunks, pin, n, b, nseg, 0, 0, lk);
-        else proj_chunks<false>(s, gc, X, d, R, H, n_try, segs, chunks, pin, n, b, nseg, 0, 0, lk);
+        if (vec) proj_chunks<true>(s, gc, X, d, R, H, segs, chunks, pin, n, b, nseg, lk);
+        else proj_chunks<false>(s, gc, X, d, R, H, segs, chunks, pin, n, b, nseg, lk);
     }
     {
         ProfScope ps(s, "select_passes", 0, 0);

@@ -20,11 +20,18 @@ namespace rpf {
 // ---- launchers defined in build_kernels.hip / knn_kernels.hip
 size_t cand_bytes();
 size_t level_small_lds(int max_m, int d, int n_try);
+size_t level_try_lds(int max_m, int d, int n_try);
+void launch_level_try(hipStream_t s, bool vec, const float *X, int d, const float *R, int64_t H, int n_try,
+                      const SegDesc *segs, int nseg, int max_m, int T, const int32_t *pin, int32_t *pout, int64_t n,
+                      double *split, int32_t *split_idx, int32_t *chosen, int32_t *err);
+void launch_level_score(hipStream_t s, bool vec, const float *X, int d, const float *R, int64_t H, int n_try,
+                        const SegDesc *segs, int nseg, const ChunkDesc *subs, int nsub, int T, const int32_t *pin,
+                        int64_t n, const TryBufs &tb, int32_t *chosen, uint64_t *keys);
 void launch_level_small(hipStream_t s, bool vec, const float *X, int d, const float *R, int64_t H, int n_try,
                         const SegDesc *segs, int nseg, int max_m, int T, const int32_t *pin, int32_t *pout,
                         int64_t n, double *split, int32_t *split_idx, int32_t *chosen, int32_t *err,
                         const LevelLink &lk);
-void launch_level_large(hipStream_t s, bool vec, const float *X, int d, const float *R, int64_t H, int n_try,
+void launch_level_large(hipStream_t s, bool vec, const float *X, int d, const float *R, int64_t H,
                         const SegDesc *segs, int nseg, const ChunkDesc *chunks, int nchunk, int T,
                         const int32_t *pin, int32_t *pout, int64_t n, double *split, int32_t *split_idx,
                         int32_t *chosen, int32_t *err, const LargeBufs &b, double proj_bytes,
@@ -292,13 +299,15 @@ namespace rpf {
 struct LevelPlan {
     std::vector<SegDesc> segs;     // internal nodes
     std::vector<ChunkDesc> chunks; // multi-block path
+    std::vector<ChunkDesc> subs;   // tries scored over many blocks: pieces of kTrySub members
     std::vector<LeafDesc> copy;    // leaves formed at or before this level (carried over)
     std::vector<LookDesc> look;    // per internal node: its children at the next level
     std::vector<int32_t> hbase;    // per internal node: its data set's first heap slot
     int max_m = 0;
     bool large = false;
+    bool tries = false;  // several tries per node, scored over many blocks (else in one workgroup)
     bool lead = false, fed = false;  // linked pair: the lead also makes the fed level's keys
-    int64_t seg_off = 0, chunk_off = 0, copy_off = 0;  // offsets into the device descriptor arrays
+    int64_t seg_off = 0, chunk_off = 0, copy_off = 0, sub_off = 0;  // offsets into the device descriptor arrays
 };
 }  // namespace rpf
 
@@ -328,6 +337,7 @@ struct rpf_forest {
     // descriptors
     SegDesc *d_segs = nullptr;
     ChunkDesc *d_chunks = nullptr;
+    ChunkDesc *d_subs = nullptr;
     LeafDesc *d_leaves = nullptr;
     LeafDesc *d_copy = nullptr;
     LookDesc *d_look = nullptr;  // per internal node of every level, indexed like d_segs
@@ -341,6 +351,8 @@ struct rpf_forest {
     // the closed-form plan of the build, kept so the build launches can be replayed
     std::vector<rpf::LevelPlan> levels;
     rpf::LargeBufs lb{};         // temporaries of the multi-block levels
+    rpf::TryBufs tb{};           // temporaries of the levels that score tries over many blocks
+    int try_cap = 0;             // nodes up to this size score their tries in one workgroup
     std::vector<void *> tmps;    // their blocks (released after a one-shot build)
     int lds_max = 0;
     // persistent subtree schedule (RPF_BUILD_SUBTREES): levels sub_level .. L-1 in one launch
@@ -471,7 +483,7 @@ static void pin_give(int k) {
 // cycles reuse device blocks instead of mapping fresh pages; callers synchronise first
 static void free_forest_memory(rpf_forest *f) {
     void *ptrs[] = {f->X, f->R, f->split, f->split_idx, f->chosen, f->perm[0], f->perm[1], f->leaf_of,
-                    f->centroid, f->Xc, f->nrm, f->err, f->heap_leaf, f->d_segs, f->d_chunks, f->d_leaves,
+                    f->centroid, f->Xc, f->nrm, f->err, f->heap_leaf, f->d_segs, f->d_chunks, f->d_subs, f->d_leaves,
                     f->d_copy, f->d_look, f->d_jobs, f->stats, f->d_batch_off, f->Xq, f->qn, f->d_sub_items,
                     f->sub_next};
     for (void *p : ptrs) cache_free_idle(p);
@@ -563,7 +575,7 @@ static rpf_status prepare_forest(const int64_t *sizes, int count, int32_t d, con
                 const rpf_batch_entry &r = roots[nd.root];
                 if (nd.size > n0 && l < r.depth) {
                     node_seg[q] = (int32_t)levels[l].segs.size();
-                    levels[l].segs.push_back(SegDesc{nd.off, (int32_t)nd.size, (int32_t)(r.heap_base + nd.heap), 0, 0});
+                    levels[l].segs.push_back(SegDesc{nd.off, (int32_t)nd.size, (int32_t)(r.heap_base + nd.heap), 0, 0, 0, 0});
                     levels[l].hbase.push_back((int32_t)r.heap_base);
                     levels[l].max_m = std::max<int>(levels[l].max_m, (int)nd.size);
                     next.push_back({2 * nd.heap, nd.off, nd.size / 2, nd.root});
@@ -591,10 +603,21 @@ static rpf_status prepare_forest(const int64_t *sizes, int count, int32_t d, con
     const int lds_max = lds_limit(dev);
     int small_max = kLarge;
     while (small_max > 2 && level_small_lds(small_max, d, n_try) > (size_t)lds_max) small_max /= 2;
+    // several tries per node: nodes of up to try_cap members are scored in one workgroup, whose
+    // LDS holds every try's projections (64 KB, or 32 KB beside long directions, so that at
+    // least two workgroups share a CU); larger ones over many blocks
+    int try_cap = 0;
+    if (n_try > 1) {
+        const size_t lim = std::max<size_t>(64 * 1024, level_try_lds(0, d, n_try) + 32 * 1024);
+        try_cap = 512;
+        while (try_cap >= 16 && level_try_lds(try_cap, d, n_try) > lim) try_cap /= 2;
+        if (try_cap < 16) try_cap = 0;
+    }
     int64_t max_seg_large = 0, max_chunk_large = 0;
     int64_t nseg_tot = 0, nchunk_tot = 0, ncopy_tot = 0;
     for (auto &lv : levels) {
         lv.large = lv.max_m > small_max;
+        lv.tries = n_try > 1 && (lv.large || lv.max_m > try_cap);
         lv.seg_off = nseg_tot;
         lv.copy_off = ncopy_tot;
         lv.chunk_off = nchunk_tot;
@@ -670,12 +693,59 @@ static rpf_status prepare_forest(const int64_t *sizes, int count, int32_t d, con
     uint64_t tmp_bytes = 0;
     if (max_seg_large > 0) {
         tmp_bytes += (uint64_t)T * n * 8;                                      // keys
-        if (n_try > 1) tmp_bytes += (uint64_t)T * n * 8;                       // praw
         tmp_bytes += (uint64_t)T * max_seg_large * (sizeof(SelState) + 4 * kDigitBins + cand_bytes() * kCandCap + 4);
-        tmp_bytes += (uint64_t)T * max_chunk_large * (4 + 8);
+        tmp_bytes += (uint64_t)T * max_chunk_large * 4;
     }
     if (any_link) tmp_bytes += (uint64_t)T * n * (16 + 8);                    // ahead, keys2
     if (any_large_fed) tmp_bytes += (uint64_t)T * max_seg_large * 4 * kDigitBins;  // hist2
+    // levels that score tries over many blocks: the projections of `try_group` tries at once
+    // (all of them where they fit 4 GiB and the budget), the sums' partials in the norms array
+    // (written after the last level) where they fit it.  A budget that holds no projections
+    // beside a forest without multi-block levels leaves the scoring to k_level_small.
+    int try_group = 0;
+    int64_t nsub_tot = 0, max_seg_try = 0, max_sub_try = 0;
+    bool try_scratch = false;  // the partials need memory of their own
+    if (n_try > 1) {
+        auto scan = [&]() {
+            max_seg_try = max_sub_try = 0;
+            for (auto &lv : levels) {
+                if (!lv.tries) continue;
+                int64_t subs = 0;
+                for (auto &sg : lv.segs) subs += (sg.size + kTrySub - 1) / kTrySub;
+                max_seg_try = std::max<int64_t>(max_seg_try, (int64_t)lv.segs.size());
+                max_sub_try = std::max(max_sub_try, subs);
+            }
+        };
+        auto scratch = [&](int G) { return (uint64_t)T * 8 * (G * max_sub_try + (G + 1) * max_seg_try); };
+        auto need = [&](int G) {
+            if (!max_seg_try) return (uint64_t)0;
+            const uint64_t praw = (uint64_t)G * T * n * 8, keys = max_seg_large > 0 ? 0 : (uint64_t)T * n * 8;
+            return praw + keys + (scratch(G) > (uint64_t)T * n * 8 ? scratch(G) : 0);
+        };
+        scan();
+        try_group = std::min(n_try, 16);
+        while (try_group > 1 && (uint64_t)try_group * T * n * 8 > ((uint64_t)4 << 30)) try_group--;
+        if (p->mem_budget_bytes) {
+            while (try_group > 1 && bytes + tmp_bytes + need(try_group) > p->mem_budget_bytes) try_group--;
+            if (bytes + tmp_bytes + need(try_group) > p->mem_budget_bytes) {
+                for (auto &lv : levels) lv.tries = lv.large;
+                scan();
+            }
+        }
+        tmp_bytes += need(try_group);
+        try_scratch = max_seg_try && scratch(try_group) > (uint64_t)T * n * 8;
+        for (auto &lv : levels) {
+            if (!lv.tries) continue;
+            lv.sub_off = nsub_tot;
+            for (auto &sg : lv.segs) {
+                sg.sub0 = (int32_t)lv.subs.size();
+                for (int64_t q = 0; q < sg.size; q += kTrySub)
+                    lv.subs.push_back(ChunkDesc{sg.off + q, (int32_t)std::min<int64_t>(kTrySub, sg.size - q),
+                                                (int32_t)(&sg - lv.segs.data())});
+            }
+            nsub_tot += (int64_t)lv.subs.size();
+        }
+    }
     if (p->mem_budget_bytes && bytes + tmp_bytes > p->mem_budget_bytes)
         return fail(RPF_ENOMEM, "rpf_build: forest needs " + std::to_string(bytes + tmp_bytes) +
                                     " bytes, over mem_budget_bytes");
@@ -730,6 +800,7 @@ static rpf_status prepare_forest(const int64_t *sizes, int count, int32_t d, con
     RPF_ALLOC(f->d_batch_off, ((size_t)count + 1) * sizeof(int64_t));
     if (nseg_tot) RPF_ALLOC(f->d_segs, nseg_tot * sizeof(SegDesc));
     if (nchunk_tot) RPF_ALLOC(f->d_chunks, nchunk_tot * sizeof(ChunkDesc));
+    if (nsub_tot) RPF_ALLOC(f->d_subs, nsub_tot * sizeof(ChunkDesc));
     RPF_ALLOC(f->d_leaves, nleaf * sizeof(LeafDesc));
     if (ncopy_tot) RPF_ALLOC(f->d_copy, ncopy_tot * sizeof(LeafDesc));
     if (nseg_tot && any_link) RPF_ALLOC(f->d_look, nseg_tot * sizeof(LookDesc));
@@ -751,7 +822,7 @@ static rpf_status prepare_forest(const int64_t *sizes, int count, int32_t d, con
 
     // ---- descriptors (host copies stay alive until the synchronisation below)
     std::vector<SegDesc> all_segs;
-    std::vector<ChunkDesc> all_chunks;
+    std::vector<ChunkDesc> all_chunks, all_subs;
     std::vector<LeafDesc> all_copy;
     std::vector<LookDesc> all_look;
     for (auto &lv : levels) {
@@ -759,6 +830,7 @@ static rpf_status prepare_forest(const int64_t *sizes, int count, int32_t d, con
         lv.look.resize(lv.segs.size(), LookDesc{{-1, -1}, {0, 0}});
         all_look.insert(all_look.end(), lv.look.begin(), lv.look.end());
         all_chunks.insert(all_chunks.end(), lv.chunks.begin(), lv.chunks.end());
+        all_subs.insert(all_subs.end(), lv.subs.begin(), lv.subs.end());
         all_copy.insert(all_copy.end(), lv.copy.begin(), lv.copy.end());
     }
     std::vector<int32_t> hl((size_t)LB + 1, -1);
@@ -770,6 +842,7 @@ static rpf_status prepare_forest(const int64_t *sizes, int count, int32_t d, con
     if (nseg_tot) hipMemcpyAsync(f->d_segs, all_segs.data(), nseg_tot * sizeof(SegDesc), hipMemcpyHostToDevice, s);
     if (nchunk_tot)
         hipMemcpyAsync(f->d_chunks, all_chunks.data(), nchunk_tot * sizeof(ChunkDesc), hipMemcpyHostToDevice, s);
+    if (nsub_tot) hipMemcpyAsync(f->d_subs, all_subs.data(), nsub_tot * sizeof(ChunkDesc), hipMemcpyHostToDevice, s);
     if (ncopy_tot) hipMemcpyAsync(f->d_copy, all_copy.data(), ncopy_tot * sizeof(LeafDesc), hipMemcpyHostToDevice, s);
     if (f->d_look) hipMemcpyAsync(f->d_look, all_look.data(), nseg_tot * sizeof(LookDesc), hipMemcpyHostToDevice, s);
     hipMemcpyAsync(f->d_leaves, leaves.data(), nleaf * sizeof(LeafDesc), hipMemcpyHostToDevice, s);
@@ -791,14 +864,24 @@ static rpf_status prepare_forest(const int64_t *sizes, int count, int32_t d, con
     bool ok = true;
     if (max_seg_large > 0) {
         ok &= talloc((void **)&lb.keys, (size_t)T * n * 8);
-        if (n_try > 1) ok &= talloc((void **)&lb.praw, (size_t)T * n * 8);
         ok &= talloc((void **)&lb.state, (size_t)T * max_seg_large * sizeof(SelState));
         ok &= talloc((void **)&lb.hist, (size_t)T * max_seg_large * 4 * kDigitBins);
         ok &= talloc((void **)&lb.cand, (size_t)T * max_seg_large * cand_bytes() * kCandCap);
         ok &= talloc((void **)&lb.cand_cnt, (size_t)T * max_seg_large * 4);
         ok &= talloc((void **)&lb.lcount, (size_t)T * max_chunk_large * 4);
-        ok &= talloc((void **)&lb.part, (size_t)T * max_chunk_large * 8);
     }
+    if (max_seg_try > 0) {
+        TryBufs &tb = f->tb;
+        tb.group = try_group;
+        if (!lb.keys) ok &= talloc((void **)&lb.keys, (size_t)T * n * 8);
+        ok &= talloc((void **)&tb.praw, (size_t)try_group * T * n * 8);
+        tb.part = reinterpret_cast<double *>(f->nrm);
+        if (try_scratch)
+            ok &= talloc((void **)&tb.part, (size_t)T * 8 * (try_group * max_sub_try + (try_group + 1) * max_seg_try));
+        tb.mean = tb.part + (int64_t)try_group * T * max_sub_try;
+        tb.best = tb.mean + (int64_t)try_group * T * max_seg_try;
+    }
+    f->try_cap = try_cap;
     if (any_link) {
         ok &= talloc((void **)&lb.ahead, (size_t)T * n * 16);
         ok &= talloc((void **)&lb.keys2, (size_t)T * n * 8);
@@ -908,15 +991,30 @@ static void build_launches(rpf_forest *f, hipStream_t s) {
         const double row_bytes = (lv.fed ? 8.0 : xb + 8) + 4 + (lv.lead ? 16.0 : 0.0);
         const double proj_bytes = lk.roots ? members * (4.0 * d) + (double)T * members * (8 + 16)
                                            : (double)T * members * (xb + 4 + 8 + (lv.lead ? 16.0 : 0.0));
+        int32_t *chosen = f->chosen;
+        if (lv.tries) {  // Alg. 2 over many blocks; the selection then starts from the keys
+            ProfScope ps(s, "proj_try", (double)T * members * (xb + 4 + 8.0 * n_try), 0);
+            launch_level_score(s, vec, f->X, d, f->R, H, n_try, f->d_segs + lv.seg_off, (int)lv.segs.size(),
+                               f->d_subs + lv.sub_off, (int)lv.subs.size(), T, pin, n, f->tb, f->chosen, f->lb.keys);
+            launch_check(s, "level_score");
+            chosen = nullptr;  // written by the scoring
+            if (lv.large) lk.keys_ready = true;
+            else lk.keys_in = f->lb.keys;
+        }
         if (!lv.large) {
             ProfScope ps(s, "level_small", (double)T * members * row_bytes, 0);
-            launch_level_small(s, vec, f->X, d, f->R, H, n_try, f->d_segs + lv.seg_off, (int)lv.segs.size(),
-                               lv.max_m, T, pin, pout, n, f->split, f->split_idx, f->chosen, f->err, lk);
+            if (n_try > 1 && !lv.tries && lv.max_m <= f->try_cap)
+                launch_level_try(s, vec, f->X, d, f->R, H, n_try, f->d_segs + lv.seg_off, (int)lv.segs.size(), lv.max_m,
+                                 T, pin, pout, n, f->split, f->split_idx, f->chosen, f->err);
+            else
+                launch_level_small(s, vec, f->X, d, f->R, H, lv.tries ? 1 : n_try, f->d_segs + lv.seg_off,
+                                   (int)lv.segs.size(), lv.max_m, T, pin, pout, n, f->split, f->split_idx, chosen,
+                                   f->err, lk);
             launch_check(s, "level_small");
         } else {
-            launch_level_large(s, vec, f->X, d, f->R, H, n_try, f->d_segs + lv.seg_off, (int)lv.segs.size(),
+            launch_level_large(s, vec, f->X, d, f->R, H, f->d_segs + lv.seg_off, (int)lv.segs.size(),
                                f->d_chunks + lv.chunk_off, (int)lv.chunks.size(), T, pin, pout, n, f->split,
-                               f->split_idx, f->chosen, f->err, f->lb, proj_bytes, lk);
+                               f->split_idx, chosen, f->err, f->lb, proj_bytes, lk);
             launch_check(s, "level_large");
         }
         cur ^= 1;
@@ -990,6 +1088,7 @@ static void release_temporaries(rpf_forest *f, hipStream_t s) {
     for (void *q : f->tmps) cache_free(q, s);
     f->tmps.clear();
     f->lb = LargeBufs{};
+    f->tb = TryBufs{};
 }
 
 static rpf_status build_impl(const float *X, const int64_t *sizes, int count, int32_t d, const rpf_params *p,

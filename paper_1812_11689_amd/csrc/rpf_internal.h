@@ -39,6 +39,8 @@ struct SegDesc {      // one internal node of a level (same shape for every tree
     int32_t heap;     // heap id h (root 1)
     int32_t chunk0;   // multi-block path: first chunk of this segment
     int32_t nchunk;   // multi-block path: number of chunks
+    int32_t sub0;     // levels that score several tries in many blocks: first sub-chunk
+    int32_t pad;
 };
 
 struct ChunkDesc {
@@ -63,11 +65,7 @@ struct SelState {
     int64_t rank;      // rank of the target among the keys that match the prefix
     int64_t cnt;       // number of keys that match the prefix
     int32_t mode;
-    int32_t chosen;    // chosen try (Alg. 2)
-    double best_s2;    // Alg. 2 running best spread
-    double s1;         // Alg. 2 scratch: sum of projections of the current try
     int32_t counted;   // 1: the final step filled the partition's left counts of the chunks
-    int32_t pad;
 };
 
 struct Ent {           // one pruning candidate: point index and bounds on its squared distance
@@ -106,6 +104,7 @@ struct LevelLink {
     int nseg_next = 0;
     const uint64_t *keys_in = nullptr;  // fed: keys made by the lead (null: project)
     uint32_t *hist_in = nullptr;        // fed multi-block level: histograms made by the lead
+    bool keys_ready = false;  // multi-block level: its keys are in the key buffer, without histograms
     bool roots = false;  // lead at the roots (identity permutation): one read of X for all trees
     // grid forests: the projections read each row from the int8 copy (k - 128, stride dq)
     // instead of X, a quarter of the bytes for the same binary32 values
@@ -131,13 +130,22 @@ struct LargeBufs {     // temporaries of the multi-block level path (and of the 
     uint64_t *keys2;      // keys made one level ahead
     uint32_t *hist2;      // their digit-0 histograms
     double2 *ahead;       // projections onto the children, by position
-    double *praw;
     SelState *state;
     uint32_t *hist;
     Cand *cand;
     uint32_t *cand_cnt;
     uint32_t *lcount;
-    double *part;
+};
+
+// Alg. 2 over many blocks (a level whose nodes are too large to be scored in one workgroup):
+// the projections of up to `group` tries at a time, and the partials of their canonical sums.
+constexpr int kTrySub = 256;  // members per block: an aligned piece of the sums' pairwise tree
+struct TryBufs {
+    int group = 0;            // tries projected per pass over the rows
+    double *praw = nullptr;   // [group][T][n]
+    double *part = nullptr;   // [group][T][sub-chunks of the level]
+    double *mean = nullptr;   // [group][T][segments of the level]
+    double *best = nullptr;   // [T][segments of the level]
 };
 
 struct TileJob {       // one MFMA tile: A rows x B rows (<= 32*MB each) of one tree
@@ -460,6 +468,70 @@ __device__ inline void group8_dot64r2(const float *__restrict__ xa, const float 
     }
     pa = v[0];
     pb = v[1];
+}
+
+// Four binary32 values at p, of which `left` (>= 1) exist; the others read as 0.  V16: p is
+// 16-byte aligned and left >= 4.  Otherwise one 16-byte load at 4-byte alignment (global
+// memory takes it) wherever the four values exist.
+struct __attribute__((packed, aligned(4))) Float4u { float x, y, z, w; };
+template <bool V16>
+__device__ inline float4 load4(const float *p, int left) {
+    if (V16) return *reinterpret_cast<const float4 *>(p);
+    if (left >= 4) {
+        const Float4u u = *reinterpret_cast<const Float4u *>(p);
+        return make_float4(u.x, u.y, u.z, u.w);
+    }
+    return make_float4(p[0], left > 1 ? p[1] : 0.f, left > 2 ? p[2] : 0.f, 0.f);
+}
+
+// Projections of NR rows onto NT directions r, r + rs, ... (binary32 values held as binary64 in
+// LDS, zero past d up to a multiple of four) from one read of each row; each projection is
+// computed exactly as group8_dot64 computes it (a column past d adds fma(0, 0, s) = s: the
+// sums are never -0).  p[k * NR + i]: direction k, row i.
+template <bool VEC, int NT, int NR>
+__device__ inline void group8_dots(const float *const (&x)[NR], const double *__restrict__ r, int rs, int d, int g,
+                                   double (&p)[NT * NR]) {
+    double s[NT * NR][4];
+#pragma unroll
+    for (int k = 0; k < NT * NR; k++) s[k][0] = s[k][1] = s[k][2] = s[k][3] = 0.0;
+#pragma unroll 2
+    for (int j = 4 * g; j < d; j += 32) {
+        float4 v[NR];
+#pragma unroll
+        for (int i = 0; i < NR; i++) v[i] = load4<VEC>(x[i] + j, d - j);
+#pragma unroll
+        for (int k = 0; k < NT; k++) {
+            const double2 ra = *reinterpret_cast<const double2 *>(r + k * rs + j);
+            const double2 rb = *reinterpret_cast<const double2 *>(r + k * rs + j + 2);
+#pragma unroll
+            for (int i = 0; i < NR; i++) {
+                double *q = s[k * NR + i];
+                q[0] = __builtin_fma((double)v[i].x, ra.x, q[0]);
+                q[1] = __builtin_fma((double)v[i].y, ra.y, q[1]);
+                q[2] = __builtin_fma((double)v[i].z, rb.x, q[2]);
+                q[3] = __builtin_fma((double)v[i].w, rb.y, q[3]);
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < NT * NR; k++) {
+        double w = (s[k][0] + s[k][1]) + (s[k][2] + s[k][3]);
+        w = w + shfl_xor_d(w, 1);
+        w = w + shfl_xor_d(w, 2);
+        w = w + shfl_xor_d(w, 4);
+        p[k] = w + 0.0;
+    }
+}
+
+// canon_sum of the 256 values v(0..255) by one wave (every lane returns it): lane l adds its
+// four neighbours 4l..4l+3, then the lanes combine in the same adjacent-pair order.
+template <typename F>
+__device__ inline double wave_canon256(const F &v) {
+    const int l = 4 * lane_id();
+    double w = (v(l) + v(l + 1)) + (v(l + 2) + v(l + 3));
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) w = w + shfl_xor_d(w, o);
+    return w;
 }
 
 // Projections of two rows xa, xb onto three directions r, r + rs, r + 2 rs (binary32 values

@@ -55,6 +55,44 @@ def test_build_matches_oracle(case):
     f.free()
 
 
+TRY_CASES = [
+    # several tries per node: sums over pieces of 256 members, nodes scored in one workgroup
+    # (up to 512 members) or over many blocks, 2 to 5 tries per read, more than 16 tries
+    # name, n, d, T, n0, n_try, kind, dup
+    ("try2_513_over_the_workgroup", 513, 7, 3, 40, 2, "aniso", 0),
+    ("try10_512_one_workgroup", 512, 49, 3, 20, 10, "aniso", 0),
+    ("try7_257_members", 257, 166, 2, 16, 7, "mixture", 0),
+    ("try3_pieces_at_the_root", 70_000, 5, 2, 64, 3, "aniso", 0),  # 274 pieces of 256
+    ("try19_two_groups", 9000, 18, 2, 30, 19, "mixture", 0),
+    ("try4_duplicates", 3000, 8, 2, 25, 4, "mixture", 7),
+    ("try2_d1100_long_rows", 1500, 1100, 1, 100, 2, "mixture", 0),
+    ("try5_n0_1", 61, 3, 2, 1, 5, "mixture", 0),
+]
+
+
+@pytest.mark.parametrize("case", TRY_CASES, ids=[c[0] for c in TRY_CASES])
+def test_tries_match_oracle(case):
+    test_build_matches_oracle(case)
+
+
+def test_tries_within_a_tight_memory_budget():
+    """A budget that leaves no room for the tries' projections still grows the same forest."""
+    from paper_1812_11689_amd import rpf
+    n, d, T, n0, n_try = 1500, 12, 2, 20, 4
+    x, R = problem(n, d, T, n0, n_try, seed=23, kind="aniso")
+    ref = oracle.build_forest(x, R, T, n0, n_try)
+    Xd, Rd = torch.from_numpy(x).cuda(), torch.from_numpy(np.ascontiguousarray(R[:T])).cuda()
+    f = rpf.build(Xd, T, n0, Rd, n_try=n_try)
+    budget = f.info()["device_bytes"] + T * n * 16 * 4  # and the query copies (rows padded to 16)
+    f.free()
+    f = rpf.build(Xd, T, n0, Rd, n_try=n_try, mem_budget_bytes=budget)
+    for t in range(T):
+        g = {k: v.cpu().numpy() for k, v in f.tree_dump(t).items()}
+        np.testing.assert_array_equal(g["perm"], ref.perm[t])
+        np.testing.assert_array_equal(g["chosen"], ref.chosen[t])
+    f.free()
+
+
 GRID_CASES = [
     # points on the 1/255 grid, built with RPF_DIST_U8GRID: the projections read each row from
     # the int8 copy (k - 128) instead of X and must give the same splits bit for bit
