@@ -1076,9 +1076,7 @@ __global__ __launch_bounds__(256) void k_proj_root(const float *__restrict__ X, 
 #pragma unroll
         for (int q = 0; q < 6; q++) {
             double w = (s[q][0] + s[q][1]) + (s[q][2] + s[q][3]);
-            w = w + shfl_xor_d(w, 1);
-            w = w + shfl_xor_d(w, 2);
-            w = w + shfl_xor_d(w, 4);
+            w = group8_add(w);
             p[q] = w + 0.0;
         }
         if (g == 0) {

@@ -99,9 +99,7 @@ __global__ __launch_bounds__(256) void k_exact_dist(const float *__restrict__ X,
 #pragma unroll
             for (int r = 0; r < 8; r++) {
                 double v = (s[r][0] + s[r][1]) + (s[r][2] + s[r][3]);
-                v = v + shfl_xor_d(v, 1);
-                v = v + shfl_xor_d(v, 2);
-                v = v + shfl_xor_d(v, 4);
+                v = group8_add(v);
                 if (r == g) mine = v;
             }
             const int qr = t * 8 + g;  // this lane writes query qr of the block

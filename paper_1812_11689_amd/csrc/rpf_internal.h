@@ -331,6 +331,26 @@ __device__ inline int mask_rank(uint64_t mask) {  // set bits of mask below this
 __device__ inline double shfl_xor_d(double v, int m) { return __shfl_xor(v, m, 64); }
 __device__ inline float shfl_xor_f(float v, int m) { return __shfl_xor(v, m, 64); }
 
+// Adjacent-pair sum over an aligned group of eight lanes (all active): the additions of
+// v + shfl_xor(v, 1), 2, 4, with the partner's value read through DPP in the vector unit
+// instead of the LDS crossbar (once a quad holds one value, the mirrored half row is lane
+// xor 4's).  A projection of a 49-column row spends more on these exchanges than on its fma.
+template <int CTRL>
+__device__ inline float dpp_read(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ inline double dpp_read(double v) {
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true));
+}
+template <typename T>
+__device__ inline T group8_add(T v) {
+    v = v + dpp_read<0xB1>(v);   // quad_perm 1,0,3,2
+    v = v + dpp_read<0x4E>(v);   // quad_perm 2,3,0,1
+    return v + dpp_read<0x141>(v);  // row_half_mirror
+}
+
 // exclusive scan over a 256-thread block (4 waves); s_w needs 4 words
 __device__ inline void block_excl_scan256(uint32_t v, uint32_t *s_w, uint32_t &excl, uint32_t &total) {
     // 256 threads = 4 waves
@@ -419,9 +439,7 @@ __device__ inline double group8_dot64(const float *__restrict__ x, const float *
         }
     }
     double v = (s0 + s1) + (s2 + s3);
-    v = v + shfl_xor_d(v, 1);
-    v = v + shfl_xor_d(v, 2);
-    v = v + shfl_xor_d(v, 4);
+    v = group8_add(v);
     return v + 0.0;
 }
 
@@ -461,9 +479,7 @@ __device__ inline void group8_dot64r2(const float *__restrict__ xa, const float 
 #pragma unroll
     for (int k = 0; k < 2; k++) {
         double w = (s[k][0] + s[k][1]) + (s[k][2] + s[k][3]);
-        w = w + shfl_xor_d(w, 1);
-        w = w + shfl_xor_d(w, 2);
-        w = w + shfl_xor_d(w, 4);
+        w = group8_add(w);
         v[k] = w + 0.0;
     }
     pa = v[0];
@@ -516,9 +532,7 @@ __device__ inline void group8_dots(const float *const (&x)[NR], const double *__
 #pragma unroll
     for (int k = 0; k < NT * NR; k++) {
         double w = (s[k][0] + s[k][1]) + (s[k][2] + s[k][3]);
-        w = w + shfl_xor_d(w, 1);
-        w = w + shfl_xor_d(w, 2);
-        w = w + shfl_xor_d(w, 4);
+        w = group8_add(w);
         p[k] = w + 0.0;
     }
 }
@@ -528,10 +542,10 @@ __device__ inline void group8_dots(const float *const (&x)[NR], const double *__
 template <typename F>
 __device__ inline double wave_canon256(const F &v) {
     const int l = 4 * lane_id();
-    double w = (v(l) + v(l + 1)) + (v(l + 2) + v(l + 3));
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) w = w + shfl_xor_d(w, o);
-    return w;
+    double w = group8_add((v(l) + v(l + 1)) + (v(l + 2) + v(l + 3)));
+    w = w + dpp_read<0x140>(w);  // row_mirror: lane xor 8's value once eight lanes hold one
+    w = w + shfl_xor_d(w, 16);
+    return w + shfl_xor_d(w, 32);
 }
 
 // Projections of two rows xa, xb onto three directions r, r + rs, r + 2 rs (binary32 values
@@ -583,9 +597,7 @@ __device__ inline void group8_dot64x3r2(const float *__restrict__ xa, const floa
 #pragma unroll
     for (int k = 0; k < 6; k++) {
         double w = (s[k][0] + s[k][1]) + (s[k][2] + s[k][3]);
-        w = w + shfl_xor_d(w, 1);
-        w = w + shfl_xor_d(w, 2);
-        w = w + shfl_xor_d(w, 4);
+        w = group8_add(w);
         p[k] = w + 0.0;
     }
 }
@@ -618,9 +630,7 @@ __device__ inline double group8_dot64_q8(const int8_t *__restrict__ x, const flo
         }
     }
     double v = (s[0] + s[1]) + (s[2] + s[3]);
-    v = v + shfl_xor_d(v, 1);
-    v = v + shfl_xor_d(v, 2);
-    v = v + shfl_xor_d(v, 4);
+    v = group8_add(v);
     return v + 0.0;
 }
 
@@ -673,9 +683,7 @@ __device__ inline void group8_dot64x3r2_q8(const int8_t *__restrict__ xa, const 
 #pragma unroll
     for (int k = 0; k < 6; k++) {
         double w = (s[k][0] + s[k][1]) + (s[k][2] + s[k][3]);
-        w = w + shfl_xor_d(w, 1);
-        w = w + shfl_xor_d(w, 2);
-        w = w + shfl_xor_d(w, 4);
+        w = group8_add(w);
         p[k] = w + 0.0;
     }
 }
@@ -703,9 +711,7 @@ __device__ inline double group8_dist64(const float *__restrict__ a, const float 
         }
     }
     double v = (s0 + s1) + (s2 + s3);
-    v = v + shfl_xor_d(v, 1);
-    v = v + shfl_xor_d(v, 2);
-    v = v + shfl_xor_d(v, 4);
+    v = group8_add(v);
     return v;
 }
 
@@ -731,9 +737,7 @@ __device__ inline float group8_dist32(const float *__restrict__ a, const float *
         }
     }
     float v = (s0 + s1) + (s2 + s3);
-    v = v + shfl_xor_f(v, 1);
-    v = v + shfl_xor_f(v, 2);
-    v = v + shfl_xor_f(v, 4);
+    v = group8_add(v);
     return v;
 }
 
@@ -771,14 +775,10 @@ __device__ inline void group8_dist32_64(const float *__restrict__ a, const float
         s3 = __builtin_fma(d3, d3, s3);
     }
     float v = (f0 + f1) + (f2 + f3);
-    v = v + shfl_xor_f(v, 1);
-    v = v + shfl_xor_f(v, 2);
-    v = v + shfl_xor_f(v, 4);
+    v = group8_add(v);
     D32 = v;
     double u = (s0 + s1) + (s2 + s3);
-    u = u + shfl_xor_d(u, 1);
-    u = u + shfl_xor_d(u, 2);
-    u = u + shfl_xor_d(u, 4);
+    u = group8_add(u);
     D64 = u;
 }
 
@@ -839,14 +839,10 @@ __device__ inline void group8_dist32_64x2(const float *__restrict__ a, const flo
 #pragma unroll
     for (int r = 0; r < 2; r++) {
         float v = (f[r][0] + f[r][1]) + (f[r][2] + f[r][3]);
-        v = v + shfl_xor_f(v, 1);
-        v = v + shfl_xor_f(v, 2);
-        v = v + shfl_xor_f(v, 4);
+        v = group8_add(v);
         D32[r] = v;
         double u = (s[r][0] + s[r][1]) + (s[r][2] + s[r][3]);
-        u = u + shfl_xor_d(u, 1);
-        u = u + shfl_xor_d(u, 2);
-        u = u + shfl_xor_d(u, 4);
+        u = group8_add(u);
         D64[r] = u;
     }
 }
@@ -898,9 +894,7 @@ __device__ inline void group8_dist64x2(const float *__restrict__ a, const float 
 #pragma unroll
     for (int r = 0; r < 2; r++) {
         double u = (s[r][0] + s[r][1]) + (s[r][2] + s[r][3]);
-        u = u + shfl_xor_d(u, 1);
-        u = u + shfl_xor_d(u, 2);
-        u = u + shfl_xor_d(u, 4);
+        u = group8_add(u);
         D64[r] = u;
     }
 }
@@ -954,9 +948,7 @@ __device__ inline void group8_dist64x4(const float *__restrict__ a, const float 
 #pragma unroll
     for (int r = 0; r < 4; r++) {
         double u = (s[r][0] + s[r][1]) + (s[r][2] + s[r][3]);
-        u = u + shfl_xor_d(u, 1);
-        u = u + shfl_xor_d(u, 2);
-        u = u + shfl_xor_d(u, 4);
+        u = group8_add(u);
         D64[r] = u;
     }
 }
