@@ -1111,18 +1111,16 @@ __global__ __launch_bounds__(256) void k_proj_root(const float *__restrict__ X, 
 //     of 256 members, which are aligned subtrees of the sums; then the level's selection runs
 //     from the chosen try's keys as on a fed level.
 
-// directions tr .. tr + NT - 1 of a node (binary64, zero past n_try and past d)
-template <int NT>
-__device__ inline void stage_tries(const float *__restrict__ Rn, int tr, int n_try, int d, int ds, double *s_rd) {
-#pragma unroll
-    for (int k = 0; k < NT; k++)
+// directions tr .. tr + cnt - 1 of a node (zero past n_try and past d)
+__device__ inline void stage_tries(const float *__restrict__ Rn, int tr, int cnt, int n_try, int d, int ds, float *s_rd) {
+    for (int k = 0; k < cnt; k++)
         for (int j = threadIdx.x; j < ds; j += blockDim.x)
-            s_rd[k * ds + j] = tr + k < n_try && j < d ? (double)Rn[(int64_t)(tr + k) * d + j] : 0.0;
+            s_rd[k * ds + j] = tr + k < n_try && j < d ? Rn[(int64_t)(tr + k) * d + j] : 0.f;
 }
 
 template <bool VEC, int NT>
-__global__ __launch_bounds__(256) void k_level_try(const float *__restrict__ X, int d, const float *__restrict__ R,
-                                                   int64_t H, int n_try, int mp, const SegDesc *__restrict__ segs,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_level_try(const float *__restrict__ X, int d, const float *__restrict__ R,
+                                                   int64_t H, int n_try, int st, int mp, const SegDesc *__restrict__ segs,
                                                    const int32_t *__restrict__ perm_in, int32_t *__restrict__ perm_out,
                                                    int64_t n, double *__restrict__ split, int32_t *__restrict__ split_idx,
                                                    int32_t *__restrict__ chosen, int32_t *__restrict__ err) {
@@ -1130,30 +1128,32 @@ __global__ __launch_bounds__(256) void k_level_try(const float *__restrict__ X, 
     const int t = blockIdx.y, tid = threadIdx.x, nthr = blockDim.x;
     const SegDesc sg = segs[blockIdx.x];
     const int m = sg.size, ds = (d + 3) & ~3;
-    double *s_rd = reinterpret_cast<double *>(smem);  // [NT][ds]
-    double *s_p = s_rd + NT * ds;                     // [n_try][mp], mp even
-    double *s_s2 = s_p + (int64_t)n_try * mp;         // [n_try]
+    float *s_rd = reinterpret_cast<float *>(smem);                // [st][ds]
+    double *s_p = reinterpret_cast<double *>(s_rd + st * ds);     // [n_try][mp], mp even
+    double *s_s2 = s_p + (int64_t)n_try * mp;                     // [n_try]
     int32_t *s_perm = reinterpret_cast<int32_t *>(s_s2 + n_try);  // [mp]
     uint32_t *s_w = reinterpret_cast<uint32_t *>(s_perm + mp);    // [4]
     const int32_t *pin = perm_in + (int64_t)t * n + sg.off;
     for (int i = tid; i < m; i += nthr) s_perm[i] = pin[i];
     const float *Rn = R + ((int64_t)t * H + (sg.heap - 1)) * n_try * (int64_t)d;
     const int g = tid & 7, pt = tid >> 3, per = nthr >> 3;
-    for (int tr = 0; tr < n_try; tr += NT) {
+    for (int t0 = 0; t0 < n_try; t0 += st) {
         __syncthreads();
-        stage_tries<NT>(Rn, tr, n_try, d, ds, s_rd);
+        stage_tries(Rn, t0, st, n_try, d, ds, s_rd);
         __syncthreads();
         for (int base = 0; base < m; base += 2 * per) {
             const int ia = base + pt, ib = ia + per;
             const float *const x[2] = {X + (int64_t)s_perm[ia < m ? ia : 0] * d, X + (int64_t)s_perm[ib < m ? ib : 0] * d};
-            double p[2 * NT];
-            group8_dots<VEC, NT, 2>(x, s_rd, ds, d, g, p);
+            for (int tr = t0; tr < t0 + st && tr < n_try; tr += NT) {  // the rows' later passes hit the caches
+                double p[2 * NT];
+                group8_dots<VEC, NT, 2>(x, s_rd + (tr - t0) * ds, ds, d, g, p);
 #pragma unroll
-            for (int k = 0; k < NT; k++)
-                if (g == k && tr + k < n_try) {
-                    if (ia < m) s_p[(tr + k) * mp + ia] = p[2 * k];
-                    if (ib < m) s_p[(tr + k) * mp + ib] = p[2 * k + 1];
-                }
+                for (int k = 0; k < NT; k++)
+                    if (g == k && tr + k < n_try) {
+                        if (ia < m) s_p[(tr + k) * mp + ia] = p[2 * k];
+                        if (ib < m) s_p[(tr + k) * mp + ib] = p[2 * k + 1];
+                    }
+            }
         }
     }
     __syncthreads();
@@ -1226,41 +1226,43 @@ __global__ __launch_bounds__(256) void k_level_try(const float *__restrict__ X, 
 // Projections of tries tr0 .. tr0 + ntr - 1 over one piece of a node, and the partial of each
 // try's sum.
 template <bool VEC, int NT>
-__global__ __launch_bounds__(256) void k_try_proj(const float *__restrict__ X, int d, const float *__restrict__ R,
-                                                  int64_t H, int n_try, int tr0, int ntr,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_try_proj(const float *__restrict__ X, int d, const float *__restrict__ R,
+                                                  int64_t H, int n_try, int st, int tr0, int ntr,
                                                   const SegDesc *__restrict__ segs, const ChunkDesc *__restrict__ subs,
                                                   const int32_t *__restrict__ perm, int64_t n,
                                                   double *__restrict__ praw, double *__restrict__ part) {
     extern __shared__ __align__(16) uint8_t smem[];
     const int ds = (d + 3) & ~3;
-    double *s_rd = reinterpret_cast<double *>(smem);  // [NT][ds]
-    double *s_p = s_rd + NT * ds;                     // [NT][kTrySub]
+    float *s_rd = reinterpret_cast<float *>(smem);             // [st][ds]
+    double *s_p = reinterpret_cast<double *>(s_rd + st * ds);  // [st][kTrySub]
     const int t = blockIdx.y, T = gridDim.y, tid = threadIdx.x;
     const ChunkDesc c = subs[blockIdx.x];
     const int32_t *pp = perm + (int64_t)t * n + c.start;
     const float *Rn = R + ((int64_t)t * H + (segs[c.seg].heap - 1)) * n_try * (int64_t)d;
     const int g = tid & 7, pt = tid >> 3;
-    for (int tr = 0; tr < ntr; tr += NT) {
+    for (int t0 = 0; t0 < ntr; t0 += st) {
         __syncthreads();
-        stage_tries<NT>(Rn, tr0 + tr, n_try, d, ds, s_rd);
+        stage_tries(Rn, tr0 + t0, st, n_try, d, ds, s_rd);
         __syncthreads();
         for (int base = 0; base < c.len; base += 64) {
             const int ia = base + pt, ib = ia + 32;
             const float *const x[2] = {X + (int64_t)pp[ia < c.len ? ia : 0] * d, X + (int64_t)pp[ib < c.len ? ib : 0] * d};
-            double p[2 * NT];
-            group8_dots<VEC, NT, 2>(x, s_rd, ds, d, g, p);
+            for (int tr = 0; tr < st; tr += NT) {  // the rows' later passes hit the caches
+                double p[2 * NT];
+                group8_dots<VEC, NT, 2>(x, s_rd + tr * ds, ds, d, g, p);
 #pragma unroll
-            for (int k = 0; k < NT; k++)
-                if (g == k) {
-                    s_p[k * kTrySub + ia] = ia < c.len ? p[2 * k] : 0.0;
-                    s_p[k * kTrySub + ib] = ib < c.len ? p[2 * k + 1] : 0.0;
-                }
+                for (int k = 0; k < NT; k++)
+                    if (g == k) {
+                        s_p[(tr + k) * kTrySub + ia] = ia < c.len ? p[2 * k] : 0.0;
+                        s_p[(tr + k) * kTrySub + ib] = ib < c.len ? p[2 * k + 1] : 0.0;
+                    }
+            }
         }
         __syncthreads();
-        for (int k = tid >> 6; k < NT && tr + k < ntr; k += 4) {
+        for (int k = tid >> 6; k < st && t0 + k < ntr; k += 4) {
             const double *pk = s_p + k * kTrySub;
             const double s1 = wave_canon256([&](int i) { return i < c.len ? pk[i] : 0.0; });
-            const int64_t row = (int64_t)(tr + k) * T + t;
+            const int64_t row = (int64_t)(t0 + k) * T + t;
             if ((tid & 63) == 0) part[row * gridDim.x + blockIdx.x] = s1;
             for (int i = tid & 63; i < c.len; i += 64) praw[row * n + c.start + i] = pk[i];
         }
@@ -1363,8 +1365,8 @@ __global__ __launch_bounds__(256) void k_try_keys(const float *__restrict__ X, i
         return;
     }
     const int ds = (d + 3) & ~3, g = tid & 7, pt = tid >> 3;
-    double *s_rd = reinterpret_cast<double *>(smem);
-    stage_tries<1>(R + hs * n_try * (int64_t)d, ch, n_try, d, ds, s_rd);
+    float *s_rd = reinterpret_cast<float *>(smem);
+    stage_tries(R + hs * n_try * (int64_t)d, ch, 1, n_try, d, ds, s_rd);
     __syncthreads();
     const int32_t *pp = perm + (int64_t)t * n + c.start;
     for (int base = 0; base < c.len; base += 64) {
@@ -1378,19 +1380,27 @@ __global__ __launch_bounds__(256) void k_try_keys(const float *__restrict__ X, i
 }
 
 // Tries projected per read of the rows: at most five (their sums take 80 registers), their
-// directions within 80 KB of LDS, evenly spread over the passes.
+// directions within 40 KB of LDS, evenly spread over the passes.
 static int try_width(int n_try, int d) {
     const int ds = (d + 3) & ~3;
-    int most = (int)(80 * 1024 / (8 * (size_t)ds));
+    int most = (int)(40 * 1024 / (4 * (size_t)ds));
     most = most > 5 ? 5 : most < 2 ? 2 : most;
     const int passes = (n_try + most - 1) / most;
     const int w = (n_try + passes - 1) / passes;
     return w < 2 ? 2 : w;
 }
 
+// Tries whose directions are staged together, a multiple of the width: at most 15, within
+// 24 KB (or one width, if that is longer).
+static int try_stage(int n_try, int d) {
+    const int w = try_width(n_try, d), ds = (d + 3) & ~3, passes = (n_try + w - 1) / w;
+    const int per = std::min(24 * 1024 / (4 * ds * w), 15 / w);
+    return w * std::max(1, std::min(per, passes));
+}
+
 size_t level_try_lds(int max_m, int d, int n_try) {
     const size_t mp = (size_t)((max_m + 1) & ~1), ds = (size_t)((d + 3) & ~3);
-    return 8 * (try_width(n_try, d) * ds + n_try * mp + n_try) + 4 * (mp + 4);
+    return 4 * try_stage(n_try, d) * ds + 8 * (n_try * mp + n_try) + 4 * (mp + 4);
 }
 
 template <typename F>
@@ -1415,8 +1425,8 @@ void launch_level_try(hipStream_t s, bool vec, const float *X, int d, const floa
     with_tries(vec, try_width(n_try, d), [&](auto v, auto w) {
         auto kern = k_level_try<decltype(v)::value, decltype(w)::value>;
         hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL(kern, dim3(nseg, T), dim3(threads), lds, s, X, d, R, H, n_try, (max_m + 1) & ~1, segs, pin,
-                           pout, n, split, split_idx, chosen, err);
+        hipLaunchKernelGGL(kern, dim3(nseg, T), dim3(threads), lds, s, X, d, R, H, n_try, try_stage(n_try, d),
+                           (max_m + 1) & ~1, segs, pin, pout, n, split, split_idx, chosen, err);
     });
     launch_check(s, "k_level_try");
 }
@@ -1433,9 +1443,10 @@ void launch_level_score(hipStream_t s, bool vec, const float *X, int d, const fl
         with_tries(vec, try_width(ntr, d), [&](auto v, auto w) {
             constexpr int NT = decltype(w)::value;
             auto kern = k_try_proj<decltype(v)::value, NT>;
-            const size_t lds = 8 * NT * (ds + kTrySub);
+            const int st = try_stage(ntr, d);
+            const size_t lds = st * (4 * ds + 8 * kTrySub);
             hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            hipLaunchKernelGGL(kern, gp, dim3(256), lds, s, X, d, R, H, n_try, tr0, ntr, segs, subs, pin, n, tb.praw,
+            hipLaunchKernelGGL(kern, gp, dim3(256), lds, s, X, d, R, H, n_try, st, tr0, ntr, segs, subs, pin, n, tb.praw,
                                tb.part);
         });
         launch_check(s, "k_try_proj");
@@ -1448,7 +1459,7 @@ void launch_level_score(hipStream_t s, bool vec, const float *X, int d, const fl
     }
     const bool held = tb.group >= n_try;
     auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, gp, dim3(256), held ? 0 : 8 * ds, s, X, d, R, H, n_try, segs, subs, pin, n,
+        hipLaunchKernelGGL(kern, gp, dim3(256), held ? 0 : 4 * ds, s, X, d, R, H, n_try, segs, subs, pin, n,
                            held ? tb.praw : nullptr, chosen, keys);
     };
     if (vec) go(k_try_keys<true>);

@@ -500,41 +500,45 @@ __device__ inline float4 load4(const float *p, int left) {
     return make_float4(p[0], left > 1 ? p[1] : 0.f, left > 2 ? p[2] : 0.f, 0.f);
 }
 
-// Projections of NR rows onto NT directions r, r + rs, ... (binary32 values held as binary64 in
-// LDS, zero past d up to a multiple of four) from one read of each row; each projection is
-// computed exactly as group8_dot64 computes it (a column past d adds fma(0, 0, s) = s: the
-// sums are never -0).  p[k * NR + i]: direction k, row i.
+// Projections of NR rows onto NT directions r, r + rs, ... (binary32 in LDS, 16-byte aligned,
+// zero past d up to a multiple of four) from one read of each row; each projection is computed
+// exactly as group8_dot64 computes it (a column past d adds fma(0, 0, s) = s: the sums are
+// never -0).  p[k * NR + i]: direction k, row i.
 template <bool VEC, int NT, int NR>
-__device__ inline void group8_dots(const float *const (&x)[NR], const double *__restrict__ r, int rs, int d, int g,
+__device__ inline void group8_dots(const float *const (&x)[NR], const float *__restrict__ r, int rs, int d, int g,
                                    double (&p)[NT * NR]) {
     double s[NT * NR][4];
 #pragma unroll
     for (int k = 0; k < NT * NR; k++) s[k][0] = s[k][1] = s[k][2] = s[k][3] = 0.0;
-#pragma unroll 2
-    for (int j = 4 * g; j < d; j += 32) {
-        float4 v[NR];
+    float4 v[NR];
+    int j = 4 * g;
+    if (j < d) {
 #pragma unroll
         for (int i = 0; i < NR; i++) v[i] = load4<VEC>(x[i] + j, d - j);
+    }
+#pragma unroll 1
+    for (; j < d; j += 32) {
+        float4 nv[NR];  // the next step's columns, in flight behind this step's arithmetic
+        const int jn = j + 32 < d ? j + 32 : j;
+#pragma unroll
+        for (int i = 0; i < NR; i++) nv[i] = load4<VEC>(x[i] + jn, d - jn);
 #pragma unroll
         for (int k = 0; k < NT; k++) {
-            const double2 ra = *reinterpret_cast<const double2 *>(r + k * rs + j);
-            const double2 rb = *reinterpret_cast<const double2 *>(r + k * rs + j + 2);
+            const float4 rv = *reinterpret_cast<const float4 *>(r + k * rs + j);
 #pragma unroll
             for (int i = 0; i < NR; i++) {
                 double *q = s[k * NR + i];
-                q[0] = __builtin_fma((double)v[i].x, ra.x, q[0]);
-                q[1] = __builtin_fma((double)v[i].y, ra.y, q[1]);
-                q[2] = __builtin_fma((double)v[i].z, rb.x, q[2]);
-                q[3] = __builtin_fma((double)v[i].w, rb.y, q[3]);
+                q[0] = __builtin_fma((double)v[i].x, (double)rv.x, q[0]);
+                q[1] = __builtin_fma((double)v[i].y, (double)rv.y, q[1]);
+                q[2] = __builtin_fma((double)v[i].z, (double)rv.z, q[2]);
+                q[3] = __builtin_fma((double)v[i].w, (double)rv.w, q[3]);
             }
         }
+#pragma unroll
+        for (int i = 0; i < NR; i++) v[i] = nv[i];
     }
 #pragma unroll
-    for (int k = 0; k < NT * NR; k++) {
-        double w = (s[k][0] + s[k][1]) + (s[k][2] + s[k][3]);
-        w = group8_add(w);
-        p[k] = w + 0.0;
-    }
+    for (int k = 0; k < NT * NR; k++) p[k] = group8_add((s[k][0] + s[k][1]) + (s[k][2] + s[k][3])) + 0.0;
 }
 
 // canon_sum of the 256 values v(0..255) by one wave (every lane returns it): lane l adds its
