@@ -58,3 +58,49 @@ def test_exact_knn_matches_oracle(case):
     fin = np.isfinite(rd)
     assert np.array_equal(np.isfinite(gd), fin)
     np.testing.assert_allclose(gd[fin], rd[fin], rtol=1e-5, atol=0)
+
+
+FILTER_CASES = [
+    # the filtered search: from 65 536 points on, or with many queries over fewer
+    # name, n, d, m, K, what
+    ("one_query", 65_536, 16, 1, 5, "mixture"),
+    ("tail_tiles_d33", 65_567, 33, 65, 20, "mixture"),
+    ("d97_four_ksteps", 66_001, 97, 33, 1, "aniso"),
+    ("d257_two_query_tiles", 65_600, 257, 40, 10, "mixture"),
+    ("d1024_one_query_tile", 65_540, 1024, 36, 7, "mixture"),
+    ("k256_many_queries", 8_000, 20, 200, 256, "mixture"),
+    ("more_than_the_points", 1_001, 6, 1_100, 256, "mixture"),
+    ("repeated_rows_overflow", 70_000, 8, 40, 30, "dup"),   # lists overflow: exhaustive kernels
+    ("far_from_the_origin", 65_700, 12, 64, 10, "shift"),
+    ("tiny_values_underflow", 65_700, 12, 40, 10, "tiny"),
+    ("huge_values_overflow", 65_700, 12, 40, 10, "huge"),
+    ("one_far_cluster", 65_700, 12, 64, 10, "far"),
+    ("wide_exponents", 65_700, 10, 40, 10, "wide"),
+]
+
+
+@pytest.mark.parametrize("use_self", [False, True], ids=["queries", "own_rows"])
+@pytest.mark.parametrize("case", FILTER_CASES, ids=[c[0] for c in FILTER_CASES])
+def test_filtered_search_matches_oracle(case, use_self):
+    from paper_1812_11689_amd import rpf
+    name, n, d, m, K, what = case
+    print(f"[exact] {name} n={n} d={d} m={m} K={K} self={use_self}", flush=True)
+    x, _ = problem(n, d, 1, n, seed=len(name) + 700, kind=what if what in ("aniso", "wide") else "mixture",
+                   dup_every=2 if what == "dup" else 0)
+    if what == "shift":
+        x = x + np.float32(3000.0)
+    elif what in ("tiny", "huge"):
+        x = x * np.float32(1e-21 if what == "tiny" else 3e18)
+    elif what == "far":
+        x[n // 2:] += np.float32(1e6)
+    rng = np.random.default_rng(len(name))
+    pts = np.sort(rng.choice(n, size=min(m, n), replace=False))
+    pts[0] = 0  # a row of the sample
+    if what == "dup":
+        pts[1] = 1
+    q = x[pts]
+    ri, rd = oracle.bruteforce(x, q, K, pts if use_self else None)
+    gi, gd = rpf.exact_knn(torch.from_numpy(x).cuda(), torch.from_numpy(q).cuda(), K,
+                           torch.from_numpy(pts.astype(np.int64)).cuda() if use_self else None)
+    np.testing.assert_array_equal(gi.cpu().numpy(), ri)
+    np.testing.assert_allclose(gd.cpu().numpy(), rd, rtol=1e-6)
