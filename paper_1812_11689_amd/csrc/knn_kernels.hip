@@ -1638,6 +1638,7 @@ struct FinalArgs {
     unsigned long long *stats;  // [kStatSlots][8]: rows, fallback, reranked32, reranked64, bad_index,
                                 //                 kept1, emitted2, block-merged (summed over slots by the host)
     unsigned long long *fault;  // the forest's sticky count of rows that met a bad index
+    const int32_t *stop;        // nonzero word: the call ends with an error, outputs stay as they are
 };
 
 // counters are spread over slots by block so that a million rows do not meet on one address
@@ -1958,6 +1959,7 @@ __global__ __launch_bounds__(256) void k_final(FinalArgs A, int64_t nrows) {
     __shared__ int32_t s_rd[4][kHT];
     __shared__ uint32_t s_c[4][256];  // the distinct indices' ub keys, compacted
     extern __shared__ __align__(16) float s_qall[];  // 4 rows x dq floats
+    if (A.stop && *A.stop) return;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t a = (int64_t)blockIdx.x * 4 + w;
     if (a >= nrows) return;
@@ -2298,6 +2300,7 @@ __global__ __launch_bounds__(256) void k_final_blk(FinalArgs A) {
     __shared__ uint32_t s4[4];    // reductions and selection counts
     __shared__ uint32_t s_sc[4];  // block scans
     extern __shared__ __align__(16) float s_q[];      // the query row (d floats)
+    if (A.stop && *A.stop) return;
     if constexpr (LIST) {
         const int nb = *A.big_cnt;
         for (int i = blockIdx.x; i < nb; i += gridDim.x) {
@@ -2312,6 +2315,13 @@ __global__ __launch_bounds__(256) void k_final_blk(FinalArgs A) {
 // ---------------------------------------------------------------- exhaustive fallback
 
 constexpr int kFallbackThreads = 512;  // threads per row of the exhaustive path
+constexpr int kFbSplitRows = 64;       // at most this many rows are split over several blocks
+constexpr int kFbParts = 16;           // blocks per split row, at most
+
+struct FbPart {  // a result of one part of a split row
+    double D;
+    int32_t idx, pad;
+};
 
 struct FallbackArgs {
     const int32_t *fb_list;
@@ -2331,12 +2341,20 @@ struct FallbackArgs {
     int32_t exclude_self;       // all-points: row a is point a
     int32_t *out_idx;
     float *out_dist;
+    const int32_t *stop;        // see FinalArgs
+    int32_t *arrived;           // [kFbSplitRows] finished parts of each split row (zeroed)
+    FbPart *parts;              // [rows][parts][K] (the pruning records' memory, read by now)
+    int64_t parts_cap;          // entries there
 };
 
-// The exhaustive path, one row per block of NTH threads: the union of the row's leaves over
-// all trees in binary64.  The members of up to 64 trees' leaves are taken as one list, NTH at
+// The exhaustive path, one row per block of NTH threads (a few rows: each split by trees over
+// up to kFbParts blocks, the last of which to finish merges the parts' lists; one row's 64
+// leaves of 244 x 96 took a single block 180 us, mostly waiting on its gathers): the union of
+// the row's leaves over all trees in binary64.  The members of up to 64 trees' leaves are taken as one list, NTH at
 // a time (a piece spans trees); the ids of the next piece are read while the current one is
-// measured, and every group of eight lanes measures four members at once.  Only members
+// measured, and every group of eight lanes measures four members at once (two at once, with two
+// workgroups to a CU and up to 512 rows split, were slower: 0.49 against 0.42 ms for 205 rows
+// of K 100, whose time goes to the merges).  Only members
 // before the running list's last entry in (D, index) order can enter a full list; they are
 // compacted to the front, the list is appended behind them, and the K smallest distinct
 // indices are kept (a repeated index repeats its distance, so its copies sort together).
@@ -2356,16 +2374,139 @@ __global__ __launch_bounds__(NTH) void k_fallback(FallbackArgs F) {
     __shared__ int32_t s_lo[65];  // first member of each tree's leaf in the list
     extern __shared__ __align__(16) float s_q[];
     const int tid = threadIdx.x, g = tid & 7, grp = tid >> 3;
+    __shared__ int s_last;
+    if (F.stop && *F.stop) return;
     const int nfb = *F.fb_cnt;
     const int K = F.K;  // <= 256 on this path
-    for (int q = blockIdx.x; q < nfb; q += gridDim.x) {
+    int np = 1;  // blocks per row: while they fit the grid, the scratch and the trees
+    if (nfb <= kFbSplitRows)
+        while (np < kFbParts && 2 * np <= F.T && nfb * 2 * np <= (int)gridDim.x &&
+               (int64_t)nfb * 2 * np * K <= F.parts_cap)
+            np *= 2;
+    // merges candidates s_cd / s_ci [0, NTH) (index 0x7fffffff: none) into the list s_td / s_ti
+    auto merge = [&]() {
+        for (int i = NTH + tid; i < CAP; i += NTH) {
+            s_cd[i] = INFINITY;
+            s_ci[i] = 0x7fffffff;
+        }
+        __syncthreads();
+        const int tn = s_tn;
+        const double dc = s_cd[tid];
+        const int ic = s_ci[tid];
+        bool take = ic != 0x7fffffff;
+        if (tn == K) {
+            const double lastd = s_td[K - 1];
+            const int lasti = s_ti[K - 1];
+            take = take && (dc < lastd || (dc == lastd && ic < lasti));
+        }
+        uint32_t pos, ncand;
+        block_excl_scan_w<NW>(take ? 1u : 0u, s_scan, pos, ncand);  // every read above is done
+        if (ncand == 0) return;
+        if (take) {
+            s_cd[pos] = dc;
+            s_ci[pos] = ic;
+        }
+        for (int i = tid; i < tn; i += NTH) {
+            s_cd[ncand + i] = s_td[i];
+            s_ci[ncand + i] = s_ti[i];
+        }
+        const int tot = (int)ncand + tn;
+        __syncthreads();
+        if (tot <= 64) {  // the usual case: one wave sorts in registers and keeps K distinct
+            if (tid < 64) {
+                double dk = tid < tot ? s_cd[tid] : INFINITY;
+                int ik = tid < tot ? s_ci[tid] : 0x7fffffff;
+                for (int size = 2; size <= 64; size <<= 1) {
+                    for (int stride = size >> 1; stride > 0; stride >>= 1) {
+                        const double dp = __shfl_xor(dk, stride, 64);
+                        const int ip = __shfl_xor(ik, stride, 64);
+                        const bool mine_first = dk < dp || (dk == dp && ik <= ip);
+                        const bool want_first = ((tid & stride) == 0) == ((tid & size) == 0);
+                        if (mine_first != want_first) {
+                            dk = dp;
+                            ik = ip;
+                        }
+                    }
+                }
+                const int iprev = __shfl_up(ik, 1, 64);
+                const bool keep = ik != 0x7fffffff && (tid == 0 || ik != iprev);
+                const uint64_t mk = __ballot(keep);
+                const int r = mask_rank(mk);
+                if (keep && r < K) {
+                    s_td[r] = dk;
+                    s_ti[r] = ik;
+                }
+                if (tid == 0) s_tn = min(__popcll(mk), K);
+            }
+            __syncthreads();
+            return;
+        }
+        int P2 = 128;  // bitonic sort of the first P2 >= tot entries (block-uniform)
+        while (P2 < tot) P2 <<= 1;
+        for (int i = tot + tid; i < P2; i += NTH) {
+            s_cd[i] = INFINITY;
+            s_ci[i] = 0x7fffffff;
+        }
+        __syncthreads();
+        for (int size = 2; size <= P2; size <<= 1)
+            for (int stride = size >> 1; stride > 0; stride >>= 1) {
+                for (int i = tid; i < P2 / 2; i += NTH) {
+                    const int lo = 2 * i - (i & (stride - 1));
+                    const int hi = lo + stride;
+                    const bool up = (lo & size) == 0;
+                    const double dl = s_cd[lo], dh = s_cd[hi];
+                    const int il = s_ci[lo], ih = s_ci[hi];
+                    const bool gtr = dl > dh || (dl == dh && il > ih);
+                    if (gtr == up) {
+                        s_cd[lo] = dh;
+                        s_cd[hi] = dl;
+                        s_ci[lo] = ih;
+                        s_ci[hi] = il;
+                    }
+                }
+                __syncthreads();
+            }
+        {  // K smallest distinct: thread tid holds entries E tid .. E tid + E - 1
+            constexpr int EMAX = CAP / NTH;
+            const int E = P2 > NTH ? P2 / NTH : 1;
+            bool keep[EMAX];
+            double kd[EMAX];
+            int ki[EMAX];
+            uint32_t cnt = 0;
+#pragma unroll
+            for (int e = 0; e < EMAX; e++) {
+                const int i = E * tid + e;
+                const bool in = e < E && i < P2;
+                keep[e] = in && s_ci[i] != 0x7fffffff && (i == 0 || s_ci[i] != s_ci[i - 1]);
+                kd[e] = in ? s_cd[i] : INFINITY;
+                ki[e] = in ? s_ci[i] : 0x7fffffff;
+                cnt += keep[e] ? 1u : 0u;
+            }
+            uint32_t excl, total;
+            block_excl_scan_w<NW>(cnt, s_scan, excl, total);  // every read of the sorted list is done
+#pragma unroll
+            for (int e = 0; e < EMAX; e++)
+                if (keep[e]) {
+                    if (excl < (uint32_t)K) {
+                        s_td[excl] = kd[e];
+                        s_ti[excl] = ki[e];
+                    }
+                    excl++;
+                }
+            if (tid == 0) s_tn = (int)min(total, (uint32_t)K);
+        }
+        __syncthreads();
+    };
+    for (int item = blockIdx.x; item < nfb * np; item += gridDim.x) {
+        const int q = item / np, part = item - q * np;
+        const int tlo = (int)((int64_t)F.T * part / np), thi = (int)((int64_t)F.T * (part + 1) / np);
         const int64_t a = F.fb_list[q];
         __syncthreads();
         for (int j = tid; j < F.d; j += NTH) s_q[j] = F.Qr[a * F.d + j];
         if (tid == 0) s_tn = 0;
         __syncthreads();
-        for (int t0 = 0; t0 < F.T; t0 += 64) {  // the row's leaves, 64 trees at a time
-            const int nt = min(64, F.T - t0);
+        for (int t0 = tlo; t0 < thi; t0 += 64) {  // the row's leaves, 64 trees at a time
+            const int nt = min(64, thi - t0);
             __syncthreads();
             if (tid < nt)
                 s_lf[tid] = F.leaves[(t0 + tid) * F.leaf_stride + F.heap_leaf[F.row_leaf[(int64_t)(t0 + tid) * F.nrows + a]]];
@@ -2428,117 +2569,29 @@ __global__ __launch_bounds__(NTH) void k_fallback(FallbackArgs F) {
                         }
                     }
                 }
-                for (int i = NTH + tid; i < CAP; i += NTH) {
-                    s_cd[i] = INFINITY;
-                    s_ci[i] = 0x7fffffff;
-                }
-                __syncthreads();
-                const int tn = s_tn;
-                const double dc = s_cd[tid];
-                const int ic = s_ci[tid];
-                bool take = ic != 0x7fffffff;
-                if (tn == K) {
-                    const double lastd = s_td[K - 1];
-                    const int lasti = s_ti[K - 1];
-                    take = take && (dc < lastd || (dc == lastd && ic < lasti));
-                }
-                uint32_t pos, ncand;
-                block_excl_scan_w<NW>(take ? 1u : 0u, s_scan, pos, ncand);  // every read above is done
-                if (ncand == 0) continue;
-                if (take) {
-                    s_cd[pos] = dc;
-                    s_ci[pos] = ic;
-                }
-                for (int i = tid; i < tn; i += NTH) {
-                    s_cd[ncand + i] = s_td[i];
-                    s_ci[ncand + i] = s_ti[i];
-                }
-                const int tot = (int)ncand + tn;
-                __syncthreads();
-                if (tot <= 64) {  // the usual case: one wave sorts in registers and keeps K distinct
-                    if (tid < 64) {
-                        double dk = tid < tot ? s_cd[tid] : INFINITY;
-                        int ik = tid < tot ? s_ci[tid] : 0x7fffffff;
-                        for (int size = 2; size <= 64; size <<= 1) {
-                            for (int stride = size >> 1; stride > 0; stride >>= 1) {
-                                const double dp = __shfl_xor(dk, stride, 64);
-                                const int ip = __shfl_xor(ik, stride, 64);
-                                const bool mine_first = dk < dp || (dk == dp && ik <= ip);
-                                const bool want_first = ((tid & stride) == 0) == ((tid & size) == 0);
-                                if (mine_first != want_first) {
-                                    dk = dp;
-                                    ik = ip;
-                                }
-                            }
-                        }
-                        const int iprev = __shfl_up(ik, 1, 64);
-                        const bool keep = ik != 0x7fffffff && (tid == 0 || ik != iprev);
-                        const uint64_t mk = __ballot(keep);
-                        const int r = mask_rank(mk);
-                        if (keep && r < K) {
-                            s_td[r] = dk;
-                            s_ti[r] = ik;
-                        }
-                        if (tid == 0) s_tn = min(__popcll(mk), K);
-                    }
-                    __syncthreads();
-                    continue;
-                }
-                int P2 = 128;  // bitonic sort of the first P2 >= tot entries (block-uniform)
-                while (P2 < tot) P2 <<= 1;
-                for (int i = tot + tid; i < P2; i += NTH) {
-                    s_cd[i] = INFINITY;
-                    s_ci[i] = 0x7fffffff;
-                }
-                __syncthreads();
-                for (int size = 2; size <= P2; size <<= 1)
-                    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-                        for (int i = tid; i < P2 / 2; i += NTH) {
-                            const int lo = 2 * i - (i & (stride - 1));
-                            const int hi = lo + stride;
-                            const bool up = (lo & size) == 0;
-                            const double dl = s_cd[lo], dh = s_cd[hi];
-                            const int il = s_ci[lo], ih = s_ci[hi];
-                            const bool gtr = dl > dh || (dl == dh && il > ih);
-                            if (gtr == up) {
-                                s_cd[lo] = dh;
-                                s_cd[hi] = dl;
-                                s_ci[lo] = ih;
-                                s_ci[hi] = il;
-                            }
-                        }
-                        __syncthreads();
-                    }
-                {  // K smallest distinct: thread tid holds entries E tid .. E tid + E - 1
-                    constexpr int EMAX = CAP / NTH;
-                    const int E = P2 > NTH ? P2 / NTH : 1;
-                    bool keep[EMAX];
-                    double kd[EMAX];
-                    int ki[EMAX];
-                    uint32_t cnt = 0;
-#pragma unroll
-                    for (int e = 0; e < EMAX; e++) {
-                        const int i = E * tid + e;
-                        const bool in = e < E && i < P2;
-                        keep[e] = in && s_ci[i] != 0x7fffffff && (i == 0 || s_ci[i] != s_ci[i - 1]);
-                        kd[e] = in ? s_cd[i] : INFINITY;
-                        ki[e] = in ? s_ci[i] : 0x7fffffff;
-                        cnt += keep[e] ? 1u : 0u;
-                    }
-                    uint32_t excl, total;
-                    block_excl_scan_w<NW>(cnt, s_scan, excl, total);  // every read of the sorted list is done
-#pragma unroll
-                    for (int e = 0; e < EMAX; e++)
-                        if (keep[e]) {
-                            if (excl < (uint32_t)K) {
-                                s_td[excl] = kd[e];
-                                s_ti[excl] = ki[e];
-                            }
-                            excl++;
-                        }
-                    if (tid == 0) s_tn = (int)min(total, (uint32_t)K);
-                }
-                __syncthreads();
+                merge();
+            }
+        }
+        if (np > 1) {
+            // this part's list, then the row's last part to finish merges all of them
+            FbPart *row = F.parts + (int64_t)q * np * K;
+            for (int k = tid; k < K; k += NTH) {
+                const bool ok = k < s_tn;
+                row[part * K + k] = FbPart{ok ? s_td[k] : INFINITY, ok ? s_ti[k] : 0x7fffffff, 0};
+            }
+            __threadfence();
+            __syncthreads();
+            if (tid == 0) s_last = atomicAdd(&F.arrived[q], 1) == np - 1;
+            __syncthreads();
+            if (!s_last) continue;
+            __threadfence();
+            if (tid == 0) s_tn = 0;
+            __syncthreads();
+            for (int base = 0; base < np * K; base += NTH) {
+                const FbPart e = base + tid < np * K ? row[base + tid] : FbPart{INFINITY, 0x7fffffff, 0};
+                s_cd[tid] = e.D;
+                s_ci[tid] = e.idx;
+                merge();
             }
         }
         for (int k = tid; k < K; k += NTH) {
@@ -2813,15 +2866,32 @@ static void tile_dispatch(int prec, int MB, hipStream_t s, int64_t njobs, const 
         tile_dispatch_mb<RPF_DIST_FP32>(MB, s, njobs, jobs, A, B, dp, as, bs, an, bn, ad, bp, bc, excl, out);
 }
 
-// per-call workspace from the caching allocator; blocks go back ordered after the call's work
+// Per-call workspace from the caching allocator: buffers are carved from one block of `hint`
+// bytes (a block is given back with an event of its own, about 4 us each), and what does not
+// fit it, or a hint that cannot be had, from blocks of their own.  They go back ordered after
+// the call's work.
 struct Workspace {
     hipStream_t s;
     std::vector<void *> ptrs;
+    uint8_t *base = nullptr;
+    size_t cap = 0, used = 0;
     bool ok = true;
-    explicit Workspace(hipStream_t st) : s(st) {}
+    explicit Workspace(hipStream_t st, size_t hint = 0) : s(st) {
+        if (!hint) return;
+        base = static_cast<uint8_t *>(cache_alloc(hint, s));
+        if (!base) return;
+        cap = hint;
+        ptrs.push_back(base);
+    }
     template <typename P>
     P *get(size_t bytes) {
-        void *p = cache_alloc(bytes ? bytes : 16, s);
+        if (!bytes) bytes = 16;
+        const size_t at = (used + 255) & ~(size_t)255;
+        if (at + bytes <= cap) {
+            used = at + bytes;
+            return reinterpret_cast<P *>(base + at);
+        }
+        void *p = cache_alloc(bytes, s);
         if (!p) {
             ok = false;
             return nullptr;
@@ -2856,6 +2926,8 @@ struct CandStage {
     int B;                  // trees of Phase I
     const TileJob *sjobs0 = nullptr, *sjobs1 = nullptr;  // query groups of <= qs rows (GEMV-shaped)
     int64_t nsjobs0 = 0, nsjobs1 = 0;
+    const int32_t *stop = nullptr;  // direct queries: the input check's flag, while it is not yet known
+    const int32_t *qleaf = nullptr; // direct queries: [T][rows] heap ids (no tile jobs)
 };
 
 // group size and chunks per lane of the GEMV-shaped query kernel (64 registers of query per
@@ -2973,6 +3045,277 @@ static void sym_dispatch(int prec, int NB, hipStream_t s, int64_t njobs, const T
         sym_dispatch_nb<RPF_DIST_FP32>(NB, s, njobs, jobs, src, nrm, pt, bc, excl, out);
 }
 
+// ================================================================ direct queries
+//
+// A batch of few queries for the forest's leaves (at most one query to two leaves, so that
+// groups of several queries in one leaf are rare): every (query, tree) pair is a job of its own
+// and nothing is sorted, counted or read back.  Launches: one clear, routing with the finite
+// check, the Phase I rows, the first merge, the Phase II rows, the final merge and the
+// exhaustive path.  The host waits for the check's event only after it has queued them all;
+// a rejected batch stops at the final kernels, before its outputs (see FinalArgs.stop).
+
+constexpr int kDirectWaves = 4096;  // waves a phase is cut into, where it has fewer pairs
+
+// Routes one query per eight lanes; tree 0's lanes check that the query is finite.
+// WIDE (few pairs): one wave per (query, tree), whose eight-lane groups project onto the node,
+// its children and its grandchildren at once, so the descent takes a third of the dependent
+// steps (11 levels of one query over 32 trees: 12.2 -> 6 us).
+template <bool VEC, bool WIDE>
+__global__ __launch_bounds__(256) void k_query_route(const float *__restrict__ Q, int64_t m, int d,
+                                                     const float *__restrict__ R, int64_t H, int n_try,
+                                                     const int32_t *__restrict__ chosen,
+                                                     const double *__restrict__ split, int64_t n, int n0,
+                                                     int32_t *__restrict__ out_leaf, int32_t *__restrict__ flag,
+                                                     int32_t *host_flag) {
+    const int t = blockIdx.y, lane = threadIdx.x & 63, g = lane & 7, grp = lane >> 3;
+    const int64_t q = (int64_t)blockIdx.x * (WIDE ? 4 : 32) + (threadIdx.x >> (WIDE ? 6 : 3));
+    const bool have = q < m;
+    const float *x = Q + (have ? q : 0) * d;
+    if (t == 0 && have) {
+        bool bad = false;
+        for (int j = 4 * (WIDE ? lane : g); j < d; j += WIDE ? 256 : 32) {
+            const float4 v = load4<VEC>(x + j, d - j);
+            bad |= !(v.x - v.x == 0.f) || !(v.y - v.y == 0.f) || !(v.z - v.z == 0.f) || !(v.w - v.w == 0.f);
+        }
+        if (bad) {
+            *flag = 1;
+            __hip_atomic_store(host_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
+    auto dot = [&](int64_t hs) {
+        const float *r = R + (hs * n_try + (n_try > 1 ? chosen[hs] : 0)) * (int64_t)d;
+        return group8_dot64<VEC>(x, r, d, g);
+    };
+    int64_t h = 1, size = n;
+    if (WIDE) {
+        const int dep = grp == 0 ? 0 : grp < 3 ? 1 : 2, off = grp - ((1 << dep) - 1);
+        while (size > n0) {  // wave-uniform
+            int64_t sz = size;
+            for (int b = dep - 1; b >= 0; b--) sz = (off >> b) & 1 ? sz - sz / 2 : sz / 2;
+            bool right = false;
+            if (grp < 7 && sz > n0) {  // (a node below a leaf is no larger than the leaf)
+                const int64_t hs = (int64_t)t * H + (((h << dep) + off) - 1);
+                right = dot(hs) >= split[hs];
+            }
+            const uint64_t mask = __ballot(right);
+            int node = 0;  // node of the seven the descent stands on
+            for (int b = 0; b < 3 && size > n0; b++) {
+                const int r = (int)(mask >> (8 * node)) & 1;
+                size = r ? size - size / 2 : size / 2;
+                h = 2 * h + r;
+                node = 2 * node + 1 + r;
+            }
+        }
+    } else {
+        while (size > n0) {
+            const int64_t hs = (int64_t)t * H + (h - 1);
+            const bool right = dot(hs) >= split[hs];
+            size = right ? size - size / 2 : size / 2;
+            h = 2 * h + (right ? 1 : 0);
+        }
+    }
+    if (have && (WIDE ? lane == 0 : g == 0)) out_leaf[(int64_t)t * m + q] = (int32_t)h;
+}
+
+// The rows of one (query, tree) pair's leaf, or every parts-th 64 of them: one wave, eight
+// lanes per row as in k_qtile, the query centred on the leaf in registers.  Sixty-four rows'
+// products are made before their bounds, which then take one lane per row (k_qtile spends a
+// wave's bounds on eight rows), and a wave appends its records with one atomic.
+// Bound: HBM, |leaf| dp (tile bytes) per pair.  4 096 queries over 64 trees of 4M x 96 in
+// float16, K 100: 2.35 ms for 60 trees, 5.4 TB/s (k_qtile: 4.13 ms, bound by its bounds).
+template <int PREC, int NCH, int MODE>
+__global__ __launch_bounds__(256) void k_qdirect(const float *__restrict__ Q, int64_t m, int d, int t_first,
+                                                 int64_t npairs, int parts, const int32_t *__restrict__ qleaf,
+                                                 const int32_t *__restrict__ heap_leaf,
+                                                 const LeafDesc *__restrict__ leaves,
+                                                 const float *__restrict__ centroid, int64_t nleaf,
+                                                 const void *__restrict__ B_, int dp, int64_t n,
+                                                 const float2 *__restrict__ b_nrm, const int32_t *__restrict__ b_pt,
+                                                 BoundCoef bc, float range_max, TileOut out,
+                                                 const int32_t *__restrict__ stop,
+                                                 unsigned long long *__restrict__ stats) {
+    using T = typename TileCfg<PREC>::T;
+    constexpr int EPC = 16 / (int)sizeof(T);
+    // the call's counters start here, once the batch is known to be finite (a rejected call
+    // leaves the last call's)
+    if (MODE == 0 && blockIdx.x == 0 && !*stop)
+        for (int i = threadIdx.x; i < kStatSlots * 8; i += 256) stats[i] = 0;
+    const int lane = threadIdx.x & 63, g = lane & 7, grp = lane >> 3;
+    const int64_t wid = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t pair = wid / parts;
+    const int part = (int)(wid - pair * parts);
+    if (pair >= npairs) return;
+    const int t = t_first + (int)(pair / m), tb = t - out.t0;
+    const int64_t q = pair % m;
+    const float tq = MODE == 1 ? out.tau[q] : INFINITY;
+    if (MODE == 1 && tq < 0.f) return;  // the row takes the exhaustive path
+    const int32_t li = heap_leaf[qleaf[(int64_t)t * m + q]];
+    const LeafDesc lf = leaves[li];
+    const int nchunk = dp / EPC;
+    const float *mu = centroid + ((int64_t)t * nleaf + li) * d;
+    T av[NCH][EPC];  // the centred query: this lane's chunks g, g + 8, ...
+    float na = 0.f, ra = 0.f;
+    bool over = false;
+#pragma unroll
+    for (int ch = 0; ch < NCH; ch++)
+#pragma unroll
+        for (int e = 0; e < EPC; e += 4) {
+            const int j = (g + 8 * ch) * EPC + e;
+            float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (j < d) {
+                const float4 x = load4<false>(Q + q * d + j, d - j), c = load4<false>(mu + j, d - j);
+                a = make_float4(x.x - c.x, x.y - c.y, x.z - c.z, x.w - c.w);
+            }
+            const float av4[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                over |= !(fabsf(av4[k]) <= range_max);
+                av[ch][e + k] = (T)av4[k];
+                const float vf = (float)av[ch][e + k];
+                na = __builtin_fmaf(vf, vf, na);
+                ra = __builtin_fmaf(av4[k], av4[k], ra);
+            }
+        }
+    na = group8_add(na);
+    ra = __ballot(over) ? INFINITY : sqrtf(group8_add(ra));
+    const int64_t b0 = (int64_t)t * n + lf.off;
+    const T *B = reinterpret_cast<const T *>(B_) + b0 * dp;
+    const int rows = MODE == 0 ? out.ML : lf.size;  // Phase I also marks the slots past the leaf
+    if (MODE == 0 && part == 0 && lane == 0) out.roff[(int64_t)tb * out.nrows + q] = (int32_t)lf.off;
+    constexpr int U = NCH <= 2 ? 8 : NCH <= 4 ? 4 : NCH <= 8 ? 2 : 1;  // groups of eight rows in flight
+    for (int r0 = 64 * part; r0 < rows; r0 += 64 * parts) {
+        const int r = r0 + 8 * g + grp;  // this lane's row of the sixty-four
+        const bool ok = r < lf.size;
+        float lb = INFINITY, ub = INFINITY;
+        int32_t pt = 0;
+        if (r0 < lf.size) {
+            const float2 nb = b_nrm[b0 + (ok ? r : 0)];
+            if (MODE == 1) pt = b_pt[b0 + (ok ? r : 0)];
+            float mine = 0.f;
+#pragma unroll
+            for (int u0 = 0; u0 < 8; u0 += U) {
+                uint4 v[U][NCH];
+#pragma unroll
+                for (int u = 0; u < U; u++) {
+                    const int rr = r0 + 8 * (u0 + u) + grp;
+                    const T *row = B + (int64_t)(rr < lf.size ? rr : 0) * dp;
+#pragma unroll
+                    for (int ch = 0; ch < NCH; ch++)
+                        v[u][ch] = *reinterpret_cast<const uint4 *>(row + (g + 8 * ch < nchunk ? g + 8 * ch : 0) * EPC);
+                }
+#pragma unroll
+                for (int u = 0; u < U; u++) {
+                    float acc = 0.f;
+#pragma unroll
+                    for (int ch = 0; ch < NCH; ch++) {
+                        T pv[EPC];
+                        __builtin_memcpy(pv, &v[u][ch], 16);
+                        // (chunks past the row hold zeros of the query and finite values here)
+#pragma unroll
+                        for (int e = 0; e < EPC; e++) acc = __builtin_fmaf((float)pv[e], (float)av[ch][e], acc);
+                    }
+                    acc = group8_add(acc);
+                    mine = g == u0 + u ? acc : mine;
+                }
+            }
+            if (ok) pair_bounds(na, nb.x, ra, nb.y, mine, bc, lb, ub);
+        }
+        if (MODE == 0) {
+            put_first(out, q * out.cap + (int64_t)tb * out.ML + r, lb, ub);
+        } else {
+            const bool emit = ok && lb <= tq;
+            const uint64_t mask = __ballot(emit);
+            if (mask) {
+                int slot = 0;
+                if (lane == 0) slot = atomicAdd(&out.cnt[q], (int)__popcll(mask));
+                slot = __shfl(slot, 0, 64) + mask_rank(mask);
+                if (emit && slot < out.cap) out.ent[q * out.cap + slot] = make_ent(pt, lb, ub);
+            }
+        }
+    }
+}
+
+// A pending input check: an event behind the routing launch and a pinned word it sets.  Kept
+// in a pool (one word each of one pinned page for the process), a pair per call in flight; a
+// call that finds none takes the grouped path.
+struct CheckSlot {
+    hipEvent_t ev = nullptr;
+    int32_t *flag = nullptr;
+    int dev = -1;
+};
+constexpr int kCheckSlots = 64;
+static std::mutex g_check_mu;
+static std::vector<CheckSlot> g_check_idle;
+static int32_t *g_check_page = nullptr;
+static int g_check_made = 0;
+
+static bool check_take(CheckSlot &c) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    std::lock_guard<std::mutex> lk(g_check_mu);
+    for (size_t i = 0; i < g_check_idle.size(); i++)
+        if (g_check_idle[i].dev == dev) {
+            c = g_check_idle[i];
+            g_check_idle.erase(g_check_idle.begin() + (long)i);
+            return true;
+        }
+    if (g_check_made >= kCheckSlots) return false;
+    if (!g_check_page) {
+        void *p = nullptr;
+        if (hipHostMalloc(&p, kCheckSlots * 64, hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        g_check_page = static_cast<int32_t *>(p);
+    }
+    CheckSlot n;
+    if (hipEventCreateWithFlags(&n.ev, hipEventDisableTiming) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    n.flag = g_check_page + 16 * g_check_made++;
+    n.dev = dev;
+    c = n;
+    return true;
+}
+
+static void check_give(const CheckSlot &c) {
+    std::lock_guard<std::mutex> lk(g_check_mu);
+    g_check_idle.push_back(c);
+}
+
+template <int PREC, int MODE>
+static void qdirect_launch(hipStream_t s, const ForestView &v, const float *Q, int64_t m, int t_first, int ntree,
+                           const int32_t *qleaf, const int32_t *stop, const BoundCoef &bc, const TileOut &out) {
+    if (ntree <= 0) return;
+    constexpr int E = PREC == RPF_DIST_FP32 ? 4 : 8;
+    const int nch = (v.dp / E + 7) / 8;
+    const int64_t npairs = m * ntree;
+    const int pieces = MODE == 0 ? out.ML / 64 : (v.max_leaf + 63) / 64;
+    int parts = 1;
+    while (2 * parts <= pieces && npairs * 2 * parts <= kDirectWaves) parts *= 2;
+    const float range = PREC == RPF_DIST_FP16 ? 60000.f : 3.0e38f;
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)((npairs * parts + 3) / 4)), dim3(256), 0, s, Q, m, v.d, t_first, npairs,
+                           parts, qleaf, v.heap_leaf, v.leaves, v.centroid, v.nleaf, v.Xc, v.dp, v.n, v.nrm, v.perm, bc,
+                           range, out, stop, v.stats);
+    };
+    if (nch <= 1) go(k_qdirect<PREC, 1, MODE>);
+    else if (nch <= 2) go(k_qdirect<PREC, 2, MODE>);
+    else if (nch <= 4) go(k_qdirect<PREC, 4, MODE>);
+    else if (nch <= 8) go(k_qdirect<PREC, 8, MODE>);
+    else if constexpr (PREC == RPF_DIST_FP32) go(k_qdirect<PREC, 16, MODE>);
+    launch_check(s, "k_qdirect");
+}
+
+template <int MODE>
+static void qdirect_dispatch(hipStream_t s, const ForestView &v, const float *Q, int64_t m, int t_first, int ntree,
+                             const int32_t *qleaf, const int32_t *stop, const BoundCoef &bc, const TileOut &out) {
+    if (v.prec == RPF_DIST_BF16) qdirect_launch<RPF_DIST_BF16, MODE>(s, v, Q, m, t_first, ntree, qleaf, stop, bc, out);
+    else if (v.prec == RPF_DIST_FP16) qdirect_launch<RPF_DIST_FP16, MODE>(s, v, Q, m, t_first, ntree, qleaf, stop, bc, out);
+    else qdirect_launch<RPF_DIST_FP32, MODE>(s, v, Q, m, t_first, ntree, qleaf, stop, bc, out);
+}
+
 // device buffers of the candidate stage (one call)
 // Per-row record capacities of a candidate stage.  want2 sizes the wave merge (the Phase II
 // records a row is expected to hold at most); cap2 is the row's Phase II record area.  In
@@ -2983,7 +3326,12 @@ struct RecLayout {
     int S = 0, nT2 = 0, capO = 0;
 };
 
+// the row-list counters (fallback rows, block-merge rows, 2 spare), then the arrivals of the
+// exhaustive path's split rows
+constexpr int kFbWords = 4 + kFbSplitRows;
+
 struct CandWs {
+    size_t region_bytes = 0;
     int lcap = 0, cap1 = 0, cap2 = 0;
     RecLayout lay;
     uint8_t *region = nullptr;  // Phase I index / lb / ub arrays, then the Phase II records
@@ -3086,13 +3434,14 @@ static bool cand_ws_alloc(const ForestView &v, const CandStage &cs, int K, Get g
     // the Phase II records reuse the Phase I arrays, dead once the first merge has run
     const size_t first_bytes = (size_t)rows * w.cap1 * 4 + (size_t)rows * cs.B * 4;  // slots, leaf starts
     const size_t second_bytes = (size_t)rows * w.cap2 * sizeof(Ent);
-    w.region = static_cast<uint8_t *>(get(std::max(first_bytes, second_bytes) + 256));
+    w.region_bytes = std::max(first_bytes, second_bytes) + 256;
+    w.region = static_cast<uint8_t *>(get(w.region_bytes));
     w.tau = static_cast<float *>(get(rows * 4));
     w.cnt = static_cast<int32_t *>(get(rows * 4));
     w.list = static_cast<Ent *>(get((size_t)rows * w.lcap * sizeof(Ent)));
     w.lcnt = static_cast<int32_t *>(get(rows * 4));
     w.fb_list = static_cast<int32_t *>(get(rows * 8));  // fallback rows, then block-merge rows
-    w.fb_cnt = static_cast<int32_t *>(get(16));
+    w.fb_cnt = static_cast<int32_t *>(get(4 * kFbWords));
     if (w.lay.S) w.bcnt = static_cast<uint8_t *>(get((size_t)rows * w.lay.nT2));
     return w.region && w.tau && w.cnt && w.list && w.lcnt && w.fb_list && w.fb_cnt && (!w.lay.S || w.bcnt);
 }
@@ -3120,6 +3469,31 @@ void fill_u64(void *p, int64_t count, uint64_t value, hipStream_t s) {
     const unsigned blocks = (unsigned)std::min<int64_t>((count + 255) / 256, 2048);
     hipLaunchKernelGGL(k_fill_u64, dim3(blocks), dim3(256), 0, s, static_cast<uint64_t *>(p), count, value);
     launch_check(s, "k_fill_u64");
+}
+
+struct FillSet {
+    Fill f[kFillMax];
+};
+__global__ __launch_bounds__(256) void k_fill_many(FillSet fs) {
+    const Fill f = fs.f[blockIdx.y];
+    uint32_t *p = static_cast<uint32_t *>(f.p);
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < f.words; i += (int64_t)gridDim.x * 256)
+        p[i] = i & 1 ? f.odd : f.even;
+}
+
+void fill_many(std::initializer_list<Fill> fills, hipStream_t s) {
+    FillSet fs{};
+    unsigned k = 0;
+    int64_t most = 0;
+    for (const Fill &f : fills)
+        if (f.p && f.words > 0 && k < kFillMax) {
+            fs.f[k++] = f;
+            most = std::max(most, f.words);
+        }
+    if (!k) return;
+    const unsigned blocks = (unsigned)std::min<int64_t>((most + 255) / 256, 2048);
+    hipLaunchKernelGGL(k_fill_many, dim3(blocks, k), dim3(256), 0, s, fs);
+    launch_check(s, "k_fill_many");
 }
 
 // Every tree has the same leaf shapes, so the all-points tile list of tree 0 (jobs[0, njt))
@@ -3153,9 +3527,8 @@ static void cand_launches(const ForestView &v, const CandStage &cs, int K, const
     Ent *ent = reinterpret_cast<Ent *>(region);
     uint32_t *plub = reinterpret_cast<uint32_t *>(region);
     int32_t *roff = reinterpret_cast<int32_t *>(region + (size_t)rows * cap1 * 4);
-    fill_u32(cnt, rows, 0, s);
-    fill_u32(fb_cnt, 4, 0, s);
-    fill_u32(v.stats, kStatSlots * 8 * 2, 0, s);
+    if (!cs.stop)  // (the direct queries' first launch cleared them)
+        fill_many({{cnt, rows}, {fb_cnt, kFbWords}, {v.stats, kStatSlots * 8 * 2}}, s);
     const BoundCoef bc = bound_coef(v.prec, v.d);
     // the all-points symmetric tiles may run split bfloat16 over a binary32 forest
     const BoundCoef bc_sym = v.sym_prec == v.prec ? bc : bound_coef(v.sym_prec, v.d);
@@ -3191,14 +3564,17 @@ static void cand_launches(const ForestView &v, const CandStage &cs, int K, const
     };
     {
         ProfScope ps(s, "tile_phase1", cs.bytes0, cs.flops0);
-        if (grid)
+        if (cs.qleaf)
+            qdirect_dispatch<0>(s, v, cs.Qr, rows, 0, cs.B, cs.qleaf, cs.stop, bc, o1);
+        else if (grid)
             grid_launch(cs.jobs0, cs.njobs0, o1);
         else if (cs.sym)
             sym_dispatch(v.sym_prec, MB, s, cs.njobs0, cs.jobs0, sym_src(v), v.nrm, v.perm, bc_sym, cs.excl, o1);
         else
             tile_dispatch(v.prec, MB, s, cs.njobs0, cs.jobs0, cs.A, v.Xc, v.dp, cs.a_stride, v.n, cs.a_nrm, v.nrm,
                           cs.a_dest, v.perm, bc, cs.excl, o1);
-        qtile_dispatch(v.prec, qtile_qs(v.prec, v.dp), s, cs.nsjobs0, cs.sjobs0, cs.A, v.Xc, v.dp, cs.a_stride, v.n,
+        if (!cs.qleaf)
+            qtile_dispatch(v.prec, qtile_qs(v.prec, v.dp), s, cs.nsjobs0, cs.sjobs0, cs.A, v.Xc, v.dp, cs.a_stride, v.n,
                        cs.a_nrm, v.nrm, cs.a_dest, v.perm, bc, o1);
     }
     {
@@ -3221,7 +3597,7 @@ static void cand_launches(const ForestView &v, const CandStage &cs, int K, const
         }
         launch_check(s, "k_merge_first");
     }
-    if (cs.njobs1 > 0 || cs.nsjobs1 > 0) {
+    if (cs.njobs1 > 0 || cs.nsjobs1 > 0 || (cs.qleaf && v.T > cs.B)) {
         TileOut o2 = o1;
         o2.mode = 1;
         o2.cap = cap2;
@@ -3236,14 +3612,17 @@ static void cand_launches(const ForestView &v, const CandStage &cs, int K, const
             o2.capO = w.lay.capO;
         }
         ProfScope ps(s, "tile_phase2", cs.bytes1, cs.flops1);
-        if (grid)
+        if (cs.qleaf)
+            qdirect_dispatch<1>(s, v, cs.Qr, rows, cs.B, v.T - cs.B, cs.qleaf, cs.stop, bc, o2);
+        else if (grid)
             grid_launch(cs.jobs1, cs.njobs1, o2);
         else if (cs.sym)
             sym_dispatch(v.sym_prec, MB, s, cs.njobs1, cs.jobs1, sym_src(v), v.nrm, v.perm, bc_sym, cs.excl, o2);
         else
             tile_dispatch(v.prec, MB, s, cs.njobs1, cs.jobs1, cs.A, v.Xc, v.dp, cs.a_stride, v.n, cs.a_nrm, v.nrm,
                           cs.a_dest, v.perm, bc, cs.excl, o2);
-        qtile_dispatch(v.prec, qtile_qs(v.prec, v.dp), s, cs.nsjobs1, cs.sjobs1, cs.A, v.Xc, v.dp, cs.a_stride, v.n,
+        if (!cs.qleaf)
+            qtile_dispatch(v.prec, qtile_qs(v.prec, v.dp), s, cs.nsjobs1, cs.sjobs1, cs.A, v.Xc, v.dp, cs.a_stride, v.n,
                        cs.a_nrm, v.nrm, cs.a_dest, v.perm, bc, o2);
     }
     FinalArgs fa;
@@ -3252,6 +3631,7 @@ static void cand_launches(const ForestView &v, const CandStage &cs, int K, const
     fa.out_dist = out_dist; fa.fb_list = fb_list; fa.fb_cnt = fb_cnt; fa.npts = v.n;
     fa.stats = v.stats;
     fa.fault = v.fault;
+    fa.stop = cs.stop;
     fa.bcnt = w.lay.S ? w.bcnt : nullptr;
     fa.S = w.lay.S;
     fa.nT2 = w.lay.nT2;
@@ -3301,9 +3681,13 @@ static void cand_launches(const ForestView &v, const CandStage &cs, int K, const
     fb.n = v.n; fb.perm = v.perm; fb.row_leaf = cs.row_leaf; fb.nrows = rows; fb.heap_leaf = v.heap_leaf;
     fb.leaves = v.leaves; fb.leaf_stride = v.leaf_stride; fb.exclude_self = cs.excl; fb.out_idx = out_idx;
     fb.out_dist = out_dist;
+    fb.stop = cs.stop;
+    fb.arrived = fb_cnt + 4;
+    fb.parts = reinterpret_cast<FbPart *>(region);
+    fb.parts_cap = (int64_t)(w.region_bytes / sizeof(FbPart));
     {
         ProfScope ps(s, "fallback", 0, 0);
-        const unsigned nb = (unsigned)std::min<int64_t>(rows, 1024);
+        const unsigned nb = (unsigned)std::min<int64_t>(rows * kFbParts, 1024);
         constexpr int NTH = kFallbackThreads;
         if (vec)
             hipLaunchKernelGGL((k_fallback<true, NTH>), dim3(nb), dim3(NTH), v.d * 4, s, fb);
@@ -3327,7 +3711,11 @@ static rpf_status run_cand_stage_get(const ForestView &v, const CandStage &cs, i
 
 static rpf_status run_cand_stage(const ForestView &v, const CandStage &cs, int K, int32_t *out_idx,
                                  float *out_dist, hipStream_t s) {
-    Workspace ws(s);
+    // the buffers' sizes added up by a first, dry call
+    size_t hint = 0;
+    CandWs dry;
+    cand_ws_alloc(v, cs, K, [&](size_t b) -> void * { hint += (b + 511) & ~(size_t)255; return nullptr; }, dry);
+    Workspace ws(s, hint);
     return run_cand_stage_get(v, cs, K, out_idx, out_dist, s, [&](size_t b) { return ws.get<void>(b); });
 }
 
@@ -3433,13 +3821,14 @@ KnnShared *knn_shared_create(const std::vector<const rpf_forest *> &parts, const
         return q;
     };
     CandWs &w = p->w;
+    w.region_bytes = b_region;
     w.region = static_cast<uint8_t *>(get(b_region));
     w.tau = static_cast<float *>(get(b_rows));
     w.cnt = static_cast<int32_t *>(get(b_rows));
     w.list = static_cast<Ent *>(get(b_list));
     w.lcnt = static_cast<int32_t *>(get(b_rows));
     w.fb_list = static_cast<int32_t *>(get(2 * b_rows));  // fallback rows, then block-merge rows
-    w.fb_cnt = static_cast<int32_t *>(get(16));
+    w.fb_cnt = static_cast<int32_t *>(get(4 * kFbWords));
     if (b_bcnt) w.bcnt = static_cast<uint8_t *>(get(b_bcnt));
     if (!w.region || !w.tau || !w.cnt || !w.list || !w.lcnt || !w.fb_list || !w.fb_cnt || (b_bcnt && !w.bcnt)) {
         knn_shared_destroy(p, s);
@@ -3505,6 +3894,56 @@ rpf_status route(const rpf_forest *f, const float *Q, int64_t m, int32_t *out_le
     return RPF_OK;
 }
 
+// The direct search (see "direct queries"): the check slot's word and event tell whether the
+// batch was finite.
+template <typename Get>
+static rpf_status knn_direct(const ForestView &v, const CheckSlot &chk, const float *Q, int64_t m, int K,
+                             int32_t *out_idx, float *out_dist, hipStream_t s, Get get) {
+    CandStage cs;
+    cs.rows = m;
+    cs.jobs0 = cs.jobs1 = nullptr;
+    cs.njobs0 = cs.njobs1 = 0;
+    cs.B = first_trees(v.T, K, first_slot_leaf(v));
+    cs.A = nullptr;
+    cs.a_stride = 0;
+    cs.a_nrm = nullptr;
+    cs.a_dest = nullptr;
+    cs.Qr = Q;
+    cs.excl = 0;
+    cs.flops0 = cs.flops1 = cs.bytes0 = cs.bytes1 = 0;
+    cs.sym = false;
+    int32_t *flag = static_cast<int32_t *>(get(16));
+    int32_t *qleaf = static_cast<int32_t *>(get((size_t)v.T * m * 4));
+    CandWs w;
+    if (!flag || !qleaf || !cand_ws_alloc(v, cs, K, get, w)) return fail(RPF_ENOMEM, "kNN workspace allocation failed");
+    cs.row_leaf = cs.qleaf = qleaf;
+    cs.stop = flag;
+    __atomic_store_n(chk.flag, 0, __ATOMIC_RELEASE);
+    fill_many({{flag, 4}, {w.cnt, m}, {w.fb_cnt, kFbWords}}, s);
+    {
+        const bool vec = (v.d % 4) == 0 && ((uintptr_t)Q % 16) == 0;
+        // one wave per pair while that leaves the chip unfilled
+        const bool wide = m * v.T <= 8192;
+        ProfScope ps(s, "route", (double)m * v.T * (v.L * (8.0 * v.d + 16)), 0);
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3((unsigned)(wide ? (m + 3) / 4 : (m + 31) / 32), v.T), dim3(256), 0, s, Q, m, v.d,
+                               v.R, v.H, v.n_try, v.chosen, v.split, v.n, v.n0, qleaf, flag, chk.flag);
+        };
+        if (vec) wide ? go(k_query_route<true, true>) : go(k_query_route<true, false>);
+        else wide ? go(k_query_route<false, true>) : go(k_query_route<false, false>);
+        launch_check(s, "k_query_route");
+    }
+    rpf_status st = check_hip(hipEventRecord(chk.ev, s), "rpf_query input check");
+    if (st != RPF_OK) return st;
+    cand_launches(v, cs, K, w, out_idx, out_dist, s);
+    st = check_hip(hipEventSynchronize(chk.ev), "rpf_query input check");
+    const std::string le = take_launch_error();
+    if (st != RPF_OK) return st;
+    if (__atomic_load_n(chk.flag, __ATOMIC_ACQUIRE)) return fail(RPF_EINVAL, "rpf_query: Q holds NaN or Inf");
+    if (!le.empty()) return fail(RPF_EDEVICE, "kNN: " + le);
+    return RPF_OK;
+}
+
 // The query search with every device buffer taken from `get` (device bytes, nullptr =
 // failure): the library's cache (knn_query) or a fixed scratch area (rpf_query_noalloc).
 // may_copy: the forest's leaf copies may be made (allocated) here on its first query.
@@ -3516,6 +3955,14 @@ static rpf_status knn_query_get(const rpf_forest *f, const float *Q, int64_t m, 
         if (st != RPF_OK) return st;
     }
     const ForestView v = view(f);
+    // one query to two leaves at most: pairs rather than groups (the rows of a leaf are shared by
+    // too few queries to pay for sorting them); rows above 512 columns take the MFMA tiles
+    CheckSlot chk;
+    if (2 * m <= v.nleaf && v.dp <= 512 && !capturing(s) && check_take(chk)) {
+        const rpf_status st = knn_direct(v, chk, Q, m, K, out_idx, out_dist, s, get);
+        check_give(chk);
+        return st;
+    }
     {   // queries must be finite (one synchronisation)
         int32_t *flag = static_cast<int32_t *>(get(16));
         if (!flag) return fail(RPF_ENOMEM, "rpf_query: allocation");
@@ -3559,9 +4006,7 @@ static rpf_status knn_query_get(const rpf_forest *f, const float *Q, int64_t m, 
     if (!ok) return fail(RPF_ENOMEM, "rpf_query: workspace allocation failed");
     rpf_status st = route(f, Q, m, qleaf, s);
     if (st != RPF_OK) return st;
-    fill_u32(gcount, (int64_t)T * nleaf, 0, s);
-    fill_u32(gfill, (int64_t)T * nleaf, 0, s);
-    fill_u32(njobs, 4, 0, s);
+    fill_many({{gcount, (int64_t)T * nleaf}, {gfill, (int64_t)T * nleaf}, {njobs, 4}}, s);
     const unsigned qb = (unsigned)std::min<int64_t>((m + 255) / 256, 1024);
     hipLaunchKernelGGL(k_group_count, dim3(qb, T), dim3(256), 0, s, qleaf, m, v.heap_leaf, nleaf, gcount);
     hipLaunchKernelGGL(k_group_scan, dim3(T), dim3(1024), 0, s, gcount, nleaf, goff);
@@ -3616,9 +4061,11 @@ static rpf_status knn_query_get(const rpf_forest *f, const float *Q, int64_t m, 
     return run_cand_stage_get(v, cs, K, out_idx, out_dist, s, get);
 }
 
+uint64_t query_workspace_bytes(const rpf_forest *f, int64_t m, int K);
+
 rpf_status knn_query(const rpf_forest *f, const float *Q, int64_t m, int K, int32_t *out_idx, float *out_dist,
                      hipStream_t s) {
-    Workspace ws(s);
+    Workspace ws(s, (size_t)query_workspace_bytes(f, m, K));
     return knn_query_get(f, Q, m, K, out_idx, out_dist, s, [&](size_t b) { return ws.get<void>(b); }, true);
 }
 

@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <initializer_list>
 #include <string>
 #include <vector>
 
@@ -219,6 +220,14 @@ int knn_part_bucket_size(const rpf_forest *f, int K, int B);
 void knn_part_launch(const KnnShared *p, const rpf_forest *f, int B, int shape, int bucket_S, int32_t *out_idx,
                      float *out_dist, hipStream_t s);
 void knn_shared_destroy(KnnShared *p, hipStream_t s);
+// words of a range set to even / odd (by position); several ranges in one launch
+struct Fill {
+    void *p;
+    int64_t words;
+    uint32_t even = 0, odd = 0;
+};
+constexpr unsigned kFillMax = 8;
+void fill_many(std::initializer_list<Fill> fills, hipStream_t s);
 void fill_u32(void *p, int64_t count, uint32_t value, hipStream_t s);
 void fill_u64(void *p, int64_t count, uint64_t value, hipStream_t s);
 // the leaf-ordered, centred copy in the tile precision, made on a query's first use (the

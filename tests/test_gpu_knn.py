@@ -222,3 +222,50 @@ def test_rerank_set_is_reproducible():
             assert r[:3] == runs[0][:3], (prec, [q[:3] for q in runs])
             np.testing.assert_array_equal(r[3], runs[0][3])
         f.free()
+
+
+DIRECT_CASES = [
+    # queries taken pair by pair (at most one query to two leaves), beside the grouped path
+    # name, n, d, T, n0, n_try, m, K, prec, far
+    ("at_the_line", 4096, 12, 5, 32, 1, 64, 7, "fp32", False),       # 128 leaves
+    ("past_the_line", 4096, 12, 5, 32, 1, 65, 7, "fp32", False),     # grouped
+    ("one_query_d5", 3000, 5, 9, 20, 1, 1, 3, "fp32", False),
+    ("d33_unaligned", 6000, 33, 4, 40, 1, 50, 10, "bf16", False),
+    ("d97_fp16_tries", 6000, 97, 3, 70, 3, 20, 10, "fp16", False),
+    ("d500_fp32_leaves_of_300", 5000, 500, 3, 300, 1, 8, 5, "fp32", False),
+    ("d512_fp16", 3000, 512, 2, 100, 1, 15, 5, "fp16", False),
+    ("eight_lanes_per_pair", 40_000, 8, 30, 16, 1, 400, 4, "fp32", False),
+    ("k100_block_merge", 12_000, 16, 12, 64, 1, 60, 100, "fp32", False),
+    ("far_queries_split_rows", 20_000, 24, 40, 64, 1, 50, 10, "bf16", True),
+    ("first_trees_only", 5000, 10, 2, 50, 1, 30, 200, "fp32", False),
+]
+
+
+@pytest.mark.parametrize("case", DIRECT_CASES, ids=[c[0] for c in DIRECT_CASES])
+def test_direct_queries_match_oracle(case):
+    from paper_1812_11689_amd import rpf
+    name, n, d, T, n0, n_try, m, K, prec, far = case
+    print(f"[direct] {name} n={n} d={d} T={T} n0={n0} m={m} K={K} {prec}", flush=True)
+    x, R = problem(n, d, T, n0, n_try, seed=len(name) + 900)
+    q, _ = problem(m, d, 1, m, seed=len(name) + 901)
+    if far:
+        q = q * np.float32(20.0)
+    ref = oracle.build_forest(x, R, T, n0, n_try)
+    f = rpf.build(torch.from_numpy(x).cuda(), T, n0, torch.from_numpy(R).cuda(), n_try=n_try, dist_prec=prec)
+    ri, rd = oracle.query_knn(ref, q, K)
+    for _ in range(2):
+        gi, gd = f.query(torch.from_numpy(q).cuda(), K)
+        np.testing.assert_array_equal(gi.cpu().numpy(), ri)
+        np.testing.assert_allclose(gd.cpu().numpy(), rd, rtol=1e-5)
+    assert f.knn_stats()["rows"] == m
+    # a batch with a NaN is refused: outputs and counters stay as they are
+    bad = torch.from_numpy(q).cuda()
+    bad[m - 1, d - 1] = float("nan")
+    out = (torch.full((m, K), 7, dtype=torch.int32, device="cuda"), torch.full((m, K), 7.0, device="cuda"))
+    before = f.knn_stats()
+    with pytest.raises(rpf.RpfError) as e:
+        f.query(bad, K, out=out)
+    assert e.value.status == rpf.RPF_EINVAL
+    assert bool((out[0] == 7).all()) and bool((out[1] == 7).all())
+    assert f.knn_stats() == before
+    f.free()
