@@ -8,10 +8,9 @@
 // Two paths:
 //   - segments of at most kLarge members: one workgroup per (segment, tree) does the whole
 //     step in LDS (k_level_small);
-//   - larger segments: chunked projection with a fused first-digit histogram, radix
-//     passes narrowing an 11-bit digit of the 96-bit key (p, index) per pass until at most
-//     kCandCap candidates remain, an in-block select over the candidates, then a stable
-//     chunked partition (count, scan, scatter).
+//   - larger segments: chunked projection, a median select by one workgroup per segment
+//     (the largest segments bracket the median from a sample first), then a stable chunked
+//     partition.
 #include "rpf_internal.h"
 
 namespace rpf {
@@ -551,19 +550,17 @@ template <bool VEC, bool LEAD, bool Q8 = false>
 __global__ __launch_bounds__(256) void k_proj_chunks(
     const float *__restrict__ X, int d, const float *__restrict__ R, int64_t H,
     const SegDesc *__restrict__ segs, const ChunkDesc *__restrict__ chunks,
-    const int32_t *__restrict__ perm, int64_t n, int nseg, uint64_t *__restrict__ keys, uint32_t *__restrict__ hist,
+    const int32_t *__restrict__ perm, int64_t n, uint64_t *__restrict__ keys,
     const LookDesc *__restrict__ look, double2 *__restrict__ ahead, const int8_t *__restrict__ Xq, int dq) {
     // the node's direction (binary32); on a lead level it and its children's, as binary64
     extern __shared__ __align__(16) uint8_t s_dir[];
     float *s_r = reinterpret_cast<float *>(s_dir);
-    __shared__ uint32_t s_hist[kDigitBins];
     const int t = blockIdx.y;
     const ChunkDesc c = chunks[blockIdx.x];
     const SegDesc sg = segs[c.seg];
     const int tid = threadIdx.x;
     const float *Rn = R + ((int64_t)t * H + (sg.heap - 1)) * (int64_t)d;
     const int32_t *pp = perm + (int64_t)t * n;
-    for (int b = tid; b < kDigitBins; b += 256) s_hist[b] = 0;
     const int g = tid & 7, pt = tid >> 3;
     if (LEAD && d <= 1024) {  // lead level: the children's projections from the same read of X
         const LookDesc lk = look[c.seg];
@@ -588,10 +585,8 @@ __global__ __launch_bounds__(256) void k_proj_chunks(
                 const int i = h ? ib : ia;
                 const int64_t s = h ? sb : sa;
                 if (g == 0 && i < c.len) {
-                    uint64_t u = key_of(p[3 * h]);
-                    keys[(int64_t)t * n + s] = u;
+                    keys[(int64_t)t * n + s] = key_of(p[3 * h]);
                     ahead[(int64_t)t * n + s] = make_double2(p[3 * h + 1], p[3 * h + 2]);
-                    atomicAdd(&s_hist[(uint32_t)(u >> 53)], 1u);
                 }
             }
         }
@@ -604,11 +599,7 @@ __global__ __launch_bounds__(256) void k_proj_chunks(
             double p;
             if constexpr (Q8) p = group8_dot64_q8<VEC>(Xq + (int64_t)pp[s] * dq, s_r, d, g);
             else p = group8_dot64<VEC>(X + (int64_t)pp[s] * d, s_r, d, g);
-            if (g == 0 && i < c.len) {
-                uint64_t u = key_of(p);
-                keys[(int64_t)t * n + s] = u;
-                atomicAdd(&s_hist[(uint32_t)(u >> 53)], 1u);
-            }
+            if (g == 0 && i < c.len) keys[(int64_t)t * n + s] = key_of(p);
         }
     } else {
         for (int base = 0; base < c.len; base += 32) {
@@ -617,314 +608,461 @@ __global__ __launch_bounds__(256) void k_proj_chunks(
             double p;
             if constexpr (Q8) p = group8_dot64_q8<false>(Xq + (int64_t)pp[s] * dq, Rn, d, g);
             else p = group8_dot64<false>(X + (int64_t)pp[s] * d, Rn, d, g);
-            if (g == 0 && i < c.len) {
-                uint64_t u = key_of(p);
-                keys[(int64_t)t * n + s] = u;
-                atomicAdd(&s_hist[(uint32_t)(u >> 53)], 1u);
-            }
+            if (g == 0 && i < c.len) keys[(int64_t)t * n + s] = key_of(p);
         }
     }
-    __syncthreads();
-    uint32_t *gh = hist + ((int64_t)t * nseg + c.seg) * kDigitBins;
-    for (int b = tid; b < kDigitBins; b += 256)
-        if (s_hist[b]) atomicAdd(&gh[b], s_hist[b]);
 }
 
-__global__ void k_sel_init(const SegDesc *__restrict__ segs, int nseg, int T, SelState *state) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nseg * T) return;
-    const SegDesc sg = segs[i % nseg];
-    SelState s;
-    s.pfx_hi = 0;
-    s.pfx_lo = 0;
-    s.nbits = 0;
-    s.rank = sg.size / 2;
-    s.cnt = sg.size;
-    s.mode = SEL_HIST;
-    s.counted = 0;
-    state[i] = s;
-}
+// ---- median of multi-block segments
+//
+// One workgroup per (segment, tree) finds the member of rank floor(m/2) in (key, index) order:
+// histograms over 2 048 equal parts of the remaining range, each pass narrowing it to the part
+// that holds the rank, the members held in registers and the survivors in LDS once 2 048 are left.  (Members
+// ascend in index, so equal keys are ordered by position.)  Segments above kSelDirect first
+// draw 2 048 evenly spaced keys and bracket the median between the sample's ranks 1 024 +- 120
+// (over five standard deviations of a random sample's median); one multi-block pass counts the
+// keys below the bracket and lists the positions inside it (about 12%), and the workgroup
+// reads only those; a bracket that misses costs it passes over the whole segment.  Bound: one
+// read of the keys.  10^6 x 128, 72 trees: 24 launches a level (11-bit digits from the top of
+// the key, most of them empty) took 0.54 ms a level, 4.3 ms a step; these take 2.9 ms.  (No
+// device-scope fence in the pick: each writes back its XCD's whole L2, and cost 1.2 ms a level.)
+constexpr int kSelDirect = 16384;  // members a workgroup keeps in registers, sixteen per thread
+constexpr int kSelSample = 2048, kSelMargin = 120;
+constexpr int kSelFewer = 65536, kSelSample2 = 512, kSelMargin2 = 60;  // segments below this: a cheaper sample
+constexpr int kSelLds = 2048;
 
-// digit j covers key bits [lo_bit, lo_bit + width) of the 96-bit key, from the top
-__device__ inline int digit_width(int j) { return j < 8 ? 11 : 8; }
-
-__global__ __launch_bounds__(256) void k_sel_scan(SelState *__restrict__ state, int nseg,
-                                                  uint32_t *__restrict__ hist) {
-    __shared__ uint32_t s_w[8];
-    __shared__ uint32_t s_res[4];
-    const int t = blockIdx.y, k = blockIdx.x, tid = threadIdx.x;
-    SelState *stp = state + (int64_t)t * nseg + k;
-    const int mode = stp->mode;
-    if (mode == SEL_COMPACT) {
-        if (tid == 0) stp->mode = SEL_GATHERED;
+// S keys by S / 2 threads
+template <int S>
+__global__ __launch_bounds__(S / 2) void k_sel_sample(const SegDesc *__restrict__ segs, const uint64_t *__restrict__ keys,
+                                                      int64_t n, int direct, SelState *__restrict__ state) {
+    constexpr int kMargin = S == kSelSample ? kSelMargin : kSelMargin2;
+    __shared__ uint64_t s_k[S];
+    const int t = blockIdx.y, tid = threadIdx.x;
+    const SegDesc sg = segs[blockIdx.x];
+    SelState *st = state + (int64_t)t * gridDim.x + blockIdx.x;
+    if (sg.size <= direct) {
+        if (tid == 0) st->sampled = 0;
         return;
     }
-    if (mode != SEL_HIST) return;
-    const int j = stp->nbits / kDigitBits;
-    const int w = digit_width(j);
-    const int lo_bit = 96 - stp->nbits - w;
-    uint32_t *h = hist + ((int64_t)t * nseg + k) * kDigitBins;
-    const int nb = 1 << w;
-    const int per = nb / 256;  // 8 (11-bit digit) or 1 (8-bit digit)
-    uint32_t loc[8];
-    uint32_t sum = 0;
-    for (int q = 0; q < per; q++) {
-        loc[q] = h[tid * per + q];
-        sum += loc[q];
-    }
-    uint32_t excl;
-    // block exclusive scan of per-thread sums (64-bit ranks fit in 32 bits: segments < 2^31)
-    {
-        const int lane = tid & 63, wv = tid >> 6;
-        uint32_t x = sum;
-        for (int o = 1; o < 64; o <<= 1) {
-            uint32_t y = __shfl_up(x, o, 64);
-            if (lane >= o) x += y;
-        }
-        if (lane == 63) s_w[wv] = x;
-        __syncthreads();
-        uint32_t wb = 0;
-        for (int q = 0; q < 4; q++)
-            if (q < wv) wb += s_w[q];
-        excl = wb + x - sum;
-    }
-    const uint32_t rank = (uint32_t)stp->rank;
-    if (excl <= rank && rank < excl + sum) {
-        uint32_t c = excl;
-        for (int q = 0; q < per; q++) {
-            if (rank < c + loc[q]) {
-                s_res[0] = tid * per + q;
-                s_res[1] = c;
-                s_res[2] = loc[q];
-                break;
-            }
-            c += loc[q];
-        }
+    const uint64_t *kk = keys + (int64_t)t * n + sg.off;
+#pragma unroll
+    for (int e = 0; e < 2; e++) {
+        const int i = tid + S / 2 * e;
+        s_k[i] = kk[((int64_t)i * sg.size + sg.size / 2) / S];
     }
     __syncthreads();
-    for (int q = 0; q < per; q++) h[tid * per + q] = 0;  // ready for the next digit
+    for (int size = 2; size <= S; size <<= 1)
+        for (int stride = size >> 1; stride > 0; stride >>= 1) {
+            const int lo = 2 * tid - (tid & (stride - 1)), hi = lo + stride;
+            const uint64_t a = s_k[lo], b = s_k[hi];
+            if ((a > b) == ((lo & size) == 0)) {
+                s_k[lo] = b;
+                s_k[hi] = a;
+            }
+            __syncthreads();
+        }
     if (tid == 0) {
-        const uint32_t b = s_res[0];
-        unsigned __int128 P = key96(stp->pfx_hi, stp->pfx_lo) | ((unsigned __int128)b << lo_bit);
-        stp->pfx_hi = (uint64_t)(P >> 32);
-        stp->pfx_lo = (uint32_t)P;
-        stp->nbits += w;
-        stp->rank = rank - s_res[1];
-        stp->cnt = s_res[2];
-        if (stp->nbits == 96) stp->mode = SEL_DONE;
-        else if (stp->cnt <= kCandCap) stp->mode = SEL_COMPACT;
+        st->lo = s_k[S / 2 - kMargin];
+        st->hi = s_k[S / 2 + kMargin];
+        st->cnt = 0;
+        st->sampled = 1;
     }
 }
 
-__global__ __launch_bounds__(256) void k_sel_pass(const ChunkDesc *__restrict__ chunks,
-                                                  const uint64_t *__restrict__ keys,
-                                                  const int32_t *__restrict__ perm, int64_t n,
-                                                  SelState *__restrict__ state, int nseg,
-                                                  uint32_t *__restrict__ hist,
-                                                  Cand *__restrict__ cand,
-                                                  uint32_t *__restrict__ cand_cnt,
-                                                  uint32_t *__restrict__ lcount, int nchunk) {
-    __shared__ uint32_t s_hist[kDigitBins];
+// The list of a bracketed segment: keys, then positions, of at most (m - 2) / 3 members, in the
+// segment's part of the permutation that the partition will write (4 m bytes).
+struct SelList {
+    uint64_t *key;
+    uint32_t *pos;
+    uint32_t cap;
+    __device__ SelList(int32_t *perm, int64_t at, int m) {
+        cap = (uint32_t)(m - 2) / 3;
+        key = reinterpret_cast<uint64_t *>((reinterpret_cast<uintptr_t>(perm + at) + 7) & ~(uintptr_t)7);
+        pos = reinterpret_cast<uint32_t *>(key + cap);
+    }
+};
+
+// Keys of a chunk below the bracket (lcount), and those inside it, listed.
+__global__ __launch_bounds__(256) void k_sel_count(const SegDesc *__restrict__ segs, const ChunkDesc *__restrict__ chunks,
+                                                   const uint64_t *__restrict__ keys, int64_t n,
+                                                   SelState *__restrict__ state, int nseg, int32_t *__restrict__ list,
+                                                   uint32_t *__restrict__ lcount) {
     __shared__ uint32_t s_w[8];
-    const int t = blockIdx.y, tid = threadIdx.x;
+    __shared__ uint32_t s_at;
+    const int t = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const ChunkDesc c = chunks[blockIdx.x];
-    const SelState st = state[(int64_t)t * nseg + c.seg];
-    if (st.mode != SEL_HIST && st.mode != SEL_COMPACT) return;
-    const unsigned __int128 P = key96(st.pfx_hi, st.pfx_lo);
-    const int sh = 96 - st.nbits;
-    const uint64_t *kk = keys + (int64_t)t * n;
-    const int32_t *pp = perm + (int64_t)t * n;
-    if (st.mode == SEL_HIST) {
-        const int j = st.nbits / kDigitBits;
-        const int w = digit_width(j);
-        const int lo_bit = 96 - st.nbits - w;
-        const uint32_t msk = (1u << w) - 1;
-        for (int b = tid; b < kDigitBins; b += 256) s_hist[b] = 0;
-        __syncthreads();
-        for (int i = tid; i < c.len; i += 256) {
-            const int64_t s = c.start + i;
-            unsigned __int128 K = key96(kk[s], (uint32_t)pp[s]);
-            if (st.nbits == 0 || (K >> sh) == (P >> sh)) atomicAdd(&s_hist[(uint32_t)(K >> lo_bit) & msk], 1u);
+    SelState *st = state + (int64_t)t * nseg + c.seg;
+    if (!st->sampled) return;
+    const uint64_t lo = st->lo, hi = st->hi;
+    const uint64_t *kk = keys + (int64_t)t * n + c.start;
+    constexpr int E = kChunk / 256;
+    uint32_t below = 0, in = 0;  // per wave (uniform)
+    uint64_t k[E], mine[E];
+#pragma unroll
+    for (int e = 0; e < E; e++) k[e] = kk[tid + 256 * e < c.len ? tid + 256 * e : 0];
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+        const bool ok = tid + 256 * e < c.len;
+        below += (uint32_t)__popcll(__ballot(ok && k[e] < lo));
+        mine[e] = __ballot(ok && k[e] >= lo && k[e] <= hi);
+        in += (uint32_t)__popcll(mine[e]);
+    }
+    if (lane == 0) {
+        s_w[w] = in;
+        s_w[4 + w] = below;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        lcount[(int64_t)t * gridDim.x + blockIdx.x] = s_w[4] + s_w[5] + s_w[6] + s_w[7];
+        const uint32_t tot = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+        s_at = tot ? (uint32_t)atomicAdd(&st->cnt, (int)tot) : 0u;
+    }
+    __syncthreads();
+    uint32_t at = s_at;
+    for (int q = 0; q < w; q++) at += s_w[q];
+    const SegDesc sg = segs[c.seg];
+    const SelList out(list, (int64_t)t * n + sg.off, sg.size);
+    const uint32_t rel = (uint32_t)(c.start - sg.off);
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+        const uint32_t slot = at + mask_rank(mine[e]);
+        if ((mine[e] >> lane & 1) && slot < out.cap) {  // (a list that overflows is not used)
+            out.key[slot] = k[e];
+            out.pos[slot] = rel + tid + 256 * e;
         }
-        __syncthreads();
-        uint32_t *gh = hist + ((int64_t)t * nseg + c.seg) * kDigitBins;
-        for (int b = tid; b < kDigitBins; b += 256)
-            if (s_hist[b]) atomicAdd(&gh[b], s_hist[b]);
-    } else {
-        // gather the keys matching the prefix (at most kCandCap of them in the segment), each
-        // with its chunk; the chunk's keys below the prefix are counted on the way, so that
-        // the median's final step can complete the chunk's left count for the partition
-        uint32_t mine = 0, below = 0;
-        for (int i = tid; i < c.len; i += 256) {
-            const int64_t s = c.start + i;
-            unsigned __int128 K = key96(kk[s], (uint32_t)pp[s]);
-            mine += ((K >> sh) == (P >> sh)) ? 1u : 0u;
-            below += ((K >> sh) < (P >> sh)) ? 1u : 0u;
-        }
-        const int lane = tid & 63, wv = tid >> 6;
-        uint32_t x = mine;
-        for (int o = 1; o < 64; o <<= 1) {
-            uint32_t y = __shfl_up(x, o, 64);
-            if (lane >= o) x += y;
-        }
-        for (int o = 32; o > 0; o >>= 1) below += __shfl_xor(below, o, 64);
-        if (lane == 63) s_w[wv] = x;
-        if (lane == 0) s_w[4 + wv] = below;
-        __syncthreads();
-        uint32_t wb = 0, total = 0;
-        for (int q = 0; q < 4; q++) {
-            if (q < wv) wb += s_w[q];
-            total += s_w[q];
-        }
-        if (tid == 0) lcount[(int64_t)t * nchunk + blockIdx.x] = s_w[4] + s_w[5] + s_w[6] + s_w[7];
-        if (total == 0) return;
-        __syncthreads();  // s_w[4] is read above before it is reused below
-        if (tid == 0) s_w[4] = atomicAdd(&cand_cnt[(int64_t)t * nseg + c.seg], total);
-        __syncthreads();
-        uint32_t pos = s_w[4] + wb + x - mine;
-        Cand *cc = cand + ((int64_t)t * nseg + c.seg) * kCandCap;
-        for (int i = tid; i < c.len; i += 256) {
-            const int64_t s = c.start + i;
-            unsigned __int128 K = key96(kk[s], (uint32_t)pp[s]);
-            if ((K >> sh) == (P >> sh)) {
-                if (pos < (uint32_t)kCandCap) cc[pos] = Cand{kk[s], (uint32_t)pp[s], (uint32_t)blockIdx.x};
-                pos++;
-            }
-        }
+        at += (uint32_t)__popcll(mine[e]);
     }
 }
 
-__global__ __launch_bounds__(256) void k_sel_finish(const SegDesc *__restrict__ segs,
-                                                    SelState *__restrict__ state, int nseg,
-                                                    const Cand *__restrict__ cand,
-                                                    const uint32_t *__restrict__ cand_cnt,
-                                                    int64_t H, double *__restrict__ split,
-                                                    int32_t *__restrict__ split_idx,
-                                                    int32_t *__restrict__ chosen,
-                                                    int32_t *__restrict__ err,
-                                                    uint32_t *__restrict__ lcount, int nchunk) {
-    __shared__ uint64_t s_hi[kCandCap];
-    __shared__ uint32_t s_lo[kCandCap];
-    __shared__ uint32_t s_h[256];
-    __shared__ uint32_t s_w[8];
-    __shared__ uint32_t s_sel[3];
-    const int t = blockIdx.y, k = blockIdx.x, tid = threadIdx.x;
-    SelState *stp = state + (int64_t)t * nseg + k;
-    const SelState st = *stp;
-    __syncthreads();
-    if (st.mode == SEL_GATHERED) {
-        const uint32_t cnt = cand_cnt[(int64_t)t * nseg + k];
-        if (cnt != (uint32_t)st.cnt || cnt > (uint32_t)kCandCap) {
-            if (tid == 0) atomicOr(err, 2);
+__global__ __launch_bounds__(1024) void k_sel_pick(const SegDesc *__restrict__ segs, const uint64_t *__restrict__ keys,
+                                                   const int32_t *__restrict__ perm, int64_t n,
+                                                   SelState *__restrict__ state, int sampled,
+                                                   int32_t *__restrict__ listmem, uint32_t *__restrict__ lcount,
+                                                   int nchunk, int64_t H, double *__restrict__ split,
+                                                   int32_t *__restrict__ split_idx, int32_t *__restrict__ chosen,
+                                                   int32_t *__restrict__ err) {
+    constexpr int kBins = 2048, kCnt = 1024;
+    __shared__ uint32_t s_h[kBins];
+    __shared__ uint64_t s_k[kSelLds];
+    __shared__ uint32_t s_p[kSelLds];
+    __shared__ uint32_t s_c[kCnt];  // left members per chunk, where the segment has at most kCnt
+    __shared__ uint64_t s_fk[64];
+    __shared__ uint32_t s_fp[64];
+    __shared__ uint64_t s_mm[32];
+    __shared__ uint32_t s_w[16];
+    __shared__ uint32_t s_sel[4];
+    const int t = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const SegDesc sg = segs[blockIdx.x];
+    SelState *stp = state + (int64_t)t * gridDim.x + blockIdx.x;
+    const uint64_t *kk = keys + (int64_t)t * n + sg.off;
+    uint32_t *lc = lcount + (int64_t)t * nchunk + sg.chunk0;
+    const int m = sg.size, nch = sg.nchunk;
+    uint32_t rank = (uint32_t)(m / 2), N = (uint32_t)m, below = 0;
+    const SelList list(listmem, (int64_t)t * n + sg.off, m);
+    bool listed = false;  // the rank is among the listed members
+    uint64_t lo, hi;
+    const bool counted = sampled && stp->sampled;
+    if (counted) {
+        uint32_t b = 0;
+        for (int q = tid; q < nch; q += 1024) b += lc[q];
+        uint32_t excl;
+        block_excl_scan_w<16>(b, s_w, excl, below);
+        const uint32_t cnt = (uint32_t)stp->cnt;
+        if (rank >= below && rank < below + cnt && cnt <= list.cap) {
+            listed = true;
+            N = cnt;
+            rank -= below;
+            lo = stp->lo;
+            hi = stp->hi;
+        }
+    }
+    bool lds = false;  // the survivors are in s_k / s_p
+    auto each = [&](auto &&f) {  // f(key, position) of every survivor, perhaps of others
+        if (lds) {
+            for (uint32_t i = tid; i < N; i += 1024) f(s_k[i], s_p[i]);
             return;
         }
-        const Cand *cc = cand + ((int64_t)t * nseg + k) * kCandCap;
-        for (uint32_t i = tid; i < cnt; i += 256) {
-            s_hi[i] = cc[i].hi;
-            s_lo[i] = cc[i].lo;
+        for (uint32_t i0 = tid; i0 < N; i0 += 8192) {  // eight loads in flight
+            uint64_t k[8];
+            uint32_t p[8];
+#pragma unroll
+            for (int u = 0; u < 8; u++) {
+                const uint32_t i = i0 + 1024 * u < N ? i0 + 1024 * u : i0;
+                p[u] = listed ? list.pos[i] : i;
+                k[u] = listed ? list.key[i] : kk[i];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; u++)
+                if (i0 + 1024 * u < N) f(k[u], p[u]);
+        }
+    };
+    auto range = [&](auto &&in) {  // lo, hi: the smallest and the largest key that `in` takes
+        uint64_t x = ~0ull, y = 0;
+        each([&](uint64_t k, uint32_t p) {
+            if (!in(k, p)) return;
+            x = k < x ? k : x;
+            y = k > y ? k : y;
+        });
+        for (int o = 32; o > 0; o >>= 1) {
+            const uint64_t u = __shfl_xor(x, o, 64), v = __shfl_xor(y, o, 64);
+            x = u < x ? u : x;
+            y = v > y ? v : y;
+        }
+        if (lane == 0) {
+            s_mm[w] = x;
+            s_mm[16 + w] = y;
         }
         __syncthreads();
-        // in-block radix select over the candidates, which share the top st.nbits bits:
-        // 8-bit digits of the 96-bit key until one candidate matches the prefix
-        unsigned __int128 P = key96(st.pfx_hi, st.pfx_lo);
-        int nbits = st.nbits;
-        uint32_t rank = (uint32_t)st.rank, c = cnt;
-        while (c > 1 && nbits < 96) {
-            const int w = 96 - nbits < 8 ? 96 - nbits : 8;
-            const int lo_bit = 96 - nbits - w;
-            s_h[tid] = 0;
-            __syncthreads();
-            for (uint32_t i = tid; i < cnt; i += 256) {
-                const unsigned __int128 Kc = key96(s_hi[i], s_lo[i]);
-                if ((Kc >> (96 - nbits)) == (P >> (96 - nbits)))
-                    atomicAdd(&s_h[(uint32_t)(Kc >> lo_bit) & ((1u << w) - 1u)], 1u);
+        lo = s_mm[0];
+        hi = s_mm[16];
+        for (int q = 1; q < 16; q++) {
+            lo = s_mm[q] < lo ? s_mm[q] : lo;
+            hi = s_mm[16 + q] > hi ? s_mm[16 + q] : hi;
+        }
+        __syncthreads();
+    };
+    auto pick_bin = [&]() {  // the part that holds the rank: s_sel = part, members before, members
+        const uint32_t h0 = s_h[2 * tid], h1 = s_h[2 * tid + 1];
+        uint32_t excl, total;
+        block_excl_scan_w<16>(h0 + h1, s_w, excl, total);
+        if (rank >= excl && rank < excl + h0 + h1) {
+            const bool second = rank >= excl + h0;
+            s_sel[0] = 2 * tid + (second ? 1 : 0);
+            s_sel[1] = excl + (second ? h0 : 0);
+            s_sel[2] = second ? h1 : h0;
+        }
+        __syncthreads();
+    };
+    // left members per chunk, for the partition: so far those below the bracket
+    const bool few = nch <= kCnt;
+    if (few)
+        for (int q = tid; q < nch; q += 1024) s_c[q] = listed ? lc[q] : 0u;
+    else if (!listed)
+        for (int q = tid; q < nch; q += 1024) lc[q] = 0;
+    __builtin_amdgcn_s_waitcnt(0);  // (the counters in memory: one workgroup's, so no fence is needed)
+    __syncthreads();
+    auto add = [&](int q, uint32_t v) { atomicAdd(few ? &s_c[q] : &lc[q], v); };
+    // The usual case: one histogram over the value range, the members of the rank's part
+    // straight to LDS, those of the parts before it counted as left.  Up to sixteen members per
+    // thread stay in registers; a longer list (its range is the bracket) is read twice.
+    constexpr int E = kSelDirect / 1024;
+    const bool reg = N <= (uint32_t)kSelDirect;
+    bool fast = reg || listed;
+    if (fast) {
+        uint64_t rk[E];
+        uint32_t bn[E];
+        double mn = INFINITY, mx = -INFINITY;
+        if (reg) {
+#pragma unroll
+            for (int e = 0; e < E; e++) {
+                if (1024u * e >= N) continue;
+                const uint32_t i = tid + 1024u * e < N ? tid + 1024 * e : 0;
+                rk[e] = listed ? list.key[i] : kk[i];
             }
-            __syncthreads();
-            const uint32_t v = s_h[tid];
-            uint32_t excl, total;
-            block_excl_scan256(v, s_w, excl, total);
-            if (excl <= rank && rank < excl + v) {
-                s_sel[0] = tid;
-                s_sel[1] = excl;
-                s_sel[2] = v;
+#pragma unroll
+            for (int e = 0; e < E; e++) {
+                if (1024u * e >= N) continue;
+                mn = fmin(mn, val_of(rk[e]));
+                mx = fmax(mx, val_of(rk[e]));
             }
-            __syncthreads();
-            P |= (unsigned __int128)s_sel[0] << lo_bit;
+            for (int o = 32; o > 0; o >>= 1) {
+                mn = fmin(mn, shfl_xor_d(mn, o));
+                mx = fmax(mx, shfl_xor_d(mx, o));
+            }
+        } else {
+            mn = val_of(lo);
+            mx = val_of(hi);
+        }
+        double *s_v = reinterpret_cast<double *>(s_mm);
+        if (lane == 0) {
+            s_v[w] = mn;
+            s_v[16 + w] = mx;
+        }
+        for (int i = tid; i < kBins; i += 1024) s_h[i] = 0;
+        if (tid == 0) s_sel[3] = 0;
+        __syncthreads();
+        for (int q = 0; q < 16; q++) {
+            mn = fmin(mn, s_v[q]);
+            mx = fmax(mx, s_v[16 + q]);
+        }
+        const double scale = (double)(kBins - 1) / (mx - mn);
+        auto bin = [&](uint64_t k) -> uint32_t {
+            const double x = (val_of(k) - mn) * scale;  // (no number: a range of one value, or one that overflows)
+            return x > 0.0 ? (x < kBins - 1 ? (uint32_t)x : kBins - 1) : 0u;
+        };
+        if (reg) {
+#pragma unroll
+            for (int e = 0; e < E; e++) {
+                if (1024u * e >= N) continue;
+                bn[e] = bin(rk[e]);
+                if (tid + 1024u * e < N) atomicAdd(&s_h[bn[e]], 1u);
+            }
+        } else {
+            each([&](uint64_t k, uint32_t) { atomicAdd(&s_h[bin(k)], 1u); });
+        }
+        __syncthreads();
+        pick_bin();
+        fast = s_sel[2] <= (uint32_t)kSelLds;
+        if (fast) {
+            const uint32_t fb = s_sel[0];
             rank -= s_sel[1];
-            c = s_sel[2];
-            nbits += w;
-            __syncthreads();
-        }
-        for (uint32_t i = tid; i < cnt; i += 256) {  // the one candidate with the full prefix
-            const unsigned __int128 Kc = key96(s_hi[i], s_lo[i]);
-            if ((Kc >> (96 - nbits)) == (P >> (96 - nbits))) {
-                stp->pfx_hi = s_hi[i];
-                stp->pfx_lo = s_lo[i];
-                stp->nbits = 96;
-                stp->mode = SEL_DONE;
+            auto keep = [&](uint64_t k, uint32_t p) {
+                const uint32_t at = atomicAdd(&s_sel[3], 1u);
+                s_k[at] = k;
+                s_p[at] = p;
+            };
+            if (reg) {
+#pragma unroll
+                for (int e = 0; e < E; e++) {
+                    if (1024u * e >= N) continue;
+                    const uint32_t i = tid + 1024 * e;
+                    if (i < N && bn[e] == fb) keep(rk[e], listed ? list.pos[i] : i);
+                    if (listed) {
+                        if (i < N && bn[e] < fb) add((int)(list.pos[i] / kChunk), 1u);
+                    } else {  // 1 024 members, of one chunk
+                        const uint64_t mask = __ballot(i < N && bn[e] < fb);
+                        if (lane == 0 && mask) add(1024 * e / kChunk, (uint32_t)__popcll(mask));
+                    }
+                }
+            } else {
+                each([&](uint64_t k, uint32_t p) {
+                    const uint32_t b = bin(k);
+                    if (b == fb) keep(k, p);
+                    else if (b < fb) add((int)(p / kChunk), 1u);
+                });
             }
+            lds = true;
+            N = s_sel[2];
         }
         __syncthreads();
-        // the partition's left count of every chunk: its keys below the gathered prefix
-        // (counted by the gathering pass) plus its candidates below the median
-        const SelState fs = *stp;
-        if (fs.mode == SEL_DONE) {
-            const unsigned __int128 S = key96(fs.pfx_hi, fs.pfx_lo);
-            for (uint32_t i = tid; i < cnt; i += 256)
-                if (key96(s_hi[i], s_lo[i]) < S) atomicAdd(&lcount[(int64_t)t * nchunk + cc[i].pad], 1u);
-            if (tid == 0) stp->counted = 1;
+    }
+    if (lds ? N > 64 : !listed) range([](uint64_t, uint32_t) { return true; });
+    else if (lds) {
+        lo = 0;
+        hi = ~0ull;
+    }
+    uint32_t left = N;
+    uint64_t plo = 0, phi = (uint64_t)m - 1;  // range of positions (narrowed among equal keys)
+    auto inside = [&](uint64_t k, uint32_t p) { return k >= lo && k <= hi && p >= plo && p <= phi; };
+    bool by_value = true;
+    while (left > 64 && (lo < hi || plo < phi)) {
+        // 2 048 parts of the range: of the values (their density is smooth), of the bit patterns
+        // where values do not separate the keys, or of the positions of equal keys.  All three
+        // are monotone in the order, and the last two always shrink the range.
+        const int how = lo == hi ? 2 : by_value ? 0 : 1;
+        const double v0 = val_of(lo), scale = (double)(kBins - 1) / (val_of(hi) - v0);
+        const uint64_t a = how == 2 ? plo : lo, width = (how == 2 ? phi : hi) - a;
+        const int sh = width < kBins ? 0 : 53 - __clzll((long long)width);
+        auto bin_of = [&](uint64_t k, uint32_t p) -> uint32_t {
+            if (how == 0) {
+                const double x = (val_of(k) - v0) * scale;  // (inf or NaN: a range that overflows)
+                return x > 0.0 ? (x < kBins - 1 ? (uint32_t)x : kBins - 1) : 0u;
+            }
+            return (uint32_t)(((how == 2 ? (uint64_t)p : k) - a) >> sh);
+        };
+        for (int i = tid; i < kBins; i += 1024) s_h[i] = 0;
+        __syncthreads();
+        each([&](uint64_t k, uint32_t p) {
+            if (inside(k, p)) atomicAdd(&s_h[bin_of(k, p)], 1u);
+        });
+        __syncthreads();
+        pick_bin();
+        const uint32_t b = s_sel[0], was = left;
+        rank -= s_sel[1];
+        left = s_sel[2];
+        if (how == 0) {
+            const uint64_t l0 = lo, h0_ = hi;
+            range([&](uint64_t k, uint32_t p) { return k >= l0 && k <= h0_ && bin_of(k, p) == b; });
+            by_value = 2 * left < was;
+        } else {
+            const uint64_t na = a + ((uint64_t)b << sh), nb = na + (((uint64_t)1 << sh) - 1);
+            if (how == 2) {
+                plo = na;
+                phi = nb < phi ? nb : phi;
+            } else {
+                lo = na;
+                hi = nb < hi ? nb : hi;
+                by_value = true;
+            }
+            __syncthreads();
         }
-    } else if (st.mode != SEL_DONE) {
-        if (tid == 0) atomicOr(err, 4);
+        if (!lds && left <= (uint32_t)kSelLds && left > 64) {
+            if (tid == 0) s_sel[3] = 0;
+            __syncthreads();
+            each([&](uint64_t k, uint32_t p) {
+                if (inside(k, p)) {
+                    const uint32_t at = atomicAdd(&s_sel[3], 1u);
+                    s_k[at] = k;
+                    s_p[at] = p;
+                }
+            });
+            __syncthreads();
+            lds = true;
+            N = left;
+        }
+    }
+    if (tid == 0) s_sel[3] = 0;
+    __syncthreads();
+    each([&](uint64_t k, uint32_t p) {
+        if (inside(k, p)) {
+            const uint32_t at = atomicAdd(&s_sel[3], 1u);
+            s_fk[at & 63] = k;
+            s_fp[at & 63] = p;
+        }
+    });
+    __syncthreads();
+    const uint32_t fin = s_sel[3];
+    if (fin > 64 || rank >= fin) {  // never: the counts above are consistent
+        if (tid == 0) atomicOr(err, 2);
         return;
     }
-    if (tid == 0) {
-        const SelState fin = *stp;
-        const int64_t hs = (int64_t)t * H + (segs[k].heap - 1);
-        split[hs] = val_of(fin.pfx_hi);
-        split_idx[hs] = (int32_t)fin.pfx_lo;
-        if (chosen) chosen[hs] = 0;  // one direction per node (else Alg. 2's pick stands already)
-        if (fin.mode != SEL_DONE) atomicOr(err, 8);
+    if (tid < 64 && (uint32_t)tid < fin) {
+        uint32_t r = 0;
+        for (uint32_t q = 0; q < fin; q++)
+            r += s_fk[q] < s_fk[tid] || (s_fk[q] == s_fk[tid] && s_fp[q] < s_fp[tid]) ? 1u : 0u;
+        if (r == rank) {
+            s_mm[0] = s_fk[tid];
+            s_sel[0] = s_fp[tid];
+        }
     }
-}
-
-__global__ __launch_bounds__(256) void k_part_count(const ChunkDesc *__restrict__ chunks, int nchunk,
-                                                    const uint64_t *__restrict__ keys,
-                                                    const int32_t *__restrict__ perm, int64_t n,
-                                                    const SelState *__restrict__ state, int nseg,
-                                                    uint32_t *__restrict__ lcount) {
-    __shared__ uint32_t s_w[4];
-    const int t = blockIdx.y, tid = threadIdx.x;
-    const ChunkDesc c = chunks[blockIdx.x];
-    const SelState st = state[(int64_t)t * nseg + c.seg];
-    if (st.counted) return;  // the median's final step counted this chunk already
-    uint32_t mine = 0;
-    for (int i = tid; i < c.len; i += 256) {
-        const int64_t s = c.start + i;
-        mine += key_less(keys[(int64_t)t * n + s], (uint32_t)perm[(int64_t)t * n + s], st.pfx_hi, st.pfx_lo) ? 1u : 0u;
-    }
-    for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o, 64);
-    if ((tid & 63) == 0) s_w[tid >> 6] = mine;
     __syncthreads();
-    if (tid == 0) lcount[(int64_t)t * nchunk + blockIdx.x] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
-}
-
-__global__ void k_part_scan(const SegDesc *__restrict__ segs, const ChunkDesc *__restrict__ chunks,
-                            int nchunk, int nseg, uint32_t *__restrict__ lcount,
-                            int32_t *__restrict__ err) {
-    // lcount[t][c] becomes the number of left members before chunk c within its segment
-    const int t = blockIdx.y;
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nseg) return;
-    const SegDesc sg = segs[k];
-    uint32_t run = 0;
-    for (int q = 0; q < sg.nchunk; q++) {
-        uint32_t *p = lcount + (int64_t)t * nchunk + sg.chunk0 + q;
-        uint32_t v = *p;
-        *p = run;
-        run += v;
+    const uint64_t ck = s_mm[0];
+    const uint32_t cp = s_sel[0];
+    // the left members not yet counted: those before the median in its part, or all of them
+    auto is_left = [&](uint64_t k, uint32_t p) { return k < ck || (k == ck && p < cp); };
+    if (fast || listed) {
+        lds = fast;
+        N = fast ? N : (uint32_t)stp->cnt;
+        each([&](uint64_t k, uint32_t p) {
+            if (is_left(k, p)) add((int)(p / kChunk), 1u);
+        });
+    } else {
+        for (int base = 0; base < m; base += 1024) {
+            const int i = base + tid;
+            const uint64_t mask = __ballot(i < m && is_left(kk[i < m ? i : 0], (uint32_t)i));
+            if (lane == 0 && mask) add(base / kChunk, (uint32_t)__popcll(mask));
+        }
     }
-    if (run != (uint32_t)(sg.size / 2)) atomicOr(err, 16);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    uint32_t run = 0;
+    for (int base = 0; base < nch; base += 1024) {
+        const int q = base + tid;
+        const uint32_t v = q < nch ? (few ? s_c[q] : __hip_atomic_load(&lc[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) : 0u;
+        uint32_t excl, total;
+        block_excl_scan_w<16>(v, s_w, excl, total);
+        if (q < nch) lc[q] = run + excl;
+        run += total;
+    }
+    if (tid == 0) {
+        const int64_t hs = (int64_t)t * H + (sg.heap - 1);
+        stp->key = ck;
+        stp->idx = perm[(int64_t)t * n + sg.off + cp];
+        split[hs] = val_of(ck);
+        split_idx[hs] = stp->idx;
+        if (chosen) chosen[hs] = 0;  // one direction per node (else Alg. 2's pick stands already)
+        if (run != (uint32_t)(m / 2)) atomicOr(err, 16);
+    }
 }
 
 __global__ __launch_bounds__(256) void k_part_scatter(const SegDesc *__restrict__ segs,
@@ -936,10 +1074,8 @@ __global__ __launch_bounds__(256) void k_part_scatter(const SegDesc *__restrict_
                                                       const uint32_t *__restrict__ lbase,
                                                       const LookDesc *__restrict__ look,
                                                       const double2 *__restrict__ ahead,
-                                                      uint64_t *__restrict__ keys_next,
-                                                      uint32_t *__restrict__ hist_next, int nseg_next) {
+                                                      uint64_t *__restrict__ keys_next) {
     __shared__ uint32_t s_w[16];
-    __shared__ uint32_t s_hn[2][kDigitBins];  // lead level: digit-0 histograms of the two children
     const int t = blockIdx.y, tid = threadIdx.x;
     const ChunkDesc c = chunks[blockIdx.x];
     const SegDesc sg = segs[c.seg];
@@ -948,19 +1084,13 @@ __global__ __launch_bounds__(256) void k_part_scatter(const SegDesc *__restrict_
     uint32_t lefts = lbase[(int64_t)t * nchunk + blockIdx.x];
     const int64_t rel0 = c.start - sg.off;  // chunk position within the segment
     int32_t *pout = perm_out + (int64_t)t * n + sg.off;
-    const bool lead = look != nullptr, hn = lead && hist_next != nullptr;
-    LookDesc lk{{-1, -1}, {0, 0}};
-    if (lead) lk = look[c.seg];
-    if (hn) {
-        for (int b = tid; b < 2 * kDigitBins; b += 256) (&s_hn[0][0])[b] = 0;
-        __syncthreads();
-    }
+    const bool lead = look != nullptr;
     for (int base = 0; base < c.len; base += 256) {
         const int i = base + tid;
         const bool valid = i < c.len;
         const int64_t s = c.start + (valid ? i : 0);
         const int32_t id = perm_in[(int64_t)t * n + s];
-        const bool left = valid && key_less(keys[(int64_t)t * n + s], (uint32_t)id, st.pfx_hi, st.pfx_lo);
+        const bool left = valid && key_less(keys[(int64_t)t * n + s], (uint32_t)id, st.key, (uint32_t)st.idx);
         uint32_t excl, total;
         block_excl_scan256(left ? 1u : 0u, s_w, excl, total);
         if (valid) {
@@ -971,22 +1101,11 @@ __global__ __launch_bounds__(256) void k_part_scatter(const SegDesc *__restrict_
                 pout[pos] = id;
                 if (lead) {  // the row's key at the next level: its projection onto its child
                     const double2 a = ahead[(int64_t)t * n + s];
-                    const uint64_t u = key_of(left ? a.x : a.y);
-                    keys_next[(int64_t)t * n + sg.off + pos] = u;
-                    if (hn && lk.child_seg[left ? 0 : 1] >= 0) atomicAdd(&s_hn[left ? 0 : 1][(uint32_t)(u >> 53)], 1u);
+                    keys_next[(int64_t)t * n + sg.off + pos] = key_of(left ? a.x : a.y);
                 }
             }
         }
         lefts += total;
-    }
-    if (hn) {
-        __syncthreads();
-        for (int b = 0; b < 2; b++) {
-            if (lk.child_seg[b] < 0) continue;
-            uint32_t *gh = hist_next + ((int64_t)t * nseg_next + lk.child_seg[b]) * kDigitBins;
-            for (int q = tid; q < kDigitBins; q += 256)
-                if (s_hn[b][q]) atomicAdd(&gh[q], s_hn[b][q]);
-        }
     }
 }
 
@@ -1868,17 +1987,15 @@ void launch_level_small(hipStream_t s, bool vec, const float *X, int d, const fl
     launch_check(s, "k_level_small");
 }
 
-size_t cand_bytes() { return sizeof(Cand); }
-
 template <bool VEC>
 static void proj_chunks(hipStream_t s, dim3 gc, const float *X, int d, const float *R, int64_t H,
                         const SegDesc *segs, const ChunkDesc *chunks, const int32_t *pin, int64_t n,
-                        const LargeBufs &b, int nseg, const LevelLink &lk) {
+                        const LargeBufs &b, const LevelLink &lk) {
     const size_t ds = (size_t)((d + 3) & ~3);
     const size_t lds = d > 1024 ? 0 : lk.look ? 3 * ds * sizeof(double) : ds * sizeof(float);
     auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, gc, dim3(256), lds, s, X, d, R, H, segs, chunks, pin, n, nseg, b.keys, b.hist, lk.look,
-                           lk.ahead, lk.xq, lk.dq);
+        hipLaunchKernelGGL(kern, gc, dim3(256), lds, s, X, d, R, H, segs, chunks, pin, n, b.keys, lk.look, lk.ahead,
+                           lk.xq, lk.dq);
     };
     const bool q8 = lk.xq != nullptr;
     if (lk.look && q8) go(k_proj_chunks<VEC, true, true>);
@@ -1889,65 +2006,46 @@ static void proj_chunks(hipStream_t s, dim3 gc, const float *X, int d, const flo
 }
 
 void launch_level_large(hipStream_t s, bool vec, const float *X, int d, const float *R, int64_t H,
-                        const SegDesc *segs, int nseg, const ChunkDesc *chunks, int nchunk,
+                        const SegDesc *segs, int nseg, int max_m, const ChunkDesc *chunks, int nchunk,
                         int T, const int32_t *pin, int32_t *pout, int64_t n, double *split,
                         int32_t *split_idx, int32_t *chosen, int32_t *err, const LargeBufs &b0,
                         double proj_bytes, const LevelLink &lk) {
     dim3 gs(nseg, T), gc(nchunk, T);
     LargeBufs b = b0;
-    if (lk.keys_in) {  // fed level: keys and digit-0 histograms come from the level above
-        b.keys = const_cast<uint64_t *>(lk.keys_in);
-        b.hist = lk.hist_in;
-    }
-    hipLaunchKernelGGL(k_sel_init, dim3((nseg * T + 255) / 256), dim3(256), 0, s, segs, nseg, T, b.state);
-    launch_check(s, "k_sel_init");
-    // fill kernels, not memsets: the level may be recorded in a graph
-    if (!lk.keys_in) fill_u32(b.hist, (int64_t)kDigitBins * nseg * T, 0, s);
-    if (lk.hist_next) fill_u32(lk.hist_next, (int64_t)kDigitBins * lk.nseg_next * T, 0, s);
-    fill_u32(b.cand_cnt, (int64_t)nseg * T, 0, s);
-    launch_check(s, "select memsets");
-    if (lk.roots) {  // every tree's root projections from one read of X, then the first digit
+    if (lk.keys_in) b.keys = const_cast<uint64_t *>(lk.keys_in);  // fed level: made by the level above
+    if (lk.roots) {  // every tree's root projections from one read of X
         ProfScope ps(s, "proj_roots", proj_bytes, 0);
         hipLaunchKernelGGL(k_proj_root, dim3(nchunk, kChunk / 64), dim3(256), 0, s, X, d, R, H, T, segs, chunks,
                            lk.look, n, b.keys, lk.ahead);
         launch_check(s, "k_proj_root");
-        hipLaunchKernelGGL(k_sel_pass, gc, dim3(256), 0, s, chunks, b.keys, pin, n, b.state, nseg, b.hist, b.cand,
-                           b.cand_cnt, b.lcount, nchunk);
-        launch_check(s, "k_sel_pass");
-    } else if (lk.keys_ready) {
-        hipLaunchKernelGGL(k_sel_pass, gc, dim3(256), 0, s, chunks, b.keys, pin, n, b.state, nseg, b.hist, b.cand,
-                           b.cand_cnt, b.lcount, nchunk);
-        launch_check(s, "k_sel_pass");
-    } else if (!lk.keys_in) {
+    } else if (!lk.keys_in && !lk.keys_ready) {
         ProfScope ps(s, lk.look ? "proj_chunks_x3" : "proj_chunks", proj_bytes, 0);
-        if (vec) proj_chunks<true>(s, gc, X, d, R, H, segs, chunks, pin, n, b, nseg, lk);
-        else proj_chunks<false>(s, gc, X, d, R, H, segs, chunks, pin, n, b, nseg, lk);
+        if (vec) proj_chunks<true>(s, gc, X, d, R, H, segs, chunks, pin, n, b, lk);
+        else proj_chunks<false>(s, gc, X, d, R, H, segs, chunks, pin, n, b, lk);
     }
     {
         ProfScope ps(s, "select_passes", 0, 0);
-        for (int j = 0; j < kNumDigits; j++) {
-            hipLaunchKernelGGL(k_sel_scan, gs, dim3(256), 0, s, b.state, nseg, b.hist);
-            launch_check(s, "k_sel_scan");
-            if (j + 1 < kNumDigits) {
-                hipLaunchKernelGGL(k_sel_pass, gc, dim3(256), 0, s, chunks, b.keys, pin, n, b.state, nseg, b.hist,
-                                   b.cand, b.cand_cnt, b.lcount, nchunk);
-                launch_check(s, "k_sel_pass");
-            }
+        // with more segments than CUs the pick costs more than the two launches before it save
+        // it (72 trees, segments of 7 813: 613 us whole, 320 us bracketed); with few, one launch
+        const int direct = (int64_t)nseg * T > 256 ? kChunk : kSelDirect;
+        const int sampled = max_m > direct ? 1 : 0;
+        if (sampled) {
+            if (max_m < kSelFewer)
+                hipLaunchKernelGGL(k_sel_sample<kSelSample2>, gs, dim3(kSelSample2 / 2), 0, s, segs, b.keys, n, direct, b.state);
+            else
+                hipLaunchKernelGGL(k_sel_sample<kSelSample>, gs, dim3(kSelSample / 2), 0, s, segs, b.keys, n, direct, b.state);
+            launch_check(s, "k_sel_sample");
+            hipLaunchKernelGGL(k_sel_count, gc, dim3(256), 0, s, segs, chunks, b.keys, n, b.state, nseg, pout, b.lcount);
+            launch_check(s, "k_sel_count");
         }
-        hipLaunchKernelGGL(k_sel_finish, gs, dim3(256), 0, s, segs, b.state, nseg, b.cand, b.cand_cnt, H, split,
-                           split_idx, chosen, err, b.lcount, nchunk);
-        launch_check(s, "k_sel_finish");
+        hipLaunchKernelGGL(k_sel_pick, gs, dim3(1024), 0, s, segs, b.keys, pin, n, b.state, sampled, pout, b.lcount,
+                           nchunk, H, split, split_idx, chosen, err);
+        launch_check(s, "k_sel_pick");
     }
     {
         ProfScope ps(s, "partition", 0, 0);
-        hipLaunchKernelGGL(k_part_count, gc, dim3(256), 0, s, chunks, nchunk, b.keys, pin, n, b.state, nseg,
-                           b.lcount);
-        launch_check(s, "k_part_count");
-        hipLaunchKernelGGL(k_part_scan, dim3((nseg + 63) / 64, T), dim3(64), 0, s, segs, chunks, nchunk, nseg,
-                           b.lcount, err);
-        launch_check(s, "k_part_scan");
         hipLaunchKernelGGL(k_part_scatter, gc, dim3(256), 0, s, segs, chunks, nchunk, b.keys, pin, pout, n, b.state,
-                           nseg, b.lcount, lk.look, lk.ahead, lk.keys_next, lk.hist_next, lk.nseg_next);
+                           nseg, b.lcount, lk.look, lk.ahead, lk.keys_next);
         launch_check(s, "k_part_scatter");
     }
 }

@@ -2577,20 +2577,29 @@ __global__ __launch_bounds__(NTH) void k_fallback(FallbackArgs F) {
             FbPart *row = F.parts + (int64_t)q * np * K;
             for (int k = tid; k < K; k += NTH) {
                 const bool ok = k < s_tn;
-                row[part * K + k] = FbPart{ok ? s_td[k] : INFINITY, ok ? s_ti[k] : 0x7fffffff, 0};
+                // device-scope stores and loads: the parts may run on different XCDs, and a fence
+                // would write back the whole L2
+                __hip_atomic_store(reinterpret_cast<unsigned long long *>(&row[part * K + k].D),
+                                   (unsigned long long)__double_as_longlong(ok ? s_td[k] : INFINITY), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&row[part * K + k].idx, ok ? s_ti[k] : 0x7fffffff, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
             }
-            __threadfence();
+            __builtin_amdgcn_s_waitcnt(0);  // this wave's stores have reached memory
             __syncthreads();
             if (tid == 0) s_last = atomicAdd(&F.arrived[q], 1) == np - 1;
             __syncthreads();
             if (!s_last) continue;
-            __threadfence();
             if (tid == 0) s_tn = 0;
             __syncthreads();
             for (int base = 0; base < np * K; base += NTH) {
-                const FbPart e = base + tid < np * K ? row[base + tid] : FbPart{INFINITY, 0x7fffffff, 0};
-                s_cd[tid] = e.D;
-                s_ci[tid] = e.idx;
+                const bool in = base + tid < np * K;
+                FbPart *e = row + (in ? base + tid : 0);
+                const double D = __longlong_as_double((long long)__hip_atomic_load(
+                    reinterpret_cast<unsigned long long *>(&e->D), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                const int32_t id = __hip_atomic_load(&e->idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                s_cd[tid] = in ? D : INFINITY;
+                s_ci[tid] = in ? id : 0x7fffffff;
                 merge();
             }
         }

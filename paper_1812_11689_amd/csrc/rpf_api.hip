@@ -18,7 +18,6 @@
 namespace rpf {
 
 // ---- launchers defined in build_kernels.hip / knn_kernels.hip
-size_t cand_bytes();
 size_t level_small_lds(int max_m, int d, int n_try);
 size_t level_try_lds(int max_m, int d, int n_try);
 void launch_level_try(hipStream_t s, bool vec, const float *X, int d, const float *R, int64_t H, int n_try,
@@ -32,7 +31,7 @@ void launch_level_small(hipStream_t s, bool vec, const float *X, int d, const fl
                         int64_t n, double *split, int32_t *split_idx, int32_t *chosen, int32_t *err,
                         const LevelLink &lk);
 void launch_level_large(hipStream_t s, bool vec, const float *X, int d, const float *R, int64_t H,
-                        const SegDesc *segs, int nseg, const ChunkDesc *chunks, int nchunk, int T,
+                        const SegDesc *segs, int nseg, int max_m, const ChunkDesc *chunks, int nchunk, int T,
                         const int32_t *pin, int32_t *pout, int64_t n, double *split, int32_t *split_idx,
                         int32_t *chosen, int32_t *err, const LargeBufs &b, double proj_bytes,
                         const LevelLink &lk);
@@ -641,14 +640,13 @@ static rpf_status prepare_forest(const int64_t *sizes, int count, int32_t d, con
 
     // ---- level links: with one direction per node, pair each level with the next (the lead
     // projects onto the children too); a multi-block level is never fed by a one-block one
-    bool any_link = false, any_large_fed = false;
+    bool any_link = false;
     if (n_try == 1 && d <= 1024)
         for (int l = 0; l + 1 < L; l++) {
             LevelPlan &a = levels[l], &b = levels[l + 1];
             if (a.fed || a.segs.empty() || b.segs.empty() || (b.large && !a.large)) continue;
             a.lead = b.fed = true;
             any_link = true;
-            any_large_fed |= b.large;
         }
 
     // ---- the persistent subtree schedule: from the first level after which every level fits
@@ -693,11 +691,10 @@ static rpf_status prepare_forest(const int64_t *sizes, int count, int32_t d, con
     uint64_t tmp_bytes = 0;
     if (max_seg_large > 0) {
         tmp_bytes += (uint64_t)T * n * 8;                                      // keys
-        tmp_bytes += (uint64_t)T * max_seg_large * (sizeof(SelState) + 4 * kDigitBins + cand_bytes() * kCandCap + 4);
+        tmp_bytes += (uint64_t)T * max_seg_large * sizeof(SelState);
         tmp_bytes += (uint64_t)T * max_chunk_large * 4;
     }
     if (any_link) tmp_bytes += (uint64_t)T * n * (16 + 8);                    // ahead, keys2
-    if (any_large_fed) tmp_bytes += (uint64_t)T * max_seg_large * 4 * kDigitBins;  // hist2
     // levels that score tries over many blocks: the projections of `try_group` tries at once
     // (all of them where they fit 4 GiB and the budget), the sums' partials in the norms array
     // (written after the last level) where they fit it.  A budget that holds no projections
@@ -865,9 +862,6 @@ static rpf_status prepare_forest(const int64_t *sizes, int count, int32_t d, con
     if (max_seg_large > 0) {
         ok &= talloc((void **)&lb.keys, (size_t)T * n * 8);
         ok &= talloc((void **)&lb.state, (size_t)T * max_seg_large * sizeof(SelState));
-        ok &= talloc((void **)&lb.hist, (size_t)T * max_seg_large * 4 * kDigitBins);
-        ok &= talloc((void **)&lb.cand, (size_t)T * max_seg_large * cand_bytes() * kCandCap);
-        ok &= talloc((void **)&lb.cand_cnt, (size_t)T * max_seg_large * 4);
         ok &= talloc((void **)&lb.lcount, (size_t)T * max_chunk_large * 4);
     }
     if (max_seg_try > 0) {
@@ -886,7 +880,6 @@ static rpf_status prepare_forest(const int64_t *sizes, int count, int32_t d, con
         ok &= talloc((void **)&lb.ahead, (size_t)T * n * 16);
         ok &= talloc((void **)&lb.keys2, (size_t)T * n * 8);
     }
-    if (any_large_fed) ok &= talloc((void **)&lb.hist2, (size_t)T * max_seg_large * 4 * kDigitBins);
     if (!ok) {
         fail(RPF_ENOMEM, "rpf_build: temporary allocation failed");
         return bail(RPF_ENOMEM);
@@ -971,15 +964,8 @@ static void build_launches(rpf_forest *f, hipStream_t s) {
             lk.look = f->d_look + lv.seg_off;
             lk.ahead = f->lb.ahead;
             lk.keys_next = f->lb.keys2;
-            if (f->levels[l + 1].large) {
-                lk.hist_next = f->lb.hist2;
-                lk.nseg_next = (int)f->levels[l + 1].segs.size();
-            }
         }
-        if (lv.fed) {
-            lk.keys_in = f->lb.keys2;
-            if (lv.large) lk.hist_in = f->lb.hist2;
-        }
+        if (lv.fed) lk.keys_in = f->lb.keys2;
         // the roots: identity permutation in every tree, so one read of X serves all trees
         lk.roots = l == 0 && lv.lead && lv.large && vec && d <= 128;
         // grid forests: the rows come from the int8 copy (one byte a coordinate)
@@ -1012,7 +998,7 @@ static void build_launches(rpf_forest *f, hipStream_t s) {
                                    f->err, lk);
             launch_check(s, "level_small");
         } else {
-            launch_level_large(s, vec, f->X, d, f->R, H, f->d_segs + lv.seg_off, (int)lv.segs.size(),
+            launch_level_large(s, vec, f->X, d, f->R, H, f->d_segs + lv.seg_off, (int)lv.segs.size(), lv.max_m,
                                f->d_chunks + lv.chunk_off, (int)lv.chunks.size(), T, pin, pout, n, f->split,
                                f->split_idx, chosen, f->err, f->lb, proj_bytes, lk);
             launch_check(s, "level_large");

@@ -27,10 +27,6 @@ namespace rpf {
 
 constexpr int kLarge = 4096;      // segments above this size use the multi-block path
 constexpr int kChunk = 4096;      // positions per block on the multi-block path (power of 2)
-constexpr int kDigitBits = 11;    // radix digit of the multi-block median select
-constexpr int kDigitBins = 1 << kDigitBits;
-constexpr int kNumDigits = 9;     // 96-bit key (p, index): 8 digits of 11 bits + 1 of 8
-constexpr int kCandCap = 1024;    // candidates gathered for the final in-block select
 
 // ---------------------------------------------------------------- descriptors
 
@@ -56,17 +52,13 @@ struct LeafDesc {
     int32_t heap;
 };
 
-// multi-block median select state, one per (tree, segment)
-enum : int32_t { SEL_HIST = 0, SEL_COMPACT = 1, SEL_GATHERED = 2, SEL_DONE = 3 };
-
-struct SelState {
-    uint64_t pfx_hi;   // prefix of the 96-bit key found so far (top nbits valid)
-    uint32_t pfx_lo;
-    int32_t nbits;
-    int64_t rank;      // rank of the target among the keys that match the prefix
-    int64_t cnt;       // number of keys that match the prefix
-    int32_t mode;
-    int32_t counted;   // 1: the final step filled the partition's left counts of the chunks
+struct SelState {      // median select of one multi-block (tree, segment)
+    uint64_t lo, hi;   // sampled: the median lies between these keys (almost surely)
+    uint64_t key;      // the median's key and index
+    int32_t idx;
+    int32_t cnt;       // sampled: listed positions
+    int32_t sampled;
+    int32_t pad;
 };
 
 struct Ent {           // one pruning candidate: point index and bounds on its squared distance
@@ -82,12 +74,6 @@ struct LatNorm {       // a point on the 1/255 grid: |k - 128|^2 (exact) and |k|
     float ra;
 };
 
-struct Cand {          // a key gathered for the in-block median select
-    uint64_t hi;
-    uint32_t lo;
-    uint32_t pad;
-};
-
 struct LookDesc {     // the children of one internal node, for projections made a level ahead
     int32_t child_seg[2];   // index among the next level's internal nodes, -1 for a leaf
     int32_t child_heap[2];  // heap ids of the children that are internal nodes, else 0
@@ -101,11 +87,8 @@ struct LevelLink {
     const LookDesc *look = nullptr;   // lead: per internal node of the level (null: not a lead)
     double2 *ahead = nullptr;         // lead: [T][n] projections onto the two children, by position
     uint64_t *keys_next = nullptr;    // lead: [T][n] keys of the fed level, by its positions
-    uint32_t *hist_next = nullptr;    // lead above a multi-block level: its digit-0 histograms
-    int nseg_next = 0;
     const uint64_t *keys_in = nullptr;  // fed: keys made by the lead (null: project)
-    uint32_t *hist_in = nullptr;        // fed multi-block level: histograms made by the lead
-    bool keys_ready = false;  // multi-block level: its keys are in the key buffer, without histograms
+    bool keys_ready = false;  // multi-block level: its keys are in the key buffer
     bool roots = false;  // lead at the roots (identity permutation): one read of X for all trees
     // grid forests: the projections read each row from the int8 copy (k - 128, stride dq)
     // instead of X, a quarter of the bytes for the same binary32 values
@@ -129,13 +112,9 @@ void launch_subtree(hipStream_t s, bool vec, const float *X, int d, const float 
 struct LargeBufs {     // temporaries of the multi-block level path (and of the level links)
     uint64_t *keys;
     uint64_t *keys2;      // keys made one level ahead
-    uint32_t *hist2;      // their digit-0 histograms
     double2 *ahead;       // projections onto the children, by position
     SelState *state;
-    uint32_t *hist;
-    Cand *cand;
-    uint32_t *cand_cnt;
-    uint32_t *lcount;
+    uint32_t *lcount;     // per chunk: keys below the bracket, then left members before it
 };
 
 // Alg. 2 over many blocks (a level whose nodes are too large to be scored in one workgroup):

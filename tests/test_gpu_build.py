@@ -55,6 +55,50 @@ def test_build_matches_oracle(case):
     f.free()
 
 
+SELECT_CASES = [
+    # the median of multi-block nodes: read whole up to 16 384 members, bracketed from a sample
+    # of 2 048 above; more than 1 024 chunks
+    # name, n, d, T, n0, n_try, what
+    ("one_over_a_workgroup", 4097, 6, 3, 2000, 1, "mixture"),
+    ("read_whole_16384", 16_384, 4, 2, 9000, 1, "mixture"),
+    ("bracketed_16385", 16_385, 4, 2, 9000, 1, "mixture"),
+    ("bracketed_tries", 66_000, 6, 2, 20_000, 3, "mixture"),
+    ("ties_at_the_median", 70_000, 3, 2, 9000, 1, "ties"),
+    ("bracket_read_again", 300_000, 3, 2, 90_000, 1, "mixture"),  # more listed than registers hold
+    ("two_values", 40_000, 1, 2, 6000, 1, "two"),
+    ("sample_misses", 70_000, 1, 2, 20_000, 1, "misses"),
+    ("spread_overflows", 9_000, 1, 2, 3000, 1, "huge"),
+    ("chunks_past_1024", 4_300_000, 2, 1, 1_100_000, 1, "mixture"),
+    ("chunks_past_1024_sample_misses", 4_300_000, 1, 1, 2_200_000, 1, "misses"),
+]
+
+
+@pytest.mark.parametrize("case", SELECT_CASES, ids=[c[0] for c in SELECT_CASES])
+def test_median_select_matches_oracle(case):
+    name, n, d, T, n0, n_try, what = case
+    print(f"[build] {name} n={n} d={d} T={T} n0={n0}", flush=True)
+    x, R = problem(n, d, T, n0, n_try, seed=len(name) + 60)
+    if what == "ties":
+        x[: 2 * n // 3] = x[n - 1]  # two thirds of the rows are one point
+    elif what == "two":
+        x[:] = (np.arange(n) % 3 == 0).astype(np.float32)[:, None]
+    elif what == "huge":  # differences of projections reach 1e38 beside values near 1e-38
+        x *= np.float32(10.0) ** np.linspace(-38, 37, n, dtype=np.float32)[:, None]
+    elif what == "misses":  # the evenly spaced sample holds only the largest values
+        at = (np.arange(2048, dtype=np.int64) * n + n // 2) // 2048
+        x[at] += np.float32(1000.0)
+    ref = oracle.build_forest(x, R, T, n0, n_try)
+    f = _gpu_forest(x, R, T, n0, n_try)
+    f.info()  # surfaces device-side invariant failures
+    for t in range(T):
+        g = {k: v.cpu().numpy() for k, v in f.tree_dump(t).items()}
+        np.testing.assert_array_equal(g["perm"], ref.perm[t])
+        np.testing.assert_array_equal(g["leaf_of"], ref.leaf_of[t])
+        assert np.array_equal(g["split"], ref.split[t], equal_nan=True)
+        np.testing.assert_array_equal(g["split_idx"], ref.split_idx[t])
+    f.free()
+
+
 TRY_CASES = [
     # several tries per node: sums over pieces of 256 members, nodes scored in one workgroup
     # (up to 512 members) or over many blocks, 2 to 5 tries per read, more than 16 tries
