@@ -1782,20 +1782,26 @@ __global__ __launch_bounds__(256) void k_leaf_copy(const float *__restrict__ X, 
 // rows of a step in registers, so X is read once.
 // NT threads hold leaves of up to NT / 4 points (1024 threads for 256-point leaves, 256 for
 // leaves of at most 64, where a larger block would leave most of its rows empty).
-template <typename T, bool VEC, int NT>
+// Ragged leaves (uniform rule: a few of up to 256 points, most far below 64) run in two launches,
+// each for its sizes: 256 threads for leaves of at most 64 points, with the same 32 row groups
+// (CL; a thread group of 32 lanes takes CL / RG of them), so the sums do not depend on the
+// launch, and 1024 threads for the rest (100 000 x 32, 32 trees, leaves of 21 points on average:
+// 1 470 -> 540 us).
+template <typename T, bool VEC, int NT, int CL = NT / 32>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_leaf_stats(const float *__restrict__ X, int d, int dp,
                                                      const LeafDesc *__restrict__ leaves, int nleaf,
                                                      const int32_t *__restrict__ perm, int64_t n,
                                                      int32_t *__restrict__ leaf_of, float *__restrict__ centroid,
-                                                     float2 *__restrict__ nrm, float range_max) {
-    constexpr int ML = NT / 4, RG = NT / 32, RK = ML / RG;  // rows, row groups, rows per group
-    __shared__ __align__(16) float s_part[RG][128];
+                                                     float2 *__restrict__ nrm, float range_max, int64_t leaf_stride, int m_lo, int m_hi) {
+    constexpr int ML = NT / 4, RG = NT / 32, RK = ML / RG;  // rows, thread groups, rows per thread group
+    __shared__ __align__(16) float s_part[CL][128];
     __shared__ __align__(16) float s_mu[128];
     __shared__ int32_t s_id[ML];
     __shared__ float s_na[ML], s_ra[ML];  // the rows' norms, summed over the steps in order
     const int t = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
-    const LeafDesc lf = leaves[blockIdx.x];
+    const LeafDesc lf = leaves[t * leaf_stride + blockIdx.x];  // (stride 0: one table for all trees)
     const int m = lf.size;
+    if (m <= m_lo || m > m_hi) return;  // another launch's leaf, or none: m == 0
     const int32_t *pp = perm + (int64_t)t * n + lf.off;
     for (int i = tid; i < m; i += NT) {
         const int id = pp[i];
@@ -1825,21 +1831,24 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
                 }
             }
         }
-        float4 cs = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-        for (int k = 0; k < RK; k++) {
-            if (g + RG * k < m) {
-                cs.x += x[k].x;
-                cs.y += x[k].y;
-                cs.z += x[k].z;
-                cs.w += x[k].w;
+        for (int c = 0; c < CL / RG; c++) {
+            float4 cs = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int k = c; k < RK; k += CL / RG) {
+                if (g + RG * k < m) {
+                    cs.x += x[k].x;
+                    cs.y += x[k].y;
+                    cs.z += x[k].z;
+                    cs.w += x[k].w;
+                }
             }
+            *reinterpret_cast<float4 *>(&s_part[g + RG * c][4 * l32]) = cs;
         }
-        *reinterpret_cast<float4 *>(&s_part[g][4 * l32]) = cs;
         __syncthreads();
         if (tid < 128) {
             float v = 0.f;
-            for (int q = 0; q < RG; q++) v += s_part[q][tid];
+            for (int q = 0; q < CL; q++) v += s_part[q][tid];
             const int jj = cb + tid;
             const float mu = jj < d ? v / (float)m : 0.f;
             s_mu[tid] = mu;
@@ -1879,22 +1888,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
 template <typename T>
 static void leaf_stats(hipStream_t s, bool vec, const float *X, int d, int dp, const LeafDesc *leaves, int nleaf,
                        int ntree, const int32_t *perm, int64_t n, int32_t *leaf_of, float *centroid, float2 *nrm,
-                       float range_max, int max_leaf) {
+                       float range_max, int max_leaf, int64_t leaf_stride) {
     const dim3 grid(nleaf, ntree);
+    auto go = [&](auto kern, int nt, int lo, int hi) {
+        hipLaunchKernelGGL(kern, grid, dim3(nt), 0, s, X, d, dp, leaves, nleaf, perm, n, leaf_of, centroid, nrm, range_max,
+                           leaf_stride, lo, hi);
+    };
     if (max_leaf <= 64) {
-        if (vec)
-            hipLaunchKernelGGL((k_leaf_stats<T, true, 256>), grid, dim3(256), 0, s, X, d, dp, leaves, nleaf, perm, n,
-                               leaf_of, centroid, nrm, range_max);
-        else
-            hipLaunchKernelGGL((k_leaf_stats<T, false, 256>), grid, dim3(256), 0, s, X, d, dp, leaves, nleaf, perm, n,
-                               leaf_of, centroid, nrm, range_max);
+        vec ? go(k_leaf_stats<T, true, 256>, 256, 0, 64) : go(k_leaf_stats<T, false, 256>, 256, 0, 64);
     } else {
-        if (vec)
-            hipLaunchKernelGGL((k_leaf_stats<T, true, 1024>), grid, dim3(1024), 0, s, X, d, dp, leaves, nleaf, perm, n,
-                               leaf_of, centroid, nrm, range_max);
-        else
-            hipLaunchKernelGGL((k_leaf_stats<T, false, 1024>), grid, dim3(1024), 0, s, X, d, dp, leaves, nleaf, perm, n,
-                               leaf_of, centroid, nrm, range_max);
+        const int lo = leaf_stride ? 64 : 0;
+        if (lo) vec ? go(k_leaf_stats<T, true, 256, 32>, 256, 0, 64) : go(k_leaf_stats<T, false, 256, 32>, 256, 0, 64);
+        vec ? go(k_leaf_stats<T, true, 1024>, 1024, lo, 256) : go(k_leaf_stats<T, false, 1024>, 1024, lo, 256);
     }
     launch_check(s, "k_leaf_stats");
 }
@@ -1903,15 +1908,15 @@ static void leaf_stats(hipStream_t s, bool vec, const float *X, int d, int dp, c
 
 void launch_leaf_stats(hipStream_t s, int prec, const float *X, int d, int dp, const LeafDesc *leaves, int nleaf,
                        int ntree, const int32_t *perm, int64_t n, int32_t *leaf_of, float *centroid, float2 *nrm,
-                       int max_leaf) {
+                       int max_leaf, int64_t leaf_stride) {
     if (nleaf <= 0 || ntree <= 0 || max_leaf > 256) return;  // the caller runs the full leaf pass instead
     const bool vec = (d % 4) == 0;
     if (prec == RPF_DIST_BF16)
-        leaf_stats<__bf16>(s, vec, X, d, dp, leaves, nleaf, ntree, perm, n, leaf_of, centroid, nrm, 3.0e38f, max_leaf);
+        leaf_stats<__bf16>(s, vec, X, d, dp, leaves, nleaf, ntree, perm, n, leaf_of, centroid, nrm, 3.0e38f, max_leaf, leaf_stride);
     else if (prec == RPF_DIST_FP16)
-        leaf_stats<_Float16>(s, vec, X, d, dp, leaves, nleaf, ntree, perm, n, leaf_of, centroid, nrm, 60000.f, max_leaf);
+        leaf_stats<_Float16>(s, vec, X, d, dp, leaves, nleaf, ntree, perm, n, leaf_of, centroid, nrm, 60000.f, max_leaf, leaf_stride);
     else
-        leaf_stats<float>(s, vec, X, d, dp, leaves, nleaf, ntree, perm, n, leaf_of, centroid, nrm, 3.0e38f, max_leaf);
+        leaf_stats<float>(s, vec, X, d, dp, leaves, nleaf, ntree, perm, n, leaf_of, centroid, nrm, 3.0e38f, max_leaf, leaf_stride);
 }
 
 template <typename T>

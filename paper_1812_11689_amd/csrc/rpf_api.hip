@@ -45,7 +45,7 @@ void launch_leaf_copy(hipStream_t s, int prec, const float *X, int d, int dp, co
                       int ntree, const int32_t *perm, int64_t n, const float *centroid, void *Xc);
 void launch_leaf_stats(hipStream_t s, int prec, const float *X, int d, int dp, const LeafDesc *leaves, int nleaf,
                        int ntree, const int32_t *perm, int64_t n, int32_t *leaf_of, float *centroid, float2 *nrm,
-                       int max_leaf);
+                       int max_leaf, int64_t leaf_stride);
 void launch_nonfinite(hipStream_t s, const float *x, int64_t count, int32_t *flag);
 void launch_localize(int32_t *idx, int64_t rows, int K, const int64_t *off, int count, hipStream_t s);
 
@@ -383,7 +383,8 @@ struct rpf_forest {
     std::vector<int32_t> tree_nleaf;       // leaves of each tree
     std::vector<int64_t> job_off;          // [T + 1]
     std::vector<double> flops_off;         // [T + 1]
-    std::vector<std::vector<rpf_node>> nodes;
+    std::vector<rpf_node> nodes;           // of all trees, tree after tree, level by level
+    std::vector<int64_t> node_off;         // [T + 1]
 };
 
 namespace rpf {
@@ -1021,7 +1022,7 @@ static void build_launches(rpf_forest *f, hipStream_t s) {
     } else {  // centroids and norms only: the tiles centre the rows as they stage them
         ProfScope ps(s, "leaf_finalize", (double)T * n * (4.0 * d + 16), 0);
         launch_leaf_stats(s, prec, f->X, d, dp, f->d_leaves, (int)nleaf, T, f->perm[cur], n, f->leaf_of, f->centroid,
-                          f->nrm, f->max_leaf);
+                          f->nrm, f->max_leaf, 0);
         launch_check(s, "leaf_stats");
     }
 }
@@ -1132,6 +1133,12 @@ static void uniform_leaf_pass(rpf_forest *f, hipStream_t s) {
     const int d = f->d, dp = f->dp, prec = f->prec;
     const size_t esz = prec == RPF_DIST_FP32 ? 4 : 2;
     const int32_t *perm = f->perm[f->final_buf];
+    if (!f->Xc && f->max_leaf <= 256) {  // every tree's leaves in one launch
+        launch_leaf_stats(s, prec, f->X, d, dp, f->d_leaves, (int)ls, f->T, perm, n, f->leaf_of, f->centroid, f->nrm,
+                          f->max_leaf, ls);
+        launch_check(s, "uniform leaf pass");
+        return;
+    }
     for (int t = 0; t < f->T; t++) {
         const LeafDesc *lv = f->d_leaves + (int64_t)t * ls;
         const int nl = f->tree_nleaf[t];
@@ -1145,7 +1152,7 @@ static void uniform_leaf_pass(rpf_forest *f, hipStream_t s) {
         else if (f->Xq && f->max_leaf > 256)
             launch_leaf_ids(s, lv, nl, 1, pt, n, lo);
         else
-            launch_leaf_stats(s, prec, f->X, d, dp, lv, nl, 1, pt, n, lo, cen, nr, f->max_leaf);
+            launch_leaf_stats(s, prec, f->X, d, dp, lv, nl, 1, pt, n, lo, cen, nr, f->max_leaf, 0);
     }
     launch_check(s, "uniform leaf pass");
 }
@@ -1153,6 +1160,8 @@ static void uniform_leaf_pass(rpf_forest *f, hipStream_t s) {
 // Grow a forest by the uniform split rule: a host-driven level loop over the open nodes of
 // every tree (the shapes depend on the data), then the same leaf pass and all-points tile
 // jobs as the median rule, per tree.  Synchronises the stream once per level.
+// With one direction per node the loop stops at nodes of kGrowBlock members, whose subtrees
+// grow on the device in two launches.
 static rpf_status build_uniform(const float *X, int64_t n, int32_t d, const rpf_params *p, void *stream,
                                 rpf_forest **out) {
     if (out) *out = nullptr;
@@ -1185,6 +1194,22 @@ static rpf_status build_uniform(const float *X, int64_t n, int32_t d, const rpf_
     const bool chunked = n > small_max;  // only nodes above small_max take the chunked path
     // open nodes are larger than n0, chunked ones larger than small_max
     const int64_t seg_cap = TN / (n0 + 1) + T + 1;
+    // One direction per node: subtrees of at most kGrowBlock members grow on the device (build at
+    // 100 000 x 32, 32 trees: 326 -> 43 ms at leaves of 1, 19.5 -> 6.6 at 64, 9.3 -> 6.0 at 800;
+    // 5 000 x 16, 8 trees: 4.9 -> 3.5, 2.4 -> 1.0 and 1.8 -> 0.8).  Not where that leaves a wave
+    // to grow most of a tree by itself into many small leaves (1 000 x 8, 4 trees: 1.2 against
+    // 1.5 ms at leaves of 4, 0.96 against 0.79 at 16), nor for a level or two (0.35 against 0.41
+    // at 800).  The node records go to memory of their own, or where a budget is set or that
+    // memory is not to be had to the norms array, which is written after the last node; should
+    // they outgrow it, the whole forest is grown level by level.
+    bool device_growth = n_try == 1 && (n > 4096 || n0 >= 16) && n0 <= n / 2 &&
+                         uni_grow_lds(kGrowBlock, d) + 4096 <= (size_t)lds_max;
+    constexpr int64_t kRecBytes = sizeof(UniRec) + sizeof(rpf_node) + 12;
+    int64_t rec_cap = std::min<int64_t>(TN, 6 * (TN / (n0 + 1))) + 64 * T;
+    const bool rec_own = !p->mem_budget_bytes && rec_cap * kRecBytes > TN * 8;
+    if (!rec_own) rec_cap = TN * 8 / kRecBytes;
+    rec_cap = std::min<int64_t>(rec_cap, ((int64_t)1 << 31) - 1);
+    const int64_t blk_cap = TN / (kGrowWave + 1) + T + 1;
     const int64_t lseg_cap = chunked ? TN / (small_max + 1) + T + 1 : 0;
     const int64_t chunk_cap = chunked ? TN / kChunk + lseg_cap + 1 : 0;
 
@@ -1194,6 +1219,10 @@ static rpf_status build_uniform(const float *X, int64_t n, int32_t d, const rpf_
     if (chunked)
         tmp_bytes += (uint64_t)n_try * TN * 8 + (uint64_t)TN * 4 + (uint64_t)chunk_cap * (sizeof(UniChunk) + n_try * 24 + 8) +
                      (uint64_t)lseg_cap * (sizeof(UniSeg) + sizeof(UniSplit) + n_try * 8);
+    const int64_t nb = (n >> 8) + 1;  // position ranges of a tree's records
+    const size_t ctr_words = 16 + 2 * (size_t)(T * nb + 1);
+    const uint64_t grow_bytes = (uint64_t)blk_cap * sizeof(UniSeg) + ctr_words * 4 + (uint64_t)T * (sizeof(UniTree) + 8);
+    device_growth &= !p->mem_budget_bytes || bytes + tmp_bytes + grow_bytes <= p->mem_budget_bytes;
     if (p->mem_budget_bytes && bytes + tmp_bytes > p->mem_budget_bytes)
         return fail(RPF_ENOMEM, "rpf_build: forest needs " + std::to_string(bytes + tmp_bytes) +
                                     " bytes, over mem_budget_bytes");
@@ -1250,6 +1279,21 @@ static rpf_status build_uniform(const float *X, int64_t n, int32_t d, const rpf_
     UniBufs ub;
     RPF_UTEMP(d_seg, (size_t)seg_cap * sizeof(UniSeg));
     RPF_UTEMP(d_split, (size_t)seg_cap * sizeof(UniSplit));
+    UniSeg *d_blk = nullptr;      // the block list
+    uint8_t *recmem = reinterpret_cast<uint8_t *>(f->nrm);
+    uint32_t *ctr = nullptr;      // work and record counters, then the records' buckets
+    if (device_growth) {
+        RPF_UTEMP(d_blk, (size_t)blk_cap * sizeof(UniSeg));
+        if (rec_own) {
+            if (void *own = dalloc((size_t)(rec_cap * kRecBytes))) {
+                recmem = static_cast<uint8_t *>(own);
+                temps.push_back(own);
+            } else {
+                rec_cap = std::min<int64_t>(TN * 8 / kRecBytes, ((int64_t)1 << 31) - 1);
+            }
+        }
+        RPF_UTEMP(ctr, ctr_words * 4);
+    }
     if (chunked) {
         RPF_UTEMP(d_lseg, (size_t)lseg_cap * sizeof(UniSeg));
         RPF_UTEMP(d_lsplit, (size_t)lseg_cap * sizeof(UniSplit));
@@ -1281,68 +1325,155 @@ static rpf_status build_uniform(const float *X, int64_t n, int32_t d, const rpf_
         return bail(RPF_EINVAL);
     }
 
-    // ---- growth, level by level
+    // ---- growth, level by level (device growth: the levels of the largest nodes)
     struct Open { int64_t pos, heap; int32_t size, tree, depth; };
     std::vector<Open> open;
     std::vector<std::vector<LeafDesc>> tleaves(T);
-    f->nodes.assign(T, {});
+    std::vector<std::vector<rpf_node>> tnodes(T);
+    std::vector<UniSeg> to_block, to_wave, closed;
+    std::vector<UniRec> recs;
+    std::vector<UniTree> totals(T);
     int max_depth = 0;
     auto close_leaf = [&](const Open &o) {
-        tleaves[o.tree].push_back(LeafDesc{o.pos - (int64_t)o.tree * n, o.size, 0});
+        if (device_growth) closed.push_back(UniSeg{o.pos, o.heap, o.size, o.tree, o.depth, 0});
+        else tleaves[o.tree].push_back(LeafDesc{o.pos - (int64_t)o.tree * n, o.size, 0});
         max_depth = std::max(max_depth, (int)o.depth);
     };
-    for (int64_t t = 0; t < T; t++) {
-        const Open r{t * n, 1, (int32_t)n, (int32_t)t, 0};
-        if (n > n0) open.push_back(r);
-        else close_leaf(r);
-    }
-    std::vector<UniSeg> hs, hl;
-    std::vector<UniChunk> hc;
-    std::vector<int64_t> is_small, is_large;  // indices into `open`
-    std::vector<UniSplit> rs, rl;
-    while (!open.empty()) {
-        hs.clear(); hl.clear(); hc.clear(); is_small.clear(); is_large.clear();
-        int max_small = 2;
-        for (int64_t k = 0; k < (int64_t)open.size(); k++) {
-            const Open &o = open[k];
-            UniSeg g{o.pos, o.heap, o.size, o.tree, 0, 0};
-            if (o.size <= small_max) {
-                hs.push_back(g);
-                is_small.push_back(k);
-                max_small = std::max(max_small, (int)o.size);
-            } else {
-                g.chunk0 = (int32_t)hc.size();
-                g.nchunk = (int32_t)((o.size + kChunk - 1) / kChunk);
-                for (int q = 0; q < g.nchunk; q++) {
-                    const int64_t st0 = o.pos + (int64_t)q * kChunk;
-                    hc.push_back(UniChunk{st0, (int32_t)std::min<int64_t>(kChunk, o.pos + o.size - st0),
-                                          (int32_t)hl.size()});
-                }
-                hl.push_back(g);
-                is_large.push_back(k);
-            }
+    for (;;) {
+        open.clear();
+        for (int64_t t = 0; t < T; t++) {
+            const Open r{t * n, 1, (int32_t)n, (int32_t)t, 0};
+            if (n > n0) open.push_back(r);
+            else close_leaf(r);
         }
-        if ((int64_t)hs.size() > seg_cap || (int64_t)hl.size() > lseg_cap || (int64_t)hc.size() > chunk_cap) {
+        std::vector<UniSeg> hs, hl;
+        std::vector<UniChunk> hc;
+        std::vector<int64_t> is_small, is_large;  // indices into `open`
+        std::vector<UniSplit> rs, rl;
+        while (!open.empty()) {
+            hs.clear(); hl.clear(); hc.clear(); is_small.clear(); is_large.clear();
+            int max_small = 2;
+            for (int64_t k = 0; k < (int64_t)open.size(); k++) {
+                const Open &o = open[k];
+                UniSeg g{o.pos, o.heap, o.size, o.tree, 0, 0};
+                if (device_growth && o.size <= kGrowBlock) {  // its subtree grows on the device
+                    g.chunk0 = o.depth;
+                    g.nchunk = o.size <= small_max ? o.depth : kRecLarge;
+                    (o.size > kGrowWave ? to_block : to_wave).push_back(g);
+                } else if (o.size <= small_max) {
+                    hs.push_back(g);
+                    is_small.push_back(k);
+                    max_small = std::max(max_small, (int)o.size);
+                } else {
+                    g.chunk0 = (int32_t)hc.size();
+                    g.nchunk = (int32_t)((o.size + kChunk - 1) / kChunk);
+                    for (int q = 0; q < g.nchunk; q++) {
+                        const int64_t st0 = o.pos + (int64_t)q * kChunk;
+                        hc.push_back(UniChunk{st0, (int32_t)std::min<int64_t>(kChunk, o.pos + o.size - st0),
+                                              (int32_t)hl.size()});
+                    }
+                    hl.push_back(g);
+                    is_large.push_back(k);
+                }
+            }
+            if ((int64_t)hs.size() > seg_cap || (int64_t)hl.size() > lseg_cap || (int64_t)hc.size() > chunk_cap) {
+                fail(RPF_EINTERNAL, "rpf_build: uniform growth outgrew its node capacity");
+                return bail(RPF_EINTERNAL);
+            }
+            if (hs.empty() && hl.empty()) {
+                open.clear();
+                break;
+            }
+            if (!hs.empty()) {
+                hipMemcpyAsync(d_seg, hs.data(), hs.size() * sizeof(UniSeg), hipMemcpyHostToDevice, s);
+                ProfScope ps(s, "uniform_level_block", 0, 0);
+                launch_uni_block(s, f->X, d, n_try, seed, d_seg, (int)hs.size(), max_small, f->perm[0], d_split);
+            }
+            if (!hl.empty()) {
+                hipMemcpyAsync(d_lseg, hl.data(), hl.size() * sizeof(UniSeg), hipMemcpyHostToDevice, s);
+                hipMemcpyAsync(d_chunk, hc.data(), hc.size() * sizeof(UniChunk), hipMemcpyHostToDevice, s);
+                ProfScope ps(s, "uniform_level_chunked", 0, 0);
+                launch_uni_chunked(s, f->X, d, n_try, seed, d_lseg, (int)hl.size(), d_chunk, (int)hc.size(), f->perm[0], TN,
+                                   ub, d_lsplit);
+            }
+            rs.resize(hs.size());
+            rl.resize(hl.size());
+            if (!rs.empty()) hipMemcpyAsync(rs.data(), d_split, rs.size() * sizeof(UniSplit), hipMemcpyDeviceToHost, s);
+            if (!rl.empty()) hipMemcpyAsync(rl.data(), d_lsplit, rl.size() * sizeof(UniSplit), hipMemcpyDeviceToHost, s);
+            if ((st = check_hip(hipStreamSynchronize(s), "rpf_build uniform level")) != RPF_OK) return bail(st);
+            {
+                const std::string le = take_launch_error();
+                if (!le.empty()) {
+                    fail(RPF_EDEVICE, "rpf_build: " + le);
+                    return bail(RPF_EDEVICE);
+                }
+            }
+            std::vector<Open> next;
+            auto settle = [&](const Open &o, const UniSplit &r) -> bool {
+                if (r.nl < 0 || r.nl > o.size || r.chosen < 0 || r.chosen >= n_try) return false;
+                if (device_growth) recs.push_back(UniRec{o.heap, r.c, o.pos, o.size, r.nl, r.chosen, o.depth, o.tree, kRecLarge});
+                else tnodes[o.tree].push_back(rpf_node{o.heap, r.c, o.size, r.nl, r.chosen, o.depth});
+                if (r.nl == 0 || r.nl == o.size) {  // an empty child: the node stays whole
+                    close_leaf(o);
+                    return true;
+                }
+                const Open kids[2] = {{o.pos, 2 * o.heap, r.nl, o.tree, o.depth + 1},
+                                      {o.pos + r.nl, 2 * o.heap + 1, o.size - r.nl, o.tree, o.depth + 1}};
+                for (const Open &c : kids) {
+                    if (c.size > n0 && c.depth < kUniformDepth) next.push_back(c);
+                    else close_leaf(c);
+                }
+                return true;
+            };
+            bool ok = true;
+            for (size_t k = 0; k < hs.size(); k++) ok &= settle(open[is_small[k]], rs[k]);
+            for (size_t k = 0; k < hl.size(); k++) ok &= settle(open[is_large[k]], rl[k]);
+            if (!ok) {
+                fail(RPF_EINTERNAL, "rpf_build: a uniform split came back out of range");
+                return bail(RPF_EINTERNAL);
+            }
+            open.swap(next);
+        }
+        if (!device_growth) break;
+        // the subtrees: blocks, then waves (whose list the blocks lengthen)
+        if ((int64_t)recs.size() > rec_cap || (int64_t)to_block.size() > blk_cap || (int64_t)to_wave.size() > seg_cap) {
             fail(RPF_EINTERNAL, "rpf_build: uniform growth outgrew its node capacity");
             return bail(RPF_EINTERNAL);
         }
-        if (!hs.empty()) {
-            hipMemcpyAsync(d_seg, hs.data(), hs.size() * sizeof(UniSeg), hipMemcpyHostToDevice, s);
-            ProfScope ps(s, "uniform_level_block", 0, 0);
-            launch_uni_block(s, f->X, d, n_try, seed, d_seg, (int)hs.size(), max_small, f->perm[0], d_split);
+        UniGrow u;
+        u.recs = reinterpret_cast<UniRec *>(recmem);
+        u.rec_cnt = ctr + 2;
+        u.rec_cap = (uint32_t)rec_cap;
+        u.mark = f->leaf_of;
+        u.more = d_seg;
+        u.more_cnt = ctr + 1;
+        u.more_cap = (uint32_t)std::min<int64_t>(seg_cap, 0x7fffffff);
+        fill_many({{ctr, (int64_t)ctr_words}, {f->leaf_of, TN}}, s);
+        const uint32_t first[3] = {(uint32_t)to_block.size(), (uint32_t)to_wave.size(), (uint32_t)recs.size()};
+        hipMemcpyAsync(ctr, first, 12, hipMemcpyHostToDevice, s);
+        if (!to_block.empty()) hipMemcpyAsync(d_blk, to_block.data(), to_block.size() * sizeof(UniSeg), hipMemcpyHostToDevice, s);
+        if (!to_wave.empty()) hipMemcpyAsync(d_seg, to_wave.data(), to_wave.size() * sizeof(UniSeg), hipMemcpyHostToDevice, s);
+        if (!recs.empty()) hipMemcpyAsync(u.recs, recs.data(), recs.size() * sizeof(UniRec), hipMemcpyHostToDevice, s);
+        UniTree *d_tree = nullptr;
+        RPF_UTEMP(d_tree, (size_t)T * sizeof(UniTree));
+        UniSeg *d_closed = nullptr;
+        if (!closed.empty()) {
+            RPF_UTEMP(d_closed, closed.size() * sizeof(UniSeg));
+            hipMemcpyAsync(d_closed, closed.data(), closed.size() * sizeof(UniSeg), hipMemcpyHostToDevice, s);
+            launch_uni_mark(s, d_closed, (int)closed.size(), u.mark);
         }
-        if (!hl.empty()) {
-            hipMemcpyAsync(d_lseg, hl.data(), hl.size() * sizeof(UniSeg), hipMemcpyHostToDevice, s);
-            hipMemcpyAsync(d_chunk, hc.data(), hc.size() * sizeof(UniChunk), hipMemcpyHostToDevice, s);
-            ProfScope ps(s, "uniform_level_chunked", 0, 0);
-            launch_uni_chunked(s, f->X, d, n_try, seed, d_lseg, (int)hl.size(), d_chunk, (int)hc.size(), f->perm[0], TN,
-                               ub, d_lsplit);
+        {
+            ProfScope ps(s, "uniform_subtrees", 0, 0);
+            launch_uni_grow(s, false, f->X, d, seed, d_blk, ctr, ctr + 3, (int64_t)to_block.size(), n0, small_max,
+                            f->perm[0], u);
+            const int64_t waves = to_block.empty() ? (int64_t)to_wave.size() : seg_cap;
+            launch_uni_grow(s, true, f->X, d, seed, d_seg, ctr + 1, ctr + 4, waves, n0, small_max, f->perm[0], u);
+            launch_uni_leaf_count(s, u.mark, n, (int)T, 256, d_tree);
         }
-        rs.resize(hs.size());
-        rl.resize(hl.size());
-        if (!rs.empty()) hipMemcpyAsync(rs.data(), d_split, rs.size() * sizeof(UniSplit), hipMemcpyDeviceToHost, s);
-        if (!rl.empty()) hipMemcpyAsync(rl.data(), d_lsplit, rl.size() * sizeof(UniSplit), hipMemcpyDeviceToHost, s);
-        if ((st = check_hip(hipStreamSynchronize(s), "rpf_build uniform level")) != RPF_OK) return bail(st);
+        uint32_t got[3] = {0, 0, 0};
+        hipMemcpyAsync(got, ctr, 12, hipMemcpyDeviceToHost, s);
+        hipMemcpyAsync(totals.data(), d_tree, (size_t)T * sizeof(UniTree), hipMemcpyDeviceToHost, s);
+        if ((st = check_hip(hipStreamSynchronize(s), "rpf_build uniform subtrees")) != RPF_OK) return bail(st);
         {
             const std::string le = take_launch_error();
             if (!le.empty()) {
@@ -1350,31 +1481,53 @@ static rpf_status build_uniform(const float *X, int64_t n, int32_t d, const rpf_
                 return bail(RPF_EDEVICE);
             }
         }
-        std::vector<Open> next;
-        auto settle = [&](const Open &o, const UniSplit &r) -> bool {
-            if (r.nl < 0 || r.nl > o.size || r.chosen < 0 || r.chosen >= n_try) return false;
-            f->nodes[o.tree].push_back(rpf_node{o.heap, r.c, o.size, r.nl, r.chosen, o.depth});
-            if (r.nl == 0 || r.nl == o.size) {  // an empty child: the node stays whole
-                close_leaf(o);
-                return true;
-            }
-            const Open kids[2] = {{o.pos, 2 * o.heap, r.nl, o.tree, o.depth + 1},
-                                  {o.pos + r.nl, 2 * o.heap + 1, o.size - r.nl, o.tree, o.depth + 1}};
-            for (const Open &c : kids) {
-                if (c.size > n0 && c.depth < kUniformDepth) next.push_back(c);
-                else close_leaf(c);
-            }
-            return true;
-        };
-        bool ok = true;
-        for (size_t k = 0; k < hs.size(); k++) ok &= settle(open[is_small[k]], rs[k]);
-        for (size_t k = 0; k < hl.size(); k++) ok &= settle(open[is_large[k]], rl[k]);
-        if (!ok) {
-            fail(RPF_EINTERNAL, "rpf_build: a uniform split came back out of range");
+        if (got[1] > u.more_cap) {
+            fail(RPF_EINTERNAL, "rpf_build: uniform growth outgrew its node capacity");
             return bail(RPF_EINTERNAL);
         }
-        open.swap(next);
+        if (got[2] <= u.rec_cap) {  // the records in order, to the host
+            const uint32_t cnt = got[2];
+            uint32_t *bucket = ctr + 16, *fill = bucket + T * nb + 1;
+            rpf_node *ordered = reinterpret_cast<rpf_node *>(u.recs + rec_cap);
+            uint32_t *words = reinterpret_cast<uint32_t *>(ordered + rec_cap);
+            std::vector<uint32_t> start((size_t)(T * nb + 1), 0);
+            launch_uni_rec_count(s, u.recs, cnt, n, nb, bucket);
+            hipMemcpyAsync(start.data(), bucket, start.size() * 4, hipMemcpyDeviceToHost, s);
+            if ((st = check_hip(hipStreamSynchronize(s), "rpf_build uniform records")) != RPF_OK) return bail(st);
+            uint32_t run = 0;
+            f->node_off.assign(T + 1, 0);
+            for (int64_t k = 0; k <= T * nb; k++) {
+                const uint32_t c = start[k];  // (the last one: 0)
+                if (k % nb == 0) f->node_off[k / nb] = run;
+                start[k] = run;
+                run += c;
+            }
+            hipMemcpyAsync(bucket, start.data(), start.size() * 4, hipMemcpyHostToDevice, s);
+            launch_uni_rec_order(s, u.recs, cnt, (int)T, n, nb, bucket, fill, words, (uint32_t)rec_cap, ordered);
+            f->nodes.resize(cnt);
+            if (cnt) hipMemcpyAsync(f->nodes.data(), ordered, (size_t)cnt * sizeof(rpf_node), hipMemcpyDeviceToHost, s);
+            if ((st = check_hip(hipStreamSynchronize(s), "rpf_build uniform records")) != RPF_OK) return bail(st);
+            for (const rpf_node &k : f->nodes)
+                max_depth = std::max(max_depth, k.depth + (k.left > 0 && k.left < k.size ? 1 : 0));
+            break;
+        }
+        // more nodes than the records hold: from the start, level by level
+        device_growth = false;
+        to_block.clear();
+        to_wave.clear();
+        closed.clear();
+        recs.clear();
+        max_depth = 0;
+        launch_iota(s, f->perm[0], n, (int)T);
     }
+    if (!device_growth) {
+        f->node_off.assign(1, 0);
+        for (auto &v : tnodes) {
+            f->nodes.insert(f->nodes.end(), v.begin(), v.end());
+            f->node_off.push_back((int64_t)f->nodes.size());
+        }
+    }
+
     for (void *q : temps) cache_free(q, s);
     temps.clear();
 
@@ -1382,25 +1535,30 @@ static rpf_status build_uniform(const float *X, int64_t n, int32_t d, const rpf_
     int64_t stride = 0;
     int max_leaf = 0;
     f->tree_nleaf.resize(T);
+    bool tiled = true;
     for (int64_t t = 0; t < T; t++) {
-        auto &lv = tleaves[t];
-        std::sort(lv.begin(), lv.end(), [](const LeafDesc &a, const LeafDesc &b) { return a.off < b.off; });
-        int64_t at = 0;
-        for (size_t i = 0; i < lv.size(); i++) {
-            if (lv[i].off != at) {
-                fail(RPF_EINTERNAL, "rpf_build: uniform leaves do not tile the permutation");
-                return bail(RPF_EINTERNAL);
+        if (device_growth) {
+            tiled &= totals[t].points == n;
+            f->tree_nleaf[t] = (int32_t)totals[t].leaves;
+            max_leaf = std::max(max_leaf, (int)totals[t].most);
+        } else {
+            auto &lv = tleaves[t];
+            std::sort(lv.begin(), lv.end(), [](const LeafDesc &a, const LeafDesc &b) { return a.off < b.off; });
+            int64_t at = 0;
+            for (size_t i = 0; i < lv.size(); i++) {
+                tiled &= lv[i].off == at;
+                at += lv[i].size;
+                lv[i].heap = (int32_t)i;
+                max_leaf = std::max(max_leaf, (int)lv[i].size);
             }
-            at += lv[i].size;
-            lv[i].heap = (int32_t)i;
-            max_leaf = std::max(max_leaf, (int)lv[i].size);
+            tiled &= at == n;
+            f->tree_nleaf[t] = (int32_t)lv.size();
         }
-        if (at != n) {
-            fail(RPF_EINTERNAL, "rpf_build: uniform leaves do not tile the permutation");
-            return bail(RPF_EINTERNAL);
-        }
-        f->tree_nleaf[t] = (int32_t)lv.size();
-        stride = std::max<int64_t>(stride, (int64_t)lv.size());
+        stride = std::max<int64_t>(stride, (int64_t)f->tree_nleaf[t]);
+    }
+    if (!tiled) {
+        fail(RPF_EINTERNAL, "rpf_build: uniform leaves do not tile the permutation");
+        return bail(RPF_EINTERNAL);
     }
     f->leaf_stride = stride;
     f->max_leaf = max_leaf;
@@ -1416,6 +1574,11 @@ static rpf_status build_uniform(const float *X, int64_t n, int32_t d, const rpf_
     f->job_off.assign(T + 1, 0);
     f->flops_off.assign(T + 1, 0.0);
     for (int64_t t = 0; t < T; t++) {
+        if (device_growth) {  // (tiles of 256 rows or of one leaf: the same count)
+            f->job_off[t + 1] = f->job_off[t] + totals[t].jobs;
+            f->flops_off[t + 1] = f->flops_off[t] + 2.0 * d * (double)totals[t].squares;
+            continue;
+        }
         double fl = 0;
         for (size_t li = 0; li < tleaves[t].size(); li++) {
             const LeafDesc &lf = tleaves[t][li];
@@ -1442,27 +1605,40 @@ static rpf_status build_uniform(const float *X, int64_t n, int32_t d, const rpf_
     }
     f->n_jobs_tree = 0;
     f->tile_flops_tree = f->flops_off[T] / (double)T;
-    std::vector<LeafDesc> table((size_t)(T * stride), LeafDesc{0, 0, -1});
-    for (int64_t t = 0; t < T; t++)
-        std::copy(tleaves[t].begin(), tleaves[t].end(), table.begin() + t * stride);
+    const int64_t njobs = f->job_off[T];
+    std::vector<LeafDesc> table;
+    if (!device_growth) {
+        table.assign((size_t)(T * stride), LeafDesc{0, 0, -1});
+        for (int64_t t = 0; t < T; t++) std::copy(tleaves[t].begin(), tleaves[t].end(), table.begin() + t * stride);
+    }
     const bool xc_eager = max_leaf > 256 && !grid;
     const uint64_t more = (uint64_t)T * stride * (d * 4 + sizeof(LeafDesc)) + (uint64_t)(stride + 1) * 4 +
-                          (uint64_t)jobs.size() * sizeof(TileJob) + (xc_eager ? (uint64_t)TN * dp * esz : 0);
+                          (uint64_t)njobs * sizeof(TileJob) + (xc_eager ? (uint64_t)TN * dp * esz : 0);
     if (p->mem_budget_bytes && f->bytes + more > p->mem_budget_bytes) {
         fail(RPF_ENOMEM, "rpf_build: forest needs " + std::to_string(f->bytes + more) + " bytes, over mem_budget_bytes");
         return bail(RPF_ENOMEM);
     }
-    RPF_UALLOC(f->d_leaves, table.size() * sizeof(LeafDesc));
+    RPF_UALLOC(f->d_leaves, (size_t)(T * stride) * sizeof(LeafDesc));
     RPF_UALLOC(f->heap_leaf, (size_t)(stride + 1) * 4);
     RPF_UALLOC(f->centroid, (size_t)T * stride * d * 4);
-    RPF_UALLOC(f->d_jobs, jobs.size() * sizeof(TileJob));
+    RPF_UALLOC(f->d_jobs, (size_t)njobs * sizeof(TileJob));
     if (xc_eager) RPF_UALLOC(f->Xc, (size_t)TN * dp * esz);
     f->bytes += more;
-    std::vector<int32_t> ident((size_t)stride + 1);
-    for (int64_t i = 0; i <= stride; i++) ident[i] = (int32_t)i;
-    hipMemcpyAsync(f->d_leaves, table.data(), table.size() * sizeof(LeafDesc), hipMemcpyHostToDevice, s);
-    hipMemcpyAsync(f->heap_leaf, ident.data(), ident.size() * 4, hipMemcpyHostToDevice, s);
-    hipMemcpyAsync(f->d_jobs, jobs.data(), jobs.size() * sizeof(TileJob), hipMemcpyHostToDevice, s);
+    std::vector<int32_t> ident;
+    if (device_growth) {
+        int64_t *d_off = nullptr;
+        RPF_UTEMP(d_off, (size_t)(T + 1) * 8);
+        hipMemcpyAsync(d_off, f->job_off.data(), (size_t)(T + 1) * 8, hipMemcpyHostToDevice, s);
+        launch_uni_leaf_fill(s, f->leaf_of, n, (int)T, 256, stride, d_off, f->d_leaves, f->d_jobs, f->heap_leaf);
+    } else {
+        ident.resize((size_t)stride + 1);
+        for (int64_t i = 0; i <= stride; i++) ident[i] = (int32_t)i;
+        hipMemcpyAsync(f->d_leaves, table.data(), table.size() * sizeof(LeafDesc), hipMemcpyHostToDevice, s);
+        hipMemcpyAsync(f->heap_leaf, ident.data(), ident.size() * 4, hipMemcpyHostToDevice, s);
+        hipMemcpyAsync(f->d_jobs, jobs.data(), jobs.size() * sizeof(TileJob), hipMemcpyHostToDevice, s);
+    }
+    for (void *q : temps) cache_free(q, s);
+    temps.clear();
     f->final_buf = 0;
     {
         ProfScope ps(s, "leaf_finalize", (double)TN * (4.0 * d + 16), 0);
@@ -2001,10 +2177,11 @@ rpf_status rpf_tree_nodes(const rpf_forest *f, int32_t tree, rpf_node *out, int6
     if (f->split_rule != RPF_SPLIT_UNIFORM) return fail(RPF_EINVAL, "rpf_tree_nodes: not a uniform-rule forest");
     if (tree < 0 || tree >= f->T) return fail(RPF_EINVAL, "rpf_tree_nodes: tree out of range");
     if (cap < 0 || (cap > 0 && !out)) return fail(RPF_EINVAL, "rpf_tree_nodes: bad output capacity");
-    const std::vector<rpf_node> &v = f->nodes[tree];
-    const int64_t k = std::min<int64_t>(cap, (int64_t)v.size());
-    if (k > 0) std::copy(v.begin(), v.begin() + k, out);
-    *count = (int64_t)v.size();
+    const rpf_node *v = f->nodes.data() + f->node_off[tree];
+    const int64_t have = f->node_off[tree + 1] - f->node_off[tree];
+    const int64_t k = std::min<int64_t>(cap, have);
+    if (k > 0) std::copy(v, v + k, out);
+    *count = have;
     return RPF_OK;
 }
 

@@ -272,6 +272,49 @@ struct UniBufs {       // temporaries of the chunked path
     int32_t *tmp = nullptr;     // [T n] scratch permutation
 };
 
+// Growth of whole subtrees on the device: nodes of at most kGrowBlock members by a workgroup
+// each, down to kGrowWave members, those by one wave each.
+constexpr int kGrowBlock = 8192, kGrowWave = 1024;
+constexpr int kRecLarge = 64;  // UniRec::small of a node above small_max
+static_assert(kGrowBlock >= kChunk, "every node above kGrowBlock takes the chunked path");
+
+struct UniRec {        // a node where a split was attempted, as the device found it
+    int64_t heap;
+    double c;
+    int64_t pos;       // first position in the [T][n] permutation
+    int32_t size, left, chosen, depth, tree;
+    int32_t small;     // depth of its first ancestor (or itself) of at most small_max members
+};
+
+struct UniTree {       // totals of one tree's leaves
+    int64_t leaves, jobs, points, squares, most;
+};
+
+struct UniGrow {       // what a growing launch writes
+    UniRec *recs;
+    uint32_t *rec_cnt;
+    uint32_t rec_cap;
+    int32_t *mark;     // [T][n] leaf size at its first position, else 0
+    UniSeg *more;      // nodes left to the next list (chunk0: the depth, nchunk: UniRec::small)
+    uint32_t *more_cnt;
+    uint32_t more_cap;
+};
+
+size_t uni_grow_lds(int cap, int d);
+// items[0, min(*count, most))
+void launch_uni_grow(hipStream_t s, bool wave, const float *X, int d, uint64_t seed, const UniSeg *items,
+                     const uint32_t *count, uint32_t *next, int64_t most, int n0, int small_max, int32_t *perm,
+                     const UniGrow &u);
+void launch_uni_mark(hipStream_t s, const UniSeg *leaves, int count, int32_t *mark);
+void launch_uni_leaf_count(hipStream_t s, const int32_t *mark, int64_t n, int T, int TR, UniTree *out);
+struct TileJob;
+void launch_uni_leaf_fill(hipStream_t s, const int32_t *mark, int64_t n, int T, int TR, int64_t stride,
+                          const int64_t *job_off, LeafDesc *table, TileJob *jobs, int32_t *ident);
+void launch_uni_rec_count(hipStream_t s, const UniRec *recs, uint32_t cnt, int64_t n, int64_t nb, uint32_t *bucket);
+// `words`: [3][cap] of scratch
+void launch_uni_rec_order(hipStream_t s, const UniRec *recs, uint32_t cnt, int T, int64_t n, int64_t nb,
+                          const uint32_t *start, uint32_t *fill, uint32_t *words, uint32_t cap, rpf_node *out);
+
 size_t uni_block_lds(int max_m, int d, int n_try);
 void launch_uni_block(hipStream_t s, const float *X, int d, int n_try, uint64_t seed, const UniSeg *segs, int nseg,
                       int max_m, int32_t *perm, UniSplit *out);

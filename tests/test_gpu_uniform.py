@@ -68,6 +68,52 @@ def test_uniform_build_matches_oracle(case):
     f.free()
 
 
+SUBTREE_CASES = [
+    # edges of the rule and of the two subtree sizes (one wave: 1024 members, one workgroup: 8192)
+    ("wave_1024", 1024, 7, 3, 16, 1, 40, "mixture", 0),
+    ("block_1025", 1025, 8, 3, 16, 1, 41, "aniso", 0),
+    ("one_level", 1025, 8, 3, 512, 1, 42, "aniso", 0),
+    ("levels_4096", 4096, 12, 2, 15, 1, 43, "mixture", 0),       # grown level by level
+    ("block_4097_n0_1", 4097, 6, 2, 1, 1, 44, "aniso", 0),       # single points, long records
+    ("block_8192", 8192, 33, 3, 5, 1, 45, "mixture", 0),
+    ("chunked_8193", 8193, 16, 5, 40, 1, 46, "aniso", 0),
+    ("copies_8200", 8200, 4, 3, 17, 1, 47, "mixture", 2),        # a node of 4100 copies stays whole
+    ("d_4096", 4500, 4096, 1, 900, 1, 48, "aniso", 0),
+]
+
+
+@pytest.mark.parametrize("case", SUBTREE_CASES, ids=[c[0] for c in SUBTREE_CASES])
+def test_uniform_subtrees_match_oracle(case):
+    test_uniform_build_matches_oracle(case)
+    name, n, d, T, n0, n_try, seed, kind, dup = case
+    f = _gpu(_x(case), T, n0, n_try, seed)
+    for t in range(T):
+        depths = [r["depth"] for r in f.tree_nodes(t)]
+        assert depths == sorted(depths)
+    f.free()
+
+
+@pytest.mark.parametrize("n0", [4, 64])
+def test_uniform_subtrees_within_a_budget(n0):
+    """With a budget the records share the norms' memory: leaves of 64 fit, leaves of 4 do not
+    and the forest grows level by level; both equal the forest built without a budget."""
+    from paper_1812_11689_amd import rpf
+    x, _ = problem(9000, 16, 1, n0, 1, seed=49, kind="aniso")
+    xg = torch.from_numpy(x).cuda()
+    a = _gpu(x, 3, n0, 1, 5)
+    b = rpf.build(xg, 3, n0, None, dist_prec="fp32", split_rule="uniform", seed=5, mem_budget_bytes=1 << 30)
+    for t in range(3):
+        for k, v in a.tree_dump(t).items():
+            if k in ("perm", "leaf_of"):
+                assert torch.equal(v, b.tree_dump(t)[k])
+        assert a.tree_nodes(t) == b.tree_nodes(t)
+    ai, ad = a.all_knn(5)
+    bi, bd = b.all_knn(5)
+    assert torch.equal(ai, bi) and torch.equal(ad, bd)
+    a.free()
+    b.free()
+
+
 KNN_CASES = [
     # name, n, d, T, n0, n_try, seed, kind, dup, K, prec, exclude_self
     ("fp32_k10", 6000, 16, 8, 20, 1, 31, "mixture", 0, 10, "fp32", True),
