@@ -11,6 +11,8 @@
 //   - larger segments: chunked projection, a median select by one workgroup per segment
 //     (the largest segments bracket the median from a sample first), then a stable chunked
 //     partition.
+#include <type_traits>
+
 #include "rpf_internal.h"
 
 namespace rpf {
@@ -32,8 +34,9 @@ __device__ inline void project_segment(const float *__restrict__ X, int d, const
 
 // LDS layout: perm[m] int32 | key[m] u64 | dir[d] | hist[256] | misc ; nTry>1 adds p[m], tree[P2]
 // Q8: the node projections read rows from the int8 grid copy Xq (stride dq); the same values
-template <bool VEC, bool LEAD, bool Q8 = false>
-__global__ __launch_bounds__(256) void k_level_small(
+// NT: threads of a workgroup (n_try > 1: 256)
+template <bool VEC, bool LEAD, bool Q8 = false, int NT = 256>
+__global__ __launch_bounds__(NT) void k_level_small(
     const float *__restrict__ X, int d, const float *__restrict__ R, int64_t H, int n_try,
     const SegDesc *__restrict__ segs, const int32_t *__restrict__ perm_in,
     int32_t *__restrict__ perm_out, int64_t n, double *__restrict__ split,
@@ -41,6 +44,7 @@ __global__ __launch_bounds__(256) void k_level_small(
     const LookDesc *__restrict__ look, double2 *__restrict__ ahead, uint64_t *__restrict__ keys_next,
     const uint64_t *__restrict__ keys_in, const int8_t *__restrict__ Xq, int dq) {
     extern __shared__ __align__(16) uint8_t smem[];
+    __shared__ uint32_t s_wide[NT == 256 ? 1 : NT / 64];
     const int t = blockIdx.y;
     const SegDesc sg = segs[blockIdx.x];
     const int m = sg.size;
@@ -54,6 +58,7 @@ __global__ __launch_bounds__(256) void k_level_small(
     double *s_rd = reinterpret_cast<double *>(s_dir);
     uint32_t *s_hist = reinterpret_cast<uint32_t *>(s_rd + 3 * ds);
     uint32_t *s_misc = s_hist + 256;  // 16 words
+    uint32_t *s_scan = NT == 256 ? s_misc : s_wide;
     double *s_p = reinterpret_cast<double *>(s_misc + 16);
     int P2 = 1;
     while (P2 < m) P2 <<= 1;
@@ -64,7 +69,7 @@ __global__ __launch_bounds__(256) void k_level_small(
     const float *Rn = R + ((int64_t)t * H + (sg.heap - 1)) * n_try * (int64_t)d;
 
     int ch = 0;
-    if (n_try > 1) {  // Alg. 2: keep the try with the largest spread S2 (first wins ties)
+    if (NT == 256 && n_try > 1) {  // Alg. 2: keep the try with the largest spread S2 (first wins ties)
         double best = 0.0;
         int best_i = -1;
         for (int k = 0; k < n_try; k++) {
@@ -99,8 +104,8 @@ __global__ __launch_bounds__(256) void k_level_small(
         }
         __syncthreads();
         const int g = tid & 7, pt = tid >> 3;
-        for (int base = 0; base < m; base += 64) {  // rows base + pt and base + 32 + pt
-            const int ia = base + pt, ib = ia + 32;
+        for (int base = 0; base < m; base += NT / 4) {
+            const int ia = base + pt, ib = ia + NT / 8;
             double p[6];
             if constexpr (Q8)
                 group8_dot64x3r2_q8<VEC>(Xq + (int64_t)s_perm[ia < m ? ia : 0] * dq, Xq + (int64_t)s_perm[ib < m ? ib : 0] * dq,
@@ -121,7 +126,7 @@ __global__ __launch_bounds__(256) void k_level_small(
         for (int j = tid; j < d; j += blockDim.x) s_r[j] = Rn[(int64_t)ch * d + j];
         __syncthreads();
         const int g = tid & 7, pt = tid >> 3;
-        for (int base = 0; base < m; base += 32) {
+        for (int base = 0; base < m; base += NT / 8) {
             int i = base + pt;
             int ii = i < m ? i : 0;
             double p;
@@ -140,7 +145,7 @@ __global__ __launch_bounds__(256) void k_level_small(
     while (cnt > 1 && nbits < 96) {
         const int lo_bit = 88 - nbits;
         const unsigned __int128 P = key96(phi, plo);
-        s_hist[tid] = 0;
+        if (tid < 256) s_hist[tid] = 0;
         __syncthreads();
         for (int i = tid; i < m; i += blockDim.x) {
             unsigned __int128 K = key96(s_key[i], (uint32_t)s_perm[i]);
@@ -148,8 +153,8 @@ __global__ __launch_bounds__(256) void k_level_small(
                 atomicAdd(&s_hist[(uint32_t)(K >> lo_bit) & 255u], 1u);
         }
         __syncthreads();
-        uint32_t v = s_hist[tid], excl, total;
-        block_excl_scan256(v, s_misc, excl, total);
+        uint32_t v = tid < 256 ? s_hist[tid] : 0u, excl, total;
+        block_excl_scan_w<NT / 64>(v, s_scan, excl, total);
         if (excl <= rank && rank < excl + v) {
             s_misc[8] = tid;
             s_misc[9] = excl;
@@ -184,12 +189,12 @@ __global__ __launch_bounds__(256) void k_level_small(
     const int half = m / 2;
     int32_t *pout = perm_out + (int64_t)t * n + sg.off;
     uint32_t lefts = 0;
-    for (int base = 0; base < m; base += 256) {
+    for (int base = 0; base < m; base += NT) {
         const int i = base + tid;
         const bool valid = i < m;
         const bool left = valid && key_less(s_key[i], (uint32_t)s_perm[i], phi, plo);
         uint32_t excl, total;
-        block_excl_scan256(left ? 1u : 0u, s_misc, excl, total);
+        block_excl_scan_w<NT / 64>(left ? 1u : 0u, s_scan, excl, total);
         if (valid) {
             uint32_t lb = lefts + excl;
             int pos = left ? (int)lb : half + (i - (int)lb);
@@ -546,8 +551,8 @@ void launch_subtree(hipStream_t s, bool vec, const float *X, int d, const float 
 // ================================================================ large segments
 
 // Q8: rows read from the int8 grid copy Xq (stride dq) instead of X; the same values
-template <bool VEC, bool LEAD, bool Q8 = false>
-__global__ __launch_bounds__(256) void k_proj_chunks(
+template <bool VEC, bool LEAD, bool Q8 = false, int NT = 256>
+__global__ __launch_bounds__(NT) void k_proj_chunks(
     const float *__restrict__ X, int d, const float *__restrict__ R, int64_t H,
     const SegDesc *__restrict__ segs, const ChunkDesc *__restrict__ chunks,
     const int32_t *__restrict__ perm, int64_t n, uint64_t *__restrict__ keys,
@@ -566,7 +571,7 @@ __global__ __launch_bounds__(256) void k_proj_chunks(
         const LookDesc lk = look[c.seg];
         const int ds = (d + 3) & ~3;
         double *s_rd = reinterpret_cast<double *>(s_dir);
-        for (int j = tid; j < d; j += 256) {
+        for (int j = tid; j < d; j += NT) {
             s_rd[j] = Rn[j];
 #pragma unroll
             for (int b = 0; b < 2; b++)  // a leaf child has no direction: project onto zero
@@ -574,8 +579,8 @@ __global__ __launch_bounds__(256) void k_proj_chunks(
                     lk.child_heap[b] > 0 ? R[((int64_t)t * H + (lk.child_heap[b] - 1)) * (int64_t)d + j] : 0.f;
         }
         __syncthreads();
-        for (int base = 0; base < c.len; base += 64) {  // rows base + pt and base + 32 + pt
-            const int ia = base + pt, ib = ia + 32;
+        for (int base = 0; base < c.len; base += NT / 4) {
+            const int ia = base + pt, ib = ia + NT / 8;
             const int64_t sa = c.start + (ia < c.len ? ia : 0), sb = c.start + (ib < c.len ? ib : 0);
             double p[6];
             if constexpr (Q8) group8_dot64x3r2_q8<VEC>(Xq + (int64_t)pp[sa] * dq, Xq + (int64_t)pp[sb] * dq, s_rd, ds, d, g, p);
@@ -591,9 +596,9 @@ __global__ __launch_bounds__(256) void k_proj_chunks(
             }
         }
     } else if (d <= 1024) {  // longer directions are read from global memory by the scalar loop below
-        for (int j = tid; j < d; j += 256) s_r[j] = Rn[j];
+        for (int j = tid; j < d; j += NT) s_r[j] = Rn[j];
         __syncthreads();
-        for (int base = 0; base < c.len; base += 32) {
+        for (int base = 0; base < c.len; base += NT / 8) {
             const int i = base + pt;
             const int64_t s = c.start + (i < c.len ? i : 0);
             double p;
@@ -602,7 +607,7 @@ __global__ __launch_bounds__(256) void k_proj_chunks(
             if (g == 0 && i < c.len) keys[(int64_t)t * n + s] = key_of(p);
         }
     } else {
-        for (int base = 0; base < c.len; base += 32) {
+        for (int base = 0; base < c.len; base += NT / 8) {
             const int i = base + pt;
             const int64_t s = c.start + (i < c.len ? i : 0);
             double p;
@@ -1065,7 +1070,8 @@ __global__ __launch_bounds__(1024) void k_sel_pick(const SegDesc *__restrict__ s
     }
 }
 
-__global__ __launch_bounds__(256) void k_part_scatter(const SegDesc *__restrict__ segs,
+template <int NT>
+__global__ __launch_bounds__(NT) void k_part_scatter(const SegDesc *__restrict__ segs,
                                                       const ChunkDesc *__restrict__ chunks, int nchunk,
                                                       const uint64_t *__restrict__ keys,
                                                       const int32_t *__restrict__ perm_in,
@@ -1085,14 +1091,14 @@ __global__ __launch_bounds__(256) void k_part_scatter(const SegDesc *__restrict_
     const int64_t rel0 = c.start - sg.off;  // chunk position within the segment
     int32_t *pout = perm_out + (int64_t)t * n + sg.off;
     const bool lead = look != nullptr;
-    for (int base = 0; base < c.len; base += 256) {
+    for (int base = 0; base < c.len; base += NT) {
         const int i = base + tid;
         const bool valid = i < c.len;
         const int64_t s = c.start + (valid ? i : 0);
         const int32_t id = perm_in[(int64_t)t * n + s];
         const bool left = valid && key_less(keys[(int64_t)t * n + s], (uint32_t)id, st.key, (uint32_t)st.idx);
         uint32_t excl, total;
-        block_excl_scan256(left ? 1u : 0u, s_w, excl, total);
+        block_excl_scan_w<NT / 64>(left ? 1u : 0u, s_w, excl, total);
         if (valid) {
             const int64_t lb = (int64_t)lefts + excl;
             const int64_t rel = rel0 + i;
@@ -1956,6 +1962,12 @@ size_t level_small_lds(int max_m, int d, int n_try) {
     return lds;
 }
 
+// A level with at most one workgroup per CU runs 1024 threads in each instead of 256: such a
+// level takes the time of one workgroup's walk over its members.  Build at 10 000 x 128, 4 trees:
+// 436 -> 349 us; 40 000 x 64, 16 trees: 850 -> 722 (748 with up to 512 workgroups); 200 000 x 128,
+// 2 trees: 1 067 -> 760.
+static bool few_blocks(int64_t blocks) { return blocks <= 256; }
+
 void launch_level_small(hipStream_t s, bool vec, const float *X, int d, const float *R, int64_t H,
                         int n_try, const SegDesc *segs, int nseg, int max_m, int T,
                         const int32_t *pin, int32_t *pout, int64_t n, double *split,
@@ -1972,23 +1984,30 @@ void launch_level_small(hipStream_t s, bool vec, const float *X, int d, const fl
     }
     const size_t lds = level_small_lds(max_m, d, n_try);
     dim3 grid(nseg, T);
-    auto go = [&](auto kern) {
+    auto go = [&](auto kern, int nt) {
         hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL(kern, grid, dim3(256), lds, s, X, d, R, H, n_try, segs, pin, pout, n, split, split_idx,
+        hipLaunchKernelGGL(kern, grid, dim3(nt), lds, s, X, d, R, H, n_try, segs, pin, pout, n, split, split_idx,
                            chosen, err, lk.look, lk.ahead, lk.keys_next, lk.keys_in, lk.xq, lk.dq);
     };
     const bool q8 = lk.xq && n_try == 1;  // (several tries project through the binary32 rows)
-    if (lk.look) {
-        if (q8 && vec) go(k_level_small<true, true, true>);
-        else if (q8) go(k_level_small<false, true, true>);
-        else if (vec) go(k_level_small<true, true>);
-        else go(k_level_small<false, true>);
-    } else {
-        if (q8 && vec) go(k_level_small<true, false, true>);
-        else if (q8) go(k_level_small<false, false, true>);
-        else if (vec) go(k_level_small<true, false>);
-        else go(k_level_small<false, false>);
-    }
+    auto pick = [&](auto w) {
+        constexpr int W = decltype(w)::value;
+        if (lk.look) {
+            if (q8 && vec) go(k_level_small<true, true, true, W>, W);
+            else if (q8) go(k_level_small<false, true, true, W>, W);
+            else if (vec) go(k_level_small<true, true, false, W>, W);
+            else go(k_level_small<false, true, false, W>, W);
+        } else {
+            if (q8 && vec) go(k_level_small<true, false, true, W>, W);
+            else if (q8) go(k_level_small<false, false, true, W>, W);
+            else if (vec) go(k_level_small<true, false, false, W>, W);
+            else go(k_level_small<false, false, false, W>, W);
+        }
+    };
+    if (n_try == 1 && few_blocks((int64_t)nseg * T) && max_m >= 512 && lds <= 128 * 1024)
+        pick(std::integral_constant<int, 1024>{});
+    else
+        pick(std::integral_constant<int, 256>{});
     launch_check(s, "k_level_small");
 }
 
@@ -1998,15 +2017,20 @@ static void proj_chunks(hipStream_t s, dim3 gc, const float *X, int d, const flo
                         const LargeBufs &b, const LevelLink &lk) {
     const size_t ds = (size_t)((d + 3) & ~3);
     const size_t lds = d > 1024 ? 0 : lk.look ? 3 * ds * sizeof(double) : ds * sizeof(float);
-    auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, gc, dim3(256), lds, s, X, d, R, H, segs, chunks, pin, n, b.keys, lk.look, lk.ahead,
+    auto go = [&](auto kern, int nt) {
+        hipLaunchKernelGGL(kern, gc, dim3(nt), lds, s, X, d, R, H, segs, chunks, pin, n, b.keys, lk.look, lk.ahead,
                            lk.xq, lk.dq);
     };
     const bool q8 = lk.xq != nullptr;
-    if (lk.look && q8) go(k_proj_chunks<VEC, true, true>);
-    else if (lk.look) go(k_proj_chunks<VEC, true>);
-    else if (q8) go(k_proj_chunks<VEC, false, true>);
-    else go(k_proj_chunks<VEC, false>);
+    auto pick = [&](auto w) {
+        constexpr int W = decltype(w)::value;
+        if (lk.look && q8) go(k_proj_chunks<VEC, true, true, W>, W);
+        else if (lk.look) go(k_proj_chunks<VEC, true, false, W>, W);
+        else if (q8) go(k_proj_chunks<VEC, false, true, W>, W);
+        else go(k_proj_chunks<VEC, false, false, W>, W);
+    };
+    if (few_blocks((int64_t)gc.x * gc.y)) pick(std::integral_constant<int, 1024>{});
+    else pick(std::integral_constant<int, 256>{});
     launch_check(s, "k_proj_chunks");
 }
 
@@ -2049,8 +2073,12 @@ void launch_level_large(hipStream_t s, bool vec, const float *X, int d, const fl
     }
     {
         ProfScope ps(s, "partition", 0, 0);
-        hipLaunchKernelGGL(k_part_scatter, gc, dim3(256), 0, s, segs, chunks, nchunk, b.keys, pin, pout, n, b.state,
-                           nseg, b.lcount, lk.look, lk.ahead, lk.keys_next);
+        auto go = [&](auto kern, int nt) {
+            hipLaunchKernelGGL(kern, gc, dim3(nt), 0, s, segs, chunks, nchunk, b.keys, pin, pout, n, b.state, nseg,
+                               b.lcount, lk.look, lk.ahead, lk.keys_next);
+        };
+        if (few_blocks((int64_t)nchunk * T)) go(k_part_scatter<1024>, 1024);
+        else go(k_part_scatter<256>, 256);
         launch_check(s, "k_part_scatter");
     }
 }

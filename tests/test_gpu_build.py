@@ -99,6 +99,38 @@ def test_median_select_matches_oracle(case):
     f.free()
 
 
+WIDE_CASES = [
+    # levels of at most 256 workgroups: 1024 threads each, from 512 members on
+    # name, n, d, T, n0, n_try, kind, dup
+    ("wide_511", 511, 6, 1, 100, 1, "mixture", 0),
+    ("wide_512", 512, 7, 1, 100, 1, "aniso", 0),
+    ("wide_1025_fed", 1025, 33, 2, 200, 1, "mixture", 0),
+    ("wide_4096", 4096, 20, 1, 30, 1, "aniso", 0),
+    ("wide_4097_chunks", 4097, 20, 3, 30, 1, "aniso", 0),
+    ("wide_256_workgroups", 2048, 8, 128, 500, 1, "aniso", 0),   # 256 at the second level
+    ("wide_258_workgroups", 2048, 8, 129, 500, 1, "aniso", 0),   # 258: 256 threads
+    ("wide_ties", 3000, 4, 2, 40, 1, "mixture", 5),
+    ("wide_d1500", 5000, 1500, 1, 600, 1, "mixture", 0),         # directions past the staged length
+]
+
+
+@pytest.mark.parametrize("case", WIDE_CASES, ids=[c[0] for c in WIDE_CASES])
+def test_wide_levels_match_oracle(case):
+    test_build_matches_oracle(case)
+
+
+@pytest.mark.parametrize("d", [48, 50])
+def test_wide_levels_of_a_grid_forest(d):
+    from paper_1812_11689_amd import rpf
+    x = (np.random.default_rng(70).integers(0, 256, (9000, d)) / 255).astype(np.float32)
+    R = np.random.default_rng(71).standard_normal((2, 2 ** rpf.depth(9000, 300) - 1, 1, d)).astype(np.float32)
+    ref = oracle.build_forest(x, R, 2, 300, 1)
+    f = rpf.build(torch.from_numpy(x).cuda(), 2, 300, torch.from_numpy(R).cuda(), dist_prec="u8grid")
+    for t in range(2):
+        np.testing.assert_array_equal(f.tree_dump(t)["perm"].cpu().numpy(), ref.perm[t])
+    f.free()
+
+
 TRY_CASES = [
     # several tries per node: sums over pieces of 256 members, nodes scored in one workgroup
     # (up to 512 members) or over many blocks, 2 to 5 tries per read, more than 16 tries
