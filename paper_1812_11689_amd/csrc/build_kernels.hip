@@ -32,19 +32,225 @@ __device__ inline void project_segment(const float *__restrict__ X, int d, const
     }
 }
 
+// ================================================================ grid rows: projections by digits
+//
+// Rows of a grid forest are integers k in [0, 255] (x = k / 255), so a projection is nearly
+// s / 255 sum k q for a direction rounded to multiples q of s = max|r| / 2^22: three balanced
+// base-256 digits of q, one column of v_mfma_i32_16x16x64_i8 each, exact in integers.  The
+// node's median is taken from these keys; it is within e of the exact median and every key
+// within e of its exact value (e: k_digit_bound), so once the members within 2 e of it hold
+// their exact keys, a second selection and the partition give exactly what exact keys give:
+// every other member is on its side of the exact median by more than its key's error.
+// Binary64 needs a byte extraction, two conversions, a multiplication and three additions per
+// coordinate for the three projections of a lead level and was bound by those (10^6 x 784, 48
+// trees: 12.4 ms a lead level of multi-block nodes, 3.2 TB/s); the digits take 8.8 ms, bound by
+// the gather of the rows (4.6 TB/s, their lines not aligned), and 4.0 ms at the first level,
+// where the trees share the rows.  Only rows of 192 to 1024 coordinates: the directions' digits
+// of rows below 126 outgrow the LDS held for exact directions, longer rows are not linked.
+
+typedef int digits4 __attribute__((ext_vector_type(4)));
+constexpr double kDigitRange = 4194304.0;  // 2^22
+
+struct DigitDir {
+    double scale;      // of the integer sums
+    long long base;    // 128 sum q: the copy holds k - 128
+};
+
+// e per node: (d / 2 s + 2^-23 sum|r|), the rounding of r and that of x to binary32 (2^-24),
+// the rest covering the binary64 sums
+__global__ __launch_bounds__(256) void k_digit_bound(const float *__restrict__ R, int64_t nodes, int d,
+                                                     double *__restrict__ bound) {
+    const int lane = threadIdx.x & 63;
+    for (int64_t k = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); k < nodes; k += (int64_t)gridDim.x * 4) {
+        double mx = 0.0, sum = 0.0;
+        for (int j = lane; j < d; j += 64) {
+            const double v = fabs((double)R[k * d + j]);
+            mx = fmax(mx, v);
+            sum += v;
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            mx = fmax(mx, shfl_xor_d(mx, o));
+            sum += shfl_xor_d(sum, o);
+        }
+        if (lane == 0) bound[k] = 0.501 * d * (mx / kDigitRange) + sum * (1.0 / 8388608.0);
+    }
+}
+
+// The digits of ND directions as matrix operands, s_b [dq / 64][64 lanes][16 bytes]: lane c +
+// 16 g holds coordinates 16 g .. 16 g + 15 of column c; direction k's digit i is column k + 4 i.
+template <int NT, int ND>
+__device__ inline void digit_stage(const float *const (&dir)[ND], int d, int dq, int8_t *s_b, DigitDir *s_d,
+                                   uint32_t *s_max) {
+    const int tid = threadIdx.x;
+    __syncthreads();
+    for (int i = tid; i < dq; i += NT) reinterpret_cast<digits4 *>(s_b)[i] = digits4{0, 0, 0, 0};
+    if (tid < ND) {
+        s_max[tid] = 0;
+        s_d[tid].base = 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ND; k++) {
+        float mx = 0.f;
+        if (dir[k])
+            for (int j = tid; j < d; j += NT) mx = fmaxf(mx, fabsf(dir[k][j]));
+        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+        if ((tid & 63) == 0) atomicMax(&s_max[k], __float_as_uint(mx));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ND; k++) {
+        const double mx = (double)__uint_as_float(s_max[k]);
+        const double inv = mx > 0.0 ? kDigitRange / mx : 0.0;
+        long long sum = 0;
+        if (dir[k])
+            for (int j = tid; j < d; j += NT) {
+                const int q = (int)rint((double)dir[k][j] * inv);
+                const int d0 = (int8_t)q, q1 = (q - d0) >> 8, d1 = (int8_t)q1, d2 = (q1 - d1) >> 8;
+                int8_t *at = s_b + ((j >> 6) * 64 + 16 * ((j >> 4) & 3) + k) * 16 + (j & 15);
+                at[0] = (int8_t)d0;
+                at[4 * 16] = (int8_t)d1;
+                at[8 * 16] = (int8_t)d2;
+                sum += q;
+            }
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+        if ((tid & 63) == 0) atomicAdd(reinterpret_cast<unsigned long long *>(&s_d[k].base), (unsigned long long)(128 * sum));
+        if (tid == 0) s_d[k].scale = mx / (kDigitRange * 255.0);
+    }
+    __syncthreads();
+}
+
+// out(i, k, p) for each of the m rows id(i) and each direction k < ND, 32 rows per wave
+template <int NT, int ND, typename Id, typename Out>
+__device__ inline void digit_project(const int8_t *__restrict__ Xq, int dq, const int8_t *s_b, const DigitDir *s_d, int m,
+                                     const Id &id, const Out &out) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, col = lane & 15, kg = lane >> 4;
+    const int steps = dq >> 6;
+    const digits4 *b = reinterpret_cast<const digits4 *>(s_b) + lane;
+    for (int base = 32 * w; base < m; base += NT / 2) {
+        const int ra = base + col, rb = ra + 16;
+        const digits4 *xa = reinterpret_cast<const digits4 *>(Xq + (int64_t)id(ra < m ? ra : 0) * dq + 16 * kg);
+        const digits4 *xb = reinterpret_cast<const digits4 *>(Xq + (int64_t)id(rb < m ? rb : 0) * dq + 16 * kg);
+        digits4 acc[2] = {digits4{0, 0, 0, 0}, digits4{0, 0, 0, 0}};
+        int ks = 0;
+        for (; ks + 4 <= steps; ks += 4) {  // eight loads in flight
+            digits4 a[4], c[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                a[u] = xa[4 * (ks + u)];
+                c[u] = xb[4 * (ks + u)];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const digits4 q = b[64 * (ks + u)];
+                acc[0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[u], q, acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(c[u], q, acc[1], 0, 0, 0);
+            }
+        }
+        for (; ks < steps; ks++) {
+            const digits4 q = b[64 * ks];
+            acc[0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa[4 * ks], q, acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xb[4 * ks], q, acc[1], 0, 0, 0);
+        }
+        // lane col + 16 kg holds rows 4 kg .. 4 kg + 3 of its column
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const int s1 = __shfl(acc[h][e], lane + 4, 64), s2 = __shfl(acc[h][e], lane + 8, 64);
+                const int i = base + 16 * h + 4 * kg + e;
+                if (col < ND && i < m) {
+                    const long long v = (long long)s2 * 65536 + (long long)s1 * 256 + acc[h][e] + s_d[col].base;
+                    out(i, col, (double)v * s_d[col].scale);
+                }
+            }
+        }
+    }
+}
+
+template <bool LEAD>
+__global__ __launch_bounds__(256) void k_digit_chunks(const int8_t *__restrict__ Xq, int d, int dq,
+                                                      const float *__restrict__ R, int64_t H,
+                                                      const SegDesc *__restrict__ segs,
+                                                      const ChunkDesc *__restrict__ chunks,
+                                                      const int32_t *__restrict__ perm, int64_t n,
+                                                      uint64_t *__restrict__ keys, const LookDesc *__restrict__ look,
+                                                      double *__restrict__ ahead, int trees_first) {
+    constexpr int ND = LEAD ? 3 : 1;
+    extern __shared__ __align__(16) int8_t s_digit[];  // [dq][16]
+    __shared__ DigitDir s_d[3];
+    __shared__ uint32_t s_max[3];
+    const int t = trees_first ? blockIdx.x : blockIdx.y;
+    const ChunkDesc c = chunks[trees_first ? blockIdx.y : blockIdx.x];
+    const SegDesc sg = segs[c.seg];
+    const float *dir[ND];
+    dir[0] = R + ((int64_t)t * H + (sg.heap - 1)) * (int64_t)d;
+    if constexpr (LEAD) {
+        const LookDesc lk = look[c.seg];
+#pragma unroll
+        for (int b = 0; b < 2; b++)
+            dir[b + 1] = lk.child_heap[b] > 0 ? R + ((int64_t)t * H + (lk.child_heap[b] - 1)) * (int64_t)d : nullptr;
+    }
+    digit_stage<256, ND>(dir, d, dq, s_digit, s_d, s_max);
+    const int64_t at = (int64_t)t * n + c.start;
+    const int32_t *pp = perm + at;
+    digit_project<256, ND>(Xq, dq, s_digit, s_d, c.len, [&](int i) { return pp[i]; },
+                           [&](int i, int k, double p) {
+                               if (k == 0) keys[at + i] = key_of(p);
+                               else ahead[2 * (at + i) + (k - 1)] = p;
+                           });
+}
+
+// The exact keys of a chunk's members within 2 e of the first selection's median.
+template <bool VEC>
+__global__ __launch_bounds__(256) void k_digit_refine(const int8_t *__restrict__ Xq, int d, int dq,
+                                                      const float *__restrict__ R, int64_t H,
+                                                      const SegDesc *__restrict__ segs,
+                                                      const ChunkDesc *__restrict__ chunks,
+                                                      const int32_t *__restrict__ perm, int64_t n,
+                                                      uint64_t *__restrict__ keys, const SelState *__restrict__ state,
+                                                      int nseg, const double *__restrict__ bound) {
+    extern __shared__ __align__(16) float s_dirf[];  // [d up to a multiple of four]
+    __shared__ uint16_t s_list[kChunk];
+    __shared__ int s_cnt;
+    const int t = blockIdx.y, tid = threadIdx.x;
+    const ChunkDesc c = chunks[blockIdx.x];
+    const SegDesc sg = segs[c.seg];
+    const int64_t node = (int64_t)t * H + (sg.heap - 1), at = (int64_t)t * n + c.start;
+    const double mid = val_of(state[(int64_t)t * nseg + c.seg].key), e2 = 2.001 * bound[node];
+    if (tid == 0) s_cnt = 0;
+    __syncthreads();
+    for (int i = tid; i < c.len; i += 256)
+        if (fabs(val_of(keys[at + i]) - mid) <= e2) s_list[atomicAdd(&s_cnt, 1)] = (uint16_t)i;
+    __syncthreads();
+    const int cnt = s_cnt;
+    if (cnt == 0) return;
+    for (int j = tid; j < d; j += 256) s_dirf[j] = R[node * d + j];
+    __syncthreads();
+    const int g = tid & 7;
+    for (int k = tid >> 3; k < cnt; k += 32) {
+        const int i = s_list[k];
+        const double p = group8_dot64_q8<VEC>(Xq + (int64_t)perm[at + i] * dq, s_dirf, d, g);
+        if (g == 0) keys[at + i] = key_of(p);
+    }
+}
+
 // LDS layout: perm[m] int32 | key[m] u64 | dir[d] | hist[256] | misc ; nTry>1 adds p[m], tree[P2]
-// Q8: the node projections read rows from the int8 grid copy Xq (stride dq); the same values
+// Q8: the node projections read rows from the int8 grid copy Xq (stride dq): 1, the same values;
+// 2, by digits, the members within 2 `bound` of the median then exactly
 // NT: threads of a workgroup (n_try > 1: 256)
-template <bool VEC, bool LEAD, bool Q8 = false, int NT = 256>
+template <bool VEC, bool LEAD, int Q8 = 0, int NT = 256>
 __global__ __launch_bounds__(NT) void k_level_small(
     const float *__restrict__ X, int d, const float *__restrict__ R, int64_t H, int n_try,
     const SegDesc *__restrict__ segs, const int32_t *__restrict__ perm_in,
     int32_t *__restrict__ perm_out, int64_t n, double *__restrict__ split,
     int32_t *__restrict__ split_idx, int32_t *__restrict__ chosen, int32_t *__restrict__ err,
     const LookDesc *__restrict__ look, double2 *__restrict__ ahead, uint64_t *__restrict__ keys_next,
-    const uint64_t *__restrict__ keys_in, const int8_t *__restrict__ Xq, int dq) {
+    const uint64_t *__restrict__ keys_in, const int8_t *__restrict__ Xq, int dq, const double *__restrict__ bound) {
     extern __shared__ __align__(16) uint8_t smem[];
     __shared__ uint32_t s_wide[NT == 256 ? 1 : NT / 64];
+    __shared__ DigitDir s_d[3];
+    __shared__ uint32_t s_max[3];
     const int t = blockIdx.y;
     const SegDesc sg = segs[blockIdx.x];
     const int m = sg.size;
@@ -93,6 +299,24 @@ __global__ __launch_bounds__(NT) void k_level_small(
     __syncthreads();
     if (keys_in) {  // fed level: the keys were made by the partition of the level above
         for (int i = tid; i < m; i += blockDim.x) s_key[i] = keys_in[(int64_t)t * n + sg.off + i];
+    } else if constexpr (Q8 == 2) {
+        constexpr int ND = LEAD ? 3 : 1;
+        const float *dir[ND];
+        dir[0] = Rn;
+        if constexpr (LEAD) {
+            const LookDesc lk = look[blockIdx.x];
+#pragma unroll
+            for (int b = 0; b < 2; b++)
+                dir[b + 1] = lk.child_heap[b] > 0 ? R + ((int64_t)t * H + (lk.child_heap[b] - 1)) * (int64_t)d : nullptr;
+        }
+        int8_t *s_b = reinterpret_cast<int8_t *>(s_dir);
+        digit_stage<NT, ND>(dir, d, dq, s_b, s_d, s_max);
+        double *ah = reinterpret_cast<double *>(ahead + ((int64_t)t * n + sg.off));
+        digit_project<NT, ND>(Xq, dq, s_b, s_d, m, [&](int i) { return s_perm[i]; },
+                              [&](int i, int k, double p) {
+                                  if (k == 0) s_key[i] = key_of(p);
+                                  else ah[2 * i + (k - 1)] = p;
+                              });
     } else if (LEAD) {  // lead level: the children's projections from the same read of X
         const LookDesc lk = look[blockIdx.x];
         for (int j = tid; j < d; j += blockDim.x) {
@@ -107,7 +331,7 @@ __global__ __launch_bounds__(NT) void k_level_small(
         for (int base = 0; base < m; base += NT / 4) {
             const int ia = base + pt, ib = ia + NT / 8;
             double p[6];
-            if constexpr (Q8)
+            if constexpr (Q8 != 0)
                 group8_dot64x3r2_q8<VEC>(Xq + (int64_t)s_perm[ia < m ? ia : 0] * dq, Xq + (int64_t)s_perm[ib < m ? ib : 0] * dq,
                                     s_rd, ds, d, g, p);
             else
@@ -130,7 +354,7 @@ __global__ __launch_bounds__(NT) void k_level_small(
             int i = base + pt;
             int ii = i < m ? i : 0;
             double p;
-            if constexpr (Q8) p = group8_dot64_q8<VEC>(Xq + (int64_t)s_perm[ii] * dq, s_r, d, g);
+            if constexpr (Q8 != 0) p = group8_dot64_q8<VEC>(Xq + (int64_t)s_perm[ii] * dq, s_r, d, g);
             else p = group8_dot64<VEC>(X + (int64_t)s_perm[ii] * d, s_r, d, g);
             if (g == 0 && i < m) s_key[i] = key_of(p);
         }
@@ -140,6 +364,9 @@ __global__ __launch_bounds__(NT) void k_level_small(
     // ---- select rank floor(m/2) in (key, index) order: 8-bit radix passes over the 96-bit key
     uint64_t phi = 0;
     uint32_t plo = 0;
+    for (int pass = 0;; pass++) {
+    phi = 0;
+    plo = 0;
     int nbits = 0;
     uint32_t rank = (uint32_t)(m / 2), cnt = (uint32_t)m;
     while (cnt > 1 && nbits < 96) {
@@ -183,6 +410,31 @@ __global__ __launch_bounds__(NT) void k_level_small(
         __syncthreads();
         phi = ((uint64_t)s_misc[13] << 32) | s_misc[12];
         plo = s_misc[14];
+    }
+    if (Q8 != 2 || pass) break;
+    // exact keys around the digits' median, then the selection over them
+    __syncthreads();
+    for (int j = tid; j < d; j += NT) s_r[j] = Rn[j];
+    if (tid == 0) s_misc[15] = 0;
+    __syncthreads();
+    const double mid = val_of(phi), e2 = 2.001 * bound[(int64_t)t * H + (sg.heap - 1)];
+    const int g = tid & 7;
+    for (int i = tid >> 3; i < m; i += NT / 8) {
+        if (!(fabs(val_of(s_key[i]) - mid) <= e2)) continue;  // (the same for a row's eight lanes)
+        const double p = group8_dot64_q8<VEC>(Xq + (int64_t)s_perm[i] * dq, s_r, d, g);
+        if (g == 0) {
+            s_key[i] = key_of(p);
+            if (atomicAdd(&s_misc[15], 1u) == 0) {
+                s_misc[12] = (uint32_t)s_key[i];
+                s_misc[13] = (uint32_t)(s_key[i] >> 32);
+            }
+        }
+    }
+    __syncthreads();
+    if (s_misc[15] == 1) {  // alone: the median itself
+        phi = ((uint64_t)s_misc[13] << 32) | s_misc[12];
+        break;
+    }
     }
 
     // ---- stable partition: left = keys below (c, c_idx), in position (= index) order
@@ -1962,6 +2214,12 @@ size_t level_small_lds(int max_m, int d, int n_try) {
     return lds;
 }
 
+void launch_digit_bound(hipStream_t s, const float *R, int64_t nodes, int d, double *bound) {
+    const unsigned blocks = (unsigned)((nodes + 3) / 4 < 16384 ? (nodes + 3) / 4 : 16384);
+    hipLaunchKernelGGL(k_digit_bound, dim3(blocks), dim3(256), 0, s, R, nodes, d, bound);
+    launch_check(s, "k_digit_bound");
+}
+
 // A level with at most one workgroup per CU runs 1024 threads in each instead of 256: such a
 // level takes the time of one workgroup's walk over its members.  Build at 10 000 x 128, 4 trees:
 // 436 -> 349 us; 40 000 x 64, 16 trees: 850 -> 722 (748 with up to 512 workgroups); 200 000 x 128,
@@ -1972,7 +2230,7 @@ void launch_level_small(hipStream_t s, bool vec, const float *X, int d, const fl
                         int n_try, const SegDesc *segs, int nseg, int max_m, int T,
                         const int32_t *pin, int32_t *pout, int64_t n, double *split,
                         int32_t *split_idx, int32_t *chosen, int32_t *err, const LevelLink &lk) {
-    if (!lk.look && lk.keys_in && n_try == 1 && max_m <= kWaveSeg) {  // fed level of small segments
+    if (!lk.look && lk.keys_in && n_try == 1 && max_m <= kWaveSeg && !lk.bound) {  // fed level of small segments
         auto go = [&](auto kern) {
             hipLaunchKernelGGL(kern, dim3((nseg + 3) / 4, T), dim3(256), 0, s, segs, nseg, pin, pout, n, H, split,
                                split_idx, chosen, err, lk.keys_in);
@@ -1987,21 +2245,26 @@ void launch_level_small(hipStream_t s, bool vec, const float *X, int d, const fl
     auto go = [&](auto kern, int nt) {
         hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         hipLaunchKernelGGL(kern, grid, dim3(nt), lds, s, X, d, R, H, n_try, segs, pin, pout, n, split, split_idx,
-                           chosen, err, lk.look, lk.ahead, lk.keys_next, lk.keys_in, lk.xq, lk.dq);
+                           chosen, err, lk.look, lk.ahead, lk.keys_next, lk.keys_in, lk.xq, lk.dq, lk.bound);
     };
     const bool q8 = lk.xq && n_try == 1;  // (several tries project through the binary32 rows)
     auto pick = [&](auto w) {
         constexpr int W = decltype(w)::value;
-        if (lk.look) {
-            if (q8 && vec) go(k_level_small<true, true, true, W>, W);
-            else if (q8) go(k_level_small<false, true, true, W>, W);
-            else if (vec) go(k_level_small<true, true, false, W>, W);
-            else go(k_level_small<false, true, false, W>, W);
+        if (lk.bound) {
+            if (lk.look && vec) go(k_level_small<true, true, 2, W>, W);
+            else if (lk.look) go(k_level_small<false, true, 2, W>, W);
+            else if (vec) go(k_level_small<true, false, 2, W>, W);
+            else go(k_level_small<false, false, 2, W>, W);
+        } else if (lk.look) {
+            if (q8 && vec) go(k_level_small<true, true, 1, W>, W);
+            else if (q8) go(k_level_small<false, true, 1, W>, W);
+            else if (vec) go(k_level_small<true, true, 0, W>, W);
+            else go(k_level_small<false, true, 0, W>, W);
         } else {
-            if (q8 && vec) go(k_level_small<true, false, true, W>, W);
-            else if (q8) go(k_level_small<false, false, true, W>, W);
-            else if (vec) go(k_level_small<true, false, false, W>, W);
-            else go(k_level_small<false, false, false, W>, W);
+            if (q8 && vec) go(k_level_small<true, false, 1, W>, W);
+            else if (q8) go(k_level_small<false, false, 1, W>, W);
+            else if (vec) go(k_level_small<true, false, 0, W>, W);
+            else go(k_level_small<false, false, 0, W>, W);
         }
     };
     if (n_try == 1 && few_blocks((int64_t)nseg * T) && max_m >= 512 && lds <= 128 * 1024)
@@ -2022,6 +2285,20 @@ static void proj_chunks(hipStream_t s, dim3 gc, const float *X, int d, const flo
                            lk.xq, lk.dq);
     };
     const bool q8 = lk.xq != nullptr;
+    if (lk.bound) {
+        auto digits = [&](auto kern) {
+            const int bytes = 16 * lk.dq;
+            // the first level: the same rows in every tree, whose workgroups share them in cache
+            const bool trees_first = lk.top && gc.x <= 65535;
+            hipLaunchKernelGGL(kern, trees_first ? dim3(gc.y, gc.x) : gc, dim3(256), bytes, s, lk.xq, d, lk.dq, R, H,
+                               segs, chunks, pin, n, b.keys, lk.look, reinterpret_cast<double *>(lk.ahead),
+                               (int)trees_first);
+        };
+        if (lk.look) digits(k_digit_chunks<true>);
+        else digits(k_digit_chunks<false>);
+        launch_check(s, "k_digit_chunks");
+        return;
+    }
     auto pick = [&](auto w) {
         constexpr int W = decltype(w)::value;
         if (lk.look && q8) go(k_proj_chunks<VEC, true, true, W>, W);
@@ -2052,7 +2329,7 @@ void launch_level_large(hipStream_t s, bool vec, const float *X, int d, const fl
         if (vec) proj_chunks<true>(s, gc, X, d, R, H, segs, chunks, pin, n, b, lk);
         else proj_chunks<false>(s, gc, X, d, R, H, segs, chunks, pin, n, b, lk);
     }
-    {
+    auto select = [&]() {
         ProfScope ps(s, "select_passes", 0, 0);
         // with more segments than CUs the pick costs more than the two launches before it save
         // it (72 trees, segments of 7 813: 613 us whole, 320 us bracketed); with few, one launch
@@ -2070,6 +2347,17 @@ void launch_level_large(hipStream_t s, bool vec, const float *X, int d, const fl
         hipLaunchKernelGGL(k_sel_pick, gs, dim3(1024), 0, s, segs, b.keys, pin, n, b.state, sampled, pout, b.lcount,
                            nchunk, H, split, split_idx, chosen, err);
         launch_check(s, "k_sel_pick");
+    };
+    select();
+    if (lk.bound) {  // keys by digits: exact ones around the median, and the median of those
+        auto refine = [&](auto kern) {
+            hipLaunchKernelGGL(kern, gc, dim3(256), (size_t)((d + 3) & ~3) * 4, s, lk.xq, d, lk.dq, R, H, segs, chunks,
+                               pin, n, b.keys, b.state, nseg, lk.bound);
+        };
+        if (vec) refine(k_digit_refine<true>);
+        else refine(k_digit_refine<false>);
+        launch_check(s, "k_digit_refine");
+        select();
     }
     {
         ProfScope ps(s, "partition", 0, 0);

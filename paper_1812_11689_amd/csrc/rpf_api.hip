@@ -939,6 +939,22 @@ static void build_launches(rpf_forest *f, hipStream_t s) {
     const bool vec = (d % 4) == 0;
     launch_iota(s, f->perm[0], n, T);
     launch_check(s, "iota");
+    // grid forests of long rows: projections by digits, their bounds in the norms array (written
+    // after the last level).  A second selection a level is the price (four launches where nodes
+    // take many workgroups).  Build at d = 784: 3 000 rows, 4 trees 484 -> 404 us, 60 000 rows, 4
+    // trees 1 279 -> 1 105; d = 256: 60 000 rows, 8 trees 877 -> 1 014, so not there, 40 trees
+    // 2 265 -> 1 960; d = 192, 200 000 rows, 16 trees 2 766 -> 2 500; d = 128: 1 995 -> 2 108.
+    // Nodes below kDigitSeg members project exactly: staging three directions costs more than
+    // their rows (60 000 x 784, 64 trees, leaves of 16: 10.9 ms with every node by digits, 9.6 with
+    // those of 128 and more, 10.1 with those above 1 024).
+    double *bound = nullptr;
+    constexpr int kDigitSeg = 128;
+    if (f->Xq && n_try == 1 && d <= 1024 && H > 0 && H <= n &&
+        (d >= 512 || (d >= 192 && (double)T * n * d >= 4e8))) {
+        bound = reinterpret_cast<double *>(f->nrm);
+        launch_digit_bound(s, f->R, (int64_t)T * H, d, bound);
+    }
+    bool by_digits = false;  // this level's keys
     int cur = 0;
     for (size_t l = 0; l < f->levels.size(); l++) {
         LevelPlan &lv = f->levels[l];
@@ -972,6 +988,9 @@ static void build_launches(rpf_forest *f, hipStream_t s) {
         // grid forests: the rows come from the int8 copy (one byte a coordinate)
         lk.xq = f->Xq;
         lk.dq = f->dq;
+        if (!lv.fed) by_digits = bound && lv.max_m >= kDigitSeg;  // (a fed level's are its lead's)
+        lk.bound = by_digits ? bound : nullptr;
+        lk.top = l == 0;
         const double xb = f->Xq ? (double)f->dq : 4.0 * d;  // bytes of a row read
         // algorithmic bytes: X rows (none on a fed level), ids and keys, the children's
         // projections out and back on a lead level

@@ -94,7 +94,13 @@ struct LevelLink {
     // instead of X, a quarter of the bytes for the same binary32 values
     const int8_t *xq = nullptr;
     int dq = 0;
+    // grid forests: per node, how far a projection by digits may be from the exact one (null:
+    // every projection exact)
+    const double *bound = nullptr;
+    bool top = false;  // the first level: the identity permutation in every tree
 };
+
+void launch_digit_bound(hipStream_t s, const float *R, int64_t nodes, int d, double *bound);
 
 struct SubItem {       // an internal node at the first level of the persistent subtree launch
     int64_t off;      // first position in the node-ordered permutation

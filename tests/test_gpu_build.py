@@ -131,6 +131,52 @@ def test_wide_levels_of_a_grid_forest(d):
     f.free()
 
 
+DIGIT_CASES = [
+    # grid forests of long rows: keys by digits, exact ones around the median
+    # name, n, d, T, n0, what
+    ("d512_chunks", 9000, 512, 2, 300, "images"),
+    ("d513_scalar", 5000, 513, 2, 60, "images"),
+    ("d1024", 4097, 1024, 1, 100, "images"),
+    ("d1023_small_nodes", 700, 1023, 3, 20, "images"),
+    ("nodes_of_128", 512, 600, 2, 30, "images"),
+    ("two_values_ties", 6000, 512, 2, 100, "binary"),       # members in the band by the hundred
+    ("few_distinct_rows", 9000, 520, 2, 100, "copies"),
+    ("one_row", 5000, 512, 1, 600, "one"),                  # every member in the band
+    ("zero_directions", 3000, 512, 2, 100, "zero"),
+    ("wide_directions", 9000, 700, 2, 100, "wide"),         # 1e30 beside 1e-30: a band of many
+]
+
+
+@pytest.mark.parametrize("case", DIGIT_CASES, ids=[c[0] for c in DIGIT_CASES])
+def test_digit_projections_match_oracle(case):
+    from paper_1812_11689_amd import rpf
+    name, n, d, T, n0, what = case
+    print(f"[build] {name} n={n} d={d} T={T} n0={n0}", flush=True)
+    rng = np.random.default_rng(len(name) + 72)
+    k = rng.integers(0, 256, (n, d))
+    if what == "binary":
+        k = 255 * (k[:, :1] < 128) * (np.arange(d) < 4)[None] + 0 * k
+    elif what == "copies":
+        k = k[rng.integers(0, 5, n)]
+    elif what == "one":
+        k = np.broadcast_to(k[:1], (n, d))
+    x = (np.ascontiguousarray(k).astype(np.float32) / np.float32(255)).astype(np.float32)
+    R = rng.standard_normal((T, 2 ** rpf.depth(n, n0) - 1, 1, d)).astype(np.float32)
+    if what == "zero":
+        R[:, ::2] = 0
+    elif what == "wide":
+        R *= (np.float32(10.0) ** rng.uniform(-30, 30, R.shape)).astype(np.float32)
+    ref = oracle.build_forest(x, R, T, n0, 1)
+    f = rpf.build(torch.from_numpy(x).cuda(), T, n0, torch.from_numpy(R).cuda(), dist_prec="u8grid")
+    f.info()
+    for t in range(T):
+        g = {k: v.cpu().numpy() for k, v in f.tree_dump(t).items()}
+        np.testing.assert_array_equal(g["perm"], ref.perm[t])
+        assert np.array_equal(g["split"], ref.split[t], equal_nan=True)
+        np.testing.assert_array_equal(g["split_idx"], ref.split_idx[t])
+    f.free()
+
+
 TRY_CASES = [
     # several tries per node: sums over pieces of 256 members, nodes scored in one workgroup
     # (up to 512 members) or over many blocks, 2 to 5 tries per read, more than 16 tries
