@@ -872,7 +872,7 @@ __global__ __launch_bounds__(64 * MB) void k_tile_q8(const TileJob *__restrict__
         const bool full = (same && exclude_self != 0 && cb == wu) || 32 * cb + 32 > job.b_rows;
 #pragma unroll
         for (int h = 0; h < 2; h++) {
-            uint32_t bits = 0;
+            bool hit[8];
             uint64_t mk[8];
             uint32_t tot = 0;
             auto test = [&](auto FULL) {
@@ -884,7 +884,7 @@ __global__ __launch_bounds__(64 * MB) void k_tile_q8(const TileJob *__restrict__
                         const int row = 32 * wu + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
                         p = p & colok & !(same & (exclude_self != 0) & (row == col));
                     }
-                    bits |= (p ? 1u : 0u) << v8;
+                    hit[v8] = p;
                     mk[v8] = __ballot(p);
                     tot += (uint32_t)__popcll(mk[v8]);
                 }
@@ -897,8 +897,10 @@ __global__ __launch_bounds__(64 * MB) void k_tile_q8(const TileJob *__restrict__
             }
 #pragma unroll
             for (int v8 = 0; v8 < 8; v8++) {
+                // (uniform) most values pass in no lane: 10^6 x 784, 48 trees 38.1 -> 36.0 ms
+                if (mk[v8] == 0) continue;
                 const int v = 8 * h + v8;
-                if ((bits >> v8) & 1u) {
+                if (hit[v8]) {
                     const int row = 32 * wu + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
                     que[qc + mask_rank(mk[v8])] = make_uint2((uint32_t)row | ((uint32_t)col << 8), (uint32_t)acc[cb][v]);
                 }
