@@ -1109,6 +1109,7 @@ __global__ __launch_bounds__(1024) void k_sel_pick(const SegDesc *__restrict__ s
         uint64_t rk[E];
         uint32_t bn[E];
         double mn = INFINITY, mx = -INFINITY;
+        bool nan = false;
         if (reg) {
 #pragma unroll
             for (int e = 0; e < E; e++) {
@@ -1119,12 +1120,22 @@ __global__ __launch_bounds__(1024) void k_sel_pick(const SegDesc *__restrict__ s
 #pragma unroll
             for (int e = 0; e < E; e++) {
                 if (1024u * e >= N) continue;
-                mn = fmin(mn, val_of(rk[e]));
-                mx = fmax(mx, val_of(rk[e]));
+                const double v = val_of(rk[e]);
+                mn = fmin(mn, v);
+                mx = fmax(mx, v);
+                nan |= v != v;
             }
             for (int o = 32; o > 0; o >>= 1) {
                 mn = fmin(mn, shfl_xor_d(mn, o));
                 mx = fmax(mx, shfl_xor_d(mx, o));
+            }
+            // A plan checks its inputs after the launch, so a key may be a NaN, whose place in the
+            // order of the keys its value does not tell: one part for all, and the passes below,
+            // which go by the keys.  (By value it counted as left here and as right in the
+            // partition, which left a slot of the permutation unwritten.)
+            if (__any(nan)) {
+                mn = -INFINITY;
+                mx = INFINITY;
             }
         } else {
             mn = val_of(lo);
@@ -1232,13 +1243,15 @@ __global__ __launch_bounds__(1024) void k_sel_pick(const SegDesc *__restrict__ s
             range([&](uint64_t k, uint32_t p) { return k >= l0 && k <= h0_ && bin_of(k, p) == b; });
             by_value = 2 * left < was;
         } else {
-            const uint64_t na = a + ((uint64_t)b << sh), nb = na + (((uint64_t)1 << sh) - 1);
+            // the part's last key or position, or the range's (past an infinity or a NaN the part's
+            // last key could lie beyond 64 bits)
+            const uint64_t na = a + ((uint64_t)b << sh), span = ((uint64_t)1 << sh) - 1;
             if (how == 2) {
+                phi = phi - na > span ? na + span : phi;
                 plo = na;
-                phi = nb < phi ? nb : phi;
             } else {
+                hi = hi - na > span ? na + span : hi;
                 lo = na;
-                hi = nb < hi ? nb : hi;
                 by_value = true;
             }
             __syncthreads();

@@ -170,3 +170,36 @@ def test_tuner_records_its_choices(tmp_path):
         again.close()
     finally:
         rpf.tune_clear()
+
+
+@pytest.mark.parametrize("n,T", [(9000, 2), (9000, 60), (70_000, 2)])  # nodes read whole, many nodes, bracketed nodes
+@pytest.mark.parametrize("bad", [np.nan, -np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("where", ["row", "half", "directions"])
+def test_plan_nonfinite_input_of_large_nodes(n, T, bad, where):
+    # the check comes after the launch: until then every node above 4096 members must still be
+    # split into two whole halves (a permutation of the points), whatever its keys are
+    from paper_1812_11689_amd import rpf
+    d, n0 = 6, 500
+    print(f"[plan] non-finite n={n} T={T} {bad} {where}", flush=True)
+    plan = rpf.Plan([n], [d], T, n0, 3)
+    xs, Rs = _inputs(3100, [n], [d], T, n0)
+    if where == "row":
+        xs[0][n // 3, 2] = bad
+    elif where == "half":
+        xs[0][::2, 1] = bad
+    else:
+        Rs[0].reshape(-1)[::7] = bad
+    plan.set_inputs(xs, Rs)
+    for _ in range(2):
+        plan.launch()
+        with pytest.raises(rpf.RpfError) as e:
+            plan.check()
+        assert e.value.status == rpf.RPF_EINVAL
+    f = rpf.Forest(plan.parts[0]["forest"], n, d, T, n0, 1, rpf.depth(n, n0))
+    try:
+        for t in (0, T - 1):
+            perm = np.sort(f.tree_dump(t)["perm"].cpu().numpy())
+            np.testing.assert_array_equal(perm, np.arange(n))
+    finally:
+        f._h = None  # the plan's, not to be freed
+    plan.close()
