@@ -294,6 +294,11 @@ __global__ __launch_bounds__(kSelThreads) void k_exact_select(const double *__re
 //   k_exact_rank    binary64 distance of every listed point, top-K by (D, index).
 // A query whose list overflows (many equal or nearly equal distances, or values outside what
 // the bracket covers) goes to the exhaustive kernels above, so results are theirs bit for bit.
+// Such queries cost the passes before the tiles (k_exact_tau finds most of them), and a wave
+// stops listing points of a query once it has seen its list full: 2 000 queries x 500 000 x
+// 128 in two clusters far from the centre 21.8 ms (180 when every point was counted by an
+// atomic, 23.2 by the exhaustive kernels alone), norms past 1e37 22.1 (325, 23.5), 50 distinct
+// rows 32.3 (48.6, 34.4); 64 x 100 000, 10 distinct rows 1.23 (5.6, 1.05).
 //
 // Bracket: with a' = fl(a - centre), G the computed hi.hi + hi.lo + lo.hi of a'.b' and na, nb
 // the squared norms of a', b':  |D - (na + nb - 2G)| <= E (na + nb) + eta.  The split leaves
@@ -395,17 +400,29 @@ __global__ __launch_bounds__(512) void k_exact_tile(const __bf16 *__restrict__ Q
                                                     uint2 *__restrict__ cand, float *__restrict__ ub, int64_t ldS) {
     extern __shared__ __align__(16) uint8_t smem[];
     bf16x8 *s_a = reinterpret_cast<bf16x8 *>(smem);                        // [QB][KS][2][64]
-    float *s_phi = reinterpret_cast<float *>(s_a + (size_t)QB * KS * 128);  // [32 QB]
-    uint4 *s_queue = reinterpret_cast<uint4 *>(s_phi + 32 * QB);            // MODE 1: [8][kFiltQueue]
+    // [8][32 QB], a copy per wave; MODE 1: -inf for a query whose list the wave has seen overflow
+    // (and for padding), which no bound passes
+    float *s_phis = reinterpret_cast<float *>(s_a + (size_t)QB * KS * 128);
+    uint4 *s_queue = reinterpret_cast<uint4 *>(s_phis + 8 * 32 * QB);  // MODE 1: [8][kFiltQueue]
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    float *s_phi = s_phis + w * 32 * QB;
     const int64_t q0 = (int64_t)blockIdx.y * 32 * QB;
     {
         const bf16x8 *src = reinterpret_cast<const bf16x8 *>(QF) + (int64_t)blockIdx.y * QB * KS * 128;
         for (int i = threadIdx.x; i < QB * KS * 128; i += 512) s_a[i] = src[i];
-        for (int i = threadIdx.x; i < 32 * QB; i += 512)
-            s_phi[i] = MODE == 0 ? (1.0f + E) * qn[q0 + i] : q0 + i < m ? phi[q0 + i] : -INFINITY;
+        bool open = MODE == 0;
+        for (int i = lane; i < 32 * QB; i += 64) {
+            const int64_t q = q0 + i;
+            if (MODE == 0) {
+                s_phi[i] = (1.0f + E) * qn[q];
+            } else {
+                const bool take = q < m && cnt[q] <= (uint32_t)kFiltCap;
+                s_phi[i] = take ? phi[q] : -INFINITY;
+                open |= take;
+            }
+        }
+        if (!__syncthreads_or(open)) return;  // every query of the block is left to the exhaustive kernels
     }
-    __syncthreads();
     const int64_t ntile = (npts + 31) / 32, step = (int64_t)gridDim.x * 8;
     const bf16x8 *P = reinterpret_cast<const bf16x8 *>(PF) + lane;
     uint4 *queue = s_queue + w * kFiltQueue;  // (query, point, (1 - E) nb - 2G, nb)
@@ -414,9 +431,12 @@ __global__ __launch_bounds__(512) void k_exact_tile(const __bf16 *__restrict__ Q
         wave_sync();
         for (int e = lane; e < nq; e += 64) {
             const uint4 it = queue[e];
-            if (q0 + it.x >= m) continue;  // a padding row of the last block
+            if (s_phi[it.x] == -INFINITY) continue;  // (a norm that is no number passes even this)
             const uint32_t at = atomicAdd(&cnt[q0 + it.x], 1u);
-            if (at >= (uint32_t)kFiltCap) continue;
+            if (at >= (uint32_t)kFiltCap) {
+                s_phi[it.x] = -INFINITY;
+                continue;
+            }
             const float na = qn[q0 + it.x], v = __uint_as_float(it.z), nb = __uint_as_float(it.w);
             const float lb = v + (1.0f - E) * na, ub = lb + 2.0f * E * (na + nb) + 2.0f * kFiltEta + (na + nb) * 1e-6f;
             cand[(q0 + it.x) * kFiltCap + at] = make_uint2(it.y, pack_bounds(lb - (na + nb) * 1e-6f - kFiltEta, ub));
@@ -517,11 +537,15 @@ __global__ __launch_bounds__(512) void k_exact_tile(const __bf16 *__restrict__ Q
 }
 
 // phi of a query: its threshold (the upper edge of the 24-bit prefix bucket that holds the
-// K-th smallest of its S upper bounds, so at or above it) less its own norm's share.
+// K-th smallest of its S upper bounds, so at or above it) less its own norm's share.  A query
+// of which the sample says that far more points than a list holds would pass (repeated rows,
+// clusters far from the centre, norms that are no number) is left to the exhaustive kernels
+// here, before the tiles list thousands of its points for nothing: cnt above kFiltCap.
 __global__ __launch_bounds__(256) void k_exact_tau(const float *__restrict__ ub, int64_t ldS, int64_t S, int K,
                                                    const float *__restrict__ qn, float E,
-                                                   const int64_t *__restrict__ self, int64_t stride,
-                                                   float *__restrict__ phi) {
+                                                   const int64_t *__restrict__ self, int64_t n, int64_t stride,
+                                                   const float *__restrict__ sn, float *__restrict__ phi,
+                                                   uint32_t *__restrict__ cnt) {
     // 12-bit digits: sixteen bins per octave, so that one query's distances, which share their
     // exponents, do not all meet in one counter
     __shared__ uint32_t s_h[4096];
@@ -555,16 +579,32 @@ __global__ __launch_bounds__(256) void k_exact_tau(const float *__restrict__ ub,
         }
         __syncthreads();
         if (s_sel[0] == 4096) {  // fewer than K finite bounds: nothing is excluded
-            if (tid == 0) phi[blockIdx.x] = INFINITY;
+            if (tid == 0) {
+                phi[blockIdx.x] = INFINITY;
+                cnt[blockIdx.x] = n > kFiltCap ? kFiltCap + 1 : 0;
+            }
             return;
         }
         prefix |= s_sel[0] << sh;
         rank -= s_sel[1];
         __syncthreads();
     }
+    const float tau = __uint_as_float(prefix | 0x7fu), na = qn[blockIdx.x];
+    const float ph = (tau - (1.0f - E) * na) + kFiltEta + (tau + na) * 1e-6f;
+    // sampled points by the tiles' test, (1 - E) nb - 2G from the upper bound: 32 runs of 16 points
+    const float top = ph + (1.0f + E) * na;
+    uint32_t pass = 0;
+#pragma unroll
+    for (int e = 0; e < 2; e++) {
+        const int64_t i = (16 * e + (tid >> 4)) * S / 32 + (tid & 15);
+        const float u = i < S ? __uint_as_float(row[i]) : 0.f;
+        if (i < S) pass += !(u < 3e38f) || !(u - 2.0f * E * sn[i] > top) ? 1u : 0u;
+    }
+    uint32_t excl, total;
+    block_excl_scan256(pass, s_w, excl, total);
     if (tid == 0) {
-        const float tau = __uint_as_float(prefix | 0x7fu), na = qn[blockIdx.x];
-        phi[blockIdx.x] = (tau - (1.0f - E) * na) + kFiltEta + (tau + na) * 1e-6f;
+        phi[blockIdx.x] = ph;
+        cnt[blockIdx.x] = (int64_t)total * n > (int64_t)2 * kFiltCap * 512 ? kFiltCap + 1 : 0;
     }
 }
 
@@ -680,7 +720,7 @@ void launch_tile(hipStream_t s, int QB, int d, int64_t m, const __bf16 *QF, cons
     // of one range of points then run on one XCD and share its L2
     const int64_t want = std::max<int64_t>(8, 512 / gy / 8 * 8), tiles = (npts + 31) / 32;
     const unsigned gx = (unsigned)std::min<int64_t>(want, (tiles + 7) / 8);
-    const size_t lds = (size_t)QB * KS * 2048 + 128 * QB + (MODE == 1 ? 8 * kFiltQueue * 16 : 0);
+    const size_t lds = (size_t)QB * KS * 2048 + 8 * 128 * QB + (MODE == 1 ? 8 * kFiltQueue * 16 : 0);
     auto go = [&](auto kern) {
         hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         hipLaunchKernelGGL(kern, dim3(gx, gy), dim3(512), lds, s, QF, qn, m, PF, pn, npts, base, KS, E, phi, cnt, cand,
@@ -746,11 +786,10 @@ bool filtered_search(hipStream_t s, const float *X, int64_t n, int d, const floa
             const int64_t nq = std::min(mq, m - q0);
             const int64_t *sc = self ? self + q0 : nullptr;
             split(Q + q0 * d, nq, 1, qt, QF, QN);
-            fill_u32(cnt, nq, 0, s);
             launch_tile<0>(s, QB, d, nq, B(QF), F(QN), B(SF), F(SN), S, 0, E, nullptr, nullptr, nullptr,
                            static_cast<float *>(sbuf), S);
             hipLaunchKernelGGL(k_exact_tau, dim3((unsigned)nq), dim3(256), 0, s, static_cast<float *>(sbuf), S, S, K, F(QN),
-                               E, sc, stride, F(PHI));
+                               E, sc, n, stride, F(SN), F(PHI), cnt);
             launch_check(s, "k_exact_tau");
             for (int64_t p0 = 0; p0 < n; p0 += slab) {
                 const int64_t np = std::min(slab, n - p0);

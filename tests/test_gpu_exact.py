@@ -104,3 +104,56 @@ def test_filtered_search_matches_oracle(case, use_self):
                            torch.from_numpy(pts.astype(np.int64)).cuda() if use_self else None)
     np.testing.assert_array_equal(gi.cpu().numpy(), ri)
     np.testing.assert_allclose(gd.cpu().numpy(), rd, rtol=1e-6)
+
+
+INSEPARABLE = [
+    # inputs of which the filter's bounds separate little: most queries are left to the
+    # exhaustive kernels
+    # name, n, d, m, what
+    ("two_far_clusters", 500_000, 64, 1000, "far"),
+    ("norms_past_1e37", 500_000, 64, 1000, "huge"),
+    ("fifty_distinct_rows", 500_000, 64, 1000, "fifty"),
+    ("ten_distinct_rows_64_queries", 200_000, 64, 64, "ten"),
+    ("some_queries", 300_000, 32, 500, "some"),  # a block's queries of both kinds
+]
+
+
+@pytest.mark.parametrize("case", INSEPARABLE, ids=[c[0] for c in INSEPARABLE])
+def test_filter_costs_little_where_it_separates_little(case):
+    """The filter's kernels take a fraction of the exhaustive kernels' time on such inputs (they
+    once listed a point at a time, each by an atomic, whatever the list could hold: up to 13
+    times the exhaustive kernels' time), and the results are theirs."""
+    from paper_1812_11689_amd import rpf
+    name, n, d, m, what = case
+    print(f"[exact] {name} n={n} d={d} m={m}", flush=True)
+    rng = np.random.default_rng(len(name))
+    K = 10
+    x = rng.standard_normal((n, d)).astype(np.float32)
+    if what == "far":
+        x *= np.float32(1e-3)
+        x[n // 2:] += np.float32(1e3)
+    elif what == "huge":
+        x *= np.float32(1e18)
+    elif what in ("fifty", "ten"):
+        x = np.ascontiguousarray(x[np.arange(n) % (50 if what == "fifty" else 10)])
+    else:
+        x[: n // 4] = x[0]
+    pts = np.sort(rng.choice(n, size=m, replace=False))
+    X, Q = torch.from_numpy(x).cuda(), torch.from_numpy(x[pts]).cuda()
+    rpf.exact_knn(X, Q, K)
+    torch.cuda.synchronize()
+    rpf.profile_enable(True)
+    rpf.profile_reset()
+    try:
+        gi, gd = rpf.exact_knn(X, Q, K)
+        torch.cuda.synchronize()
+        ms = {k: v["total_ms"] for k, v in rpf.profile_read().items()}
+    finally:
+        rpf.profile_enable(False)
+    print("   ", {k: round(v, 3) for k, v in ms.items()}, flush=True)
+    take = np.arange(0, m, max(1, m // 16))
+    ri, rd = oracle.bruteforce(x, x[pts[take]], K, None)
+    np.testing.assert_array_equal(gi.cpu().numpy()[take], ri)
+    np.testing.assert_allclose(gd.cpu().numpy()[take], rd, rtol=1e-6)
+    # a small share of the pairs' time, and 1 ms for the passes that every call makes
+    assert ms["exact_filter"] < 0.25 * (ms["exact_dist"] + ms["exact_select"]) + 1.0
