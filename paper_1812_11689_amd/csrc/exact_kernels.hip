@@ -315,6 +315,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kFiltCap = 4096;     // listed points of a query
 constexpr int kFiltQueue = 192;    // pairs a wave holds before it appends them to the lists
+constexpr int64_t kFiltBounds = (int64_t)1 << 30;  // bytes of the bounds to the sample
 constexpr float kFiltEta = 1e-33f;
 
 // mean of at most 512 rows (every stride-th), 64 columns per block
@@ -541,15 +542,17 @@ __global__ __launch_bounds__(512) void k_exact_tile(const __bf16 *__restrict__ Q
 // of which the sample says that far more points than a list holds would pass (repeated rows,
 // clusters far from the centre, norms that are no number) is left to the exhaustive kernels
 // here, before the tiles list thousands of its points for nothing: cnt above kFiltCap.
-__global__ __launch_bounds__(256) void k_exact_tau(const float *__restrict__ ub, int64_t ldS, int64_t S, int K,
+template <int NT>
+__global__ __launch_bounds__(NT) void k_exact_tau(const float *__restrict__ ub, int64_t ldS, int64_t S, int K,
                                                    const float *__restrict__ qn, float E,
                                                    const int64_t *__restrict__ self, int64_t n, int64_t stride,
                                                    const float *__restrict__ sn, float *__restrict__ phi,
                                                    uint32_t *__restrict__ cnt) {
     // 12-bit digits: sixteen bins per octave, so that one query's distances, which share their
     // exponents, do not all meet in one counter
+    constexpr int kBins = 4096 / NT;  // bins of a thread
     __shared__ uint32_t s_h[4096];
-    __shared__ uint32_t s_w[8];
+    __shared__ uint32_t s_w[NT / 64];
     __shared__ uint32_t s_sel[2];
     const uint32_t *row = reinterpret_cast<const uint32_t *>(ub + blockIdx.x * ldS);
     const int tid = threadIdx.x;
@@ -557,22 +560,23 @@ __global__ __launch_bounds__(256) void k_exact_tau(const float *__restrict__ ub,
     // the query's own row, where it is in the sample, bounds nothing
     const int64_t me = self && self[blockIdx.x] >= 0 && self[blockIdx.x] % stride == 0 ? self[blockIdx.x] / stride : -1;
     for (int b = 0; b < 2; b++) {
-        for (int i = tid; i < 4096; i += 256) s_h[i] = 0;
+        for (int i = tid; i < 4096; i += NT) s_h[i] = 0;
         if (tid == 0) s_sel[0] = 4096;
         __syncthreads();
         const int sh = 19 - 12 * b;
-        for (int64_t i = tid; i < S; i += 256) {
+#pragma unroll 4
+        for (int64_t i = tid; i < S; i += NT) {
             const uint32_t v = row[i];
             if (v < 0x7f800000u && i != me && (b == 0 || v >> 19 == prefix >> 19)) atomicAdd(&s_h[(v >> sh) & 4095u], 1u);
         }
         __syncthreads();
         uint32_t mine = 0;
 #pragma unroll
-        for (int i = 0; i < 16; i++) mine += s_h[16 * tid + i];
+        for (int i = 0; i < kBins; i++) mine += s_h[kBins * tid + i];
         uint32_t excl, total;
-        block_excl_scan256(mine, s_w, excl, total);
+        block_excl_scan_w<NT / 64>(mine, s_w, excl, total);
         if (excl <= rank && rank < excl + mine) {
-            int i = 16 * tid;
+            int i = kBins * tid;
             while (rank >= excl + s_h[i]) excl += s_h[i++];
             s_sel[0] = i;
             s_sel[1] = excl;
@@ -594,17 +598,17 @@ __global__ __launch_bounds__(256) void k_exact_tau(const float *__restrict__ ub,
     // sampled points by the tiles' test, (1 - E) nb - 2G from the upper bound: 32 runs of 16 points
     const float top = ph + (1.0f + E) * na;
     uint32_t pass = 0;
-#pragma unroll
-    for (int e = 0; e < 2; e++) {
-        const int64_t i = (16 * e + (tid >> 4)) * S / 32 + (tid & 15);
+    for (int e = tid; e < 512; e += NT) {
+        const int64_t i = (e >> 4) * S / 32 + (e & 15);
         const float u = i < S ? __uint_as_float(row[i]) : 0.f;
         if (i < S) pass += !(u < 3e38f) || !(u - 2.0f * E * sn[i] > top) ? 1u : 0u;
     }
     uint32_t excl, total;
-    block_excl_scan256(pass, s_w, excl, total);
+    block_excl_scan_w<NT / 64>(pass, s_w, excl, total);
     if (tid == 0) {
         phi[blockIdx.x] = ph;
-        cnt[blockIdx.x] = (int64_t)total * n > (int64_t)2 * kFiltCap * 512 ? kFiltCap + 1 : 0;
+        // (eight of 512 at least: of more points than 500 000 a few in the runs say little)
+        cnt[blockIdx.x] = total > 8 && (int64_t)total * n > (int64_t)2 * kFiltCap * 512 ? kFiltCap + 1 : 0;
     }
 }
 
@@ -733,8 +737,12 @@ void launch_tile(hipStream_t s, int QB, int d, int64_t m, const __bf16 *QF, cons
     launch_check(s, "k_exact_tile");
 }
 
-// The filtered search of all m queries.  False: its workspace could not be had (nothing was
-// launched).  over / n_over receive the queries left to the exhaustive kernels.
+// The filtered search of all m queries.  False: its workspace could not be had, or a sample that
+// its bounds' memory can hold would list too many points (nothing was launched).  over / n_over
+// receive the queries left to the exhaustive kernels.
+// Workspace: at most 2 GiB of the points' fragments, 1 GiB of bounds to the sample, 0.7 GiB of the
+// sample's fragments (a third of the points' at K 256; where the points pass through in slabs, so
+// does the sample), 0.5 GiB of lists and a little more.
 bool filtered_search(hipStream_t s, const float *X, int64_t n, int d, const float *Q, int64_t m, const int64_t *self,
                      int K, int32_t *out_idx, float *out_dist, int32_t *over, uint32_t *n_over) {
     const int KS = filt_ks(d), dp = 16 * KS;
@@ -742,20 +750,26 @@ bool filtered_search(hipStream_t s, const float *X, int64_t n, int d, const floa
     int QB = dp <= 256 ? 4 : dp <= 512 ? 2 : 1;
     while (QB > 1 && 16 * QB >= m) QB /= 2;
     // the sample: a query lists about K n / S points, with a relative spread of K^-1/2 (for a
-    // small K a long tail), so 768 of them, or 256 for K < 8, overflow a list about once in 1e6
-    const int64_t aim = K < 8 ? 256 : 768;
+    // small K a long tail), so 768 of them, or 256 for K < 8, overflow a list about once in 1e6.
+    // The bounds of at least 32 queries have to fit, so 2^23 rows at most; past 2 048 points a
+    // list (K n above 2^34) it would overflow too often to be of use.
+    const int64_t aim = K < 8 ? 256 : 768, most = kFiltBounds / (4 * 32);
     int64_t S = std::max<int64_t>((K * n + aim - 1) / aim, 16384);
-    int64_t stride = std::max<int64_t>(1, n / std::min(S, n));
+    int64_t stride = std::max<int64_t>(1, (n + S / 8) / std::min(S, n));
+    while ((n + stride - 1) / stride > most) stride++;
     S = (n + stride - 1) / stride;
+    if (K * n / S > 2048 && S < n) return false;
     const int64_t slab = std::min<int64_t>(n, std::max<int64_t>(32, (((int64_t)2 << 30) / (4 * dp)) & ~(int64_t)31));
-    const int64_t mq = std::min<int64_t>(m, std::max<int64_t>(128, std::min<int64_t>(16384, ((int64_t)1 << 28) / S) & ~(int64_t)127));
+    const int64_t rows = std::min<int64_t>(16384, kFiltBounds / (4 * S));
+    const int64_t mq = std::min<int64_t>(m, rows >= 128 ? rows & ~(int64_t)127 : rows >= 64 ? 64 : 32);
+    while (QB > 1 && 32 * QB > rows) QB /= 2;
     const int64_t qt = (mq + 32 * QB - 1) / (32 * QB) * QB;  // query tiles of 32, whole blocks
     struct { void *p; size_t bytes; } a[10] = {};
     enum { MU, SF, SN, PF, PN, QF, QN, PHI, CNT, CAND };
     void *sbuf = nullptr;
     auto frag = [&](int64_t tiles) { return (size_t)tiles * KS * 2048; };
     a[MU].bytes = 4 * (size_t)(dp + 64);
-    a[SF].bytes = frag((S + 31) / 32);
+    a[SF].bytes = slab < n ? 0 : frag((S + 31) / 32);
     a[SN].bytes = 128 * (size_t)((S + 31) / 32);
     a[PF].bytes = frag((slab + 31) / 32);
     a[PN].bytes = 128 * (size_t)((slab + 31) / 32);
@@ -765,35 +779,47 @@ bool filtered_search(hipStream_t s, const float *X, int64_t n, int d, const floa
     a[CNT].bytes = 4 * (size_t)mq;
     a[CAND].bytes = 8 * (size_t)mq * kFiltCap;
     bool ok = (sbuf = cache_alloc((size_t)qt * 32 * S * 4, s)) != nullptr;
-    for (auto &b : a) ok = ok && (b.p = cache_alloc(b.bytes, s)) != nullptr;
+    for (auto &b : a) ok = ok && (!b.bytes || (b.p = cache_alloc(b.bytes, s)) != nullptr);
     if (ok) {
         const float E = 1.2e-5f + (3.0f * dp + 32) * 1.3e-7f + 3e-6f;
         auto F = [&](int k) { return static_cast<float *>(a[k].p); };
         auto B = [&](int k) { return static_cast<__bf16 *>(a[k].p); };
         uint32_t *cnt = static_cast<uint32_t *>(a[CNT].p);
         uint2 *cand = static_cast<uint2 *>(a[CAND].p);
-        auto split = [&](const float *x, int64_t rows, int64_t st, int64_t tiles, int f, int nr) {
-            hipLaunchKernelGGL(k_exact_split, dim3((unsigned)tiles), dim3(256), 0, s, x, rows, d, st, F(MU), KS, B(f), F(nr));
+        auto split = [&](const float *x, int64_t left, int64_t st, int64_t tiles, int f, float *nr) {
+            hipLaunchKernelGGL(k_exact_split, dim3((unsigned)tiles), dim3(256), 0, s, x, left, d, st, F(MU), KS, B(f), nr);
             launch_check(s, "k_exact_split");
         };
         ProfScope ps(s, "exact_filter", 4.0 * n * d + 8.0 * m * K, 2.0 * m * n * d);
         hipLaunchKernelGGL(k_exact_centre, dim3((d + 63) / 64), dim3(1024), 0, s, X, n, d, std::max<int64_t>(1, n / 512), F(MU));
         launch_check(s, "k_exact_centre");
-        split(X, n, stride, (S + 31) / 32, SF, SN);
-        if (slab >= n) split(X, n, 1, (n + 31) / 32, PF, PN);
+        if (slab >= n) {
+            split(X, n, stride, (S + 31) / 32, SF, F(SN));
+            split(X, n, 1, (n + 31) / 32, PF, F(PN));
+        }
         const bool vec = d % 4 == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)Q % 16 == 0;
         for (int64_t q0 = 0; q0 < m; q0 += mq) {
             const int64_t nq = std::min(mq, m - q0);
             const int64_t *sc = self ? self + q0 : nullptr;
-            split(Q + q0 * d, nq, 1, qt, QF, QN);
-            launch_tile<0>(s, QB, d, nq, B(QF), F(QN), B(SF), F(SN), S, 0, E, nullptr, nullptr, nullptr,
-                           static_cast<float *>(sbuf), S);
-            hipLaunchKernelGGL(k_exact_tau, dim3((unsigned)nq), dim3(256), 0, s, static_cast<float *>(sbuf), S, S, K, F(QN),
-                               E, sc, n, stride, F(SN), F(PHI), cnt);
+            split(Q + q0 * d, nq, 1, qt, QF, F(QN));
+            for (int64_t s0 = 0; s0 < S; s0 += slab) {
+                const int64_t ns = std::min(slab, S - s0);
+                if (slab < n) split(X + s0 * stride * d, n - s0 * stride, stride, (ns + 31) / 32, PF, F(SN) + s0);
+                launch_tile<0>(s, QB, d, nq, B(QF), F(QN), B(slab < n ? PF : SF), F(SN) + s0, ns, 0, E, nullptr, nullptr,
+                               nullptr, static_cast<float *>(sbuf) + s0, S);
+            }
+            // a large sample, of which few queries' bounds are held at once, takes 1024 threads a query
+            // (5 000 000 x 128, K 256: 8.5 -> 1.6 ms for 128 queries)
+            auto tau = [&](auto kern, int nt) {
+                hipLaunchKernelGGL(kern, dim3((unsigned)nq), dim3(nt), 0, s, static_cast<float *>(sbuf), S, S, K, F(QN), E, sc,
+                                   n, stride, F(SN), F(PHI), cnt);
+            };
+            if (S >= 65536) tau(k_exact_tau<1024>, 1024);
+            else tau(k_exact_tau<256>, 256);
             launch_check(s, "k_exact_tau");
             for (int64_t p0 = 0; p0 < n; p0 += slab) {
                 const int64_t np = std::min(slab, n - p0);
-                if (slab < n) split(X + p0 * d, np, 1, (np + 31) / 32, PF, PN);
+                if (slab < n) split(X + p0 * d, np, 1, (np + 31) / 32, PF, F(PN));
                 launch_tile<1>(s, QB, d, nq, B(QF), F(QN), B(PF), F(PN), np, p0, E, F(PHI), cnt, cand, nullptr, 0);
             }
             auto rank = [&](auto kern) {
@@ -839,7 +865,7 @@ extern "C" rpf_status rpf_exact_knn(const float *X, int64_t n, int32_t d, const 
         if (h[0] || h[1]) return fail(RPF_EINVAL, "rpf_exact_knn: X or Q holds NaN or Inf");
     }
     // queries of a distance block (a multiple of 8, LDS within 64 KiB), and per chunk: the
-    // distance buffer stays within 4 GiB (at least one block of queries)
+    // distance buffer stays within 4 GiB (at least eight queries)
     const int dq = (d + 31) & ~31;
     const int ql = std::max(8, std::min(kQL, 16384 / dq / 8 * 8));
     const size_t lds = (size_t)ql * dq * 4;
@@ -848,7 +874,7 @@ extern "C" rpf_status rpf_exact_knn(const float *X, int64_t n, int32_t d, const 
     // 128, 64 queries 0.21 against 0.20, 256 queries 0.23 against 0.28; 100 000 x 128, 1 query
     // 0.23 against 0.28); rows above 1 024 columns do not fit a block's LDS
     int32_t *over = nullptr;
-    if ((n >= 65536 || (m >= 128 && n * m >= 1000000)) && d <= 1024 && m < ((int64_t)1 << 31)) {
+    if (m < ((int64_t)1 << 31) && d <= 1024 && (n >= 65536 || (m >= 128 && n * m >= 1000000))) {
         over = static_cast<int32_t *>(cache_alloc((size_t)(m + 4) * 4, s));
         if (over) {
             fill_u32(reinterpret_cast<uint32_t *>(over), 4, 0, s);
@@ -858,8 +884,9 @@ extern "C" rpf_status rpf_exact_knn(const float *X, int64_t n, int32_t d, const 
             }
         }
     }
-    const int64_t chunk = std::max<int64_t>(ql, std::min<int64_t>(((int64_t)1 << 29) / n / ql * ql, m));
-    double *Dbuf = static_cast<double *>(cache_alloc((size_t)std::min(chunk, m) * n * 8, s));
+    int64_t chunk = ((int64_t)1 << 29) / n;
+    chunk = std::min(m, chunk >= ql ? chunk / ql * ql : std::max<int64_t>(8, chunk & ~(int64_t)7));
+    double *Dbuf = static_cast<double *>(cache_alloc((size_t)chunk * n * 8, s));
     if (!Dbuf) {
         if (over) cache_free(over, s);
         return fail(RPF_ENOMEM, "rpf_exact_knn: distance buffer allocation failed");

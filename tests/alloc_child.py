@@ -1,0 +1,70 @@
+"""One case of the allocation tests, in a process of its own whose HIP allocation calls pass
+through tests/hip_shim.cpp: python alloc_child.py SHIM CASE."""
+
+import ctypes
+import os
+import sys
+
+SHIM = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)  # before anything that uses the runtime
+for _name, _res in (("shim_live", ctypes.c_size_t), ("shim_peak", ctypes.c_size_t), ("shim_calls", ctypes.c_long)):
+    getattr(SHIM, _name).restype = _res
+SHIM.shim_limit.argtypes = [ctypes.c_size_t]
+NO_LIMIT = ctypes.c_size_t(-1).value
+
+sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+
+import torch  # noqa: E402
+
+from paper_1812_11689_amd import rpf  # noqa: E402
+
+
+def calls():
+    return tuple(SHIM.shim_calls(k) for k in range(4))
+
+
+def library_peak(fn):
+    """fn's result, and the bytes of device memory the library took for it at most."""
+    rpf.release_cached_memory()
+    torch.cuda.synchronize()
+    before = SHIM.shim_live()
+    SHIM.shim_peak(1)
+    r = fn()
+    torch.cuda.synchronize()
+    return r, SHIM.shim_peak(1) - before
+
+
+def case_shim():
+    """The library's allocations pass through the shim (else the other cases prove nothing)."""
+    before = calls()
+    rpf.release_cached_memory()
+    x = torch.randn(1000, 8, device="cuda")
+    rpf.exact_knn(x, x[:4], 3)
+    torch.cuda.synchronize()
+    assert calls()[0] > before[0]
+    SHIM.shim_limit(0)
+    rpf.release_cached_memory()
+    try:
+        rpf.exact_knn(x, x[:4], 3, None)
+        raise SystemExit("an exact search without any memory")
+    except rpf.RpfError as e:
+        assert e.status == rpf.RPF_ENOMEM, e
+    SHIM.shim_limit(NO_LIMIT)
+
+
+def case_exact_workspace():
+    """rpf_exact_knn's workspace stays within what rpf.h states, for a deep result list over
+    many points too (the sample, and the bounds to it, grow with K n)."""
+    n, d, m, K = 20_000_000, 4, 128, 256
+    x = torch.randn(n, d, device="cuda")
+    q = x[:m].clone()
+    out = (torch.empty(m, K, dtype=torch.int32, device="cuda"), torch.empty(m, K, device="cuda"))
+    torch.cuda.synchronize()
+    (i, _), peak = library_peak(lambda: rpf.exact_knn(x, q, K))
+    del out
+    print(f"n={n} m={m} K={K}: {peak / 2**30:.2f} GiB", flush=True)
+    assert bool((i[:, 0] == torch.arange(m, device="cuda")).all())
+    assert peak <= (9 << 30), f"{peak} bytes"  # the filter's 4.5 GiB and the distance rows' 4
+
+
+globals()["case_" + sys.argv[2]]()
+print("done", flush=True)

@@ -157,3 +157,44 @@ def test_filter_costs_little_where_it_separates_little(case):
     np.testing.assert_allclose(gd.cpu().numpy()[take], rd, rtol=1e-6)
     # a small share of the pairs' time, and 1 ms for the passes that every call makes
     assert ms["exact_filter"] < 0.25 * (ms["exact_dist"] + ms["exact_select"]) + 1.0
+
+
+@pytest.mark.parametrize("use_self", [False, True], ids=["queries", "own_rows"])
+def test_filter_takes_queries_in_chunks(use_self):
+    """More queries than a chunk of the filter (16 384): the second chunk's outputs, own rows and
+    exhaustive queries."""
+    from paper_1812_11689_amd import rpf
+    n, d, m, K = 9000, 4, 16_500, 5
+    print(f"[exact] n={n} m={m} self={use_self}", flush=True)
+    rng = np.random.default_rng(71)
+    x = rng.standard_normal((n, d)).astype(np.float32)
+    x[:6000] = x[5]  # more equal distances than a list holds
+    pts = rng.integers(0, n, m)
+    pts[16_384:16_450] = 5999 - np.arange(66)
+    ri, rd = oracle.bruteforce(x, x[pts], K, pts if use_self else None)
+    gi, gd = rpf.exact_knn(torch.from_numpy(x).cuda(), torch.from_numpy(x[pts]).cuda(), K,
+                           torch.from_numpy(pts.astype(np.int64)).cuda() if use_self else None)
+    np.testing.assert_array_equal(gi.cpu().numpy(), ri)
+    np.testing.assert_allclose(gd.cpu().numpy(), rd, rtol=1e-6)
+
+
+def test_filter_takes_points_in_slabs():
+    """More points than the fragments' 2 GiB hold (524 288 rows of 1 024): the second slab's
+    points and sample."""
+    from paper_1812_11689_amd import rpf
+    n, d, K = 524_400, 1024, 6
+    print(f"[exact] n={n} d={d}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(72)
+    x = torch.randn(n, d, generator=g, device="cuda")
+    at = torch.tensor([0, 1, 262_143, 524_287, 524_288, 524_290, 524_399, 100], device="cuda")
+    x[524_300:524_360] = x[100] + 0.01 * torch.randn(60, d, generator=g, device="cuda")
+    q = x[at] + 0.001 * torch.randn(len(at), d, generator=g, device="cuda")
+    gi, gd = rpf.exact_knn(x, q, K)
+    dist = torch.empty(len(at), n, dtype=torch.float64, device="cuda")
+    for s in range(0, n, 1 << 16):
+        xs = x[s:s + (1 << 16)].double()
+        for r in range(len(at)):
+            dist[r, s:s + (1 << 16)] = (xs - q[r].double()).square().sum(1)
+    rd, ri = dist.sort(dim=1, stable=True)
+    assert torch.equal(gi.long(), ri[:, :K])
+    np.testing.assert_allclose(gd.cpu().numpy(), rd[:, :K].sqrt().cpu().numpy(), rtol=1e-6)
