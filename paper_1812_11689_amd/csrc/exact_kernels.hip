@@ -886,7 +886,12 @@ extern "C" rpf_status rpf_exact_knn(const float *X, int64_t n, int32_t d, const 
     }
     int64_t chunk = ((int64_t)1 << 29) / n;
     chunk = std::min(m, chunk >= ql ? chunk / ql * ql : std::max<int64_t>(8, chunk & ~(int64_t)7));
+    // (after the filter it is usually not read: the answer must not fail for it)
     double *Dbuf = static_cast<double *>(cache_alloc((size_t)chunk * n * 8, s));
+    while (!Dbuf && over && chunk > 1) {
+        chunk = (chunk + 1) / 2;
+        Dbuf = static_cast<double *>(cache_alloc((size_t)chunk * n * 8, s));
+    }
     if (!Dbuf) {
         if (over) cache_free(over, s);
         return fail(RPF_ENOMEM, "rpf_exact_knn: distance buffer allocation failed");

@@ -66,5 +66,33 @@ def case_exact_workspace():
     assert peak <= (9 << 30), f"{peak} bytes"  # the filter's 4.5 GiB and the distance rows' 4
 
 
+def case_exact_answer_without_distance_rows():
+    """A search that the filter answers does not fail for the exhaustive kernels' buffer."""
+    n, d, m, K = 1_000_000, 16, 600, 10
+    x = torch.randn(n, d, device="cuda")
+    q = x[:m].clone()
+    want = rpf.exact_knn(x, q, K)
+    torch.cuda.synchronize()
+    rpf.release_cached_memory()
+    SHIM.shim_limit(1 << 30)
+    refused = calls()[3]
+    got = rpf.exact_knn(x, q, K)
+    torch.cuda.synchronize()
+    SHIM.shim_limit(NO_LIMIT)
+    assert calls()[3] > refused
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    # and queries left to those kernels get theirs from the rows that could be had
+    x[: n // 2] = x[0]
+    q = x[:m].clone()
+    want = rpf.exact_knn(x, q, K)
+    torch.cuda.synchronize()
+    rpf.release_cached_memory()
+    SHIM.shim_limit(200 << 20)
+    got = rpf.exact_knn(x, q, K)
+    torch.cuda.synchronize()
+    SHIM.shim_limit(NO_LIMIT)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
 globals()["case_" + sys.argv[2]]()
 print("done", flush=True)
