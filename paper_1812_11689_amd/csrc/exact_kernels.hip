@@ -635,7 +635,7 @@ __global__ __launch_bounds__(256) void k_exact_rank(const float *__restrict__ X,
         return;
     }
     const uint2 *list = cand + q * kFiltCap;
-    const uint32_t me = self && self[q] >= 0 ? (uint32_t)self[q] : ~0u;
+    const int64_t me = self ? self[q] : -1;
     // 15 bits of the upper bound: twelve, then three
     uint32_t lim = 0x7f80u, rank = (uint32_t)K - 1;
     for (int i = tid; i < 4096; i += 256) s_h[i] = 0;
@@ -643,7 +643,7 @@ __global__ __launch_bounds__(256) void k_exact_rank(const float *__restrict__ X,
     if (tid == 0) s_sel[0] = ~0u;
     __syncthreads();
     for (uint32_t i = tid; i < c; i += 256)
-        if (list[i].x != me) atomicAdd(&s_h[list[i].y >> 19], 1u);
+        if ((int64_t)list[i].x != me) atomicAdd(&s_h[list[i].y >> 19], 1u);
     __syncthreads();
     {
         uint32_t mine = 0;
@@ -665,7 +665,7 @@ __global__ __launch_bounds__(256) void k_exact_rank(const float *__restrict__ X,
         if (tid < 8) s_h[tid] = 0;
         __syncthreads();
         for (uint32_t i = tid; i < c; i += 256)
-            if (list[i].x != me && list[i].y >> 19 == bin) atomicAdd(&s_h[(list[i].y >> 16) & 7u], 1u);
+            if ((int64_t)list[i].x != me && list[i].y >> 19 == bin) atomicAdd(&s_h[(list[i].y >> 16) & 7u], 1u);
         __syncthreads();
         rank -= s_sel[1];
         int i = 0;
@@ -675,7 +675,7 @@ __global__ __launch_bounds__(256) void k_exact_rank(const float *__restrict__ X,
     __syncthreads();
     for (uint32_t i = tid; i < c; i += 256) {  // (any order: the sort decides)
         const uint2 r = list[i];
-        if (r.x != me && (r.y & 0xffffu) <= lim) s_lo[atomicAdd(&s_sel[2], 1u)] = r.x;
+        if ((int64_t)r.x != me && (r.y & 0xffffu) <= lim) s_lo[atomicAdd(&s_sel[2], 1u)] = r.x;
     }
     __syncthreads();
     const int nr = (int)s_sel[2];

@@ -198,3 +198,15 @@ def test_filter_takes_points_in_slabs():
     rd, ri = dist.sort(dim=1, stable=True)
     assert torch.equal(gi.long(), ri[:, :K])
     np.testing.assert_allclose(gd.cpu().numpy(), rd[:, :K].sqrt().cpu().numpy(), rtol=1e-6)
+
+
+def test_own_rows_outside_the_points_leave_nothing_out():
+    from paper_1812_11689_amd import rpf
+    n, d, m, K = 66_000, 8, 40, 6
+    print(f"[exact] own rows outside [0, n): n={n}", flush=True)
+    x = torch.randn(n, d, generator=torch.Generator(device="cuda").manual_seed(73), device="cuda")
+    own = torch.arange(m, device="cuda")
+    for shift in (n, 1 << 32, -(1 << 32)):  # the last two are the row's own index in 32 bits
+        gi, gd = rpf.exact_knn(x, x[:m].clone(), K, own + shift)
+        ri, rd = rpf.exact_knn(x, x[:m].clone(), K)
+        assert torch.equal(gi, ri) and torch.equal(gd, rd)
