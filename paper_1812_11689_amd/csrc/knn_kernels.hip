@@ -3248,7 +3248,8 @@ __global__ __launch_bounds__(256) void k_qdirect(const float *__restrict__ Q, in
 
 // A pending input check: an event behind the routing launch and a pinned word it sets.  Kept
 // in a pool (one word each of one pinned page for the process), a pair per call in flight; a
-// call that finds none takes the grouped path.
+// call that finds none takes the grouped path.  A build makes a device's first pair, so that
+// rpf_query_noalloc, which may not make one, has it.
 struct CheckSlot {
     hipEvent_t ev = nullptr;
     int32_t *flag = nullptr;
@@ -3259,17 +3260,10 @@ static std::mutex g_check_mu;
 static std::vector<CheckSlot> g_check_idle;
 static int32_t *g_check_page = nullptr;
 static int g_check_made = 0;
+static uint64_t g_check_devs = 0;  // devices (below 64) that have one
 
-static bool check_take(CheckSlot &c) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return false;
-    std::lock_guard<std::mutex> lk(g_check_mu);
-    for (size_t i = 0; i < g_check_idle.size(); i++)
-        if (g_check_idle[i].dev == dev) {
-            c = g_check_idle[i];
-            g_check_idle.erase(g_check_idle.begin() + (long)i);
-            return true;
-        }
+// (the mutex is held)
+static bool check_make(CheckSlot &c, int dev) {
     if (g_check_made >= kCheckSlots) return false;
     if (!g_check_page) {
         void *p = nullptr;
@@ -3286,8 +3280,30 @@ static bool check_take(CheckSlot &c) {
     }
     n.flag = g_check_page + 16 * g_check_made++;
     n.dev = dev;
+    if (dev < 64) g_check_devs |= (uint64_t)1 << dev;
     c = n;
     return true;
+}
+
+static bool check_take(CheckSlot &c, bool may_make) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    std::lock_guard<std::mutex> lk(g_check_mu);
+    for (size_t i = 0; i < g_check_idle.size(); i++)
+        if (g_check_idle[i].dev == dev) {
+            c = g_check_idle[i];
+            g_check_idle.erase(g_check_idle.begin() + (long)i);
+            return true;
+        }
+    return may_make && check_make(c, dev);
+}
+
+void check_prepare() {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev >= 64) return;
+    std::lock_guard<std::mutex> lk(g_check_mu);
+    CheckSlot c;
+    if (!(g_check_devs >> dev & 1) && check_make(c, dev)) g_check_idle.push_back(c);
 }
 
 static void check_give(const CheckSlot &c) {
@@ -3957,7 +3973,8 @@ static rpf_status knn_direct(const ForestView &v, const CheckSlot &chk, const fl
 
 // The query search with every device buffer taken from `get` (device bytes, nullptr =
 // failure): the library's cache (knn_query) or a fixed scratch area (rpf_query_noalloc).
-// may_copy: the forest's leaf copies may be made (allocated) here on its first query.
+// may_copy: the forest's leaf copies may be made (allocated) here on its first query, and an
+// input check's event and word.
 template <typename Get>
 static rpf_status knn_query_get(const rpf_forest *f, const float *Q, int64_t m, int K, int32_t *out_idx,
                                 float *out_dist, hipStream_t s, Get get, bool may_copy) {
@@ -3969,7 +3986,7 @@ static rpf_status knn_query_get(const rpf_forest *f, const float *Q, int64_t m, 
     // one query to two leaves at most: pairs rather than groups (the rows of a leaf are shared by
     // too few queries to pay for sorting them); rows above 512 columns take the MFMA tiles
     CheckSlot chk;
-    if (2 * m <= v.nleaf && v.dp <= 512 && !capturing(s) && check_take(chk)) {
+    if (2 * m <= v.nleaf && v.dp <= 512 && !capturing(s) && check_take(chk, may_copy)) {
         const rpf_status st = knn_direct(v, chk, Q, m, K, out_idx, out_dist, s, get);
         check_give(chk);
         return st;

@@ -1139,6 +1139,7 @@ static rpf_status build_impl(const float *X, const int64_t *sizes, int count, in
         fail(RPF_EDEVICE, "rpf_build: " + le);
         return bail(RPF_EDEVICE);
     }
+    check_prepare();
     *out = f;
     return RPF_OK;
 }

@@ -219,6 +219,8 @@ void fill_u64(void *p, int64_t count, uint64_t value, hipStream_t s);
 // all-points search of leaves that fit one tile stages its rows from X instead)
 // (may_make = false: RPF_ENOTREADY instead of allocating them when they do not exist yet)
 rpf_status ensure_leaf_copies(const rpf_forest *f, hipStream_t s, bool may_make = true);
+// makes what a query's input check waits on, where this device has none yet
+void check_prepare();
 // copies tree 0's all-points tiles (jobs[0, njt)) to trees 1 .. T - 1
 void replicate_jobs(TileJob *jobs, int64_t njt, int T, hipStream_t s);
 int64_t forest_points(const rpf_forest *f);

@@ -94,5 +94,41 @@ def case_exact_answer_without_distance_rows():
     assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
 
 
+def case_noalloc():
+    """rpf_query_noalloc allocates nothing: no device block, no host memory, no event, not on a
+    process's first call either (leaves above 256 points: their query copies come with the
+    build)."""
+    import threading
+    n, d, T, n0, K = 20_000, 16, 4, 400, 5
+    x = torch.randn(n, d, device="cuda")
+    R = torch.randn(T, 2 ** rpf.depth(n, n0) - 1, 1, d, device="cuda")
+    f = rpf.build(x, T, n0, R, dist_prec="bf16")
+    q = [x[i:i + m].contiguous() for i, m in ((0, 1), (5, 20), (40, 700))]  # pair by pair; grouped
+    o = [(torch.empty(len(v), K, dtype=torch.int32, device="cuda"), torch.empty(len(v), K, device="cuda")) for v in q]
+    torch.cuda.synchronize()
+    before = calls()
+    for v, w in zip(q, o):
+        f.query_noalloc(v, K, w)
+    torch.cuda.synchronize()
+    after = calls()
+    assert after == before, (before, after)
+    for v, w in zip(q, o):
+        i, dist = f.query(v, K)
+        assert torch.equal(i, w[0]) and torch.equal(dist, w[1])
+    # beside other threads' queries, which may hold the event
+    def other():
+        for _ in range(200):
+            f.query(q[1], K)
+    th = threading.Thread(target=other)
+    torch.cuda.synchronize()
+    th.start()
+    for _ in range(200):
+        f.query_noalloc(q[1], K, o[1])
+    th.join()
+    torch.cuda.synchronize()
+    i, dist = f.query(q[1], K)
+    assert torch.equal(i, o[1][0]) and torch.equal(dist, o[1][1])
+
+
 globals()["case_" + sys.argv[2]]()
 print("done", flush=True)
