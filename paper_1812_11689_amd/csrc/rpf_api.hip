@@ -511,8 +511,11 @@ rpf_status rpf_free(rpf_forest *f) {
 // with hbase_i = sum over j < i of (2^L_j - 1): the direction and split arrays are
 // [T][sum H_i] and the kernels index them as for one tree.  Leaf h of data set i has the id
 // lbase_i + h, lbase_i = sum over j < i of 2^(L_j + 1), in leaf_of and in the leaf table.
+// try_bytes: what the projections of several tries may take at once (0: those of one try, and
+// only in forests with multi-block levels; a caller that ran out of memory tries this).
+constexpr int64_t kTryBytes = (int64_t)4 << 30;
 static rpf_status prepare_forest(const int64_t *sizes, int count, int32_t d, const rpf_params *p, void *stream,
-                                 rpf_forest **out, bool need_directions = true) {
+                                 rpf_forest **out, bool need_directions = true, int64_t try_bytes = kTryBytes) {
     if (out) *out = nullptr;
     if (!out) return fail(RPF_EINVAL, "rpf_build: out is NULL");
     if (!p) return fail(RPF_EINVAL, "rpf_build: params is NULL");
@@ -697,7 +700,7 @@ static rpf_status prepare_forest(const int64_t *sizes, int count, int32_t d, con
     }
     if (any_link) tmp_bytes += (uint64_t)T * n * (16 + 8);                    // ahead, keys2
     // levels that score tries over many blocks: the projections of `try_group` tries at once
-    // (all of them where they fit 4 GiB and the budget), the sums' partials in the norms array
+    // (all of them where they fit try_bytes and the budget), the sums' partials in the norms array
     // (written after the last level) where they fit it.  A budget that holds no projections
     // beside a forest without multi-block levels leaves the scoring to k_level_small.
     int try_group = 0;
@@ -720,9 +723,11 @@ static rpf_status prepare_forest(const int64_t *sizes, int count, int32_t d, con
             const uint64_t praw = (uint64_t)G * T * n * 8, keys = max_seg_large > 0 ? 0 : (uint64_t)T * n * 8;
             return praw + keys + (scratch(G) > (uint64_t)T * n * 8 ? scratch(G) : 0);
         };
+        if (!try_bytes)
+            for (auto &lv : levels) lv.tries = lv.large;
         scan();
         try_group = std::min(n_try, 16);
-        while (try_group > 1 && (uint64_t)try_group * T * n * 8 > ((uint64_t)4 << 30)) try_group--;
+        while (try_group > 1 && (uint64_t)try_group * T * n * 8 > (uint64_t)try_bytes) try_group--;
         if (p->mem_budget_bytes) {
             while (try_group > 1 && bytes + tmp_bytes + need(try_group) > p->mem_budget_bytes) try_group--;
             if (bytes + tmp_bytes + need(try_group) > p->mem_budget_bytes) {
@@ -1103,6 +1108,7 @@ static rpf_status build_impl(const float *X, const int64_t *sizes, int count, in
     if (!X) return fail(RPF_EINVAL, "rpf_build: X is NULL");
     rpf_forest *f = nullptr;
     rpf_status st = prepare_forest(sizes, count, d, p, stream, &f);
+    if (st == RPF_ENOMEM && p->n_try > 1) st = prepare_forest(sizes, count, d, p, stream, &f, true, 0);
     if (st != RPF_OK) return st;
     hipStream_t s = (hipStream_t)stream;
     auto bail = [&](rpf_status e) {
@@ -1787,8 +1793,10 @@ static rpf_status plan_record(rpf_plan *pl) {
 
 extern "C" {
 
-rpf_status rpf_plan_create(const int64_t *n_host, const int32_t *d_host, int32_t count, const rpf_params *p, int32_t K,
-                           int32_t exclude_self, int64_t max_part_points, void *stream, rpf_plan **out) {
+// try_bytes: of all parts, which keep their temporaries (see prepare_forest)
+static rpf_status plan_create(const int64_t *n_host, const int32_t *d_host, int32_t count, const rpf_params *p, int32_t K,
+                              int32_t exclude_self, int64_t max_part_points, void *stream, rpf_plan **out,
+                              int64_t try_bytes) {
     if (out) *out = nullptr;
     if (!out || !n_host || !d_host || !p || count < 1)
         return fail(RPF_EINVAL, "rpf_plan_create: NULL pointer or count < 1");
@@ -1829,7 +1837,8 @@ rpf_status rpf_plan_create(const int64_t *n_host, const int32_t *d_host, int32_t
         std::vector<int64_t> sizes;
         for (int i : pt.sets) sizes.push_back(n_host[i]);
         const int32_t d = d_host[pt.sets[0]];
-        rpf_status st = prepare_forest(sizes.data(), (int)sizes.size(), d, p, stream, &pt.f, false);
+        rpf_status st = prepare_forest(sizes.data(), (int)sizes.size(), d, p, stream, &pt.f, false,
+                                       try_bytes / (int64_t)pl->parts.size());
         if (st != RPF_OK) {
             plan_free(pl);
             return st;
@@ -1883,6 +1892,14 @@ rpf_status rpf_plan_create(const int64_t *n_host, const int32_t *d_host, int32_t
     }
     *out = pl;
     return RPF_OK;
+}
+
+rpf_status rpf_plan_create(const int64_t *n_host, const int32_t *d_host, int32_t count, const rpf_params *p, int32_t K,
+                           int32_t exclude_self, int64_t max_part_points, void *stream, rpf_plan **out) {
+    rpf_status st = plan_create(n_host, d_host, count, p, K, exclude_self, max_part_points, stream, out, kTryBytes);
+    if (st == RPF_ENOMEM && p->n_try > 1)
+        st = plan_create(n_host, d_host, count, p, K, exclude_self, max_part_points, stream, out, 0);
+    return st;
 }
 
 rpf_status rpf_plan_info(const rpf_plan *pl, int32_t *n_parts, int32_t *count) {

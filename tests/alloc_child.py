@@ -8,7 +8,7 @@ import sys
 SHIM = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)  # before anything that uses the runtime
 for _name, _res in (("shim_live", ctypes.c_size_t), ("shim_peak", ctypes.c_size_t), ("shim_calls", ctypes.c_long)):
     getattr(SHIM, _name).restype = _res
-SHIM.shim_limit.argtypes = [ctypes.c_size_t]
+SHIM.shim_limit.argtypes = SHIM.shim_total.argtypes = [ctypes.c_size_t]
 NO_LIMIT = ctypes.c_size_t(-1).value
 
 sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
@@ -128,6 +128,55 @@ def case_noalloc():
     torch.cuda.synchronize()
     i, dist = f.query(q[1], K)
     assert torch.equal(i, o[1][0]) and torch.equal(dist, o[1][1])
+
+
+def case_tries():
+    """Several tries per node where the device cannot hold the projections of all of them at once,
+    or of any: the same forest, from fewer at a time."""
+    for n, d, T, n0, n_try, limit in ((200_000, 4, 16, 64, 16, 100 << 20), (3000, 4, 64, 20, 10, 5 << 20)):
+        x = torch.randn(n, d, device="cuda")
+        R = torch.randn(T, 2 ** rpf.depth(n, n0) - 1, n_try, d, device="cuda")
+        dumps = []
+        for lim in (NO_LIMIT, limit):
+            torch.cuda.synchronize()
+            rpf.release_cached_memory()
+            SHIM.shim_limit(lim)
+            refused = calls()[3]
+            f = rpf.build(x, T, n0, R, n_try=n_try)
+            torch.cuda.synchronize()
+            SHIM.shim_limit(NO_LIMIT)
+            assert (calls()[3] > refused) == (lim == limit)
+            dumps.append([f.tree_dump(t) for t in range(T)])
+            f.free()
+        for a, b in zip(*dumps):
+            for k in ("perm", "chosen", "split_idx"):
+                assert torch.equal(a[k], b[k]), k
+        print(f"n={n}: as with all tries at once", flush=True)
+
+
+def case_plan_tries():
+    """The same for the parts of a plan, which keep their temporaries: 4 GiB over all parts."""
+    sizes, T, n0, n_try = [60_000, 50_000, 3000], 16, 64, 16
+    xs = [torch.randn(n, 4, device="cuda") for n in sizes]
+    Rs = [torch.randn(T, 2 ** rpf.depth(n, n0) - 1, n_try, 4, device="cuda") for n in sizes]
+    got = []
+    for short in (False, True):
+        torch.cuda.synchronize()
+        rpf.release_cached_memory()
+        if short:  # the projections of all tries take 230 MB of `peak`, those of one 15
+            SHIM.shim_total(SHIM.shim_live() + peak - (100 << 20))
+        refused = calls()[3]
+        plan, p = library_peak(lambda: rpf.Plan(sizes, 4, T, n0, 5, n_try=n_try, max_part_points=60_000))
+        peak = p
+        SHIM.shim_total(NO_LIMIT)
+        assert (calls()[3] > refused) == short
+        plan.set_inputs(xs, Rs)
+        plan.launch()
+        plan.check()
+        got.append([tuple(v.clone() for v in plan.result(i)) for i in range(len(sizes))])
+        plan.close()
+    for a, b in zip(*got):
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
 
 
 globals()["case_" + sys.argv[2]]()

@@ -1,6 +1,6 @@
 // Stands between the library and the HIP runtime in a child process of the allocation tests
-// (tests/alloc_child.py): counts the calls that allocate and refuses device blocks above a
-// limit, as a device without that much free memory does.  Loaded with RTLD_GLOBAL before
+// (tests/alloc_child.py): counts the calls that allocate and refuses device blocks above
+// limits, as a device without that much free memory does.  Loaded with RTLD_GLOBAL before
 // anything that uses the runtime, so that its names are found first.
 #include <dlfcn.h>
 #include <link.h>
@@ -15,7 +15,7 @@
 namespace {
 
 std::atomic<long> g_calls[4];  // hipMalloc, hipHostMalloc, hipEventCreateWithFlags, refused
-std::atomic<size_t> g_limit{~(size_t)0};
+std::atomic<size_t> g_limit{~(size_t)0}, g_total{~(size_t)0};
 std::mutex g_mu;
 std::map<void *, size_t> g_live;
 size_t g_bytes = 0, g_peak = 0;
@@ -47,7 +47,12 @@ extern "C" {
 int hipMalloc(void **p, size_t bytes) {
     static auto f = real<int (*)(void **, size_t)>("hipMalloc");
     g_calls[0]++;
-    if (bytes > g_limit) {
+    bool full;
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        full = bytes > g_limit || bytes > g_total - (g_bytes < g_total ? g_bytes : g_total.load());
+    }
+    if (full) {
         g_calls[3]++;
         return 2;  // hipErrorOutOfMemory
     }
@@ -86,7 +91,8 @@ int hipEventCreateWithFlags(void **e, unsigned flags) {
     return f(e, flags);
 }
 
-void shim_limit(size_t bytes) { g_limit = bytes; }
+void shim_limit(size_t bytes) { g_limit = bytes; }    // of one block
+void shim_total(size_t bytes) { g_total = bytes; }    // of all blocks
 long shim_calls(int k) { return g_calls[k]; }
 size_t shim_live(void) {
     std::lock_guard<std::mutex> lk(g_mu);

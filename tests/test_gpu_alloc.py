@@ -10,7 +10,8 @@ import pytest
 pytestmark = pytest.mark.gpu
 HERE = os.path.dirname(os.path.abspath(__file__))
 
-CASES = ["shim", "noalloc", "exact_workspace", "exact_answer_without_distance_rows"]
+CASES = ["shim", "noalloc", "exact_workspace", "exact_answer_without_distance_rows", "tries",
+         "plan_tries"]
 
 
 @pytest.fixture(scope="module")
