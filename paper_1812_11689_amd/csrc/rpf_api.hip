@@ -1247,7 +1247,7 @@ static rpf_status build_uniform(const float *X, int64_t n, int32_t d, const rpf_
                      (uint64_t)lseg_cap * (sizeof(UniSeg) + sizeof(UniSplit) + n_try * 8);
     const int64_t nb = (n >> 8) + 1;  // position ranges of a tree's records
     const size_t ctr_words = 16 + 2 * (size_t)(T * nb + 1);
-    const uint64_t grow_bytes = (uint64_t)blk_cap * sizeof(UniSeg) + ctr_words * 4 + (uint64_t)T * (sizeof(UniTree) + 8);
+    const uint64_t grow_bytes = (uint64_t)blk_cap * sizeof(UniSeg) + ctr_words * 4 + (uint64_t)T * uni_leaf_parts(n, (int)T) * (sizeof(UniTree) + sizeof(UniPart));
     device_growth &= !p->mem_budget_bytes || bytes + tmp_bytes + grow_bytes <= p->mem_budget_bytes;
     if (p->mem_budget_bytes && bytes + tmp_bytes > p->mem_budget_bytes)
         return fail(RPF_ENOMEM, "rpf_build: forest needs " + std::to_string(bytes + tmp_bytes) +
@@ -1358,7 +1358,8 @@ static rpf_status build_uniform(const float *X, int64_t n, int32_t d, const rpf_
     std::vector<std::vector<rpf_node>> tnodes(T);
     std::vector<UniSeg> to_block, to_wave, closed;
     std::vector<UniRec> recs;
-    std::vector<UniTree> totals(T);
+    const int parts = uni_leaf_parts(n, (int)T);  // ranges of a tree's positions
+    std::vector<UniTree> totals(T * parts);
     int max_depth = 0;
     auto close_leaf = [&](const Open &o) {
         if (device_growth) closed.push_back(UniSeg{o.pos, o.heap, o.size, o.tree, o.depth, 0});
@@ -1481,7 +1482,7 @@ static rpf_status build_uniform(const float *X, int64_t n, int32_t d, const rpf_
         if (!to_wave.empty()) hipMemcpyAsync(d_seg, to_wave.data(), to_wave.size() * sizeof(UniSeg), hipMemcpyHostToDevice, s);
         if (!recs.empty()) hipMemcpyAsync(u.recs, recs.data(), recs.size() * sizeof(UniRec), hipMemcpyHostToDevice, s);
         UniTree *d_tree = nullptr;
-        RPF_UTEMP(d_tree, (size_t)T * sizeof(UniTree));
+        RPF_UTEMP(d_tree, totals.size() * sizeof(UniTree));
         UniSeg *d_closed = nullptr;
         if (!closed.empty()) {
             RPF_UTEMP(d_closed, closed.size() * sizeof(UniSeg));
@@ -1494,11 +1495,14 @@ static rpf_status build_uniform(const float *X, int64_t n, int32_t d, const rpf_
                             f->perm[0], u);
             const int64_t waves = to_block.empty() ? (int64_t)to_wave.size() : seg_cap;
             launch_uni_grow(s, true, f->X, d, seed, d_seg, ctr + 1, ctr + 4, waves, n0, small_max, f->perm[0], u);
-            launch_uni_leaf_count(s, u.mark, n, (int)T, 256, d_tree);
+        }
+        {
+            ProfScope ps(s, "uniform_leaf_tables", (double)TN * 4, 0);
+            launch_uni_leaf_count(s, u.mark, n, (int)T, parts, 256, d_tree);
         }
         uint32_t got[3] = {0, 0, 0};
         hipMemcpyAsync(got, ctr, 12, hipMemcpyDeviceToHost, s);
-        hipMemcpyAsync(totals.data(), d_tree, (size_t)T * sizeof(UniTree), hipMemcpyDeviceToHost, s);
+        hipMemcpyAsync(totals.data(), d_tree, totals.size() * sizeof(UniTree), hipMemcpyDeviceToHost, s);
         if ((st = check_hip(hipStreamSynchronize(s), "rpf_build uniform subtrees")) != RPF_OK) return bail(st);
         {
             const std::string le = take_launch_error();
@@ -1564,9 +1568,15 @@ static rpf_status build_uniform(const float *X, int64_t n, int32_t d, const rpf_
     bool tiled = true;
     for (int64_t t = 0; t < T; t++) {
         if (device_growth) {
-            tiled &= totals[t].points == n;
-            f->tree_nleaf[t] = (int32_t)totals[t].leaves;
-            max_leaf = std::max(max_leaf, (int)totals[t].most);
+            UniTree sum{0, 0, 0, 0, 0};
+            for (int64_t k = t * parts; k < (t + 1) * parts; k++) {
+                sum.leaves += totals[k].leaves;
+                sum.points += totals[k].points;
+                sum.most = std::max(sum.most, totals[k].most);
+            }
+            tiled &= sum.points == n;
+            f->tree_nleaf[t] = (int32_t)sum.leaves;
+            max_leaf = std::max(max_leaf, (int)sum.most);
         } else {
             auto &lv = tleaves[t];
             std::sort(lv.begin(), lv.end(), [](const LeafDesc &a, const LeafDesc &b) { return a.off < b.off; });
@@ -1599,10 +1609,18 @@ static rpf_status build_uniform(const float *X, int64_t n, int32_t d, const rpf_
     std::vector<TileJob> jobs;
     f->job_off.assign(T + 1, 0);
     f->flops_off.assign(T + 1, 0.0);
+    std::vector<UniPart> part_at(totals.size());
     for (int64_t t = 0; t < T; t++) {
         if (device_growth) {  // (tiles of 256 rows or of one leaf: the same count)
-            f->job_off[t + 1] = f->job_off[t] + totals[t].jobs;
-            f->flops_off[t + 1] = f->flops_off[t] + 2.0 * d * (double)totals[t].squares;
+            f->job_off[t + 1] = f->job_off[t];
+            f->flops_off[t + 1] = f->flops_off[t];
+            int64_t leaf = 0;
+            for (int64_t k = t * parts; k < (t + 1) * parts; k++) {
+                part_at[k] = UniPart{leaf, f->job_off[t + 1]};
+                leaf += totals[k].leaves;
+                f->job_off[t + 1] += totals[k].jobs;
+                f->flops_off[t + 1] += 2.0 * d * (double)totals[k].squares;
+            }
             continue;
         }
         double fl = 0;
@@ -1652,10 +1670,11 @@ static rpf_status build_uniform(const float *X, int64_t n, int32_t d, const rpf_
     f->bytes += more;
     std::vector<int32_t> ident;
     if (device_growth) {
-        int64_t *d_off = nullptr;
-        RPF_UTEMP(d_off, (size_t)(T + 1) * 8);
-        hipMemcpyAsync(d_off, f->job_off.data(), (size_t)(T + 1) * 8, hipMemcpyHostToDevice, s);
-        launch_uni_leaf_fill(s, f->leaf_of, n, (int)T, 256, stride, d_off, f->d_leaves, f->d_jobs, f->heap_leaf);
+        UniPart *d_at = nullptr;
+        RPF_UTEMP(d_at, part_at.size() * sizeof(UniPart));
+        hipMemcpyAsync(d_at, part_at.data(), part_at.size() * sizeof(UniPart), hipMemcpyHostToDevice, s);
+        ProfScope ps(s, "uniform_leaf_tables", (double)TN * 4, 0);
+        launch_uni_leaf_fill(s, f->leaf_of, n, (int)T, parts, 256, stride, d_at, f->d_leaves, f->d_jobs, f->heap_leaf);
     } else {
         ident.resize((size_t)stride + 1);
         for (int64_t i = 0; i <= stride; i++) ident[i] = (int32_t)i;

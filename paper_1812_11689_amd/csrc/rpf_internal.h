@@ -294,8 +294,12 @@ struct UniRec {        // a node where a split was attempted, as the device foun
     int32_t small;     // depth of its first ancestor (or itself) of at most small_max members
 };
 
-struct UniTree {       // totals of one tree's leaves
+struct UniTree {       // totals of the leaves that start in a range of a tree's positions
     int64_t leaves, jobs, points, squares, most;
+};
+
+struct UniPart {       // where such a range's leaves (of the tree) and tile jobs (of the forest) begin
+    int64_t leaf, job;
 };
 
 struct UniGrow {       // what a growing launch writes
@@ -314,10 +318,11 @@ void launch_uni_grow(hipStream_t s, bool wave, const float *X, int d, uint64_t s
                      const uint32_t *count, uint32_t *next, int64_t most, int n0, int small_max, int32_t *perm,
                      const UniGrow &u);
 void launch_uni_mark(hipStream_t s, const UniSeg *leaves, int count, int32_t *mark);
-void launch_uni_leaf_count(hipStream_t s, const int32_t *mark, int64_t n, int T, int TR, UniTree *out);
+int uni_leaf_parts(int64_t n, int T);  // ranges of a tree
+void launch_uni_leaf_count(hipStream_t s, const int32_t *mark, int64_t n, int T, int parts, int TR, UniTree *out);
 struct TileJob;
-void launch_uni_leaf_fill(hipStream_t s, const int32_t *mark, int64_t n, int T, int TR, int64_t stride,
-                          const int64_t *job_off, LeafDesc *table, TileJob *jobs, int32_t *ident);
+void launch_uni_leaf_fill(hipStream_t s, const int32_t *mark, int64_t n, int T, int parts, int TR, int64_t stride,
+                          const UniPart *at, LeafDesc *table, TileJob *jobs, int32_t *ident);
 void launch_uni_rec_count(hipStream_t s, const UniRec *recs, uint32_t cnt, int64_t n, int64_t nb, uint32_t *bucket);
 // `words`: [3][cap] of scratch
 void launch_uni_rec_order(hipStream_t s, const UniRec *recs, uint32_t cnt, int T, int64_t n, int64_t nb,

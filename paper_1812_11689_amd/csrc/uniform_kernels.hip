@@ -574,15 +574,21 @@ __global__ void k_uni_mark(const UniSeg *__restrict__ leaves, int count, int32_t
     if (i < count) mark[leaves[i].pos] = leaves[i].size;
 }
 
-// per tree: leaves, tile jobs with tiles of `TR` rows, members, squared sizes, the largest leaf
-__global__ __launch_bounds__(1024) void k_uni_leaf_count(const int32_t *__restrict__ mark, int64_t n, int TR,
+// The leaf pass's tables are made by several workgroups per tree, each for the leaves that start
+// in its range of positions, about 512 in all (build of one tree of 10^7 x 16, leaves of 64: 113 ms
+// with one workgroup, 61 with these, 103 level by level from the host).  The jobs of a leaf of many
+// tiles are written by its whole workgroup (one leaf of 200 000 copies: 82 ms by one lane, 49, 61).
+
+// per range: leaves, tile jobs with tiles of `TR` rows, members, squared sizes, the largest leaf
+__global__ __launch_bounds__(1024) void k_uni_leaf_count(const int32_t *__restrict__ mark, int64_t n, int64_t len, int TR,
                                                          UniTree *__restrict__ out) {
     __shared__ unsigned long long s_v[5];
-    const int32_t *mk = mark + blockIdx.x * n;
+    const int32_t *mk = mark + blockIdx.y * n;
     if (threadIdx.x < 5) s_v[threadIdx.x] = 0;
     __syncthreads();
     unsigned long long leaves = 0, jobs = 0, pts = 0, sq = 0, most = 0;
-    for (int64_t i = threadIdx.x; i < n; i += 1024) {
+    const int64_t end = min(n, (blockIdx.x + 1) * len);
+    for (int64_t i = blockIdx.x * len + threadIdx.x; i < end; i += 1024) {
         const unsigned long long v = (unsigned long long)mk[i];
         if (!v) continue;
         const unsigned long long nt = (v + TR - 1) / TR;
@@ -599,41 +605,64 @@ __global__ __launch_bounds__(1024) void k_uni_leaf_count(const int32_t *__restri
     atomicMax(&s_v[4], most);
     __syncthreads();
     if (threadIdx.x == 0)
-        out[blockIdx.x] = UniTree{(int64_t)s_v[0], (int64_t)s_v[1], (int64_t)s_v[2], (int64_t)s_v[3], (int64_t)s_v[4]};
+        out[blockIdx.y * (int64_t)gridDim.x + blockIdx.x] = UniTree{(int64_t)s_v[0], (int64_t)s_v[1], (int64_t)s_v[2], (int64_t)s_v[3], (int64_t)s_v[4]};
 }
 
-// the leaf table and the tile jobs of every tree, left to right
-__global__ __launch_bounds__(1024) void k_uni_leaf_fill(const int32_t *__restrict__ mark, int64_t n, int TR,
-                                                        int64_t stride, const int64_t *__restrict__ job_off,
+// the leaf table and the tile jobs, left to right
+__global__ __launch_bounds__(1024) void k_uni_leaf_fill(const int32_t *__restrict__ mark, int64_t n, int64_t len, int TR,
+                                                        int64_t stride, const UniPart *__restrict__ parts,
                                                         LeafDesc *__restrict__ table, TileJob *__restrict__ jobs,
                                                         int32_t *__restrict__ ident) {
+    constexpr uint32_t kMany = 8;  // tiles across a leaf above which the workgroup writes its jobs together
     __shared__ uint32_t s_w[16];
-    const int t = blockIdx.x, tid = threadIdx.x;
+    __shared__ uint32_t s_big[3];
+    const int t = blockIdx.y, tid = threadIdx.x;
     const int32_t *mk = mark + t * n;
     LeafDesc *tab = table + t * stride;
-    TileJob *out = jobs + job_off[t];
-    uint32_t at = 0, jat = 0;
-    for (int64_t base = 0; base < n; base += 1024) {
-        const int32_t v = base + tid < n ? mk[base + tid] : 0;
+    const UniPart pt = parts[t * (int64_t)gridDim.x + blockIdx.x];
+    TileJob *out = jobs + pt.job;
+    int64_t at = pt.leaf, jat = 0;
+    const int64_t end = min(n, (blockIdx.x + 1) * len);
+    for (int64_t base = blockIdx.x * len; base < end; base += 1024) {
+        const int32_t v = base + tid < end ? mk[base + tid] : 0;
         const uint32_t nt = (uint32_t)((v + TR - 1) / TR);
         uint32_t e1, t1, e2, t2;
         block_excl_scan_w<16>(v ? 1u : 0u, s_w, e1, t1);
         block_excl_scan_w<16>(nt * nt, s_w, e2, t2);
+        auto job = [&](int64_t off, int32_t m, int32_t leaf, uint32_t I, uint32_t J) {
+            return TileJob{off + (int64_t)I * TR, off + (int64_t)J * TR, min(TR, m - (int)I * TR), min(TR, m - (int)J * TR),
+                           t, I == J ? 1 : 0, (int)J * TR, m, leaf, 0};
+        };
         if (v) {
             const int64_t off = base + tid;
-            tab[at + e1] = LeafDesc{off, v, (int32_t)(at + e1)};
-            TileJob *q = out + jat + e2;
-            for (uint32_t I = 0; I < nt; I++)
-                for (uint32_t J = 0; J < nt; J++)
-                    *q++ = TileJob{off + (int64_t)I * TR, off + (int64_t)J * TR, min(TR, v - (int)I * TR),
-                                   min(TR, v - (int)J * TR), t, I == J ? 1 : 0, (int)J * TR, v, (int32_t)(at + e1), 0};
+            const int32_t leaf = (int32_t)(at + e1);
+            tab[leaf] = LeafDesc{off, v, leaf};
+            if (nt <= kMany) {
+                TileJob *q = out + jat + e2;
+                for (uint32_t I = 0; I < nt; I++)
+                    for (uint32_t J = 0; J < nt; J++) *q++ = job(off, v, leaf, I, J);
+            } else {  // (one at most: 1024 positions hold the start of one leaf of so many)
+                s_big[0] = (uint32_t)tid;
+                s_big[1] = e1;
+                s_big[2] = e2;
+            }
+        }
+        if (__syncthreads_or(nt > kMany)) {
+            const int64_t off = base + s_big[0];
+            const int32_t m = mk[off];
+            const uint32_t nb = (uint32_t)((m + TR - 1) / TR);
+            TileJob *q = out + jat + s_big[2];
+            for (uint64_t k = tid; k < (uint64_t)nb * nb; k += 1024)
+                q[k] = job(off, m, (int32_t)(at + s_big[1]), (uint32_t)(k / nb), (uint32_t)(k % nb));
+            __syncthreads();
         }
         at += t1;
         jat += t2;
     }
-    for (int64_t i = at + tid; i < stride; i += 1024) tab[i] = LeafDesc{0, 0, -1};
+    if (blockIdx.x + 1 == gridDim.x)
+        for (int64_t i = at + tid; i < stride; i += 1024) tab[i] = LeafDesc{0, 0, -1};
     if (t == 0)
-        for (int64_t i = tid; i <= stride; i += 1024) ident[i] = (int32_t)i;
+        for (int64_t i = blockIdx.x * 1024 + tid; i <= stride; i += gridDim.x * 1024) ident[i] = (int32_t)i;
 }
 
 // The node records in order: tree, level, small nodes before large ones (by the depth of the
@@ -751,14 +780,21 @@ void launch_uni_mark(hipStream_t s, const UniSeg *leaves, int count, int32_t *ma
     launch_check(s, "k_uni_mark");
 }
 
-void launch_uni_leaf_count(hipStream_t s, const int32_t *mark, int64_t n, int T, int TR, UniTree *out) {
-    hipLaunchKernelGGL(k_uni_leaf_count, dim3(T), dim3(1024), 0, s, mark, n, TR, out);
+int uni_leaf_parts(int64_t n, int T) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>(512 / T, (n + 4095) / 4096));
+}
+
+static int64_t uni_part_len(int64_t n, int parts) { return ((n + parts - 1) / parts + 1023) / 1024 * 1024; }
+
+void launch_uni_leaf_count(hipStream_t s, const int32_t *mark, int64_t n, int T, int parts, int TR, UniTree *out) {
+    hipLaunchKernelGGL(k_uni_leaf_count, dim3(parts, T), dim3(1024), 0, s, mark, n, uni_part_len(n, parts), TR, out);
     launch_check(s, "k_uni_leaf_count");
 }
 
-void launch_uni_leaf_fill(hipStream_t s, const int32_t *mark, int64_t n, int T, int TR, int64_t stride,
-                          const int64_t *job_off, LeafDesc *table, TileJob *jobs, int32_t *ident) {
-    hipLaunchKernelGGL(k_uni_leaf_fill, dim3(T), dim3(1024), 0, s, mark, n, TR, stride, job_off, table, jobs, ident);
+void launch_uni_leaf_fill(hipStream_t s, const int32_t *mark, int64_t n, int T, int parts, int TR, int64_t stride,
+                          const UniPart *at, LeafDesc *table, TileJob *jobs, int32_t *ident) {
+    hipLaunchKernelGGL(k_uni_leaf_fill, dim3(parts, T), dim3(1024), 0, s, mark, n, uni_part_len(n, parts), TR, stride, at,
+                       table, jobs, ident);
     launch_check(s, "k_uni_leaf_fill");
 }
 

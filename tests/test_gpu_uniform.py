@@ -114,6 +114,46 @@ def test_uniform_subtrees_within_a_budget(n0):
     b.free()
 
 
+TABLE_CASES = [
+    # the leaf tables and tile jobs by several workgroups per tree: ranges of positions with no
+    # leaf start, leaves of more than eight tiles across, trees of different leaf counts
+    # name, n, d, T, n0, n_try, seed, kind, dup, K
+    ("one_tree", 40_000, 6, 1, 30, 1, 61, "mixture", 0, 6),
+    ("half_copies", 12_000, 4, 2, 40, 1, 62, "mixture", 2, 5),   # a leaf of 6 000 copies: 24 tiles across
+    ("ragged", 9000, 5, 130, 25, 1, 63, "aniso", 0, 4),          # 3 ranges a tree
+    ("two_leaves", 16_500, 8, 3, 8200, 1, 64, "aniso", 0, 5),
+]
+
+
+@pytest.mark.parametrize("case", TABLE_CASES, ids=[c[0] for c in TABLE_CASES])
+def test_uniform_leaf_tables_match_oracle(case):
+    name, n, d, T, n0, n_try, seed, kind, dup, K = case
+    test_uniform_all_knn_matches_oracle((name, n, d, T, n0, n_try, seed, kind, dup, K, "fp32", True))
+
+
+@pytest.mark.parametrize("n,copies,most_ms", [(2_000_000, False, 1.0), (200_000, True, 3.0)])
+def test_uniform_leaf_tables_of_one_tree_take_little(n, copies, most_ms):
+    """One tree of many points, and one leaf of many tiles, leave the tables' kernels to few
+    workgroups (16 MB read, 30 MB of jobs written: once 8 and 22 ms)."""
+    from paper_1812_11689_amd import rpf
+    print(f"[uniform tables] n={n} copies={copies}", flush=True)
+    x = torch.randn(n, 4, generator=torch.Generator(device="cuda").manual_seed(5), device="cuda")
+    if copies:
+        x[:] = x[:1].clone()
+    ms = []
+    for _ in range(3):
+        rpf.profile_enable(True)
+        rpf.profile_reset()
+        try:
+            rpf.build(x, 1, 64, None, dist_prec="fp32", split_rule="uniform", seed=3).free()
+            torch.cuda.synchronize()
+            ms.append(rpf.profile_read()["uniform_leaf_tables"]["total_ms"])
+        finally:
+            rpf.profile_enable(False)
+    print("    ", ms, flush=True)
+    assert min(ms) < most_ms
+
+
 KNN_CASES = [
     # name, n, d, T, n0, n_try, seed, kind, dup, K, prec, exclude_self
     ("fp32_k10", 6000, 16, 8, 20, 1, 31, "mixture", 0, 10, "fp32", True),
