@@ -878,7 +878,7 @@ __global__ __launch_bounds__(NT) void k_proj_chunks(
 // ascend in index, so equal keys are ordered by position.)  Segments above kSelDirect first
 // draw 2 048 evenly spaced keys and bracket the median between the sample's ranks 1 024 +- 120
 // (over five standard deviations of a random sample's median); one multi-block pass counts the
-// keys below the bracket and lists the positions inside it (about 12%), and the workgroup
+// keys below the bracket and at its ends and lists those inside it (about 12%), and the workgroup
 // reads only those; a bracket that misses costs it passes over the whole segment.  Bound: one
 // read of the keys.  10^6 x 128, 72 trees: 24 launches a level (11-bit digits from the top of
 // the key, most of them empty) took 0.54 ms a level, 4.3 ms a step; these take 2.9 ms.  (No
@@ -919,32 +919,46 @@ __global__ __launch_bounds__(S / 2) void k_sel_sample(const SegDesc *__restrict_
             __syncthreads();
         }
     if (tid == 0) {
-        st->lo = s_k[S / 2 - kMargin];
-        st->hi = s_k[S / 2 + kMargin];
+        const int a = S / 2 - kMargin, b = S / 2 + kMargin;
+        st->lo = s_k[a];
+        st->hi = s_k[b];
+        // a bracket's key that the sample holds more than once: many members may share it
+        st->ties = (s_k[a - 1] == s_k[a] || s_k[a] == s_k[a + 1] ? 1 : 0) | (s_k[b - 1] == s_k[b] || s_k[b] == s_k[b + 1] ? 2 : 0);
         st->cnt = 0;
         st->sampled = 1;
     }
 }
 
-// The list of a bracketed segment: keys, then positions, of at most (m - 2) / 3 members, in the
-// segment's part of the permutation that the partition will write (4 m bytes).
+// What is kept of a bracketed segment, in its part of the permutation that the partition will
+// write (4 m bytes): keys and positions of at most (m - 2) / 3 less the chunks' members inside the
+// bracket, and before them, where many members share one of its keys, per chunk the members up to
+// the lower key, below the upper key and up to it.
 struct SelList {
+    uint32_t *upto_lo, *below_hi, *upto_hi;  // [chunks]
     uint64_t *key;
     uint32_t *pos;
     uint32_t cap;
     __device__ SelList(int32_t *perm, int64_t at, int m) {
-        cap = (uint32_t)(m - 2) / 3;
-        key = reinterpret_cast<uint64_t *>((reinterpret_cast<uintptr_t>(perm + at) + 7) & ~(uintptr_t)7);
+        const int nch = (m + kChunk - 1) / kChunk;
+        upto_lo = reinterpret_cast<uint32_t *>(perm + at);
+        below_hi = upto_lo + nch;
+        upto_hi = below_hi + nch;
+        cap = (uint32_t)(m - 2) / 3 - (uint32_t)nch;
+        key = reinterpret_cast<uint64_t *>((reinterpret_cast<uintptr_t>(upto_hi + nch) + 7) & ~(uintptr_t)7);
         pos = reinterpret_cast<uint32_t *>(key + cap);
     }
 };
 
-// Keys of a chunk below the bracket (lcount), and those inside it, listed.
+// Members of a chunk below the bracket (lcount) and those inside it, listed.  Where many members
+// share a key (repeated rows, few distinct values) the median is most often one of the bracket's
+// two keys; members at such a key are counted, not listed.  (Listed, or read by the pick from the
+// whole segment where they outgrow the list: 10^6 x 8, 4 trees, two thirds of the rows the same,
+// 19.2 ms a build, with the counts 11.6, by 24 launches a level 12.6.)
 __global__ __launch_bounds__(256) void k_sel_count(const SegDesc *__restrict__ segs, const ChunkDesc *__restrict__ chunks,
                                                    const uint64_t *__restrict__ keys, int64_t n,
                                                    SelState *__restrict__ state, int nseg, int32_t *__restrict__ list,
                                                    uint32_t *__restrict__ lcount) {
-    __shared__ uint32_t s_w[8];
+    __shared__ uint32_t s_w[16];
     __shared__ uint32_t s_at;
     const int t = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const ChunkDesc c = chunks[blockIdx.x];
@@ -953,33 +967,50 @@ __global__ __launch_bounds__(256) void k_sel_count(const SegDesc *__restrict__ s
     const uint64_t lo = st->lo, hi = st->hi;
     const uint64_t *kk = keys + (int64_t)t * n + c.start;
     constexpr int E = kChunk / 256;
-    uint32_t below = 0, in = 0;  // per wave (uniform)
+    const int ties = st->ties;
+    // (keys are integers: a bracket's key that is listed widens the bracket by one)
+    const uint64_t lo1 = ties & 1 ? lo : lo - 1, hi1 = ties & 2 ? hi : hi + 1;
+    uint32_t below = 0, in = 0, at_hi = 0, at_lo = 0;  // per wave (uniform)
     uint64_t k[E], mine[E];
 #pragma unroll
     for (int e = 0; e < E; e++) k[e] = kk[tid + 256 * e < c.len ? tid + 256 * e : 0];
 #pragma unroll
     for (int e = 0; e < E; e++) {
         const bool ok = tid + 256 * e < c.len;
-        below += (uint32_t)__popcll(__ballot(ok && k[e] < lo));
-        mine[e] = __ballot(ok && k[e] >= lo && k[e] <= hi);
+        const uint64_t up = __ballot(ok && k[e] <= lo1);
+        below += (uint32_t)__popcll(up);
+        mine[e] = __ballot(ok && k[e] > lo1 && k[e] < hi1);
         in += (uint32_t)__popcll(mine[e]);
+        if (ties) {
+            at_lo += (uint32_t)__popcll(up & __ballot(k[e] == lo));
+            at_hi += (uint32_t)__popcll(__ballot(ok && k[e] <= hi) & ~up & ~mine[e]);
+        }
     }
     if (lane == 0) {
         s_w[w] = in;
-        s_w[4 + w] = below;
+        s_w[4 + w] = below - at_lo;
+        s_w[8 + w] = at_lo;
+        s_w[12 + w] = at_hi;
     }
     __syncthreads();
+    const SegDesc sg = segs[c.seg];
+    const SelList out(list, (int64_t)t * n + sg.off, sg.size);
+    const uint32_t rel = (uint32_t)(c.start - sg.off);
     if (tid == 0) {
-        lcount[(int64_t)t * gridDim.x + blockIdx.x] = s_w[4] + s_w[5] + s_w[6] + s_w[7];
-        const uint32_t tot = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+        auto sum = [&](int k) { return s_w[k] + s_w[k + 1] + s_w[k + 2] + s_w[k + 3]; };
+        const uint32_t tot = sum(0), low = sum(4);
+        lcount[(int64_t)t * gridDim.x + blockIdx.x] = low;
+        if (ties) {
+            const uint32_t upto = low + sum(8), q = rel / kChunk;
+            out.upto_lo[q] = upto;
+            out.below_hi[q] = upto + tot;
+            out.upto_hi[q] = upto + tot + sum(12);
+        }
         s_at = tot ? (uint32_t)atomicAdd(&st->cnt, (int)tot) : 0u;
     }
     __syncthreads();
     uint32_t at = s_at;
     for (int q = 0; q < w; q++) at += s_w[q];
-    const SegDesc sg = segs[c.seg];
-    const SelList out(list, (int64_t)t * n + sg.off, sg.size);
-    const uint32_t rel = (uint32_t)(c.start - sg.off);
 #pragma unroll
     for (int e = 0; e < E; e++) {
         const uint32_t slot = at + mask_rank(mine[e]);
@@ -1014,23 +1045,59 @@ __global__ __launch_bounds__(1024) void k_sel_pick(const SegDesc *__restrict__ s
     const uint64_t *kk = keys + (int64_t)t * n + sg.off;
     uint32_t *lc = lcount + (int64_t)t * nchunk + sg.chunk0;
     const int m = sg.size, nch = sg.nchunk;
-    uint32_t rank = (uint32_t)(m / 2), N = (uint32_t)m, below = 0;
+    uint32_t rank = (uint32_t)(m / 2), N = (uint32_t)m;
     const SelList list(listmem, (int64_t)t * n + sg.off, m);
-    bool listed = false;  // the rank is among the listed members
-    uint64_t lo, hi;
-    const bool counted = sampled && stp->sampled;
+    uint32_t listN = 0;
+    bool listed = false;            // the rank is among the listed members
+    const uint32_t *from = nullptr;  // tie: it is among the equal members between these two counts per chunk
+    const uint32_t *upto = nullptr;
+    const SelState st0 = *stp;
+    uint64_t lo = st0.lo, hi = st0.hi;
+    const bool counted = sampled && st0.sampled;
+    const uint32_t *left0 = lc;     // listed: the chunks' members before the listed ones
     if (counted) {
-        uint32_t b = 0;
-        for (int q = tid; q < nch; q += 1024) b += lc[q];
-        uint32_t excl;
-        block_excl_scan_w<16>(b, s_w, excl, below);
-        const uint32_t cnt = (uint32_t)stp->cnt;
-        if (rank >= below && rank < below + cnt && cnt <= list.cap) {
+        uint32_t b1;  // members before the listed ones
+        if (st0.ties) {
+            uint32_t v[4] = {0, 0, 0, 0};
+            for (int q = tid; q < nch; q += 1024) {
+                v[0] += lc[q];
+                v[1] += list.upto_lo[q];
+                v[2] += list.below_hi[q];
+                v[3] += list.upto_hi[q];
+            }
+            if (tid < 4) s_sel[tid] = 0;
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
+                if (lane == 0 && v[k]) atomicAdd(&s_sel[k], v[k]);
+            }
+            __syncthreads();
+            const uint32_t b0 = s_sel[0], b2 = s_sel[2], b3 = s_sel[3];
+            b1 = s_sel[1];
+            __syncthreads();
+            left0 = list.upto_lo;
+            if (rank >= b0 && rank < b1) {
+                from = lc;
+                upto = list.upto_lo;
+                rank -= b0;
+            } else if (rank >= b2 && rank < b3) {
+                from = list.below_hi;
+                upto = list.upto_hi;
+                rank -= b2;
+                lo = hi;
+            }
+        } else {
+            uint32_t b = 0;
+            for (int q = tid; q < nch; q += 1024) b += lc[q];
+            uint32_t excl;
+            block_excl_scan_w<16>(b, s_w, excl, b1);
+        }
+        const uint32_t cnt = (uint32_t)st0.cnt;
+        if (!from && rank >= b1 && rank < b1 + cnt && cnt <= list.cap) {
             listed = true;
-            N = cnt;
-            rank -= below;
-            lo = stp->lo;
-            hi = stp->hi;
+            N = listN = cnt;
+            rank -= b1;
         }
     }
     bool lds = false;  // the survivors are in s_k / s_p
@@ -1090,12 +1157,67 @@ __global__ __launch_bounds__(1024) void k_sel_pick(const SegDesc *__restrict__ s
         }
         __syncthreads();
     };
-    // left members per chunk, for the partition: so far those below the bracket
+    // left members per chunk, for the partition: so far those before the listed ones
     const bool few = nch <= kCnt;
+    // the median (key, position): the partition's counts, made a running sum, and the node's split
+    auto finish = [&](uint64_t ck, uint32_t cp) {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        uint32_t run = 0;
+        for (int base = 0; base < nch; base += 1024) {
+            const int q = base + tid;
+            const uint32_t v = q < nch ? (few ? s_c[q] : __hip_atomic_load(&lc[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) : 0u;
+            uint32_t excl, total;
+            block_excl_scan_w<16>(v, s_w, excl, total);
+            if (q < nch) lc[q] = run + excl;
+            run += total;
+        }
+        if (tid == 0) {
+            const int64_t hs = (int64_t)t * H + (sg.heap - 1);
+            stp->key = ck;
+            stp->idx = perm[(int64_t)t * n + sg.off + cp];
+            split[hs] = val_of(ck);
+            split_idx[hs] = stp->idx;
+            if (chosen) chosen[hs] = 0;  // one direction per node (else Alg. 2's pick stands already)
+            if (run != (uint32_t)(m / 2)) atomicOr(err, 16);
+        }
+    };
+    if (from) {  // the median is member `rank` of those equal to lo, in order of position
+        uint32_t run = 0;
+        for (int base = 0; base < nch; base += 1024) {  // its chunk, and its rank there
+            const int q = base + tid;
+            const uint32_t v = q < nch ? upto[q] - from[q] : 0u;
+            uint32_t excl, total;
+            block_excl_scan_w<16>(v, s_w, excl, total);
+            if (rank >= run + excl && rank < run + excl + v) {
+                s_sel[0] = (uint32_t)q;
+                s_sel[1] = rank - run - excl;
+            }
+            run += total;
+        }
+        __syncthreads();
+        const uint32_t mc = s_sel[0], mr = s_sel[1];
+        run = 0;
+        for (int i = (int)mc * kChunk + tid, e = 0; e < kChunk; e += 1024, i += 1024) {
+            const bool same = i < m && kk[i] == lo;
+            uint32_t excl, total;
+            block_excl_scan_w<16>(same ? 1u : 0u, s_w, excl, total);
+            if (same && run + excl == mr) s_sel[2] = (uint32_t)i;
+            run += total;
+        }
+        for (int q = tid; q < nch; q += 1024) {
+            const uint32_t v = q < (int)mc ? upto[q] : from[q] + (q == (int)mc ? mr : 0u);
+            if (few) s_c[q] = v;
+            else lc[q] = v;
+        }
+        __syncthreads();
+        finish(lo, s_sel[2]);
+        return;
+    }
     if (few)
-        for (int q = tid; q < nch; q += 1024) s_c[q] = listed ? lc[q] : 0u;
-    else if (!listed)
-        for (int q = tid; q < nch; q += 1024) lc[q] = 0;
+        for (int q = tid; q < nch; q += 1024) s_c[q] = listed ? left0[q] : 0u;
+    else
+        for (int q = tid; q < nch; q += 1024) lc[q] = listed ? left0[q] : 0u;
     __builtin_amdgcn_s_waitcnt(0);  // (the counters in memory: one workgroup's, so no fence is needed)
     __syncthreads();
     auto add = [&](int q, uint32_t v) { atomicAdd(few ? &s_c[q] : &lc[q], v); };
@@ -1302,7 +1424,7 @@ __global__ __launch_bounds__(1024) void k_sel_pick(const SegDesc *__restrict__ s
     auto is_left = [&](uint64_t k, uint32_t p) { return k < ck || (k == ck && p < cp); };
     if (fast || listed) {
         lds = fast;
-        N = fast ? N : (uint32_t)stp->cnt;
+        N = fast ? N : listN;
         each([&](uint64_t k, uint32_t p) {
             if (is_left(k, p)) add((int)(p / kChunk), 1u);
         });
@@ -1313,26 +1435,7 @@ __global__ __launch_bounds__(1024) void k_sel_pick(const SegDesc *__restrict__ s
             if (lane == 0 && mask) add(base / kChunk, (uint32_t)__popcll(mask));
         }
     }
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    uint32_t run = 0;
-    for (int base = 0; base < nch; base += 1024) {
-        const int q = base + tid;
-        const uint32_t v = q < nch ? (few ? s_c[q] : __hip_atomic_load(&lc[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) : 0u;
-        uint32_t excl, total;
-        block_excl_scan_w<16>(v, s_w, excl, total);
-        if (q < nch) lc[q] = run + excl;
-        run += total;
-    }
-    if (tid == 0) {
-        const int64_t hs = (int64_t)t * H + (sg.heap - 1);
-        stp->key = ck;
-        stp->idx = perm[(int64_t)t * n + sg.off + cp];
-        split[hs] = val_of(ck);
-        split_idx[hs] = stp->idx;
-        if (chosen) chosen[hs] = 0;  // one direction per node (else Alg. 2's pick stands already)
-        if (run != (uint32_t)(m / 2)) atomicOr(err, 16);
-    }
+    finish(ck, cp);
 }
 
 template <int NT>

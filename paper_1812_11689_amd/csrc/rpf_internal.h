@@ -58,7 +58,7 @@ struct SelState {      // median select of one multi-block (tree, segment)
     int32_t idx;
     int32_t cnt;       // sampled: listed positions
     int32_t sampled;
-    int32_t pad;
+    int32_t ties;      // sampled: bit 0, many members may share lo; bit 1, hi
 };
 
 struct Ent {           // one pruning candidate: point index and bounds on its squared distance

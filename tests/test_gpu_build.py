@@ -99,6 +99,42 @@ def test_median_select_matches_oracle(case):
     f.free()
 
 
+EQUAL_CASES = [
+    # medians among many equal keys: at either end of the bracket or between, in any chunk
+    # name, n, d, T, n0, distinct rows, share of the first (rows in runs: whole chunks of one key)
+    ("two_thirds_one_row", 70_000, 3, 2, 5000, 0, 0.67, False),
+    ("a_fifth_one_row", 100_000, 4, 3, 5000, 0, 0.2, False),
+    ("five_rows", 100_000, 4, 3, 5000, 5, 0.0, False),
+    ("five_rows_in_runs", 100_000, 4, 3, 5000, 5, 0.0, True),
+    ("twelve_rows_many_nodes", 20_000, 3, 130, 4200, 12, 0.0, False),
+    ("one_row", 40_000, 2, 2, 5000, 1, 0.0, False),
+    ("chunks_past_1024", 4_300_000, 2, 1, 1_100_000, 3, 0.0, False),
+]
+
+
+@pytest.mark.parametrize("case", EQUAL_CASES, ids=[c[0] for c in EQUAL_CASES])
+def test_median_among_equal_keys(case):
+    name, n, d, T, n0, rows, share, runs = case
+    print(f"[build] {name} n={n} d={d} T={T} n0={n0}", flush=True)
+    rng = np.random.default_rng(len(name) + 75)
+    x, R = problem(n, d, T, n0, 1, seed=len(name) + 75)
+    if rows:
+        pick = rng.integers(0, rows, n)
+        x = x[np.sort(pick) if runs else pick]
+    if share:
+        x[rng.random(n) < share] = x[0]
+    x = np.ascontiguousarray(x)
+    ref = oracle.build_forest(x, R, T, n0, 1)
+    f = _gpu_forest(x, R, T, n0, 1)
+    f.info()
+    for t in range(T):
+        g = {k: v.cpu().numpy() for k, v in f.tree_dump(t).items()}
+        np.testing.assert_array_equal(g["perm"], ref.perm[t])
+        assert np.array_equal(g["split"], ref.split[t], equal_nan=True)
+        np.testing.assert_array_equal(g["split_idx"], ref.split_idx[t])
+    f.free()
+
+
 WIDE_CASES = [
     # levels of at most 256 workgroups: 1024 threads each, from 512 members on
     # name, n, d, T, n0, n_try, kind, dup
