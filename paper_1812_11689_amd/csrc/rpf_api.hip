@@ -954,11 +954,17 @@ static void build_launches(rpf_forest *f, hipStream_t s) {
     // those of 128 and more, 10.1 with those above 1 024).
     double *bound = nullptr;
     constexpr int kDigitSeg = 128;
-    if (f->Xq && n_try == 1 && d <= 1024 && H > 0 && H <= n &&
+    unsigned long long *band = nullptr;  // behind the bounds: a counter per pair of linked levels
+    constexpr int kPairs = 32;
+    if (f->Xq && n_try == 1 && d <= 1024 && H > 0 && T * (n - H) >= kPairs &&
         (d >= 512 || (d >= 192 && (double)T * n * d >= 4e8))) {
         bound = reinterpret_cast<double *>(f->nrm);
         launch_digit_bound(s, f->R, (int64_t)T * H, d, bound);
+        band = reinterpret_cast<unsigned long long *>(bound + T * H);
+        fill_u64(band, kPairs, 0, s);
     }
+    int pair = -1;                   // pairs of levels by digits so far, less one
+    unsigned long long above = 0;    // members of the last pair's lead
     bool by_digits = false;  // this level's keys
     int cur = 0;
     for (size_t l = 0; l < f->levels.size(); l++) {
@@ -995,6 +1001,12 @@ static void build_launches(rpf_forest *f, hipStream_t s) {
         lk.dq = f->dq;
         if (!lv.fed) by_digits = bound && lv.max_m >= kDigitSeg;  // (a fed level's are its lead's)
         lk.bound = by_digits ? bound : nullptr;
+        if (by_digits) {
+            const unsigned long long here = (unsigned long long)T * members;
+            if (!lv.fed) pair++;
+            lk.band = DigitBand{band + pair, pair > 0 ? band + pair - 1 : nullptr, above / 4, 2 * here};
+            if (lv.fed || !lv.lead) above = here;
+        }
         lk.top = l == 0;
         const double xb = f->Xq ? (double)f->dq : 4.0 * d;  // bytes of a row read
         // algorithmic bytes: X rows (none on a fed level), ids and keys, the children's

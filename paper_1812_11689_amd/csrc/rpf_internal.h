@@ -79,6 +79,13 @@ struct LookDesc {     // the children of one internal node, for projections made
     int32_t child_heap[2];  // heap ids of the children that are internal nodes, else 0
 };
 
+struct DigitBand {     // grid forests: members near their node's median, over a pair of linked levels
+    unsigned long long *cnt = nullptr;         // this pair's
+    const unsigned long long *prev = nullptr;  // the pair above's (null: none)
+    unsigned long long lim = 0;                // above it, this pair projects every member exactly,
+    unsigned long long all = 0;                // and counts this many for the next
+};
+
 // Two levels from one read of X (one direction per node): the lead level projects every row
 // onto its node's direction and onto both children's, and its partition hands each row the
 // projection onto the child it moves into, as that level's key at its new position; the fed
@@ -97,6 +104,7 @@ struct LevelLink {
     // grid forests: per node, how far a projection by digits may be from the exact one (null:
     // every projection exact)
     const double *bound = nullptr;
+    DigitBand band;
     bool top = false;  // the first level: the identity permutation in every tree
 };
 

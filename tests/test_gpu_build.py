@@ -213,6 +213,43 @@ def test_digit_projections_match_oracle(case):
     f.free()
 
 
+BAND_CASES = [
+    # most members near their node's median: the pairs of levels below the first project exactly
+    # name, n, d, T, n0, what
+    ("half_blank_chunks", 70_000, 512, 1, 900, "blank"),      # four multi-block levels
+    ("half_blank_scalar", 70_000, 513, 1, 900, "blank"),
+    ("half_blank_one_workgroup", 6000, 600, 3, 40, "blank"),
+    ("blank_then_not", 40_000, 512, 2, 200, "part"),          # some nodes full of copies, some with none
+    ("directions_of_zeros", 40_000, 512, 2, 300, "zeros"),    # every third node
+]
+
+
+@pytest.mark.parametrize("case", BAND_CASES, ids=[c[0] for c in BAND_CASES])
+def test_digit_bands_of_many_members_match_oracle(case):
+    from paper_1812_11689_amd import rpf
+    name, n, d, T, n0, what = case
+    print(f"[build] {name} n={n} d={d} T={T} n0={n0}", flush=True)
+    rng = np.random.default_rng(len(name) + 76)
+    k = rng.integers(0, 256, (n, d), dtype=np.uint8)
+    if what == "blank":
+        k[::2] = 0
+    elif what == "part":
+        k[: n // 4] = k[0]
+    x = (np.arange(256, dtype=np.float32) / np.float32(255))[k]
+    R = rng.standard_normal((T, 2 ** rpf.depth(n, n0) - 1, 1, d)).astype(np.float32)
+    if what == "zeros":
+        R[:, ::3] = 0
+    ref = oracle.build_forest(x, R, T, n0, 1)
+    f = rpf.build(torch.from_numpy(x).cuda(), T, n0, torch.from_numpy(R).cuda(), dist_prec="u8grid")
+    f.info()
+    for t in range(T):
+        g = {k: v.cpu().numpy() for k, v in f.tree_dump(t).items()}
+        np.testing.assert_array_equal(g["perm"], ref.perm[t])
+        assert np.array_equal(g["split"], ref.split[t], equal_nan=True)
+        np.testing.assert_array_equal(g["split_idx"], ref.split_idx[t])
+    f.free()
+
+
 TRY_CASES = [
     # several tries per node: sums over pieces of 256 members, nodes scored in one workgroup
     # (up to 512 members) or over many blocks, 2 to 5 tries per read, more than 16 tries
