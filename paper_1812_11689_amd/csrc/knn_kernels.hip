@@ -3954,11 +3954,15 @@ static rpf_status knn_direct(const ForestView &v, const CheckSlot &chk, const fl
         launch_check(s, "k_query_route");
     }
     rpf_status st = check_hip(hipEventRecord(chk.ev, s), "rpf_query input check");
-    if (st != RPF_OK) return st;
-    cand_launches(v, cs, K, w, out_idx, out_dist, s);
-    st = check_hip(hipEventSynchronize(chk.ev), "rpf_query input check");
+    if (st == RPF_OK) {
+        cand_launches(v, cs, K, w, out_idx, out_dist, s);
+        st = check_hip(hipEventSynchronize(chk.ev), "rpf_query input check");
+    }
     const std::string le = take_launch_error();
-    if (st != RPF_OK) return st;
+    if (st != RPF_OK) {  // (the word goes to another call: nothing may still write it)
+        (void)hipStreamSynchronize(s);
+        return st;
+    }
     if (__atomic_load_n(chk.flag, __ATOMIC_ACQUIRE)) return fail(RPF_EINVAL, "rpf_query: Q holds NaN or Inf");
     if (!le.empty()) return fail(RPF_EDEVICE, "kNN: " + le);
     return RPF_OK;
