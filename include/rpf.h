@@ -280,8 +280,9 @@ rpf_status rpf_query(const rpf_forest *f, const float *Q_dev, int64_t m, int32_t
  *     behind: calls whose work overlaps on one device (other threads, other streams with
  *     no ordering between them) race and corrupt each other's results.  Order them, e.g. on
  *     one stream, or synchronise between them.  Like rpf_query, the call waits for its input
- *     check (and, with more than one query to two leaves, for its tile counts); its last
- *     kernels are still queued when it returns. */
+ *     check (and for its tile counts, with more than one query to two leaves, or where a batch
+ *     that would read gigabytes of leaf rows turns out to share few leaves); its last kernels
+ *     are still queued when it returns. */
 rpf_status rpf_query_noalloc(const rpf_forest *f, const float *Q_dev, int64_t m, int32_t K,
                              int32_t *out_idx_dev, float *out_dist_dev, void *stream);
 

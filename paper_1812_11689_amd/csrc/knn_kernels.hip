@@ -3055,10 +3055,13 @@ static void sym_dispatch(int prec, int NB, hipStream_t s, int64_t njobs, const T
 // groups of several queries in one leaf are rare): every (query, tree) pair is a job of its own
 // and nothing is sorted, counted or read back.  Launches: one clear, routing with the finite
 // check, the Phase I rows, the first merge, the Phase II rows, the final merge and the
-// exhaustive path.  The host waits for the check's event only after it has queued them all;
+// exhaustive path.  The host waits for the check's event only after it has queued them all (but
+// see knn_direct for batches that read gigabytes);
 // a rejected batch stops at the final kernels, before its outputs (see FinalArgs.stop).
 
-constexpr int kDirectWaves = 4096;  // waves a phase is cut into, where it has fewer pairs
+// waves a phase is cut into, where it has fewer pairs (1 024, 4 096 and 16 384 measured the same,
+// within the runs' differences, for 1 to 1 024 queries of the cases at the direct route's rule)
+constexpr int kDirectWaves = 4096;
 
 // Routes one query per eight lanes; tree 0's lanes check that the query is finite.
 // WIDE (few pairs): one wave per (query, tree), whose eight-lane groups project onto the node,
@@ -3119,6 +3122,25 @@ __global__ __launch_bounds__(256) void k_query_route(const float *__restrict__ Q
         }
     }
     if (have && (WIDE ? lane == 0 : g == 0)) out_leaf[(int64_t)t * m + q] = (int32_t)h;
+}
+
+// How many different leaves of tree 0 the batch meets, to the host: a word behind the check's.
+// (Counted modulo 2^17 heap ids; the host does not use a count near that.)
+__global__ __launch_bounds__(1024) void k_query_spread(const int32_t *__restrict__ leaf, int64_t m, int32_t *host_count) {
+    __shared__ uint32_t s_seen[4096];
+    __shared__ uint32_t s_cnt;
+    for (int i = threadIdx.x; i < 4096; i += 1024) s_seen[i] = 0;
+    if (threadIdx.x == 0) s_cnt = 0;
+    __syncthreads();
+    uint32_t mine = 0;
+    for (int64_t q = threadIdx.x; q < m; q += 1024) {
+        const uint32_t h = (uint32_t)leaf[q] & 131071u, bit = 1u << (h & 31);
+        mine += (atomicOr(&s_seen[h >> 5], bit) & bit) ? 0u : 1u;
+    }
+    atomicAdd(&s_cnt, mine);
+    __syncthreads();
+    if (threadIdx.x == 0)
+        __hip_atomic_store(host_count, (int32_t)s_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // The rows of one (query, tree) pair's leaf, or every parts-th 64 of them: one wave, eight
@@ -3915,10 +3937,23 @@ rpf_status route(const rpf_forest *f, const float *Q, int64_t m, int32_t *out_le
 }
 
 // The direct search (see "direct queries"): the check slot's word and event tell whether the
-// batch was finite.
+// batch was finite.  A batch whose pairs read gigabytes waits for the routing first (some 15 us):
+// where its queries share few leaves (one spot of the points), *shared returns their leaves for
+// the grouped path, which reads a leaf once per group, and nothing else has been done.
+//   One spot, pair by pair against grouped (and as it was when all were grouped), rows read:
+//   500 000 x 512 binary32, leaves of 977: 64 queries, 2.0 GB, 473 us (596); 128, 4.1 GB, 773
+//   against 472 (613); 256, 8.2 GB, 1 380 against 578 (721)
+//   2 000 000 x 96 float16, leaves of 977: 256, 3.1 GB, 290 us (420); 512, 6.1 GB, 450 against 358
+//   (460); 1 024, 12.3 GB, 780 against 401 (510)
+// Spread over the points the pairs win throughout (the last: 3.0 ms against 4.2).
+static bool direct_early(const ForestView &v, int64_t m) {
+    const double row = (double)v.dp * (v.prec == RPF_DIST_FP32 ? 4 : 2);
+    return (double)m * v.T * v.max_leaf * row > (row > 1024 ? 2.5e9 : 6e9);
+}
+
 template <typename Get>
 static rpf_status knn_direct(const ForestView &v, const CheckSlot &chk, const float *Q, int64_t m, int K,
-                             int32_t *out_idx, float *out_dist, hipStream_t s, Get get) {
+                             int32_t *out_idx, float *out_dist, hipStream_t s, Get get, int32_t **shared) {
     CandStage cs;
     cs.rows = m;
     cs.jobs0 = cs.jobs1 = nullptr;
@@ -3932,17 +3967,22 @@ static rpf_status knn_direct(const ForestView &v, const CheckSlot &chk, const fl
     cs.excl = 0;
     cs.flops0 = cs.flops1 = cs.bytes0 = cs.bytes1 = 0;
     cs.sym = false;
+    const bool early = direct_early(v, m);
     int32_t *flag = static_cast<int32_t *>(get(16));
     int32_t *qleaf = static_cast<int32_t *>(get((size_t)v.T * m * 4));
     CandWs w;
-    if (!flag || !qleaf || !cand_ws_alloc(v, cs, K, get, w)) return fail(RPF_ENOMEM, "kNN workspace allocation failed");
+    if (!flag || !qleaf || (!early && !cand_ws_alloc(v, cs, K, get, w)))
+        return fail(RPF_ENOMEM, "kNN workspace allocation failed");
     cs.row_leaf = cs.qleaf = qleaf;
     cs.stop = flag;
     __atomic_store_n(chk.flag, 0, __ATOMIC_RELEASE);
-    fill_many({{flag, 4}, {w.cnt, m}, {w.fb_cnt, kFbWords}}, s);
+    __atomic_store_n(chk.flag + 1, -1, __ATOMIC_RELEASE);
+    if (early) fill_u32(flag, 4, 0, s);
+    else fill_many({{flag, 4}, {w.cnt, m}, {w.fb_cnt, kFbWords}}, s);
     {
         const bool vec = (v.d % 4) == 0 && ((uintptr_t)Q % 16) == 0;
-        // one wave per pair while that leaves the chip unfilled
+        // one wave per pair while that leaves the chip unfilled (whole calls, 4 096 pairs: 10^6 x 96 146
+        // against 155 us, 100 000 x 512 246 against 287; 16 384: 502, 502; 32 768: 465, 436)
         const bool wide = m * v.T <= 8192;
         ProfScope ps(s, "route", (double)m * v.T * (v.L * (8.0 * v.d + 16)), 0);
         auto go = [&](auto kern) {
@@ -3953,17 +3993,33 @@ static rpf_status knn_direct(const ForestView &v, const CheckSlot &chk, const fl
         else wide ? go(k_query_route<false, true>) : go(k_query_route<false, false>);
         launch_check(s, "k_query_route");
     }
-    rpf_status st = check_hip(hipEventRecord(chk.ev, s), "rpf_query input check");
-    if (st == RPF_OK) {
-        cand_launches(v, cs, K, w, out_idx, out_dist, s);
-        st = check_hip(hipEventSynchronize(chk.ev), "rpf_query input check");
+    if (early) {
+        hipLaunchKernelGGL(k_query_spread, dim3(1), dim3(1024), 0, s, qleaf, m, chk.flag + 1);
+        launch_check(s, "k_query_spread");
     }
-    const std::string le = take_launch_error();
+    rpf_status st = check_hip(hipEventRecord(chk.ev, s), "rpf_query input check");
+    if (st == RPF_OK && !early) cand_launches(v, cs, K, w, out_idx, out_dist, s);
+    if (st == RPF_OK && early)  // (the word is there before the event: the next launches follow sooner)
+        while (__atomic_load_n(chk.flag + 1, __ATOMIC_ACQUIRE) < 0 && hipEventQuery(chk.ev) == hipErrorNotReady) {}
+    if (st == RPF_OK && (!early || chk.flag[1] < 0)) st = check_hip(hipEventSynchronize(chk.ev), "rpf_query input check");
     if (st != RPF_OK) {  // (the word goes to another call: nothing may still write it)
         (void)hipStreamSynchronize(s);
+        take_launch_error();
         return st;
     }
-    if (__atomic_load_n(chk.flag, __ATOMIC_ACQUIRE)) return fail(RPF_EINVAL, "rpf_query: Q holds NaN or Inf");
+    const bool bad = __atomic_load_n(chk.flag, __ATOMIC_ACQUIRE) != 0;
+    if (early && !bad) {
+        const int64_t leaves = chk.flag[1];
+        if (4 * leaves <= m && leaves < 65536) {
+            *shared = qleaf;
+        } else {
+            if (!cand_ws_alloc(v, cs, K, get, w)) return fail(RPF_ENOMEM, "kNN workspace allocation failed");
+            fill_many({{w.cnt, m}, {w.fb_cnt, kFbWords}}, s);
+            cand_launches(v, cs, K, w, out_idx, out_dist, s);
+        }
+    }
+    const std::string le = take_launch_error();
+    if (bad) return fail(RPF_EINVAL, "rpf_query: Q holds NaN or Inf");
     if (!le.empty()) return fail(RPF_EDEVICE, "kNN: " + le);
     return RPF_OK;
 }
@@ -3981,14 +4037,23 @@ static rpf_status knn_query_get(const rpf_forest *f, const float *Q, int64_t m, 
     }
     const ForestView v = view(f);
     // one query to two leaves at most: pairs rather than groups (the rows of a leaf are shared by
-    // too few queries to pay for sorting them); rows above 512 columns take the MFMA tiles
+    // too few queries to pay for sorting them); rows above 512 columns, which a lane's registers
+    // do not hold, take the MFMA tiles.  Pairs against groups, K 10, us:
+    //   m / leaves         1/8            1/2             1               2
+    //   10^6 x 96, T 64    397, 735       1 202, 2 016    2 093, 3 180    3 859, 5 169   (spread)
+    //                      203, 318       530, 468        958, 758        1 852, 1 403   (one spot)
+    //   100 000 x 512      457, 591       968, 1 249      1 642, 2 433    2 888, 4 266   (spread)
+    //   binary32, T 32     292, 416       546, 459        938, 485        1 640, 583     (one spot)
+    // so the line lies where a batch on one spot begins to lose; it was 578 and 569 us at 1/2 when
+    // every batch was grouped.
     CheckSlot chk;
+    int32_t *shared = nullptr;  // the queries' leaves, where they turned out to share few
     if (2 * m <= v.nleaf && v.dp <= 512 && !capturing(s) && check_take(chk, may_copy)) {
-        const rpf_status st = knn_direct(v, chk, Q, m, K, out_idx, out_dist, s, get);
+        const rpf_status st = knn_direct(v, chk, Q, m, K, out_idx, out_dist, s, get, &shared);
         check_give(chk);
-        return st;
+        if (st != RPF_OK || !shared) return st;
     }
-    {   // queries must be finite (one synchronisation)
+    if (!shared) {  // queries must be finite (one synchronisation)
         int32_t *flag = static_cast<int32_t *>(get(16));
         if (!flag) return fail(RPF_ENOMEM, "rpf_query: allocation");
         fill_u32(flag, 4, 0, s);
@@ -4009,7 +4074,7 @@ static rpf_status knn_query_get(const rpf_forest *f, const float *Q, int64_t m, 
     const int64_t nleaf = v.nleaf;
     const int TR = 32 * v.job_mb;
     const size_t esz = v.prec == RPF_DIST_FP32 ? 4 : 2;
-    int32_t *qleaf = static_cast<int32_t *>(take((size_t)T * m * 4));
+    int32_t *qleaf = shared ? shared : static_cast<int32_t *>(take((size_t)T * m * 4));
     int32_t *gcount = static_cast<int32_t *>(take((size_t)T * nleaf * 4));
     int32_t *goff = static_cast<int32_t *>(take((size_t)T * nleaf * 4));
     int32_t *gfill = static_cast<int32_t *>(take((size_t)T * nleaf * 4));
@@ -4029,7 +4094,7 @@ static rpf_status knn_query_get(const rpf_forest *f, const float *Q, int64_t m, 
     TileJob *sjobs1 = qs ? static_cast<TileJob *>(take((size_t)jcap1 * sizeof(TileJob))) : nullptr;
     int32_t *njobs = static_cast<int32_t *>(take(16));
     if (!ok) return fail(RPF_ENOMEM, "rpf_query: workspace allocation failed");
-    rpf_status st = route(f, Q, m, qleaf, s);
+    rpf_status st = shared ? RPF_OK : route(f, Q, m, qleaf, s);
     if (st != RPF_OK) return st;
     fill_many({{gcount, (int64_t)T * nleaf}, {gfill, (int64_t)T * nleaf}, {njobs, 4}}, s);
     const unsigned qb = (unsigned)std::min<int64_t>((m + 255) / 256, 1024);

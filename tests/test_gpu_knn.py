@@ -269,3 +269,48 @@ def test_direct_queries_match_oracle(case):
     assert bool((out[0] == 7).all()) and bool((out[1] == 7).all())
     assert f.knn_stats() == before
     f.free()
+
+
+@pytest.mark.parametrize("what", ["spread", "one_spot", "few_spots", "nan", "first_nan"])
+@pytest.mark.parametrize("n,d,T,n0,m,prec", [(120_000, 512, 24, 1000, 60, "fp32"),    # 2.8 GB of leaf rows, rows of 2 KiB
+                                             (400_000, 96, 40, 1600, 120, "fp16")])   # 1.4 GB: not asked first
+def test_direct_queries_that_read_gigabytes(what, n, d, T, n0, m, prec):
+    """A batch of many leaf rows is grouped where its queries turn out to share few leaves; the
+    result is the same, and a batch that is not finite is refused with its outputs untouched."""
+    from paper_1812_11689_amd import rpf
+    K = 8
+    print(f"[direct] n={n} d={d} T={T} n0={n0} m={m} {what}", flush=True)
+    x, R = problem(n, d, T, n0, 1, seed=990)
+    g = np.random.default_rng(991)
+    if what == "spread":
+        q = x[g.integers(0, n, m)]
+    else:
+        q = x[g.integers(0, 5 if what == "few_spots" else 1, m)]
+    q = (q + 0.01 * g.standard_normal((m, d))).astype(np.float32)
+    f = rpf.build(torch.from_numpy(x).cuda(), T, n0, torch.from_numpy(R).cuda(), dist_prec=prec)
+    Q = torch.from_numpy(q).cuda()
+    if what in ("nan", "first_nan"):
+        f.query(Q, K)
+        torch.cuda.synchronize()
+        before = f.knn_stats()
+        Q[0 if what == "first_nan" else m - 1, d - 1] = float("nan")
+        out = (torch.full((m, K), 7, dtype=torch.int32, device="cuda"), torch.full((m, K), 7.0, device="cuda"))
+        with pytest.raises(rpf.RpfError) as e:
+            f.query(Q, K, out=out)
+        assert e.value.status == rpf.RPF_EINVAL
+        torch.cuda.synchronize()
+        assert bool((out[0] == 7).all()) and bool((out[1] == 7).all())
+        assert f.knn_stats() == before
+        f.free()
+        return
+    ref = oracle.build_forest(x, R, T, n0)
+    ri, rd = oracle.query_knn(ref, q, K)
+    for call in (lambda: f.query(Q, K),
+                 lambda: f.query_noalloc(Q, K, (torch.empty(m, K, dtype=torch.int32, device="cuda"),
+                                                torch.empty(m, K, device="cuda")))):
+        gi, gd = call()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(gi.cpu().numpy(), ri)
+        np.testing.assert_allclose(gd.cpu().numpy(), rd, rtol=1e-5)
+        assert f.knn_stats()["rows"] == m
+    f.free()
