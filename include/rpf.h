@@ -294,10 +294,11 @@ rpf_status rpf_query_noalloc(const rpf_forest *f, const float *Q_dev, int64_t m,
  * point index to leave out of query i's candidates (its own row in X), or -1; rows with
  * fewer than K candidates are padded with (-1, +inf).  1 <= K <= 256, 1 <= d <= 2048,
  * 1 <= n < 2^31.  Device workspace: one binary64 distance row per query of a chunk, at
- * most 4 GiB (or eight rows); from 65 536 points on, or 128 queries and 10^6 pairs, before
- * it up to 4.5 GiB for the matrix-core filter.  Without the filter where its workspace cannot
- * be allocated or K n is above 2^34, and with fewer distance rows where those cannot: same
- * results.  Synchronises `stream` once (input check). */
+ * most 4 GiB (or eight rows); where the pairs are many (from 65 536 points on, or 128 queries
+ * and 10^6 pairs, and above some 200 us of work) before it up to 4.5 GiB for the matrix-core
+ * filter.  Without the filter where its workspace cannot be allocated or K n is above 2^34,
+ * and with fewer distance rows where those cannot: same results.  Synchronises `stream` once
+ * (input check). */
 rpf_status rpf_exact_knn(const float *X_dev, int64_t n, int32_t d, const float *Q_dev, int64_t m,
                          const int64_t *self_dev, int32_t K, int32_t *out_idx_dev, float *out_dist_dev,
                          void *stream);

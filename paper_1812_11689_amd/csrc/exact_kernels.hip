@@ -546,8 +546,8 @@ template <int NT>
 __global__ __launch_bounds__(NT) void k_exact_tau(const float *__restrict__ ub, int64_t ldS, int64_t S, int K,
                                                    const float *__restrict__ qn, float E,
                                                    const int64_t *__restrict__ self, int64_t n, int64_t stride,
-                                                   const float *__restrict__ sn, float *__restrict__ phi,
-                                                   uint32_t *__restrict__ cnt) {
+                                                   const float *__restrict__ sn, int probes, int most,
+                                                   float *__restrict__ phi, uint32_t *__restrict__ cnt) {
     // 12-bit digits: sixteen bins per octave, so that one query's distances, which share their
     // exponents, do not all meet in one counter
     constexpr int kBins = 4096 / NT;  // bins of a thread
@@ -595,20 +595,22 @@ __global__ __launch_bounds__(NT) void k_exact_tau(const float *__restrict__ ub, 
     }
     const float tau = __uint_as_float(prefix | 0x7fu), na = qn[blockIdx.x];
     const float ph = (tau - (1.0f - E) * na) + kFiltEta + (tau + na) * 1e-6f;
-    // sampled points by the tiles' test, (1 - E) nb - 2G from the upper bound: 32 runs of 16 points
+    // `probes` of the sampled points, evenly spaced (neighbours in a sorted input fall together), by
+    // the tiles' test, (1 - E) nb - 2G from the upper bound
     const float top = ph + (1.0f + E) * na;
-    uint32_t pass = 0;
-    for (int e = tid; e < 512; e += NT) {
-        const int64_t i = (e >> 4) * S / 32 + (e & 15);
-        const float u = i < S ? __uint_as_float(row[i]) : 0.f;
-        if (i < S) pass += !(u < 3e38f) || !(u - 2.0f * E * sn[i] > top) ? 1u : 0u;
+    int total = 0;
+    for (int e = 0; e < probes; e += 256) {
+        uint32_t pass = 0;
+        if (tid < 256) {
+            const int64_t i = ((e + tid) * S + S / 2) / probes;
+            const float u = __uint_as_float(row[i]);
+            pass = !(u < 3e38f) || !(u - 2.0f * E * sn[i] > top) ? 1u : 0u;
+        }
+        total += __syncthreads_count((int)pass);
     }
-    uint32_t excl, total;
-    block_excl_scan_w<NT / 64>(pass, s_w, excl, total);
     if (tid == 0) {
         phi[blockIdx.x] = ph;
-        // (eight of 512 at least: of more points than 500 000 a few in the runs say little)
-        cnt[blockIdx.x] = total > 8 && (int64_t)total * n > (int64_t)2 * kFiltCap * 512 ? kFiltCap + 1 : 0;
+        cnt[blockIdx.x] = total > most ? kFiltCap + 1 : 0;
     }
 }
 
@@ -737,6 +739,19 @@ void launch_tile(hipStream_t s, int QB, int d, int64_t m, const __bf16 *QF, cons
     launch_check(s, "k_exact_tile");
 }
 
+// What the exhaustive kernels take, in us: a fit (within 10% for most, 29% at worst) to 100 calls of
+// n 1 000 to 130 000, d 4 to 256 and m 1 to 2 048 that take less than 380.  The filter takes 180 to
+// 215 there, so calls below 200 go without it: with it and without,
+//   m 512: 2 000 x 16 183, 152    4 000 x 16 185, 166    8 000 x 16 194, 201   4 000 x 64 184, 223
+//   m 128: 8 000 x 16 184, 156   16 000 x 16 197, 183   32 000 x 16 201, 232   16 000 x 64 209, 228
+//   65 536 points: m 1, d 4 197, 143; d 64 203, 221   m 16, d 4 204, 168; d 64 207, 272
+// (One line in n m, as it was, lost up to a third on short rows.)
+double exhaustive_us(int64_t n, int64_t m, int d) {
+    const double N = (double)n, M = (double)m, d64 = std::min(d, 64), more = d - d64;
+    return 96 + 1e-3 * N + 0.067 * M + 1.14e-5 * N * M + 0.34 * d64 + N * (1.16e-5 * d64 + 6.5e-6 * more) +
+           2.2e-7 * N * M * d;
+}
+
 // The filtered search of all m queries.  False: its workspace could not be had, or a sample that
 // its bounds' memory can hold would list too many points (nothing was launched).  over / n_over
 // receive the queries left to the exhaustive kernels.
@@ -810,9 +825,14 @@ bool filtered_search(hipStream_t s, const float *X, int64_t n, int d, const floa
             }
             // a large sample, of which few queries' bounds are held at once, takes 1024 threads a query
             // (5 000 000 x 128, K 256: 8.5 -> 1.6 ms for 128 queries)
+            // a list well above its aim costs more than it saves: above 5/3 of it by three standard
+            // deviations of the probes, and twelve of them (of many points a few say little)
+            const int probes = nq <= 512 ? 2048 : nq <= 1024 ? 1024 : 256;
+            const double per = (double)probes * aim / n;
+            const int probe_most = std::max(12, (int)(per * 5 / 3 + 3 * sqrt(per)));
             auto tau = [&](auto kern, int nt) {
                 hipLaunchKernelGGL(kern, dim3((unsigned)nq), dim3(nt), 0, s, static_cast<float *>(sbuf), S, S, K, F(QN), E, sc,
-                                   n, stride, F(SN), F(PHI), cnt);
+                                   n, stride, F(SN), probes, probe_most, F(PHI), cnt);
             };
             if (S >= 65536) tau(k_exact_tau<1024>, 1024);
             else tau(k_exact_tau<256>, 256);
@@ -869,12 +889,9 @@ extern "C" rpf_status rpf_exact_knn(const float *X, int64_t n, int32_t d, const 
     const int dq = (d + 31) & ~31;
     const int ql = std::max(8, std::min(kQL, 16384 / dq / 8 * 8));
     const size_t lds = (size_t)ql * dq * 4;
-    // the filter costs about 0.15 ms of launches and passes, so small problems measure every
-    // pair (5 000 x 64, 16 queries: 0.16 against 0.18 ms, 4 queries 0.16 against 0.10; 20 000 x
-    // 128, 64 queries 0.21 against 0.20, 256 queries 0.23 against 0.28; 100 000 x 128, 1 query
-    // 0.23 against 0.28); rows above 1 024 columns do not fit a block's LDS
+    // rows above 1 024 columns do not fit the filter's LDS
     int32_t *over = nullptr;
-    if (m < ((int64_t)1 << 31) && d <= 1024 && (n >= 65536 || (m >= 128 && n * m >= 1000000))) {
+    if (m < ((int64_t)1 << 31) && d <= 1024 && (n >= 65536 || (m >= 128 && n * m >= 1000000)) && exhaustive_us(n, m, d) > 200) {
         over = static_cast<int32_t *>(cache_alloc((size_t)(m + 4) * 4, s));
         if (over) {
             fill_u32(reinterpret_cast<uint32_t *>(over), 4, 0, s);

@@ -210,3 +210,34 @@ def test_own_rows_outside_the_points_leave_nothing_out():
         gi, gd = rpf.exact_knn(x, x[:m].clone(), K, own + shift)
         ri, rd = rpf.exact_knn(x, x[:m].clone(), K)
         assert torch.equal(gi, ri) and torch.equal(gd, rd)
+
+
+EDGE_CASES = [
+    # the filter's edges within its rule (a call below some 200 us goes without it)
+    ("one_query_past_the_rule", 130_000, 64, 1, 5, "mixture"),
+    ("k256_many_queries_past_the_rule", 8_000, 20, 2_100, 256, "mixture"),
+    ("more_than_the_points_past_the_rule", 200, 6, 6_000, 256, "mixture"),
+    ("lists_of_thousands", 5_565, 4, 2_000, 1, "far"),        # below what a list holds, left out by the sample
+    ("below_the_rule", 5_565, 4, 512, 1, "far"),
+]
+
+
+@pytest.mark.parametrize("use_self", [False, True], ids=["queries", "own_rows"])
+@pytest.mark.parametrize("case", EDGE_CASES, ids=[c[0] for c in EDGE_CASES])
+def test_filter_edges_match_oracle(case, use_self):
+    from paper_1812_11689_amd import rpf
+    name, n, d, m, K, what = case
+    print(f"[exact] {name} n={n} d={d} m={m} K={K} self={use_self}", flush=True)
+    rng = np.random.default_rng(len(name) + 77)
+    x, _ = problem(n, d, 1, n, seed=len(name) + 770)
+    if what == "far":
+        x *= np.float32(1e-2)
+        x[n // 3:] += np.float32(100)
+    pts = rng.integers(0, n, m)
+    ri, rd = oracle.bruteforce(x, x[pts], K, pts if use_self else None)
+    gi, gd = rpf.exact_knn(torch.from_numpy(x).cuda(), torch.from_numpy(x[pts]).cuda(), K,
+                           torch.from_numpy(pts.astype(np.int64)).cuda() if use_self else None)
+    np.testing.assert_array_equal(gi.cpu().numpy(), ri)
+    fin = np.isfinite(rd)
+    assert np.array_equal(np.isfinite(gd.cpu().numpy()), fin)
+    np.testing.assert_allclose(gd.cpu().numpy()[fin], rd[fin], rtol=1e-6)
