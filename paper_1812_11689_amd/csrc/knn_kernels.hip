@@ -3690,8 +3690,11 @@ static void cand_launches(const ForestView &v, const CandStage &cs, int K, const
         // 16 for bf16 / fp16 tiles when the capacity passes 1024 (their looser bounds emit more
         // records per row, which would otherwise send many rows to the slower block merge)
         const int wq = need <= 256 ? 4 : need <= 512 ? 8 : (need > 1024 && v.prec != RPF_DIST_FP32) ? 16 : 12;
-        // second half of the row lists; in bucket mode any row may outgrow the wave merge
-        fa.big_list = (need > 64 * wq || w.lay.S) ? fb_list + rows : nullptr;
+        // Second half of the row lists.  In bucket mode any row may outgrow the wave merge.  At
+        // need <= 512 that takes far more ties than expected, and those rows go to the exhaustive
+        // path: their leaves are few, and one more launch, mostly empty, costs every call as much
+        // as the empty exhaustive one (4 us of the 247 us of kernels at 10 000 x 16, T = 4).
+        fa.big_list = need > 512 && (need > 64 * wq || w.lay.S) ? fb_list + rows : nullptr;
         fa.big_cnt = fb_cnt + 1;
         if (need > kFinalCap && K > 64) {  // one block per row
             if (vec) hipLaunchKernelGGL((k_final_blk<true, false>), dim3((unsigned)rows), dim3(256), lds / 4, s, fa);

@@ -120,6 +120,49 @@ def test_all_knn_matches_oracle(case):
     f.free()
 
 
+# few distinct rows: rows outgrow the one-wave merge although the expected records are few (a
+# merge of 4 or 8 records per lane): every row is written; through the plan as well
+FEW_DISTINCT = [
+    # n, d, T, n0, K, prec, distinct rows
+    (577, 64, 13, 37, 5, "fp32", 20),
+    (577, 63, 13, 37, 5, "fp16", 20),
+    (2000, 8, 6, 30, 5, "fp32", 20),
+    (2000, 8, 16, 30, 16, "bf16", 60),
+]
+
+
+@pytest.mark.parametrize("case", FEW_DISTINCT, ids=["-".join(map(str, c)) for c in FEW_DISTINCT])
+def test_rows_past_a_small_wave_merge_are_written(case):
+    from paper_1812_11689_amd import rpf
+    n, d, T, n0, K, prec, nd = case
+    print(f"[past the wave merge] {case}", flush=True)
+    g = np.random.default_rng(n + d)
+    x = np.ascontiguousarray(g.standard_normal((nd, d)).astype(np.float32)[g.integers(0, nd, n)])
+    _, R = problem(n, d, T, n0, seed=n + T)
+    ref = oracle.build_forest(x, R, T, n0)
+    ri, rd = oracle.all_knn(ref, K)
+    f = _gpu_forest(x, R, T, n0, prec=prec)
+    gi = torch.full((n, K), -77, dtype=torch.int32, device="cuda")
+    gd = torch.full((n, K), -77.0, device="cuda")
+    rpf._check(rpf.load().rpf_all_knn(f.handle, K, 1, gi.data_ptr(), gd.data_ptr(), None))
+    torch.cuda.synchronize()
+    _compare(gi.cpu().numpy(), gd.cpu().numpy(), ri, rd)
+    print(f"    stats {f.knn_stats()}", flush=True)
+    f.free()
+    plan = rpf.Plan([n], [d], T, n0, K, dist_prec=prec)
+    plan.set_inputs([x], [np.ascontiguousarray(R[:T])])
+    for _ in range(2):
+        pi, pd = plan.result(0)
+        pi.fill_(-77)
+        pd.fill_(-77.0)
+        plan.launch()
+        plan.check()
+        pi, pd = plan.result(0)
+        torch.cuda.synchronize()
+        _compare(pi.cpu().numpy(), pd.cpu().numpy(), ri, rd)
+    plan.close()
+
+
 QUERY = [
     ("q_fp32", 12_000, 16, 4, 50, 10, "fp32", 2000),
     ("q_bf16", 12_000, 64, 4, 100, 10, "bf16", 1500),
