@@ -295,7 +295,9 @@ __global__ __launch_bounds__(NT) void k_level_small(
     const float *Rn = R + ((int64_t)t * H + (sg.heap - 1)) * n_try * (int64_t)d;
 
     int ch = 0;
-    if (NT == 256 && n_try > 1) {  // Alg. 2: keep the try with the largest spread S2 (first wins ties)
+    // Alg. 2: keep the try with the largest spread S2 (first wins ties).  Only builds whose memory
+    // holds no tries' projections come here; the others score them in k_level_try or over many blocks.
+    if (NT == 256 && n_try > 1) {
         double best = 0.0;
         int best_i = -1;
         for (int k = 0; k < n_try; k++) {
@@ -389,78 +391,78 @@ __global__ __launch_bounds__(NT) void k_level_small(
     uint64_t phi = 0;
     uint32_t plo = 0;
     for (int pass = 0;; pass++) {
-    phi = 0;
-    plo = 0;
-    int nbits = 0;
-    uint32_t rank = (uint32_t)(m / 2), cnt = (uint32_t)m;
-    while (cnt > 1 && nbits < 96) {
-        const int lo_bit = 88 - nbits;
-        const unsigned __int128 P = key96(phi, plo);
-        if (tid < 256) s_hist[tid] = 0;
-        __syncthreads();
-        for (int i = tid; i < m; i += blockDim.x) {
-            unsigned __int128 K = key96(s_key[i], (uint32_t)s_perm[i]);
-            if (nbits == 0 || (K >> (96 - nbits)) == (P >> (96 - nbits)))
-                atomicAdd(&s_hist[(uint32_t)(K >> lo_bit) & 255u], 1u);
+        phi = 0;
+        plo = 0;
+        int nbits = 0;
+        uint32_t rank = (uint32_t)(m / 2), cnt = (uint32_t)m;
+        while (cnt > 1 && nbits < 96) {
+            const int lo_bit = 88 - nbits;
+            const unsigned __int128 P = key96(phi, plo);
+            if (tid < 256) s_hist[tid] = 0;
+            __syncthreads();
+            for (int i = tid; i < m; i += blockDim.x) {
+                unsigned __int128 K = key96(s_key[i], (uint32_t)s_perm[i]);
+                if (nbits == 0 || (K >> (96 - nbits)) == (P >> (96 - nbits)))
+                    atomicAdd(&s_hist[(uint32_t)(K >> lo_bit) & 255u], 1u);
+            }
+            __syncthreads();
+            uint32_t v = tid < 256 ? s_hist[tid] : 0u, excl, total;
+            block_excl_scan_w<NT / 64>(v, s_scan, excl, total);
+            if (excl <= rank && rank < excl + v) {
+                s_misc[8] = tid;
+                s_misc[9] = excl;
+                s_misc[10] = v;
+            }
+            __syncthreads();
+            const uint32_t b = s_misc[8];
+            rank -= s_misc[9];
+            cnt = s_misc[10];
+            unsigned __int128 NP = P | ((unsigned __int128)b << lo_bit);
+            phi = (uint64_t)(NP >> 32);
+            plo = (uint32_t)NP;
+            nbits += 8;
+            __syncthreads();
         }
-        __syncthreads();
-        uint32_t v = tid < 256 ? s_hist[tid] : 0u, excl, total;
-        block_excl_scan_w<NT / 64>(v, s_scan, excl, total);
-        if (excl <= rank && rank < excl + v) {
-            s_misc[8] = tid;
-            s_misc[9] = excl;
-            s_misc[10] = v;
+        if (nbits < 96) {  // exactly one key matches the prefix: it is the median
+            const unsigned __int128 P = key96(phi, plo);
+            for (int i = tid; i < m; i += blockDim.x) {
+                unsigned __int128 K = key96(s_key[i], (uint32_t)s_perm[i]);
+                if ((K >> (96 - nbits)) == (P >> (96 - nbits))) {
+                    s_misc[12] = (uint32_t)s_key[i];
+                    s_misc[13] = (uint32_t)(s_key[i] >> 32);
+                    s_misc[14] = (uint32_t)s_perm[i];
+                }
+            }
+            __syncthreads();
+            phi = ((uint64_t)s_misc[13] << 32) | s_misc[12];
+            plo = s_misc[14];
         }
+        if (Q8 != 2 || pass || exact) break;
+        // exact keys around the digits' median, then the selection over them
+        const double mid = val_of(phi), e2 = 2.001 * bound[(int64_t)t * H + (sg.heap - 1)];
+        if (e2 == 0.0) break;  // a direction of zeros
         __syncthreads();
-        const uint32_t b = s_misc[8];
-        rank -= s_misc[9];
-        cnt = s_misc[10];
-        unsigned __int128 NP = P | ((unsigned __int128)b << lo_bit);
-        phi = (uint64_t)(NP >> 32);
-        plo = (uint32_t)NP;
-        nbits += 8;
+        for (int j = tid; j < d; j += NT) s_r[j] = Rn[j];
+        if (tid == 0) s_misc[15] = 0;
         __syncthreads();
-    }
-    if (nbits < 96) {  // exactly one key matches the prefix: it is the median
-        const unsigned __int128 P = key96(phi, plo);
-        for (int i = tid; i < m; i += blockDim.x) {
-            unsigned __int128 K = key96(s_key[i], (uint32_t)s_perm[i]);
-            if ((K >> (96 - nbits)) == (P >> (96 - nbits))) {
-                s_misc[12] = (uint32_t)s_key[i];
-                s_misc[13] = (uint32_t)(s_key[i] >> 32);
-                s_misc[14] = (uint32_t)s_perm[i];
+        const int g = tid & 7;
+        for (int i = tid >> 3; i < m; i += NT / 8) {
+            if (!(fabs(val_of(s_key[i]) - mid) <= e2)) continue;  // (the same for a row's eight lanes)
+            const double p = group8_dot64_q8<VEC>(Xq + (int64_t)s_perm[i] * dq, s_r, d, g);
+            if (g == 0) {
+                s_key[i] = key_of(p);
+                if (atomicAdd(&s_misc[15], 1u) == 0) {
+                    s_misc[12] = (uint32_t)s_key[i];
+                    s_misc[13] = (uint32_t)(s_key[i] >> 32);
+                }
             }
         }
         __syncthreads();
-        phi = ((uint64_t)s_misc[13] << 32) | s_misc[12];
-        plo = s_misc[14];
-    }
-    if (Q8 != 2 || pass || exact) break;
-    // exact keys around the digits' median, then the selection over them
-    const double mid = val_of(phi), e2 = 2.001 * bound[(int64_t)t * H + (sg.heap - 1)];
-    if (e2 == 0.0) break;  // a direction of zeros
-    __syncthreads();
-    for (int j = tid; j < d; j += NT) s_r[j] = Rn[j];
-    if (tid == 0) s_misc[15] = 0;
-    __syncthreads();
-    const int g = tid & 7;
-    for (int i = tid >> 3; i < m; i += NT / 8) {
-        if (!(fabs(val_of(s_key[i]) - mid) <= e2)) continue;  // (the same for a row's eight lanes)
-        const double p = group8_dot64_q8<VEC>(Xq + (int64_t)s_perm[i] * dq, s_r, d, g);
-        if (g == 0) {
-            s_key[i] = key_of(p);
-            if (atomicAdd(&s_misc[15], 1u) == 0) {
-                s_misc[12] = (uint32_t)s_key[i];
-                s_misc[13] = (uint32_t)(s_key[i] >> 32);
-            }
+        if (tid == 0 && 8 * (int)s_misc[15] > m) band_add(band, s_misc[15]);
+        if (s_misc[15] == 1) {  // alone: the median itself
+            phi = ((uint64_t)s_misc[13] << 32) | s_misc[12];
+            break;
         }
-    }
-    __syncthreads();
-    if (tid == 0 && 8 * (int)s_misc[15] > m) band_add(band, s_misc[15]);
-    if (s_misc[15] == 1) {  // alone: the median itself
-        phi = ((uint64_t)s_misc[13] << 32) | s_misc[12];
-        break;
-    }
     }
 
     // ---- stable partition: left = keys below (c, c_idx), in position (= index) order
@@ -954,7 +956,8 @@ __global__ __launch_bounds__(S / 2) void k_sel_sample(const SegDesc *__restrict_
         st->lo = s_k[a];
         st->hi = s_k[b];
         // a bracket's key that the sample holds more than once: many members may share it
-        st->ties = (s_k[a - 1] == s_k[a] || s_k[a] == s_k[a + 1] ? 1 : 0) | (s_k[b - 1] == s_k[b] || s_k[b] == s_k[b + 1] ? 2 : 0);
+        st->ties = (s_k[a - 1] == s_k[a] || s_k[a] == s_k[a + 1] ? 1 : 0) |
+                   (s_k[b - 1] == s_k[b] || s_k[b] == s_k[b + 1] ? 2 : 0);
         st->cnt = 0;
         st->sampled = 1;
     }

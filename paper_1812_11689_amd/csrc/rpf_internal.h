@@ -381,7 +381,6 @@ __device__ inline int mask_rank(uint64_t mask) {  // set bits of mask below this
 }
 
 __device__ inline double shfl_xor_d(double v, int m) { return __shfl_xor(v, m, 64); }
-__device__ inline float shfl_xor_f(float v, int m) { return __shfl_xor(v, m, 64); }
 
 // Adjacent-pair sum over an aligned group of eight lanes (all active): the additions of
 // v + shfl_xor(v, 1), 2, 4, with the partner's value read through DPP in the vector unit

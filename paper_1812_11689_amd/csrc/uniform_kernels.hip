@@ -766,11 +766,15 @@ void launch_uni_grow(hipStream_t s, bool wave, const float *X, int d, uint64_t s
         const size_t lds = uni_grow_lds(cap, d);
         hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         hipLaunchKernelGGL(kern, dim3((unsigned)std::min<int64_t>(most, resident)), dim3(nt), lds, s, X, d, seed, items,
-                           count, (uint32_t)std::min<int64_t>(most, 0x7fffffff), next, wave ? n0 : kGrowWave, n0, small_max, perm, u.recs, u.rec_cnt, u.rec_cap, u.mark, u.more,
-                           u.more_cnt, u.more_cap);
+                           count, (uint32_t)std::min<int64_t>(most, 0x7fffffff), next, wave ? n0 : kGrowWave, n0,
+                           small_max, perm, u.recs, u.rec_cnt, u.rec_cap, u.mark, u.more, u.more_cnt, u.more_cap);
     };
-    if (wave) vec ? go(k_uni_grow<64, kGrowWave, true>, 64, kGrowWave, 3072) : go(k_uni_grow<64, kGrowWave, false>, 64, kGrowWave, 3072);
-    else vec ? go(k_uni_grow<1024, kGrowBlock, true>, 1024, kGrowBlock, 256) : go(k_uni_grow<1024, kGrowBlock, false>, 1024, kGrowBlock, 256);
+    if (wave)
+        vec ? go(k_uni_grow<64, kGrowWave, true>, 64, kGrowWave, 3072)
+            : go(k_uni_grow<64, kGrowWave, false>, 64, kGrowWave, 3072);
+    else
+        vec ? go(k_uni_grow<1024, kGrowBlock, true>, 1024, kGrowBlock, 256)
+            : go(k_uni_grow<1024, kGrowBlock, false>, 1024, kGrowBlock, 256);
     launch_check(s, "k_uni_grow");
 }
 
