@@ -943,8 +943,6 @@ void k_tile_sym(
     constexpr int WPP = NB >= 2 ? NW / (NB / 2) : 1;  // waves per pair of block rows
     constexpr int SLOTS = NB >= 2 ? (PAIR + WPP - 1) / WPP : 1;
     constexpr bool SPLIT = PREC == RPF_DIST_BF16X3;   // hi and lo tiles, three products per step
-    // queue entries per wave (LDS for two blocks)
-    constexpr int QL = (SHAPE & 2) ? 256 : NW > 8 ? (SPLIT ? 352 : 384) : kQueue;
     // one LDS area: the operand tile(s) during the k loop, then the Phase II queues or the
     // Phase I transposes
     // LDS: the operand tile(s) during the k loop, whose space then holds the Phase II queues
@@ -952,12 +950,20 @@ void k_tile_sym(
     // tile's reads need not wait for the next chunk's loads into it
     static_assert(!C::DMA || C::KC == 32, "the raw tile's row groups are 32 binary32 columns");
     constexpr size_t kTileBytes = (size_t)(SPLIT ? 2 : 1) * M * C::LDW * sizeof(T);
-    constexpr size_t kQueBytes = MODE >= 1 ? (size_t)NW * QL * sizeof(uint2) : 0;
+    // Queue entries per wave: every pair of a half (512) where the operand tile's space and the
+    // raw tile's hold that, which the last waves' queues then take; else what leaves LDS for two
+    // blocks, in two parts where a half has more.
+    constexpr int kRawFloats = C::DMA ? M * C::KC : 1;
+    constexpr int kQueIn = (int)(kTileBytes / (kQueue * sizeof(uint2)));             // queues in the tile's space
+    constexpr int kQueRaw = (int)(kRawFloats * sizeof(float) / (kQueue * sizeof(uint2)));  // and in the raw tile
+    constexpr int QL = (SHAPE & 2) ? 256 : NW <= 8 || kQueIn + kQueRaw >= NW ? kQueue : SPLIT ? 352 : 384;
+    constexpr int kQueBuf = NW > 8 && QL == kQueue && kQueIn < NW ? kQueIn : NW;  // waves whose queue is in s_buf
+    constexpr size_t kQueBytes = MODE >= 1 ? (size_t)kQueBuf * QL * sizeof(uint2) : 0;
     constexpr size_t kTrBytes = MODE == 0 ? (size_t)NW * 32 * 33 * sizeof(float) : 0;
     constexpr size_t kBuf = kTileBytes > kQueBytes ? (kTileBytes > kTrBytes ? kTileBytes : kTrBytes)
                                                    : (kQueBytes > kTrBytes ? kQueBytes : kTrBytes);
     __shared__ __align__(16) uint8_t s_buf[kBuf];
-    __shared__ __align__(16) float s_raw[C::DMA ? M * C::KC : 1];
+    __shared__ __align__(16) float s_raw[kRawFloats];
     T *s_a = reinterpret_cast<T *>(s_buf);
     __shared__ __align__(16) float s_n[M];
     __shared__ __align__(16) float s_r[M];
@@ -1159,7 +1165,8 @@ void k_tile_sym(
         // compacted by ballot into a per-wave LDS queue, whose exact bounds and emissions
         // run when it would overflow and at the end (wave-uniform decisions throughout)
         __syncthreads();  // every wave is done with the operand tile: its space holds the queues
-        uint2 *que = reinterpret_cast<uint2 *>(s_buf) + (size_t)wu * QL;
+        uint2 *que = wu < kQueBuf ? reinterpret_cast<uint2 *>(s_buf) + (size_t)wu * QL
+                                  : reinterpret_cast<uint2 *>(s_raw) + (size_t)(wu - kQueBuf) * QL;
         uint32_t qc = 0;
         constexpr bool bucket = MODE == 2;
         const int tb2 = t - out.t1;
@@ -1234,21 +1241,34 @@ void k_tile_sym(
                         tot += (uint32_t)__popcll(mk[v8]);
                     }
                 }
-                if (qc + tot > (uint32_t)QL) {
-                    flush(qc);
-                    qc = 0;
-                }
+                auto append = [&](auto V0) {  // values V0 .. V0 + 3 of this half: at most 256 entries
 #pragma unroll
-                for (int v8 = 0; v8 < 8; v8++) {
-                    const int v = 8 * h + v8;
-                    const uint32_t f = (bits >> (2 * v8)) & 3u;
-                    if (f) {
-                        const int row = 32 * bi + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                        que[qc + mask_rank(mk[v8])] =
-                            make_uint2((uint32_t)row | ((uint32_t)col << 8) | (f << 16), __float_as_uint(acc[sl][v]));
+                    for (int v8 = decltype(V0)::value; v8 < decltype(V0)::value + 4; v8++) {
+                        const int v = 8 * h + v8;
+                        const uint32_t f = (bits >> (2 * v8)) & 3u;
+                        if (f) {
+                            const int row = 32 * bi + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+                            que[qc + mask_rank(mk[v8])] = make_uint2((uint32_t)row | ((uint32_t)col << 8) | (f << 16),
+                                                                     __float_as_uint(acc[sl][v]));
+                        }
+                        qc += (uint32_t)__popcll(mk[v8]);
                     }
-                    qc += (uint32_t)__popcll(mk[v8]);
+                };
+                // a half holds up to 512 passing pairs (rows without a threshold: K above what the
+                // first trees' leaves hold): more than a short queue, which takes them in two parts
+                static_assert(QL >= 256, "four values' pairs fit the queue");
+                bool parted = false;
+                if (qc + tot > (uint32_t)QL) {
+                    while (true) {
+                        flush(qc);
+                        qc = 0;
+                        if (QL >= 512 || tot <= (uint32_t)QL || parted) break;
+                        append(std::integral_constant<int, 0>{});
+                        parted = true;
+                    }
                 }
+                if (!parted) append(std::integral_constant<int, 0>{});
+                append(std::integral_constant<int, 4>{});
             }
         }
         flush(qc);

@@ -143,6 +143,43 @@ def test_every_tuned_choice_gives_the_same_result(n, d, n0, K, prec, tmp_path):
     assert len(seen) == 2 * (mask + 1)
 
 
+@pytest.mark.parametrize("prec", ["fp32", "bf16", "fp16", "bf16x3"])
+@pytest.mark.parametrize("d", [64, 37])
+def test_pairs_of_rows_without_a_threshold_are_all_found(prec, d, tmp_path):
+    # K above what the first tree's leaf holds: no threshold, so nearly every pair of a Phase II
+    # block passes its cheap test, more than a short queue holds, in every tile shape
+    import json
+    import math
+    import oracle
+    from paper_1812_11689_amd import rpf
+    n, T, n0, K = 1500, 3, 250, 200
+    xs, Rs = _inputs(6000 + d, [n], [d], T, n0)
+    ri, rd = oracle.all_knn(oracle.build_forest(xs[0], Rs[0], T, n0), K)
+    ai, ad, _ = _alone(xs[0], Rs[0], T, n0, K, prec)
+    np.testing.assert_array_equal(ai.cpu().numpy(), ri)
+    np.testing.assert_allclose(ad.cpu().numpy()[np.isfinite(rd)], rd[np.isfinite(rd)], rtol=1e-5, atol=0)
+    key = dict(d=d, max_leaf=-(-n // (1 << rpf.depth(n, n0))), prec=rpf.PREC[prec], K=K, T=T,
+               n_log2=int(math.floor(math.log2(n))))
+    try:
+        for shape in range(8):
+            print(f"[no threshold] {prec} d={d} shape={shape}", flush=True)
+            rpf.tune_clear()
+            path = tmp_path / f"t{shape}.jsonl"
+            path.write_text(json.dumps(dict(key, first_trees=1, tile_shape=shape, bucket_size=16, subtrees=0)) + "\n")
+            assert rpf.tune_load(str(path)) == 1
+            plan = rpf.Plan([n], [d], T, n0, K, dist_prec=prec)
+            ch = plan.choices()[0]
+            assert ch["tile_shape"] == shape and ch["first_trees"] == 1
+            plan.set_inputs(xs, Rs)
+            plan.launch()
+            plan.check()
+            gi, gd = plan.result(0)
+            assert torch.equal(gi, ai) and torch.equal(gd, ad), shape
+            plan.close()
+    finally:
+        rpf.tune_clear()
+
+
 def test_tuner_records_its_choices(tmp_path):
     from paper_1812_11689_amd import rpf
     sizes, dims, T, n0, K = [3000, 5000], [16, 16], 5, 40, 9
