@@ -395,7 +395,9 @@ __device__ inline void emit_bucket(const TileOut &o, int32_t *s_cnt, int r, int 
 }
 
 // per-row threshold of the cheap test  |b|^2 - 2 a.b <= phi(row),  a necessary condition for
-// lb <= tau(row) with the per-pair error terms replaced by their largest value over the tile
+// lb <= tau(row) with the per-pair error terms replaced by their largest value over the tile.
+// The test is written !(.. > phi): values past the tile type's range make products that are no
+// number, and such a pair, whose bounds are (0, inf), has to pass.
 __device__ inline float cheap_phi(float tv, float na, float ra, float nmax, float rmax, BoundCoef bc) {
     if (!(tv < INFINITY)) return INFINITY;
     if (tv < 0.f) return -INFINITY;
@@ -604,7 +606,7 @@ __global__ __launch_bounds__(64 * MB) void k_tile(
             for (int v8 = 0; v8 < 8; v8++) {
                 const int v = 8 * h + v8;
                 const int row = 32 * wu + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                const bool p = colok & (__builtin_fmaf(-2.f, acc[cb][v], nb) <= pr[v]) &
+                const bool p = colok & !(__builtin_fmaf(-2.f, acc[cb][v], nb) > pr[v]) &
                                !(same & (exclude_self != 0) & (row == col));
                 bits |= (p ? 1u : 0u) << v8;
                 mk[v8] = __ballot(p);
@@ -1217,8 +1219,8 @@ void k_tile_sym(
 #pragma unroll
                     for (int v8 = 0; v8 < 8; v8++) {
                         const float g = acc[sl][8 * h + v8];
-                        const bool p1 = __builtin_fmaf(-2.f, g, ncol) <= pr[v8];
-                        const bool p2 = __builtin_fmaf(-2.f, g, nr[v8]) <= phicol;
+                        const bool p1 = !(__builtin_fmaf(-2.f, g, ncol) > pr[v8]);
+                        const bool p2 = !(__builtin_fmaf(-2.f, g, nr[v8]) > phicol);
                         bits |= ((p1 ? 1u : 0u) | (p2 ? 2u : 0u)) << (2 * v8);
                         mk[v8] = __ballot(p1 || p2);
                         tot += (uint32_t)__popcll(mk[v8]);
@@ -1232,10 +1234,10 @@ void k_tile_sym(
                         // row -> col needs a real column and, on the diagonal block, row <= col
                         // (row < col when the point itself is excluded); col -> row needs a real
                         // row and, on the diagonal block, row < col
-                        const bool p1 = colok & (__builtin_fmaf(-2.f, g, ncol) <= pr[v8]) &
+                        const bool p1 = colok & !(__builtin_fmaf(-2.f, g, ncol) > pr[v8]) &
                                         !(diag & ((row > col) | ((row == col) & (exclude_self != 0))));
                         const bool p2 =
-                            (!diag | (row < col)) & (row < m) & (__builtin_fmaf(-2.f, g, nr[v8]) <= phicol);
+                            (!diag | (row < col)) & (row < m) & !(__builtin_fmaf(-2.f, g, nr[v8]) > phicol);
                         bits |= ((p1 ? 1u : 0u) | (p2 ? 2u : 0u)) << (2 * v8);
                         mk[v8] = __ballot(p1 || p2);
                         tot += (uint32_t)__popcll(mk[v8]);

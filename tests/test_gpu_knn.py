@@ -163,6 +163,30 @@ def test_rows_past_a_small_wave_merge_are_written(case):
     plan.close()
 
 
+@pytest.mark.parametrize("prec,big", [("fp16", 1e5), ("fp16", 1e6), ("bf16", 1e20), ("bf16x3", 1e20), ("fp32", 1e20)])
+@pytest.mark.parametrize("n0", [8, 60, 250, 600])  # one block row, several, the largest symmetric tile, two-sided tiles
+def test_values_past_the_tile_type_lose_no_neighbour(prec, big, n0):
+    # products of values past float16's range, or whose squares pass binary32's, are no number in
+    # the tiles' Gram matrix: those pairs have to be measured exactly
+    n, d, T, K = 1400, 40, 7, 9
+    g = np.random.default_rng(n0)
+    x = g.standard_normal((n, d)).astype(np.float32)
+    x[g.random((n, d)) < 0.02] *= np.float32(big)
+    _, R = problem(n, d, T, n0, seed=n0)
+    ref = oracle.build_forest(x, R, T, n0)
+    f = _gpu_forest(x, R, T, n0, prec=prec)
+    print(f"[past the range] {prec} {big} n0={n0}", flush=True)
+    gi, gd = f.all_knn(K)
+    torch.cuda.synchronize()
+    _compare(gi.cpu().numpy(), gd.cpu().numpy(), *oracle.all_knn(ref, K))
+    for m in (3, 700):  # pair by pair, and grouped
+        q = np.ascontiguousarray(x[g.integers(0, n, m)] + g.standard_normal((m, d)).astype(np.float32))
+        gi, gd = f.query(torch.from_numpy(q).cuda(), K)
+        torch.cuda.synchronize()
+        _compare(gi.cpu().numpy(), gd.cpu().numpy(), *oracle.query_knn(ref, q, K))
+    f.free()
+
+
 QUERY = [
     ("q_fp32", 12_000, 16, 4, 50, 10, "fp32", 2000),
     ("q_bf16", 12_000, 64, 4, 100, 10, "bf16", 1500),
