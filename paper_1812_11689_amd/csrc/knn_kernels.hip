@@ -309,7 +309,8 @@ __device__ inline void pair_bounds(float na, float nb, float ra, float rb, float
     const float hs = sqrtf(fmaxf(Dt + e, 0.f)) + delta;
     lb = ls * ls * (1.f - 1e-6f);
     ub = hs * hs * (1.f + 1e-6f);
-    if (!(ra < INFINITY) || !(rb < INFINITY) || !(lb == lb) || !(ub == ub)) {  // out of the copy's range
+    // out of the copy's range, or a sum past binary32's (fmaxf would turn its NaN into a bound of 0)
+    if (!(ra < INFINITY) || !(rb < INFINITY) || !(fabsf(Dt) + e < INFINITY)) {
         lb = 0.f;
         ub = INFINITY;
     }

@@ -187,6 +187,29 @@ def test_values_past_the_tile_type_lose_no_neighbour(prec, big, n0):
     f.free()
 
 
+@pytest.mark.parametrize("prec", ["fp32", "bf16", "bf16x3"])
+@pytest.mark.parametrize("scale", [1e18, 1e19, 1e20])
+@pytest.mark.parametrize("T,n0", [(3, 42), (7, 250), (5, 600)])
+def test_squared_norms_around_the_end_of_binary32(prec, scale, T, n0):
+    # rows whose squared norms are finite, infinite, or finite with an infinite sum, side by side
+    n, d, K = 1500, 128, 5
+    g = np.random.default_rng(n0)
+    x = (np.sort(g.standard_normal((n, d)), axis=0) * scale).astype(np.float32)
+    _, R = problem(n, d, T, n0, seed=n0)
+    ref = oracle.build_forest(x, R, T, n0)
+    f = _gpu_forest(x, R, T, n0, prec=prec)
+    print(f"[norms at the end] {prec} {scale} T={T} n0={n0}", flush=True)
+    gi, gd = f.all_knn(K)
+    torch.cuda.synchronize()
+    _compare(gi.cpu().numpy(), gd.cpu().numpy(), *oracle.all_knn(ref, K))
+    for m in (3, 700):
+        q = np.ascontiguousarray(x[g.integers(0, n, m)] * np.float32(1.01))
+        gi, gd = f.query(torch.from_numpy(q).cuda(), K)
+        torch.cuda.synchronize()
+        _compare(gi.cpu().numpy(), gd.cpu().numpy(), *oracle.query_knn(ref, q, K))
+    f.free()
+
+
 QUERY = [
     ("q_fp32", 12_000, 16, 4, 50, 10, "fp32", 2000),
     ("q_bf16", 12_000, 64, 4, 100, 10, "bf16", 1500),
